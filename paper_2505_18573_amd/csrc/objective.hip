@@ -2,40 +2,72 @@
 // KL term the paper drops): per token min(r A, clip(r, 1-eps, 1+eps) A) with
 // r = exp(logp_new - logp_old), averaged over the tokens of a rollout, then over the
 // rollouts of a question, then over questions.  It consumes what the vocabulary pass
-// (log-probs) and the advantage kernel (A) produce.  Two launches: one wave per rollout
-// (fp64 sums, DPP reduction), then one workgroup that folds rollouts into questions and
-// questions into the scalar in a fixed order (bit-reproducible).
+// (log-probs) and the advantage kernel (A) produce.  Two launches: one to sixteen waves per
+// rollout (fp64 sums, DPP reductions), then one workgroup that folds rollouts into questions
+// and questions into the scalar; every sum has an order fixed by the shape (bit-reproducible).
 #include "vocab_common.h"
 #include "vocab_pass.h"
 
 namespace e3 {
 
-constexpr int kSeqsPerBlock = 4;
+// The terms of one rollout, kWaves waves of a workgroup each.  The kernel moves 12 bytes per
+// token and is bound by latency, not by bytes: what counts is how many tokens are requested at
+// once, hence several waves per rollout and kUnroll tokens per lane requested before the first
+// is used.  512 rollouts of 77 - 8192 tokens (1.6 M tokens, 19 MB) on MI355X: one wave per
+// rollout with one token per lane at a time 44.2 us, this form 6.6 us (2.9 TB/s).
+constexpr int kUnroll = 8;
 
-__global__ __launch_bounds__(kSeqsPerBlock * 64)
+template <int kWaves, int kSeqsPerBlock>
+__global__ __launch_bounds__(kWaves * kSeqsPerBlock * 64)
 void grpo_seq_terms_kernel(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
                            const int32_t* __restrict__ seq_offsets, const float* __restrict__ adv,
                            int32_t num_seqs, float clip_eps, float* __restrict__ token_term_out,
                            double* __restrict__ seq_mean_out)
 {
-    const int lane = threadIdx.x & 63;
-    const int i = blockIdx.x * kSeqsPerBlock + (threadIdx.x >> 6);
+    static_assert(kWaves == 1 || kSeqsPerBlock == 1, "waves of several rollouts do not meet at one barrier");
+    constexpr int kStep = kWaves * 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = blockIdx.x * kSeqsPerBlock + (kWaves == 1 ? wave : 0);
     if (i >= num_seqs) return;
     const int64_t t0 = seq_offsets[i], t1 = seq_offsets[i + 1];
     const float A = adv[i];
     const float lo = 1.0f - clip_eps, hi = 1.0f + clip_eps;
     double acc = 0.0;
-    for (int64_t t = t0 + lane; t < t1; t += 64) {
-        const float r = __builtin_amdgcn_exp2f((logp_new[t] - logp_old[t]) * kLog2eF);
-        const float rc = fminf(fmaxf(r, lo), hi);
-        const float term = fminf(r * A, rc * A);
-        if (token_term_out) token_term_out[t] = term;
-        acc += (double)term;
+    for (int64_t t = t0 + (kWaves == 1 ? lane : (int)threadIdx.x); t < t1; t += kStep * kUnroll) {
+        float n[kUnroll], o[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int64_t tu = t + u * kStep < t1 ? t + u * kStep : t;
+            n[u] = logp_new[tu];
+            o[u] = logp_old[tu];
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const float r = __builtin_amdgcn_exp2f((n[u] - o[u]) * kLog2eF);
+            const float rc = fminf(fmaxf(r, lo), hi);
+            const float term = fminf(r * A, rc * A);
+            if (t + u * kStep < t1) {
+                if (token_term_out) token_term_out[t + u * kStep] = term;
+                acc += (double)term;
+            }
+        }
     }
     acc = wave_sum(acc);
+    if (kWaves > 1) {
+        __shared__ double partial[kWaves];
+        if (lane == 0) partial[wave] = acc;
+        __syncthreads();
+        if (threadIdx.x != 0) return;
+        acc = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) acc += partial[w];
+    }
     if (lane == 0) seq_mean_out[i] = t1 > t0 ? acc / (double)(t1 - t0) : 0.0;
 }
 
+// Questions to the scalar, one workgroup.  Eight lanes share a question, so that the usual
+// handful of rollouts is one request deep (64 questions x 8 rollouts: 4.5 us with one lane per
+// question, 1.9 us so); a question's sum and the fold over questions have a fixed order.
 __global__ __launch_bounds__(1024)
 void grpo_objective_reduce_kernel(const double* __restrict__ seq_mean,
                                   const int32_t* __restrict__ group_offsets, int32_t num_groups,
@@ -43,11 +75,17 @@ void grpo_objective_reduce_kernel(const double* __restrict__ seq_mean,
 {
     __shared__ double partial[16];
     double acc = 0.0;
-    for (int32_t q = threadIdx.x; q < num_groups; q += 1024) {
-        const int32_t i0 = group_offsets[q], i1 = group_offsets[q + 1];
+    const int sub = threadIdx.x & 7;
+    for (int32_t q0 = 0; q0 < num_groups; q0 += 1024 / 8) {        // whole waves take part in the reductions
+        const int32_t q = q0 + (int32_t)(threadIdx.x >> 3);
+        const int32_t i0 = q < num_groups ? group_offsets[q] : 0, i1 = q < num_groups ? group_offsets[q + 1] : 0;
         double g = 0.0;
-        for (int32_t i = i0; i < i1; ++i) g += seq_mean[i];
-        if (i1 > i0) acc += g / (double)(i1 - i0);
+#pragma unroll 4
+        for (int32_t i = i0 + sub; i < i1; i += 8) g += seq_mean[i];
+        g += dpp_d<kDppXor1>(0.0, g);
+        g += dpp_d<kDppXor2>(0.0, g);
+        g += dpp_d<kDppHalfMirror>(0.0, g);                         // the other four of the eight
+        if (sub == 0 && i1 > i0) acc += g / (double)(i1 - i0);
     }
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) partial[threadIdx.x >> 6] = acc;
@@ -59,6 +97,15 @@ void grpo_objective_reduce_kernel(const double* __restrict__ seq_mean,
     }
 }
 
+template <int kWaves, int kSeqsPerBlock>
+static void launch_terms(dim3 blocks, const float* logp_new, const float* logp_old, const int32_t* seq_offsets,
+                         const float* adv, int32_t num_seqs, float clip_eps, float* token_term_out,
+                         double* seq_mean_out, hipStream_t stream)
+{
+    hipLaunchKernelGGL((grpo_seq_terms_kernel<kWaves, kSeqsPerBlock>), blocks, dim3(kWaves * kSeqsPerBlock * 64), 0,
+                       stream, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out);
+}
+
 hipError_t launch_grpo_objective(const float* logp_new, const float* logp_old,
                                  const int32_t* seq_offsets, const float* adv, int32_t num_seqs,
                                  const int32_t* group_offsets, int32_t num_groups, float clip_eps,
@@ -66,10 +113,13 @@ hipError_t launch_grpo_objective(const float* logp_new, const float* logp_old,
                                  hipStream_t stream)
 {
     if (num_seqs > 0) {
-        const unsigned blocks = (unsigned)((num_seqs + kSeqsPerBlock - 1) / kSeqsPerBlock);
-        hipLaunchKernelGGL(grpo_seq_terms_kernel, dim3(blocks), dim3(kSeqsPerBlock * 64), 0, stream,
-                           logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out,
-                           seq_mean_out);
+        // as many waves per rollout as keep all rollouts resident at once (32 waves on each of
+        // 256 compute units): few rollouts get many waves, many get one
+        const dim3 one((unsigned)num_seqs);
+        if (num_seqs <= 512) launch_terms<16, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
+        else if (num_seqs <= 1024) launch_terms<8, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
+        else if (num_seqs <= 4096) launch_terms<4, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
+        else launch_terms<1, 4>(dim3((unsigned)((num_seqs + 3) / 4)), logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }

@@ -56,3 +56,32 @@ def test_objective_parity_on_gpu():
     b = e3.e3_grpo_objective(torch.from_numpy(new).to(dev), torch.from_numpy(old).to(dev),
                              torch.from_numpy(soff).to(dev), adv_t, torch.from_numpy(goff).to(dev), 0.2)[0].item()
     assert a == b
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("num_seqs", [1, 512, 513, 1024, 1025, 4096, 4097])
+def test_objective_parity_at_every_wave_count(num_seqs):
+    # 16, 8, 4 and 1 waves per rollout, on both sides of each bound; lengths around the tokens that a
+    # wave, a workgroup of each size and one unrolled round take, and empty rollouts and questions
+    dev = "cuda:0"
+    rng = np.random.default_rng(num_seqs)
+    edges = np.array([0, 1, 63, 64, 65, 511, 512, 513, 1023, 1024, 1025, 2047, 2049, 4095, 4097, 8191, 8192, 8193])
+    lens = np.where(np.arange(num_seqs) < edges.size, edges[np.arange(num_seqs) % edges.size],
+                    rng.integers(0, 200, num_seqs))
+    lens = lens[rng.permutation(num_seqs)] if num_seqs > 1 else np.array([8193])
+    soff = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cuts = np.sort(rng.integers(0, num_seqs + 1, max(1, num_seqs // 6)))     # questions of any size, some empty
+    goff = np.concatenate([[0], cuts, [num_seqs]]).astype(np.int32)
+    T = int(soff[-1])
+    old = rng.normal(-1.5, 1.0, T).astype(np.float32)
+    new = (old + rng.normal(0, 0.15, T)).astype(np.float32)
+    adv = rng.normal(0, 1, num_seqs).astype(np.float32)
+    J, seq_mean, terms = e3.e3_grpo_objective(torch.from_numpy(new).to(dev), torch.from_numpy(old).to(dev),
+                                              torch.from_numpy(soff).to(dev), torch.from_numpy(adv).to(dev),
+                                              torch.from_numpy(goff).to(dev), 0.2, want_token_terms=True)
+    want_J, want_terms, want_means = o.grpo_objective(new, old, soff, adv, goff, float(np.float32(0.2)))
+    # per token: r carries the fp32 rounding of the difference times log2(e) and one ulp of the
+    # exponential (|log ratio| < 1: below 4e-7 relative); sums are fp64
+    assert np.allclose(terms.cpu().numpy(), want_terms, rtol=2e-6, atol=1e-7)
+    assert np.allclose(seq_mean.cpu().numpy(), want_means, rtol=2e-6, atol=1e-7)
+    assert J.item() == pytest.approx(want_J, rel=2e-6, abs=1e-7)
