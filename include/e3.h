@@ -172,9 +172,11 @@ int e3_sample_entropy_noalloc(const void* logits, int dtype, int64_t rows, int64
  *   errors as for e3_sample_entropy; top_k < 0 or top_p not in (0, inf): E3_ERR_VALUE.
  * One workgroup of 1024 threads per row.  With 1 <= top_k <= 256 the row is read once
  * (vector maxima kept in LDS, the few vectors that can hold one of the k largest read
- * again, exact selection among those); otherwise (bf16 only) a histogram over the 2^16
- * stored patterns in 128 KiB of LDS: one counting sweep of the row with 16-bit counters, or,
- * for a row with 65,536 or more equal columns, one to three sweeps with 32-bit counters.
+ * again, exact selection among those); otherwise (bf16 only) the row's stored patterns are
+ * counted in LDS: one counting sweep over 32 binades of both signs, or, for the rare row
+ * that does not fit them (finite logits of 512 and more that the row's beginning does not
+ * show, more than 62 columns nearer to zero than 2^-23 without being zero, very long levels),
+ * four to ten sweeps over all patterns.
  */
 int e3_sample_restricted(const void* logits, int dtype, int64_t rows, int64_t V, int64_t row_stride,
                          const float* tau_rows, float tau_scalar, int32_t top_k, float top_p,

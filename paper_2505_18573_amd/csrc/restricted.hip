@@ -7,29 +7,37 @@
 // counts (top-k) and cumulative level masses (top-p), and the draw is a Gumbel-max
 // over the kept levels followed by a uniform choice among the winning level's columns.
 //
-// bf16 has only 65,536 bit patterns, so a row's whole value distribution fits a
-// count histogram in the compute unit's 160 KiB LDS: all 65,536 patterns with 16-bit
-// counters (128 KiB, two counters per word), or the 32,768 patterns of one sign with
-// 32-bit counters (128 KiB).  One workgroup of 16 waves owns one row:
-//   1. stream the row once, counting with LDS atomics (the columns of a wave
-//      instruction scatter over many words: few conflicts);
-//   2. every thread owns 64 (one window) or 32 (two windows) consecutive bins, i.e.
-//      equally spaced values of one binade, whose weights exp((z - z_1)/tau) form a
-//      geometric sequence: two exponentials and a product per bin give all level masses
-//      in fp64; a workgroup scan yields the cumulative counts C_j and masses M_j in rank
-//      order;
-//   3. the cuts are located by the thread whose bins contain them, the kept levels
-//      race for the draw (n_j w_j / E_j, fp32 like the unrestricted sampler), and a
-//      second sweep over the row (now in L2 / the memory-side cache) finds the pos-th
-//      column of the winning level.
-// The one-window form (16-bit counters) serves every setting with that single counting
-// sweep.  A row with a level of 65,536 or more equal columns wraps a counter; it is
-// recognised (the counts no longer add up to the row's width) and redone by the
-// two-window form: non-negative patterns first, and if the kept set reaches the negative
-// patterns steps 1-2 again on the negative half (same LDS); there, top-p without top-k
-// totals the negative half first, and the order of events "top-k cut among the
-// negatives, top-p cut back among the non-negatives" costs a third sweep.  Counts are
-// integers; masses and the cuts are fp64.
+// bf16 has only 65,536 bit patterns, so the whole value distribution of a row is a count
+// histogram.  One workgroup of 16 waves owns one row:
+//   1. stream the row once, counting with LDS atomics;
+//   2. every thread owns a run of consecutive levels of one binade, i.e. equally spaced
+//      values whose weights exp((z - z_1)/tau) form a geometric sequence: two
+//      exponentials and a product per level give all level masses in fp64; a workgroup
+//      scan yields the cumulative counts C_j and masses M_j in rank order;
+//   3. the cuts are located by the thread whose levels contain them, the kept levels
+//      race for the draw (n_j w_j / E_j, fp32 like the unrestricted sampler), and the
+//      pos-th column of the winning level is looked up in the row.
+// Counts are integers; masses and the cuts are fp64.
+//
+// THE NEAR WINDOW (every ordinary row).  The values a row really holds span few binades:
+// 32 binades of both signs, 8192 levels, are counted in 64 KiB of LDS - the 32 binades up to
+// [256, 512), or up to one above the largest logit among the first vectors read, whichever
+// is higher.  64 KiB instead of the 128 KiB all patterns need is what lets two rows share a
+// compute unit, so that one row's short dependent phases overlap the other's stream: a 512 x
+// 151,936 batch took 100 us with one row per compute unit at a time, and the counting itself
+// is no limit then (read alone 27.2 us, read and count 31.4 us; but one row on one compute
+// unit 4.2 and 12.2 us: there the LDS atomics are).  Each level has four 16-bit counters, one
+// per quarter of the row (the quarter is uniform per step of the stream, so it costs nothing), and
+// the final look-up reads only the quarter that holds the column.  What lies outside the
+// window is kept exactly too: zeros are counted apart, up to 62 nearer to zero than the window are
+// listed with their columns (the MIDDLE items, ranked between the two signs), and values
+// below the window (masked columns) are counted when they are too far down to weigh anything.
+//
+// THE WIDE ROWS.  Everything else - a value above the window, more small values than the
+// list holds, a wrapped counter (recognised because the counts no longer add up to the row's
+// width), a cut among the columns below the window - is redone over all patterns with
+// 32-bit counters, in four windows of 16,384 patterns in rank order, one sweep each; a
+// cut or the race needs its window swept again.  Slow (up to ten sweeps), exact, rare.
 #include "vocab_common.h"
 #include "vocab_pass.h"
 
@@ -38,666 +46,45 @@ namespace {
 
 constexpr int kRThreads = 1024;
 constexpr int kRWaves = kRThreads / 64;
-constexpr int kBins = 32768;            // bit patterns of one sign
-constexpr int kOwn = kBins / kRThreads; // 32 consecutive bins per thread
-constexpr int kTrashBins = 64;          // words behind the window that take the other sign's patterns
+constexpr int kBinades = 32;                    // of each sign in the near window
+constexpr int kHalf = kBinades * 128;           // its levels of one sign
+constexpr int kTopExp = 135;                    // exponent field of the lowest top binade, [256, 512)
+constexpr int kQuarters = 4;
+constexpr int kOwnN = 2 * kHalf / kRThreads;    // near window: 8 levels per thread
+constexpr int kTrash = 64;                      // words behind a counter array, one per lane
+constexpr int kArray = 2 * kHalf + kTrash;      // two quarters' counters in each word
+constexpr int kWideBins = 16384;                // patterns in one of the four wide windows
+constexpr int kWideWindows = 4;
+constexpr int kOwnW = kWideBins / kRThreads;    // 16
+constexpr int kMidList = 62;                    // listed small values; with the two zeros one item per lane
+constexpr int kBlock = 5;                       // stream steps looked up at a time (a quarter of 151,936 columns)
+static_assert(kArray * 2 >= kWideBins + kTrash, "the wide window fits the same memory");
+static_assert(kOwnN * kRThreads == 2 * kHalf && 128 % kOwnN == 0 && 128 % kOwnW == 0, "a thread's levels share a binade");
 
-struct RaceBest {
-    double q;        // n_j w_j / E_j, -1 = none
-    int bits;        // the level's stored bit pattern
-    int n;           // its column count
-};
+// Rank key of a pattern: ascending in value, -0 just below +0.
+__device__ __forceinline__ int key_of_pattern(int p) { return p < 0x8000 ? p + 0x8000 : 0xFFFF - p; }
+__device__ __forceinline__ int pattern_of_key(int key) { return key >= 0x8000 ? key - 0x8000 : 0xFFFF - key; }
+__device__ __forceinline__ float value_of_pattern(int p) { return __uint_as_float((uint32_t)p << 16); }
 
 struct Shared {
+    float wave_top[kRWaves];
     double wave_M[kRWaves];
     int wave_C[kRWaves];
-    float wave_top[kRWaves];
-    double best_q[kRWaves];
-    int best_bits[kRWaves];
-    int best_n[kRWaves];
-    int wave_hits[kRWaves];
-    int wave_A[kRWaves];
-    int first_thread;
-    int cut_bin, cut_C;
-    double cut_M;
+    Cand best[kRWaves];
+    float sample_max[kRWaves];
+    int zeros[2][kQuarters];        // +0, -0 by quarter
+    int list_n, n_below, n_not_finite, n_above;
+    int list_key[64], list_col[64]; // small values as they come
+    int mid_key[64], mid_cnt[64], mid_col[64];   // the middle items in rank order
+    int mid_C[64];                  // inclusive prefixes inside the middle
+    double mid_M[64];
+    int cut_key[kRWaves + 1], cut_C[kRWaves + 1];      // what each wave (and the middle) offers as the cut
+    double cut_M[kRWaves + 1];
+    int tot[kBlock * kRWaves];
     int token;
-    int list_n;
-    uint32_t list[1024];   // (vector index << 8 | 8-bit column mask) of vectors holding the winner
+    int C_above[kWideWindows + 1];  // wide rows: count and mass above each window
+    double M_above[kWideWindows + 1];
 };
-constexpr int kListCap = 1024;
-
-__device__ __forceinline__ double bf16_value(int bits)
-{
-    return (double)__uint_as_float((uint32_t)bits << 16);
-}
-
-// Bin <-> bit pattern.  Non-negative window: bin = pattern.  Negative window:
-// bin = 0xFFFF - pattern, so that in both windows a higher bin is a higher value.
-__device__ __forceinline__ int bin_bits(bool hi, int bin) { return hi ? bin : 0xFFFF - bin; }
-
-// Step 1: histogram of one sign's patterns over the whole row.
-__device__ __forceinline__ void build_hist(const uint16_t* __restrict__ row, int64_t V, bool hi, uint32_t* hist, int tid)
-{
-    const uint4 zero4 = {0u, 0u, 0u, 0u};
-    for (int i = tid; i < kBins / 4; i += kRThreads) reinterpret_cast<uint4*>(hist)[i] = zero4;
-    __syncthreads();
-    // bin = pattern (non-negative window) or 0xFFFF - pattern (negative window): one xor with a
-    // uniform mask, done on the packed word for both halves.  A pattern of the other sign comes
-    // out at 0x8000 or above and is counted into one of the kTrashBins words behind the window
-    // (a word of the lane's own, so that the lanes of one instruction do not queue up on one
-    // address): no branch, no lane masking around the LDS atomic.
-    const uint32_t flip = hi ? 0u : 0xFFFFFFFFu;
-    const uint32_t trash = (uint32_t)(kBins + (tid & (kTrashBins - 1)));
-    auto add = [&](uint32_t bin) {                        // bin < 0x10000
-        atomicAdd(&hist[bin < trash ? bin : trash], 1u);
-    };
-    auto add8 = [&](const u32x4& v) {
-        const uint32_t x = v.x ^ flip, y = v.y ^ flip, z = v.z ^ flip, w = v.w ^ flip;
-        add(x & 0xFFFFu); add(x >> 16); add(y & 0xFFFFu); add(y >> 16);
-        add(z & 0xFFFFu); add(z >> 16); add(w & 0xFFFFu); add(w >> 16);
-    };
-    const int64_t nvec = V >> 3;
-    const u32x4* rv = reinterpret_cast<const u32x4*>(row);
-    int64_t v = tid;
-    for (; v + 3 * kRThreads < nvec; v += 4 * kRThreads) {
-        const u32x4 a = rv[v], b = rv[v + kRThreads], c = rv[v + 2 * kRThreads], d = rv[v + 3 * kRThreads];
-        add8(a); add8(b); add8(c); add8(d);
-    }
-    for (; v < nvec; v += kRThreads) add8(rv[v]);
-    const int64_t tail0 = nvec << 3;
-    if (tid < V - tail0) add(((uint32_t)row[tail0 + tid] ^ flip) & 0xFFFFu);
-    __syncthreads();
-}
-
-// Per-thread view of the scanned window.
-template <int kOwnT>
-struct ViewT {
-    uint32_t cnt[kOwnT];  // counts of my bins; the last index is my highest bin
-    int b0;               // my lowest bin
-    double w_top, r_inv;  // weight of my highest bin; factor to the next lower bin
-    int Cl, Cx;           // my count; count of all higher levels (carry included)
-    double Ml, Mx;        // the same for mass
-};
-using View = ViewT<kOwn>;
-
-// Step 2.  carry_C / carry_M: count and mass of all levels above this window.
-// z1: value of the row's highest level; when `find_z1` it is taken from this window's
-// highest populated bin (returns false if the window is empty).
-__device__ __forceinline__ bool scan_window(const uint32_t* hist, bool hi, double inv_tau, bool find_z1, double& z1,
-                            int carry_C, double carry_M, View& vw, int& Cw, double& Mw,
-                            Shared& sh, int tid)
-{
-    const int lane = tid & 63, wave = tid >> 6;
-    vw.b0 = kBins - kOwn * (tid + 1);                 // thread 0 owns the highest bins
-#pragma unroll
-    for (int i = 0; i < kOwn / 4; ++i) {
-        const uint4 c = reinterpret_cast<const uint4*>(hist + vw.b0)[i];
-        vw.cnt[4 * i] = c.x; vw.cnt[4 * i + 1] = c.y; vw.cnt[4 * i + 2] = c.z; vw.cnt[4 * i + 3] = c.w;
-    }
-    const int top_bits_field = (bin_bits(hi, vw.b0 + kOwn - 1) >> 7) & 0xFF;
-    const bool finite = top_bits_field != 0xFF;       // inf / NaN patterns are not levels
-    int Cl = 0, my_top = -1;
-#pragma unroll
-    for (int j = 0; j < kOwn; ++j) {
-        if (!finite) vw.cnt[j] = 0;
-        Cl += (int)vw.cnt[j];
-        if (vw.cnt[j] != 0) my_top = vw.b0 + j;
-    }
-    vw.Cl = Cl;
-    if (find_z1) {
-        const float t = wave_max((float)my_top);      // bins are below 2^15: exact in fp32
-        if (lane == 0) sh.wave_top[wave] = t;
-        __syncthreads();
-        float top = -1.0f;
-        for (int w = 0; w < kRWaves; ++w) top = fmaxf(top, sh.wave_top[w]);
-        __syncthreads();
-        if (top < 0.0f) { Cw = 0; Mw = 0.0; return false; }
-        z1 = bf16_value(bin_bits(hi, (int)top));
-    }
-    // my 32 values are equally spaced (one binade, or the subnormals): geometric weights
-    double Ml = 0.0;
-    vw.w_top = 0.0; vw.r_inv = 0.0;
-    if (Cl > 0) {
-        const double z_top = bf16_value(bin_bits(hi, vw.b0 + kOwn - 1));
-        const double step = ldexp(1.0, (top_bits_field ? top_bits_field : 1) - 134);
-        vw.w_top = exp((z_top - z1) * inv_tau);
-        vw.r_inv = exp(-step * inv_tau);
-        double w = vw.w_top;
-#pragma unroll
-        for (int j = kOwn - 1; j >= 0; --j) {
-            Ml += (double)vw.cnt[j] * w;
-            w *= vw.r_inv;
-        }
-    }
-    vw.Ml = Ml;
-    // exclusive scan in thread order (= rank order)
-    int Ci = Cl;
-    double Mi = Ml;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int c = __shfl_up(Ci, d, 64);
-        const double m = __shfl_up(Mi, d, 64);
-        if (lane >= d) { Ci += c; Mi += m; }
-    }
-    if (lane == 63) { sh.wave_C[wave] = Ci; sh.wave_M[wave] = Mi; }
-    __syncthreads();
-    int Cb = carry_C;
-    double Mb = carry_M;
-    int Ct = 0;
-    double Mt = 0.0;
-    for (int w = 0; w < kRWaves; ++w) {
-        if (w < wave) { Cb += sh.wave_C[w]; Mb += sh.wave_M[w]; }
-        Ct += sh.wave_C[w]; Mt += sh.wave_M[w];
-    }
-    __syncthreads();
-    vw.Cx = Cb + Ci - Cl;
-    vw.Mx = Mb + (Mi - Ml);
-    Cw = Ct; Mw = Mt;
-    return true;
-}
-
-// First level whose cumulative count reaches k.  Exactly one thread holds it.
-template <int kOwnT>
-__device__ __forceinline__ void find_count_cut(const ViewT<kOwnT>& vw, int k, Shared& sh)
-{
-    if (vw.Cx < k && vw.Cx + vw.Cl >= k) {
-        int C = vw.Cx;
-        double M = vw.Mx, w = vw.w_top;
-        int bin = vw.b0;
-        bool done = false;
-#pragma unroll
-        for (int j = kOwnT - 1; j >= 0; --j) {
-            if (!done) {
-                C += (int)vw.cnt[j];
-                M += (double)vw.cnt[j] * w;
-                if (C >= k) { bin = vw.b0 + j; done = true; }
-            }
-            w *= vw.r_inv;
-        }
-        sh.cut_bin = bin; sh.cut_C = C; sh.cut_M = M;
-    }
-    __syncthreads();
-}
-
-// First level at or above `floor_bin` whose cumulative mass reaches T.  The scan's
-// per-thread prefixes may disagree in the last bit, so the owner is the first thread
-// whose inclusive prefix reaches T; if rounding lets none of its levels reach T the
-// owner's lowest populated level (or the floor) is taken.
-template <int kOwnT>
-__device__ __forceinline__ void find_mass_cut(const ViewT<kOwnT>& vw, double T, int floor_bin, int floor_C, double floor_M,
-                              Shared& sh, int tid)
-{
-    if (tid == 0) { sh.first_thread = kRThreads; }
-    __syncthreads();
-    if (vw.Cl > 0 && vw.Mx + vw.Ml >= T) atomicMin(&sh.first_thread, tid);
-    __syncthreads();
-    const int owner = sh.first_thread;
-    if (owner == kRThreads) {                        // nobody reaches T: keep down to the floor
-        if (tid == 0) { sh.cut_bin = floor_bin; sh.cut_C = floor_C; sh.cut_M = floor_M; }
-    } else if (tid == owner) {
-        int C = vw.Cx, bin = -1, Cb = 0;
-        double M = vw.Mx, w = vw.w_top, Mb = 0.0;
-        bool done = false;
-#pragma unroll
-        for (int j = kOwnT - 1; j >= 0; --j) {
-            if (!done && vw.cnt[j] != 0) {
-                C += (int)vw.cnt[j];
-                M += (double)vw.cnt[j] * w;
-                bin = vw.b0 + j; Cb = C; Mb = M;      // lowest populated level so far
-                if (M >= T) done = true;
-            }
-            w *= vw.r_inv;
-        }
-        if (bin < floor_bin) { bin = floor_bin; Cb = floor_C; Mb = floor_M; }
-        sh.cut_bin = bin; sh.cut_C = Cb; sh.cut_M = Mb;
-    }
-    __syncthreads();
-}
-
-// Race of the levels in bins [cut_bin, kBins) of the window in LDS: maximise
-// n_j w_j / E_j with E_j = -ln u_j, u_j from Philox stream 3 at index = bit pattern.
-// The scores are formed in fp32 (weights and variates as in the unrestricted sampler);
-// decisions closer than fp32 resolves are the near-ties the parity rule exempts.
-// Bins are dealt round-robin so that a short run of kept levels spreads over threads.
-__device__ __forceinline__ RaceBest race_window(const uint32_t* hist, bool hi, int cut_bin, double z1,
-                                                float c, uint64_t seed, uint64_t grow, RaceBest best,
-                                                Shared& sh, int tid)
-{
-    const int lane = tid & 63, wave = tid >> 6;
-    const float z1f = (float)z1;                      // a bf16 value: exact
-    RaceBest mine{-1.0, 0, 0};
-    for (int bin = kBins - 1 - tid; bin >= cut_bin; bin -= kRThreads) {
-        const uint32_t n = hist[bin];
-        const int bits = bin_bits(hi, bin);
-        if (n == 0 || ((bits >> 7) & 0xFF) == 0xFF) continue;
-        uint32_t w4[4];
-        philox4x32_10((uint32_t)bits >> 2, (uint32_t)grow, (uint32_t)(grow >> 32), 3u,
-                      (uint32_t)seed, (uint32_t)(seed >> 32), w4);
-        const int sel = bits & 3;
-        const uint32_t word = sel == 0 ? w4[0] : sel == 1 ? w4[1] : sel == 2 ? w4[2] : w4[3];
-        const float z = __uint_as_float((uint32_t)bits << 16);
-        const float q = (float)n * __builtin_amdgcn_exp2f((z - z1f) * c) * inv_exp_variate(word);
-        // a thread meets its bins in falling value order: `>` keeps the higher level on ties
-        if ((double)q > mine.q) { mine.q = (double)q; mine.bits = bits; mine.n = (int)n; }
-    }
-    // workgroup argmax; ties to the higher value = higher bin of this window
-    auto bin_of = [&](int bits) { return hi ? bits : 0xFFFF - bits; };
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        const double oq = __shfl_xor(mine.q, d, 64);
-        const int ob = __shfl_xor(mine.bits, d, 64);
-        const int on = __shfl_xor(mine.n, d, 64);
-        if (oq > mine.q || (oq == mine.q && oq >= 0.0 && bin_of(ob) > bin_of(mine.bits))) {
-            mine.q = oq; mine.bits = ob; mine.n = on;
-        }
-    }
-    if (lane == 0) { sh.best_q[wave] = mine.q; sh.best_bits[wave] = mine.bits; sh.best_n[wave] = mine.n; }
-    __syncthreads();
-    RaceBest out = best;                              // an earlier (higher) window wins ties
-    bool from_here = false;
-    for (int w = 0; w < kRWaves; ++w) {
-        const double q = sh.best_q[w];
-        if (q > out.q || (from_here && q == out.q && q >= 0.0 && bin_of(sh.best_bits[w]) > bin_of(out.bits))) {
-            out.q = q; out.bits = sh.best_bits[w]; out.n = sh.best_n[w];
-            from_here = true;
-        }
-    }
-    __syncthreads();
-    return out;
-}
-
-// ---------------------------------------------------------------------------
-// One window.  All 65,536 patterns of a row counted in one sweep, two 16-bit counters per LDS
-// word at the pattern's own index, so that one scan sees the whole row in rank order and no
-// setting needs a second or third sweep.  A counter cannot hold a level of 65,536 columns or
-// more: the counts of a row must add up to its width, a row where they do not (a wrapped
-// counter changes the sum) is handed to the two-window code below, which counts in 32 bits.
-// "Bin" here is the pattern's rank key, ascending in value: 0x8000 + pattern for non-negative
-// patterns, 0xFFFF - pattern for negative ones; thread t owns the 64 bins below 65536 - 64 t,
-// which are 64 consecutive patterns of one sign and one exponent.
-// ---------------------------------------------------------------------------
-constexpr int kBins1 = 65536;
-constexpr int kOwn1 = kBins1 / kRThreads;          // 64
-
-// A thread's share of the one window after the scan.  The counts themselves stay in LDS (64 of
-// them per thread would occupy half the register file across the cut search); the one thread
-// that holds a cut reads its own again.
-struct ScanOne {
-    int b0;               // my lowest bin
-    bool finite;          // my patterns are values (not inf / NaN)
-    double w_top, r_inv;  // weight of my highest bin; factor to the next lower bin
-    int Cl, Cx;           // my count; count of all higher levels
-    double Ml, Mx;        // the same for mass
-};
-
-__device__ __forceinline__ int bits_of_bin1(int bin) { return bin >= 0x8000 ? bin - 0x8000 : 0xFFFF - bin; }
-__device__ __forceinline__ int bin1_of_bits(int bits) { return bits < 0x8000 ? bits + 0x8000 : 0xFFFF - bits; }
-// Word that holds a pattern's counter.  One unused word follows every 32, so that the threads of
-// a wave, each reading the 32 words of its 64 patterns, start in 64 different banks.
-constexpr int kWords1 = kBins1 / 2 + kBins1 / 64;
-__device__ __forceinline__ uint32_t word1(uint32_t bits) { return (bits >> 1) + (bits >> 6); }
-__device__ __forceinline__ uint32_t count1(const uint32_t* hist, int bits)
-{
-    return (hist[word1((uint32_t)bits)] >> ((bits & 1) * 16)) & 0xFFFFu;
-}
-
-__device__ __forceinline__ void build_hist1(const uint16_t* __restrict__ row, int64_t V, uint32_t* hist, int tid)
-{
-    const uint4 zero4 = {0u, 0u, 0u, 0u};
-    for (int i = tid; i < kWords1 / 4; i += kRThreads) reinterpret_cast<uint4*>(hist)[i] = zero4;
-    __syncthreads();
-    auto add2 = [&](uint32_t x) {                       // the two patterns of one word
-        atomicAdd(&hist[word1(x & 0xFFFFu)], (x & 1u) ? 0x10000u : 1u);
-        atomicAdd(&hist[word1(x >> 16)], (x & 0x10000u) ? 0x10000u : 1u);
-    };
-    auto add8 = [&](const u32x4& v) { add2(v.x); add2(v.y); add2(v.z); add2(v.w); };
-    const int64_t nvec = V >> 3;
-    const u32x4* rv = reinterpret_cast<const u32x4*>(row);
-    int64_t v = tid;
-    for (; v + 3 * kRThreads < nvec; v += 4 * kRThreads) {
-        const u32x4 a = rv[v], b = rv[v + kRThreads], c = rv[v + 2 * kRThreads], d = rv[v + 3 * kRThreads];
-        add8(a); add8(b); add8(c); add8(d);
-    }
-    for (; v < nvec; v += kRThreads) add8(rv[v]);
-    const int64_t tail0 = nvec << 3;
-    if (tid < V - tail0) {
-        const uint32_t pat = row[tail0 + tid];
-        atomicAdd(&hist[word1(pat)], (pat & 1u) ? 0x10000u : 1u);
-    }
-    __syncthreads();
-}
-
-// Scan of the one window.  Returns 0 if a counter has wrapped (the caller falls back), 1 if
-// the row has no finite value, 2 otherwise, with z1 = the row's highest level, the window's
-// count and mass in Cw / Mw and the thread's view filled in.
-__device__ __forceinline__ int scan_one_window(const uint32_t* hist, int64_t V, double inv_tau, double& z1,
-                                               ScanOne& vw, int& Cw, double& Mw, Shared& sh, int tid)
-{
-    const int lane = tid & 63, wave = tid >> 6;
-    vw.b0 = kBins1 - kOwn1 * (tid + 1);                // thread 0 owns the highest bins
-    const bool nonneg = vw.b0 >= 0x8000;
-    const int p_low = nonneg ? vw.b0 - 0x8000 : 0xFFFF - (vw.b0 + kOwn1 - 1);    // my lowest pattern, a multiple of 64
-    const int exp_field = (p_low >> 7) & 0xFF;         // the same for all my patterns
-    const bool finite = exp_field != 0xFF;             // inf / NaN patterns are not levels
-    vw.finite = finite;
-    int all = 0, Cl = 0, my_top = -1;
-    uint32_t cnt[kOwn1];                               // in bin order; dead once my mass is summed
-    // ascending bin = ascending pattern for non-negative values, descending for negative ones:
-    // the negative half reads its words, and the two counters of a word, in reverse
-#pragma unroll
-    for (int i = 0; i < kOwn1 / 2; ++i) {
-        const uint32_t word = hist[word1((uint32_t)p_low) + (nonneg ? i : kOwn1 / 2 - 1 - i)];
-        const uint32_t lo = word & 0xFFFFu, hi = word >> 16;
-        const uint32_t n0 = nonneg ? lo : hi, n1 = nonneg ? hi : lo;
-        all += (int)(n0 + n1);
-        cnt[2 * i] = finite ? n0 : 0u;
-        cnt[2 * i + 1] = finite ? n1 : 0u;
-        Cl += (int)(cnt[2 * i] + cnt[2 * i + 1]);
-        if (cnt[2 * i] != 0) my_top = vw.b0 + 2 * i;
-        if (cnt[2 * i + 1] != 0) my_top = vw.b0 + 2 * i + 1;
-    }
-    vw.Cl = Cl;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) all += __shfl_xor(all, d, 64);
-    const float t = wave_max((float)my_top);           // bins are below 2^16: exact in fp32
-    if (lane == 0) { sh.wave_top[wave] = t; sh.wave_A[wave] = all; }
-    __syncthreads();
-    float top = -1.0f;
-    long long total = 0;
-    for (int w = 0; w < kRWaves; ++w) { top = fmaxf(top, sh.wave_top[w]); total += sh.wave_A[w]; }
-    __syncthreads();
-    if (total != (long long)V) return 0;
-    if (top < 0.0f) { Cw = 0; Mw = 0.0; return 1; }
-    z1 = bf16_value(bits_of_bin1((int)top));
-    // my 64 values are equally spaced (half a binade, or subnormals): geometric weights
-    double Ml = 0.0;
-    vw.w_top = 0.0; vw.r_inv = 0.0;
-    if (Cl > 0) {
-        const double z_top = bf16_value(bits_of_bin1(vw.b0 + kOwn1 - 1));
-        const double step = ldexp(1.0, (exp_field ? exp_field : 1) - 134);
-        vw.w_top = exp((z_top - z1) * inv_tau);
-        vw.r_inv = exp(-step * inv_tau);
-        double w = vw.w_top;
-#pragma unroll
-        for (int j = kOwn1 - 1; j >= 0; --j) {
-            Ml += (double)cnt[j] * w;
-            w *= vw.r_inv;
-        }
-    }
-    vw.Ml = Ml;
-    // exclusive scan in thread order (= rank order)
-    int Ci = Cl;
-    double Mi = Ml;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int c = __shfl_up(Ci, d, 64);
-        const double m = __shfl_up(Mi, d, 64);
-        if (lane >= d) { Ci += c; Mi += m; }
-    }
-    if (lane == 63) { sh.wave_C[wave] = Ci; sh.wave_M[wave] = Mi; }
-    __syncthreads();
-    int Cb = 0, Ct = 0;
-    double Mb = 0.0, Mt = 0.0;
-    for (int w = 0; w < kRWaves; ++w) {
-        if (w < wave) { Cb += sh.wave_C[w]; Mb += sh.wave_M[w]; }
-        Ct += sh.wave_C[w]; Mt += sh.wave_M[w];
-    }
-    __syncthreads();
-    vw.Cx = Cb + Ci - Cl;
-    vw.Mx = Mb + (Mi - Ml);
-    Cw = Ct; Mw = Mt;
-    return 2;
-}
-
-// The two cut searches of the one window: as find_count_cut / find_mass_cut, with the owner
-// thread reading its counts from LDS again.
-// The owner's 64 counts in bin order, read in one go (its 32 words are consecutive).
-__device__ __forceinline__ void own_counts1(const uint32_t* hist, const ScanOne& vw, uint32_t cnt[kOwn1])
-{
-    const bool nonneg = vw.b0 >= 0x8000;
-    const int p_low = nonneg ? vw.b0 - 0x8000 : 0xFFFF - (vw.b0 + kOwn1 - 1);
-#pragma unroll
-    for (int i = 0; i < kOwn1 / 2; ++i) {
-        const uint32_t word = hist[word1((uint32_t)p_low) + (nonneg ? i : kOwn1 / 2 - 1 - i)];
-        const uint32_t lo = word & 0xFFFFu, hi = word >> 16;
-        cnt[2 * i] = vw.finite ? (nonneg ? lo : hi) : 0u;
-        cnt[2 * i + 1] = vw.finite ? (nonneg ? hi : lo) : 0u;
-    }
-}
-
-__device__ __forceinline__ void find_count_cut1(const uint32_t* hist, const ScanOne& vw, int k, Shared& sh)
-{
-    if (vw.Cx < k && vw.Cx + vw.Cl >= k) {
-        int C = vw.Cx;
-        double M = vw.Mx, w = vw.w_top;
-        int bin = vw.b0;
-        uint32_t cnt[kOwn1];
-        own_counts1(hist, vw, cnt);
-        bool done = false;
-#pragma unroll
-        for (int j = kOwn1 - 1; j >= 0; --j) {
-            if (!done) {
-                C += (int)cnt[j];
-                M += (double)cnt[j] * w;
-                if (C >= k) { bin = vw.b0 + j; done = true; }
-            }
-            w *= vw.r_inv;
-        }
-        sh.cut_bin = bin; sh.cut_C = C; sh.cut_M = M;
-    }
-    __syncthreads();
-}
-
-__device__ __forceinline__ void find_mass_cut1(const uint32_t* hist, const ScanOne& vw, double T, int floor_bin,
-                                               int floor_C, double floor_M, Shared& sh, int tid)
-{
-    if (tid == 0) { sh.first_thread = kRThreads; }
-    __syncthreads();
-    if (vw.Cl > 0 && vw.Mx + vw.Ml >= T) atomicMin(&sh.first_thread, tid);
-    __syncthreads();
-    const int owner = sh.first_thread;
-    if (owner == kRThreads) {                        // nobody reaches T: keep down to the floor
-        if (tid == 0) { sh.cut_bin = floor_bin; sh.cut_C = floor_C; sh.cut_M = floor_M; }
-    } else if (tid == owner) {
-        int C = vw.Cx, bin = -1, Cb = 0;
-        double M = vw.Mx, w = vw.w_top, Mb = 0.0;
-        uint32_t cnt[kOwn1];
-        own_counts1(hist, vw, cnt);
-        bool done = false;
-#pragma unroll
-        for (int j = kOwn1 - 1; j >= 0; --j) {
-            if (!done && cnt[j] != 0) {
-                C += (int)cnt[j];
-                M += (double)cnt[j] * w;
-                bin = vw.b0 + j; Cb = C; Mb = M;      // lowest populated level so far
-                if (M >= T) done = true;
-            }
-            w *= vw.r_inv;
-        }
-        if (bin < floor_bin) { bin = floor_bin; Cb = floor_C; Mb = floor_M; }
-        sh.cut_bin = bin; sh.cut_C = Cb; sh.cut_M = Mb;
-    }
-    __syncthreads();
-}
-
-// Race of the levels in bins [cut_bin, 65536) of the one window; same scores, same tie
-// rule (the higher value) as race_window.
-__device__ __forceinline__ RaceBest race_one_window(const uint32_t* hist, int cut_bin, double z1, float c,
-                                                    uint64_t seed, uint64_t grow, Shared& sh, int tid)
-{
-    const int lane = tid & 63, wave = tid >> 6;
-    const float z1f = (float)z1;                      // a bf16 value: exact
-    RaceBest mine{-1.0, 0, 0};
-    for (int bin = kBins1 - 1 - tid; bin >= cut_bin; bin -= kRThreads) {
-        const int bits = bits_of_bin1(bin);
-        const uint32_t n = count1(hist, bits);
-        if (n == 0 || ((bits >> 7) & 0xFF) == 0xFF) continue;
-        uint32_t w4[4];
-        philox4x32_10((uint32_t)bits >> 2, (uint32_t)grow, (uint32_t)(grow >> 32), 3u,
-                      (uint32_t)seed, (uint32_t)(seed >> 32), w4);
-        const int sel = bits & 3;
-        const uint32_t word = sel == 0 ? w4[0] : sel == 1 ? w4[1] : sel == 2 ? w4[2] : w4[3];
-        const float z = __uint_as_float((uint32_t)bits << 16);
-        const float q = (float)n * __builtin_amdgcn_exp2f((z - z1f) * c) * inv_exp_variate(word);
-        // a thread meets its bins in falling value order: `>` keeps the higher level on ties
-        if ((double)q > mine.q) { mine.q = (double)q; mine.bits = bits; mine.n = (int)n; }
-    }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        const double oq = __shfl_xor(mine.q, d, 64);
-        const int ob = __shfl_xor(mine.bits, d, 64);
-        const int on = __shfl_xor(mine.n, d, 64);
-        if (oq > mine.q || (oq == mine.q && oq >= 0.0 && bin1_of_bits(ob) > bin1_of_bits(mine.bits))) {
-            mine.q = oq; mine.bits = ob; mine.n = on;
-        }
-    }
-    if (lane == 0) { sh.best_q[wave] = mine.q; sh.best_bits[wave] = mine.bits; sh.best_n[wave] = mine.n; }
-    __syncthreads();
-    RaceBest out{-1.0, 0, 0};
-    for (int w = 0; w < kRWaves; ++w) {
-        const double q = sh.best_q[w];
-        if (q > out.q || (q == out.q && q >= 0.0 && bin1_of_bits(sh.best_bits[w]) > bin1_of_bits(out.bits))) {
-            out.q = q; out.bits = sh.best_bits[w]; out.n = sh.best_n[w];
-        }
-    }
-    __syncthreads();
-    return out;
-}
-
-// Step 3, last part, when the winning level has at most kListCap columns (the usual
-// case): one pipelined sweep over the row in which every thread notes the vectors that
-// hold the pattern in a short LDS list; the pos-th column in column order is then picked
-// from the list by ranking its entries.
-__device__ __forceinline__ int locate_listed(const uint16_t* __restrict__ row, int64_t V, int bits,
-                                             int pos, Shared& sh, int tid)
-{
-    if (tid == 0) { sh.list_n = 0; sh.token = -1; }
-    __syncthreads();
-    const int64_t nvec = V >> 3;
-    const u32x4* rv = reinterpret_cast<const u32x4*>(row);
-    const uint32_t pat = (uint32_t)bits, pat2 = pat | (pat << 16);
-    auto zero_half = [](uint32_t x) -> uint32_t { return (x - 0x00010001u) & ~x & 0x80008000u; };
-    auto note = [&](int64_t v, const u32x4& t) {
-        const uint32_t a = t.x ^ pat2, b = t.y ^ pat2, c = t.z ^ pat2, d = t.w ^ pat2;
-        if ((zero_half(a) | zero_half(b) | zero_half(c) | zero_half(d)) != 0u) {
-            uint32_t m = 0;
-            m |= ((a & 0xFFFFu) == 0u) << 0; m |= ((a >> 16) == 0u) << 1;
-            m |= ((b & 0xFFFFu) == 0u) << 2; m |= ((b >> 16) == 0u) << 3;
-            m |= ((c & 0xFFFFu) == 0u) << 4; m |= ((c >> 16) == 0u) << 5;
-            m |= ((d & 0xFFFFu) == 0u) << 6; m |= ((d >> 16) == 0u) << 7;
-            if (m != 0u) {
-                const int slot = atomicAdd(&sh.list_n, 1);
-                if (slot < kListCap) sh.list[slot] = ((uint32_t)v << 8) | m;
-            }
-        }
-    };
-    const u32x4 filler = {~pat2, ~pat2, ~pat2, ~pat2};           // matches nothing
-    for (int64_t v0 = tid; v0 < nvec; v0 += 8 * kRThreads) {
-        u32x4 t[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int64_t vv = v0 + (int64_t)j * kRThreads;
-            t[j] = vv < nvec ? rv[vv] : filler;
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) note(v0 + (int64_t)j * kRThreads, t[j]);
-    }
-    if (tid == 0) {                                              // columns after the last whole vector
-        uint32_t m = 0;
-        for (int64_t c = nvec << 3; c < V; ++c)
-            if ((uint32_t)row[c] == pat) m |= 1u << (int)(c - (nvec << 3));
-        if (m != 0u) {
-            const int slot = atomicAdd(&sh.list_n, 1);
-            if (slot < kListCap) sh.list[slot] = ((uint32_t)nvec << 8) | m;
-        }
-    }
-    __syncthreads();
-    const int cnt = sh.list_n < kListCap ? sh.list_n : kListCap;
-    if (tid < cnt) {
-        const uint32_t mine = sh.list[tid];
-        int rank = 0;
-        for (int e = 0; e < cnt; ++e) {
-            const uint32_t o = sh.list[e];
-            if ((o >> 8) < (mine >> 8)) rank += __popc(o & 0xFFu);
-        }
-        const int here = __popc(mine & 0xFFu);
-        if (pos >= rank && pos < rank + here) {
-            uint32_t mm = mine & 0xFFu;
-            for (int skip = pos - rank; skip > 0; --skip) mm &= mm - 1;   // drop the lowest set bits
-            sh.token = (int)((mine >> 8) * 8u) + (__ffs(mm) - 1);
-        }
-    }
-    __syncthreads();
-    return sh.token;
-}
-
-// Step 3, last part, for levels of any size: the pos-th column (0-based, increasing
-// column order) that stores `bits`, by counting.  Waves take contiguous runs of 16-byte vectors; the few columns past the last
-// whole vector come last.
-__device__ __forceinline__ int locate_column(const uint16_t* __restrict__ row, int64_t V, int bits, int pos,
-                             Shared& sh, int tid)
-{
-    const int lane = tid & 63, wave = tid >> 6;
-    const int64_t nvec = V >> 3;
-    const int64_t per_wave = (nvec + kRWaves - 1) / kRWaves;
-    const int64_t v_begin = (int64_t)wave * per_wave < nvec ? (int64_t)wave * per_wave : nvec;
-    const int64_t v_end = v_begin + per_wave < nvec ? v_begin + per_wave : nvec;
-    const u32x4* rv = reinterpret_cast<const u32x4*>(row);
-    const uint32_t pat = (uint32_t)bits;
-    auto mask_of = [&](const u32x4& v) -> uint32_t {
-        uint32_t m = 0;
-        m |= ((v.x & 0xFFFFu) == pat) << 0; m |= ((v.x >> 16) == pat) << 1;
-        m |= ((v.y & 0xFFFFu) == pat) << 2; m |= ((v.y >> 16) == pat) << 3;
-        m |= ((v.z & 0xFFFFu) == pat) << 4; m |= ((v.z >> 16) == pat) << 5;
-        m |= ((v.w & 0xFFFFu) == pat) << 6; m |= ((v.w >> 16) == pat) << 7;
-        return m;
-    };
-    // hits of my wave's run
-    int hits = 0;
-    for (int64_t v = v_begin + lane; v < v_end; v += 64) hits += __popc(mask_of(rv[v]));
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) hits += __shfl_xor(hits, d, 64);
-    if (lane == 0) sh.wave_hits[wave] = hits;
-    if (tid == 0) sh.token = -1;
-    __syncthreads();
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += sh.wave_hits[w];
-    int total = 0;
-    for (int w = 0; w < kRWaves; ++w) total += sh.wave_hits[w];
-    if (pos >= before && pos < before + hits) {       // uniform per wave: my run holds it
-        int rem = pos - before;
-        for (int64_t v0 = v_begin; v0 < v_end; v0 += 64) {
-            const int64_t v = v0 + lane;
-            const uint32_t m = v < v_end ? mask_of(rv[v]) : 0u;
-            const int c = __popc(m);
-            int inc = c;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int o = __shfl_up(inc, d, 64);
-                if (lane >= d) inc += o;
-            }
-            const int sweep_total = __shfl(inc, 63, 64);
-            if (rem < sweep_total) {
-                if (rem >= inc - c && rem < inc) {    // exactly one lane
-                    int skip = rem - (inc - c);
-                    uint32_t mm = m;
-                    while (skip-- > 0) mm &= mm - 1;  // drop the lowest set bits
-                    sh.token = (int)(v * 8 + (__ffs(mm) - 1));
-                }
-                break;
-            }
-            rem -= sweep_total;
-        }
-    }
-    // the columns after the last whole vector
-    if (tid == 0 && pos >= total) {
-        int rem = pos - total;
-        for (int64_t c = nvec << 3; c < V; ++c)
-            if ((uint32_t)row[c] == pat && rem-- == 0) { sh.token = (int)c; break; }
-    }
-    __syncthreads();
-    return sh.token;
-}
 
 struct RestrictedArgs {
     const uint16_t* logits;
@@ -712,175 +99,823 @@ struct RestrictedArgs {
     int32_t* kept_out;
 };
 
-__global__ __launch_bounds__(kRThreads)
-void sample_restricted_kernel(RestrictedArgs a)
-{
-    __shared__ __align__(16) uint32_t hist[kWords1 > kBins + kTrashBins ? kWords1 : kBins + kTrashBins];
-    __shared__ Shared sh;
-    const int tid = threadIdx.x;
-    const int64_t row = blockIdx.x;
-    const int64_t V = a.V;
-    const uint16_t* rowp = a.logits + row * a.row_stride;
-    const float tau = a.tau_rows ? a.tau_rows[row] : a.tau_scalar;
-    const double inv_tau = 1.0 / (double)tau;
-    const float c = kLog2eF / tau;
-    const uint64_t grow = a.row_base + (uint64_t)row;
-    const bool k_on = a.top_k >= 1 && (int64_t)a.top_k < V;
-    const bool p_on = a.top_p < 1.0f;
-    const double p = (double)a.top_p;
-    const int k = a.top_k;
-
-    double z1 = 0.0;
-    RaceBest best{-1.0, 0, 0};
-    int kept_C = 0;
-    double kept_M = 0.0;
-
-    // One sweep, one scan, whatever the setting; rows with a level too long for a 16-bit
-    // counter take the two-window code after it.
-    bool done = false;
+// The row as 16-byte vectors, kRThreads of them per step.  The last vector may reach past the row's
+// columns (inside the row pitch, whose 16-byte multiple the interface demands): what it holds
+// there, and vectors past the row, read as patterns that are not numbers.
+struct Row {
+    const u32x4* p;
+    int nvec, last;       // vectors; columns in the last one, 1 .. 8
+    int steps, whole;     // steps, and how many of them hold nothing but complete vectors
+    __device__ __forceinline__ u32x4 guarded(int v) const
     {
-        ScanOne v1;
-        int C_all = 0;
-        double M_all = 0.0;
-        build_hist1(rowp, V, hist, tid);
-        const int state = scan_one_window(hist, V, inv_tau, z1, v1, C_all, M_all, sh, tid);
-        if (state != 0) {
-            done = true;
-            if (state == 2) {
-                int cb = 0;
-                kept_C = C_all; kept_M = M_all;
-                if (k_on && C_all >= k) {
-                    find_count_cut1(hist, v1, k, sh);
-                    cb = sh.cut_bin; kept_C = sh.cut_C; kept_M = sh.cut_M;
-                    __syncthreads();
-                }
-                if (p_on) {
-                    find_mass_cut1(hist, v1, p * kept_M, cb, kept_C, kept_M, sh, tid);
-                    cb = sh.cut_bin; kept_C = sh.cut_C; kept_M = sh.cut_M;
-                    __syncthreads();
-                }
-                best = race_one_window(hist, cb, z1, c, a.seed, grow, sh, tid);
-            }
+        constexpr uint32_t kNone = 0x7FC07FC0u;
+        u32x4 x = {kNone, kNone, kNone, kNone};
+        if (v < nvec) x = p[v];
+        if (v == nvec - 1) {
+            auto fill = [&](uint32_t word, int first) -> uint32_t {
+                return last <= first ? kNone : last == first + 1 ? (word & 0xFFFFu) | (kNone & 0xFFFF0000u) : word;
+            };
+            x = u32x4{fill(x.x, 0), fill(x.y, 2), fill(x.z, 4), fill(x.w, 6)};
         }
+        return x;
     }
-
-    View vw;
-    int C_hi = 0, C_lo = 0;
-    double M_hi = 0.0, M_lo = 0.0;
-    if (!done) {
-
-    // Without top-k the nucleus target is a fraction of the whole row's mass, which
-    // includes the negative patterns: total them first, relative to the value 0.
-    double neg_mass_ref0 = 0.0;
-    if (!k_on && p_on) {
-        build_hist(rowp, V, false, hist, tid);
-        double zero_ref = 0.0;
-        int Cn;
-        scan_window(hist, false, inv_tau, false, zero_ref, 0, 0.0, vw, Cn, neg_mass_ref0, sh, tid);
-    }
-
-    build_hist(rowp, V, true, hist, tid);
-    const bool any_hi = scan_window(hist, true, inv_tau, true, z1, 0, 0.0, vw, C_hi, M_hi, sh, tid);
-
-    // Does the kept set end inside the non-negative window?
-    bool cut_in_hi = false;
-    if (any_hi) {
-        if (k_on) {
-            if (C_hi >= k) {
-                find_count_cut(vw, k, sh);
-                const int kb = sh.cut_bin, kC = sh.cut_C;
-                const double kM = sh.cut_M;
-                __syncthreads();
-                if (p_on) find_mass_cut(vw, p * kM, kb, kC, kM, sh, tid);
-                cut_in_hi = true;
-            }
-        } else if (p_on) {
-            const double T = p * (M_hi + neg_mass_ref0 * exp(-z1 * inv_tau));
-            if (M_hi >= T) {
-                find_mass_cut(vw, T, 0, C_hi, M_hi, sh, tid);
-                cut_in_hi = true;
-            }
-        }
-        if (cut_in_hi) {
-            const int cb = sh.cut_bin;
-            kept_C = sh.cut_C; kept_M = sh.cut_M;
-            __syncthreads();
-            best = race_window(hist, true, cb, z1, c, a.seed, grow, best, sh, tid);
+    // kN steps from `step` on, requested together; those at or past `end` read as nothing
+    template <int kN>
+    __device__ __forceinline__ void request(u32x4 x[kN], int step, int end, int tid) const
+    {
+        if (step + kN <= (whole < end ? whole : end)) {           // uniform: plain loads, nothing waits on them here
+#pragma unroll
+            for (int u = 0; u < kN; ++u) x[u] = p[tid + (step + u) * kRThreads];
         } else {
-            best = race_window(hist, true, 0, z1, c, a.seed, grow, best, sh, tid);
-            kept_C = C_hi; kept_M = M_hi;
+#pragma unroll
+            for (int u = 0; u < kN; ++u) x[u] = guarded(step + u < end ? tid + (step + u) * kRThreads : nvec);
         }
     }
+};
 
-    if (!cut_in_hi) {
-        // The kept set reaches the negative patterns (or the row has no others).
-        build_hist(rowp, V, false, hist, tid);
-        const bool any_lo = scan_window(hist, false, inv_tau, !any_hi, z1, C_hi, M_hi, vw, C_lo, M_lo, sh, tid);
-        if (any_lo) {
-            int cb = 0;
-            int cC = C_hi + C_lo;
-            double cM = M_hi + M_lo;
-            bool back_to_hi = false;
-            if (k_on) {
-                if (C_hi + C_lo >= k && C_hi < k) {
-                    find_count_cut(vw, k, sh);
-                    cb = sh.cut_bin; cC = sh.cut_C; cM = sh.cut_M;
-                    __syncthreads();
-                }
-                if (p_on) {
-                    const double T = p * cM;
-                    if (any_hi && M_hi >= T) back_to_hi = true;       // nucleus ends above this window
-                    else {
-                        find_mass_cut(vw, T, cb, cC, cM, sh, tid);
-                        cb = sh.cut_bin; cC = sh.cut_C; cM = sh.cut_M;
-                        __syncthreads();
+template <typename F>
+__device__ __forceinline__ void for_each_pattern(const u32x4& v, F&& f)
+{
+    f(v.x & 0xFFFFu, 0); f(v.x >> 16, 1); f(v.y & 0xFFFFu, 2); f(v.y >> 16, 3);
+    f(v.z & 0xFFFFu, 4); f(v.z >> 16, 5); f(v.w & 0xFFFFu, 6); f(v.w >> 16, 7);
+}
+
+// Inclusive prefix sums over the lanes of a wave (see wave_max for the steps).
+template <typename T, typename Step>
+__device__ __forceinline__ T wave_prefix(T v, Step&& step)
+{
+    v += step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{}, v);    // row_shr 1, 2, 4, 8
+    v += step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{}, v);
+    v += step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{}, v);
+    v += step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{}, v);
+    v += step(std::integral_constant<int, kDppBcast15>{}, std::integral_constant<int, 0xA>{}, v);
+    v += step(std::integral_constant<int, kDppBcast31>{}, std::integral_constant<int, 0xC>{}, v);
+    return v;
+}
+__device__ __forceinline__ int wave_prefix_i(int v)
+{
+    return wave_prefix(v, [](auto c, auto m, int x) { return dpp_i<decltype(c)::value, decltype(m)::value>(0, x); });
+}
+__device__ __forceinline__ double wave_prefix_d(double v)
+{
+    return wave_prefix(v, [](auto c, auto m, double x) { return dpp_d<decltype(c)::value, decltype(m)::value>(0.0, x); });
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// A thread's levels after the scan: levels of one binade in falling rank order, `top` the first
+// with columns (weight w_top, at most 1), each later one `r` times the weight of the one before.
+struct View {
+    int top;
+    double w_top, r;
+    int Cl, Cx;           // my count; count of all higher levels
+    double Ml, Mx;        // the same for mass
+};
+
+// The weight after level j's: levels before `top` have no columns and keep w_top (their own weight
+// may lie beyond fp64 when the thread holds levels above the row's highest).
+__device__ __forceinline__ double next_weight(const View& vw, double w, int j) { return j < vw.top ? w : w * vw.r; }
+
+// Weights and mass of a thread's levels: cnt(j) columns on level j, z_top the value of level `top`,
+// e the binade's exponent field.
+template <int kOwn, int kUnroll, typename Cnt>
+__device__ __forceinline__ void own_mass(View& vw, int e, float z_top, double z1, double inv_tau, Cnt&& cnt)
+{
+    vw.w_top = 0.0; vw.r = 0.0; vw.Ml = 0.0;
+    if (vw.Cl > 0) {
+        vw.w_top = exp(((double)z_top - z1) * inv_tau);
+        vw.r = exp(-ldexp(1.0, (e ? e : 1) - 134) * inv_tau);
+        double w = vw.w_top, m = 0.0;
+#pragma unroll kUnroll
+        for (int j = 0; j < kOwn; ++j) {
+            m = fma((double)cnt(j), w, m);
+            w = next_weight(vw, w, j);
+        }
+        vw.Ml = m;
+    }
+}
+
+// Exclusive scan of counts and masses in thread order = rank order; threads from `mid_at` on
+// also have (mid_C, mid_M) before them.  Returns the totals of the scanned levels.
+__device__ __forceinline__ void scan_view(View& vw, int carry_C, double carry_M, int mid_at, int mid_C, double mid_M,
+                                          int& Ct, double& Mt, Shared& sh, int tid)
+{
+    const int lane = tid & 63, wave = tid >> 6;
+    const int Ci = wave_prefix_i(vw.Cl);
+    const double Mi = wave_prefix_d(vw.Ml);
+    if (lane == 63) { sh.wave_C[wave] = Ci; sh.wave_M[wave] = Mi; }
+    __syncthreads();
+    const int tC = wave_prefix_i(lane < kRWaves ? sh.wave_C[lane] : 0);
+    const double tM = wave_prefix_d(lane < kRWaves ? sh.wave_M[lane] : 0.0);
+    Ct = __builtin_amdgcn_readlane(tC, kRWaves - 1);
+    Mt = lane_value(tM, kRWaves - 1);
+    int Cb = carry_C;
+    double Mb = carry_M;
+    if (wave > 0) { Cb += __builtin_amdgcn_readlane(tC, wave - 1); Mb += lane_value(tM, wave - 1); }
+    if (tid >= mid_at) { Cb += mid_C; Mb += mid_M; }
+    vw.Cx = Cb + Ci - vw.Cl;
+    vw.Mx = Mb + (Mi - vw.Ml);
+}
+
+// Cut searches among one thread's levels.  Count: the level whose cumulative count reaches k.
+// Mass: the first populated level whose cumulative mass reaches T, or the lowest populated one
+// if rounding lets none reach it.
+struct Cut { int j, C; double M; };       // level j of the thread; count and mass down to it
+
+template <int kOwn, int kUnroll, typename Cnt>
+__device__ __forceinline__ Cut own_count_cut(const View& vw, int k, Cnt&& cnt)
+{
+    Cut cut{kOwn - 1, vw.Cx, vw.Mx};
+    double w = vw.w_top;
+    bool done = false;
+#pragma unroll kUnroll
+    for (int j = 0; j < kOwn; ++j) {
+        const int n = (int)cnt(j);
+        if (!done) {
+            cut.j = j; cut.C += n; cut.M = fma((double)n, w, cut.M);
+            done = cut.C >= k;
+        }
+        w = next_weight(vw, w, j);
+    }
+    return cut;
+}
+template <int kOwn, int kUnroll, typename Cnt>
+__device__ __forceinline__ Cut own_mass_cut(const View& vw, double T, Cnt&& cnt)
+{
+    Cut cut{kOwn - 1, vw.Cx, vw.Mx};
+    double w = vw.w_top;
+    bool done = false;
+#pragma unroll kUnroll
+    for (int j = 0; j < kOwn; ++j) {
+        const int n = (int)cnt(j);
+        if (!done && n != 0) {
+            cut.j = j; cut.C += n; cut.M = fma((double)n, w, cut.M);
+            done = cut.M >= T;
+        }
+        w = next_weight(vw, w, j);
+    }
+    return cut;
+}
+
+// The mass cut of the workgroup: the owner is the first thread in rank order whose inclusive prefix
+// reaches T (the scan's prefixes may disagree in the last bit, so only threads with columns count).
+// Every wave's first such thread searches its levels and offers the result; the lowest wave's is taken.
+template <int kOwn, int kUnroll, typename Cnt, typename Key>
+__device__ __forceinline__ void offer_mass_cut(const View& vw, double T, Cnt&& cnt, Key&& key, Shared& sh, int tid)
+{
+    const int lane = tid & 63, wave = tid >> 6;
+    const unsigned long long reach = __ballot(vw.Cl > 0 && vw.Mx + vw.Ml >= T);
+    if (reach == 0ull) {
+        if (lane == 0) sh.cut_key[wave] = -1;
+    } else if (lane == (int)__builtin_ctzll(reach)) {
+        const Cut cut = own_mass_cut<kOwn, kUnroll>(vw, T, cnt);
+        sh.cut_key[wave] = key(cut.j); sh.cut_C[wave] = cut.C; sh.cut_M[wave] = cut.M;
+    }
+}
+// The first wave with an offer, or kRWaves.
+__device__ __forceinline__ int first_offer(const Shared& sh, int lane)
+{
+    const unsigned long long have = __ballot(lane < kRWaves && sh.cut_key[lane & 15] >= 0);
+    return have != 0ull ? (int)__builtin_ctzll(have) : kRWaves;
+}
+
+// A contestant of the race: score n w / E and a label that is lower for a higher level (ties go
+// to the higher level, as Cand's go to the lower label).
+__device__ __forceinline__ Cand contestant(float q, int key) { return Cand{q, 0xFFFF - key}; }
+__device__ __forceinline__ int key_of(const Cand& c) { return 0xFFFF - c.idx; }
+
+// Score of the level with pattern p and n columns: n 2^{(z - z_1) c} / E, E = -ln u from Philox
+// stream 3 at index = the pattern.  fp32, as in the unrestricted sampler; decisions closer than
+// fp32 resolves are the near-ties the parity rule exempts.
+__device__ __forceinline__ float level_score(int p, int n, float z1f, float c, uint64_t seed, uint64_t grow)
+{
+    uint32_t w4[4];
+    philox4x32_10((uint32_t)p >> 2, (uint32_t)grow, (uint32_t)(grow >> 32), 3u, (uint32_t)seed, (uint32_t)(seed >> 32), w4);
+    const int sel = p & 3;
+    const uint32_t word = sel == 0 ? w4[0] : sel == 1 ? w4[1] : sel == 2 ? w4[2] : w4[3];
+    return (float)n * __builtin_amdgcn_exp2f((value_of_pattern(p) - z1f) * c) * inv_exp_variate(word);
+}
+
+// The workgroup's best contestant.
+__device__ __forceinline__ Cand reduce_best(Cand b, Shared& sh, int tid)
+{
+    const int lane = tid & 63;
+    b = wave_best(b);
+    if (lane == 0) sh.best[tid >> 6] = b;
+    __syncthreads();
+    static_assert(kRWaves == 16, "one lane of a sixteen-lane row per wave");
+    return row16_best(sh.best[lane & 15]);
+}
+
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 halves(uint32_t w) { return __builtin_bit_cast(u16x2, w); }
+
+// How many of the vector's eight patterns are not `pat`.
+__device__ __forceinline__ int columns_unlike(const u32x4& x, uint32_t pat)
+{
+    const u16x2 p2 = halves(pat | pat << 16), one = {1, 1};
+    const u16x2 n = __builtin_elementwise_min(halves(x.x) ^ p2, one) + __builtin_elementwise_min(halves(x.y) ^ p2, one)
+                  + __builtin_elementwise_min(halves(x.z) ^ p2, one) + __builtin_elementwise_min(halves(x.w) ^ p2, one);
+    return (int)n.x + (int)n.y;
+}
+
+// The rem-th column (0-based, in column order) that stores pattern `pat` within stream steps
+// [i0, i1): kBlock steps are requested at once; a (step, wave) holds 512 consecutive columns, so the
+// waves' counts per step, in that order, say where the column is, and the wave that holds it
+// finds the lane.  -1 if there are not that many.
+__device__ __forceinline__ int locate(const Row& row, int i0, int i1, uint32_t pat, int rem, Shared& sh, int tid)
+{
+    const int lane = tid & 63, wave = tid >> 6;
+    if (tid == 0) sh.token = -1;
+    for (int ib = i0; ib < i1; ib += kBlock) {
+        u32x4 x[kBlock];
+        row.request<kBlock>(x, ib, i1, tid);
+        int inc[kBlock], own[kBlock];
+#pragma unroll
+        for (int u = 0; u < kBlock; ++u) {
+            own[u] = 8 - columns_unlike(x[u], pat);
+            inc[u] = wave_prefix_i(own[u]);
+            if (lane == 63) sh.tot[u * kRWaves + wave] = inc[u];
+        }
+        __syncthreads();
+        // every wave finds the (step, wave) that holds the column: two consecutive totals per lane
+        static_assert(kBlock * kRWaves <= 128 && kBlock * kRWaves % 2 == 0, "two totals per lane");
+        const bool some = 2 * lane < kBlock * kRWaves;
+        const int t0 = some ? sh.tot[2 * lane] : 0, t1 = some ? sh.tot[2 * lane + 1] : 0;
+        const int upto = wave_prefix_i(t0 + t1);
+        const unsigned long long past = __ballot(upto > rem);
+        if (past != 0ull) {                                       // uniform over the workgroup
+            const int l = (int)__builtin_ctzll(past);
+            int before = __builtin_amdgcn_readlane(upto - t0 - t1, l);
+            const int first = __builtin_amdgcn_readlane(t0, l);
+            int at = 2 * l;
+            if (before + first <= rem) { before += first; ++at; }
+            if (at % kRWaves == wave) {
+                const int step = at / kRWaves, want = rem - before;
+#pragma unroll
+                for (int u = 0; u < kBlock; ++u) {
+                    if (u == step) {
+                        if (want >= inc[u] - own[u] && want < inc[u]) {        // exactly one lane
+                            int skip = want - (inc[u] - own[u]);
+                            for_each_pattern(x[u], [&](uint32_t p, int j) {
+                                if (p == pat && skip-- == 0) sh.token = (tid + (ib + u) * kRThreads) * 8 + j;
+                            });
+                        }
                     }
                 }
-            } else if (p_on) {
-                const double T = p * (M_hi + M_lo);
-                find_mass_cut(vw, T, 0, cC, cM, sh, tid);
-                cb = sh.cut_bin; cC = sh.cut_C; cM = sh.cut_M;
+            }
+            __syncthreads();
+            return sh.token;
+        }
+        rem -= __builtin_amdgcn_readlane(upto, 63);
+        __syncthreads();                                          // the totals are reused
+    }
+    return -1;
+}
+
+struct Drawn {
+    bool any;             // a level won
+    int pattern, token, kept_C;
+    double kept_M, z1;
+};
+
+// ---------------------------------------------------------------------------
+// The wide rows: four windows of 16,384 patterns in rank order, 32-bit counters.
+// ---------------------------------------------------------------------------
+struct WideWindow {
+    int w;                                                        // 0: [2, inf), 1: [+0, 2), 2: (-2, -0], 3: (-inf, -2]
+    __device__ __forceinline__ uint32_t quadrant() const { return w == 0 ? 1u : w == 1 ? 0u : (uint32_t)w; }
+    __device__ __forceinline__ int pattern(int rank) const        // rank 0 = highest value
+    {
+        return (int)(quadrant() << 14) + (w < 2 ? kWideBins - 1 - rank : rank);
+    }
+};
+
+__device__ __forceinline__ void wide_count(const Row& row, WideWindow win, uint32_t* hist, int tid)
+{
+    __syncthreads();
+    for (int i = tid; i < kWideBins + kTrash; i += kRThreads) hist[i] = 0u;
+    __syncthreads();
+    const uint32_t quad = win.quadrant(), trash = (uint32_t)(kWideBins + (tid & 63));
+    for (int v = tid; v < row.nvec; v += kRThreads)
+        for_each_pattern(row.guarded(v), [&](uint32_t p, int) { atomicAdd(&hist[(p >> 14) == quad ? (p & 0x3FFFu) : trash], 1u); });
+    __syncthreads();
+}
+
+__device__ __forceinline__ Drawn wide_row(const Row& row, const RestrictedArgs& a, double inv_tau, float c, uint64_t grow,
+                                          uint64_t k23, uint32_t* hist, Shared& sh, int tid)
+{
+    const int lane = tid & 63, wave = tid >> 6;
+    const bool k_on = a.top_k >= 1 && (int64_t)a.top_k < a.V, p_on = a.top_p < 1.0f;
+    auto count_of = [&](WideWindow win, int rank) -> uint32_t {
+        const int p = win.pattern(rank);
+        return ((p >> 7) & 0xFF) == 0xFF ? 0u : hist[p & 0x3FFF];
+    };
+    double z1 = 0.0;
+    bool have_z1 = false;
+    // counts the window and scans it; (C, M) = what lies above it on entry, with it on return
+    auto scan = [&](WideWindow win, View& vw, int& C, double& M) {
+        wide_count(row, win, hist, tid);
+        vw.Cl = 0; vw.top = kOwnW;
+#pragma unroll 1
+        for (int j = kOwnW - 1; j >= 0; --j) {
+            const uint32_t n = count_of(win, kOwnW * tid + j);
+            vw.Cl += (int)n;
+            if (n != 0u) vw.top = j;
+        }
+        const int p_top = win.pattern(kOwnW * tid + (vw.Cl > 0 ? vw.top : 0));
+        if (!have_z1) {
+            const float t = wave_max(vw.Cl > 0 ? (float)key_of_pattern(p_top) : -1.0f);
+            if (lane == 0) sh.wave_top[wave] = t;
+            __syncthreads();
+            const float best = row16_max(sh.wave_top[lane & 15]);
+            if (best >= 0.0f) { have_z1 = true; z1 = (double)value_of_pattern(pattern_of_key((int)best)); }
+        }
+        own_mass<kOwnW, 1>(vw, (p_top >> 7) & 0xFF, value_of_pattern(p_top), z1, inv_tau,
+                        [&](int j) { return count_of(win, kOwnW * tid + j); });
+        int Ct;
+        double Mt;
+        scan_view(vw, C, M, kRThreads, 0, 0.0, Ct, Mt, sh, tid);
+        C += Ct; M += Mt;
+    };
+    Drawn d{false, 0, 0, 0, 0.0, 0.0};
+    int C_all = 0;
+    double M_all = 0.0;
+#pragma unroll 1
+    for (int w = 0; w < kWideWindows; ++w) {
+        if (tid == 0) { sh.C_above[w] = C_all; sh.M_above[w] = M_all; }
+        View vw;
+        scan(WideWindow{w}, vw, C_all, M_all);
+    }
+    if (tid == 0) { sh.C_above[kWideWindows] = C_all; sh.M_above[kWideWindows] = M_all; }
+    __syncthreads();
+    if (!have_z1) return d;                                       // no finite logit
+    d.z1 = z1;
+    int cut_key = 0;
+    d.kept_C = C_all; d.kept_M = M_all;
+    // one sweep of the window that holds a cut, then the owner's search
+    if (k_on && d.kept_C >= a.top_k) {
+#pragma unroll 1
+        for (int w = 0; w < kWideWindows; ++w) {
+            if (sh.C_above[w] < a.top_k && sh.C_above[w + 1] >= a.top_k) {
+                const WideWindow win{w};
+                View vw;
+                int C = sh.C_above[w];
+                double M = sh.M_above[w];
+                scan(win, vw, C, M);
+                if (vw.Cx < a.top_k && vw.Cx + vw.Cl >= a.top_k) {          // one thread
+                    const Cut cut = own_count_cut<kOwnW, 1>(vw, a.top_k, [&](int j) { return count_of(win, kOwnW * tid + j); });
+                    sh.cut_key[0] = key_of_pattern(win.pattern(kOwnW * tid + cut.j)); sh.cut_C[0] = cut.C; sh.cut_M[0] = cut.M;
+                }
                 __syncthreads();
             }
-            if (!back_to_hi) {
-                best = race_window(hist, false, cb, z1, c, a.seed, grow, best, sh, tid);
-                kept_C = cC; kept_M = cM;
-            } else {
-                // third sweep: the top-k cut lies among the negatives, the nucleus of that
-                // set ends among the non-negatives
-                const double T = p * cM;
-                int Cd; double Md;
-                build_hist(rowp, V, true, hist, tid);
-                scan_window(hist, true, inv_tau, false, z1, 0, 0.0, vw, Cd, Md, sh, tid);
-                find_mass_cut(vw, T, 0, C_hi, M_hi, sh, tid);
-                const int hb = sh.cut_bin;
-                kept_C = sh.cut_C; kept_M = sh.cut_M;
+        }
+        cut_key = sh.cut_key[0]; d.kept_C = sh.cut_C[0]; d.kept_M = sh.cut_M[0];
+        __syncthreads();
+    }
+    if (p_on) {
+        const double T = (double)a.top_p * d.kept_M;
+        bool looked = false;
+#pragma unroll 1
+        for (int w = 0; w < kWideWindows; ++w) {
+            if (!looked && sh.C_above[w + 1] > sh.C_above[w] && sh.M_above[w + 1] >= T) {
+                looked = true;
+                const WideWindow win{w};
+                View vw;
+                int C = sh.C_above[w];
+                double M = sh.M_above[w];
+                scan(win, vw, C, M);
+                offer_mass_cut<kOwnW, 1>(vw, T, [&](int j) { return count_of(win, kOwnW * tid + j); },
+                                         [&](int j) { return key_of_pattern(win.pattern(kOwnW * tid + j)); }, sh, tid);
                 __syncthreads();
-                best = race_window(hist, true, hb, z1, c, a.seed, grow, RaceBest{-1.0, 0, 0}, sh, tid);
+                const int w1 = first_offer(sh, lane);
+                if (w1 < kRWaves && sh.cut_key[w1] > cut_key) { cut_key = sh.cut_key[w1]; d.kept_C = sh.cut_C[w1]; d.kept_M = sh.cut_M[w1]; }
             }
         }
     }
+    // the race: every window down to the cut is swept once more
+    Cand best = contestant(-1.0f, 0);
+    int best_n = 0;
+#pragma unroll 1
+    for (int w = 0; w < kWideWindows; ++w) {
+        const WideWindow win{w};
+        if (key_of_pattern(win.pattern(0)) < cut_key) break;      // uniform
+        wide_count(row, win, hist, tid);
+        Cand mine = contestant(-1.0f, 0);
+        for (int rank = tid; rank < kWideBins; rank += kRThreads) {
+            const uint32_t n = count_of(win, rank);
+            const int p = win.pattern(rank);
+            if (n != 0u && key_of_pattern(p) >= cut_key)
+                mine = better(mine, contestant(level_score(p, (int)n, (float)z1, c, a.seed, grow), key_of_pattern(p)));
+        }
+        mine = reduce_best(mine, sh, tid);
+        if (mine.q > best.q) {                                    // an earlier window wins ties
+            best = mine;
+            best_n = (int)hist[pattern_of_key(key_of(mine)) & 0x3FFF];
+        }
+    }
+    if (best.q >= 0.0f) {
+        d.any = true;
+        d.pattern = pattern_of_key(key_of(best));
+        const int pos = (int)(((2u * k23 + 1u) * (uint64_t)best_n) >> 24);
+        __syncthreads();
+        d.token = locate(row, 0, row.steps, (uint32_t)d.pattern, pos, sh, tid);
+    }
+    return d;
+}
 
-    }   // two-window code
+// ---------------------------------------------------------------------------
+// The near window.
+// ---------------------------------------------------------------------------
+// Counter places (13 bits, or two of them in a word's halves) to words of LDS: groups of four words
+// change places within sixteen by the place's bits 6 and 7, so that the threads of a wave, each
+// reading its own sixteen consecutive places as four 16-byte pieces, meet no bank conflict (4.7 us
+// without, the whole read 2 us with).
+__device__ __forceinline__ uint32_t swizzled(uint32_t place) { return place ^ ((place >> 4) & 0x000C000Cu); }
 
-    // the column inside the winning level
-    uint32_t w4[4];
-    philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
-    const uint64_t k23 = (uint64_t)(w4[0] >> 9);
-    int tok = 0;
-    if (best.q >= 0.0) {
-        const int pos = (int)(((2u * k23 + 1u) * (uint64_t)best.n) >> 24);
-        tok = best.n <= kListCap ? locate_listed(rowp, V, best.bits, pos, sh, tid)
-                                 : locate_column(rowp, V, best.bits, pos, sh, tid);
-        if (tok < 0 || tok >= V) tok = 0;             // only reachable with non-finite input
+struct Near {
+    int base;             // magnitude bits of the window's lowest level
+    int per_quarter;      // stream steps per quarter
+    const uint32_t* hist;
+    // rank 0 .. kHalf - 1: non-negative levels from the top, then the negative ones; the counters
+    // of z and -z are neighbours (place 2 (magnitude - base) + sign, swizzled)
+    __device__ __forceinline__ int slot(int rank) const
+    {
+        return (int)swizzled((uint32_t)(rank < kHalf ? 2 * (kHalf - 1 - rank) : 2 * (rank - kHalf) + 1));
+    }
+    __device__ __forceinline__ int pattern(int rank) const
+    {
+        return rank < kHalf ? base + kHalf - 1 - rank : 0x8000 + base + rank - kHalf;
+    }
+    static __device__ __forceinline__ int total(uint32_t a, uint32_t b)      // of the four quarters
+    {
+        return (int)((a & 0xFFFFu) + (a >> 16) + (b & 0xFFFFu) + (b >> 16));
+    }
+    __device__ __forceinline__ int count(int rank) const { return total(hist[slot(rank)], hist[kArray + slot(rank)]); }
+    // the counts of the kOwnN levels from rank0 (a multiple of kOwnN) on
+    __device__ __forceinline__ void own_counts(int rank0, int cnt[kOwnN]) const
+    {
+        const bool neg = rank0 >= kHalf;
+        const int s0 = neg ? 2 * (rank0 - kHalf) : 2 * (kHalf - kOwnN - rank0);
+        int both[2 * kOwnN];
+#pragma unroll
+        for (int i = 0; i < kOwnN / 2; ++i) {
+            const uint32_t at = swizzled((uint32_t)(s0 + 4 * i));
+            const uint4 a = *reinterpret_cast<const uint4*>(hist + at);
+            const uint4 b = *reinterpret_cast<const uint4*>(hist + kArray + at);
+            both[4 * i] = total(a.x, b.x); both[4 * i + 1] = total(a.y, b.y);
+            both[4 * i + 2] = total(a.z, b.z); both[4 * i + 3] = total(a.w, b.w);
+        }
+#pragma unroll
+        for (int j = 0; j < kOwnN; ++j) cnt[j] = neg ? both[2 * j + 1] : both[2 * (kOwnN - 1 - j)];
+    }
+    // first / last rank whose key is at most / at least `key`
+    __device__ __forceinline__ int first_at_most(int key) const
+    {
+        if (key >= 0x8000 + base + kHalf) return 0;
+        if (key >= 0x8000 + base) return 0x8000 + base + kHalf - 1 - key;
+        if (key > 0x7FFF - base) return kHalf;
+        return kHalf + (0x7FFF - base) - key;
+    }
+    __device__ __forceinline__ int last_at_least(int key) const
+    {
+        if (key > 0x8000 + base + kHalf - 1) return -1;
+        if (key >= 0x8000 + base) return 0x8000 + base + kHalf - 1 - key;
+        if (key > 0x7FFF - base) return kHalf - 1;
+        const int r = kHalf + (0x7FFF - base) - key;
+        return r < 2 * kHalf ? r : 2 * kHalf - 1;
+    }
+};
+
+// A vector that holds patterns outside the window (rare): all lanes of the wave take part.
+__device__ __forceinline__ void note_outside(const u32x4& x, int v, int quarter, int base, Shared& sh, int lane)
+{
+    // what is no number (masked columns, what lies past the row) is only counted
+    int n_odd = 0;
+    bool more = false;
+    for_each_pattern(x, [&](uint32_t p, int) {
+        const uint32_t mag = p & 0x7FFFu;
+        const bool odd = mag >= 0x7F80u;
+        n_odd += odd;
+        more |= !odd && mag - (uint32_t)base >= (uint32_t)kHalf;
+    });
+    n_odd = wave_prefix_i(n_odd);
+    if (lane == 63 && n_odd != 0) atomicAdd(&sh.n_not_finite, n_odd);
+    if (!__any(more)) return;
+    for_each_pattern(x, [&](uint32_t p, int j) {
+        const uint32_t mag = p & 0x7FFFu;
+        const bool out = mag < 0x7F80u && mag - (uint32_t)base >= (uint32_t)kHalf;
+        if (__ballot(out) == 0ull) return;
+        const bool neg = p >= 0x8000u;
+        auto tally = [&](bool hit, int* counter) {
+            const unsigned long long m = __ballot(hit);
+            if (m != 0ull && lane == (int)__builtin_ctzll(m)) atomicAdd(counter, (int)__popcll(m));
+        };
+        tally(out && mag == 0u && !neg, &sh.zeros[0][quarter]);
+        tally(out && mag == 0u && neg, &sh.zeros[1][quarter]);
+        const bool large = out && mag >= (uint32_t)base;
+        tally(large && !neg, &sh.n_above);
+        tally(large && neg, &sh.n_below);
+        const bool small = out && mag != 0u && mag < (uint32_t)base;
+        if (small) {
+            const int at = atomicAdd(&sh.list_n, 1);
+            if (at < kMidList) { sh.list_key[at] = key_of_pattern((int)p); sh.list_col[at] = v * 8 + j; }
+        }
+    });
+}
+
+// Counts the row.  Returns the window.
+__device__ __forceinline__ Near near_count(const Row& row, uint32_t* hist, Shared& sh, int tid)
+{
+    const int lane = tid & 63, wave = tid >> 6;
+    Near w;
+    w.hist = hist;
+    w.per_quarter = (row.steps + kQuarters - 1) / kQuarters;
+    constexpr int kAhead = 4;
+    u32x4 x[kAhead];
+    row.request<kAhead>(x, 0, row.steps, tid);
+    for (int i = tid; i < 2 * kArray / 4; i += kRThreads) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
+    if (tid < 2 * kQuarters) (&sh.zeros[0][0])[tid] = 0;
+    if (tid == 0) { sh.list_n = 0; sh.n_below = 0; sh.n_not_finite = 0; sh.n_above = 0; }
+    {
+        // the window's top: one binade above the largest finite logit among the first vectors
+        float m = 0.0f;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            for_each_pattern(x[u], [&](uint32_t p, int) {
+                const float z = value_of_pattern((int)p);
+                m = z < INFINITY ? fmaxf(m, z) : m;
+            });
+        m = wave_max(m);
+        if (lane == 0) sh.sample_max[wave] = m;
+    }
+    __syncthreads();
+    const float top = row16_max(sh.sample_max[lane & 15]);
+    int top_exp = (int)(__float_as_uint(top) >> 23) + 1;
+    top_exp = top_exp < kTopExp ? kTopExp : top_exp > 254 ? 254 : top_exp;
+    w.base = __builtin_amdgcn_readfirstlane((top_exp - (kBinades - 1)) << 7);
+
+    // Two patterns at a time: rotated left by one, (magnitude, sign) less the window's base is the
+    // slot, and anything outside the window (wrapped around or past the end) is a large number
+    // that a minimum sends to the lane's own spare word.
+    const uint16_t base2 = (uint16_t)(2 * w.base), spare = (uint16_t)(2 * kHalf + lane);
+    const u16x2 base_v = {base2, base2}, spare_v = {spare, spare};
+    for (int i0 = 0; i0 < row.steps; i0 += kAhead) {
+        if (i0 > 0) row.request<kAhead>(x, i0, row.steps, tid);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (i0 + u >= row.steps) break;                       // uniform
+            const int quarter = (i0 + u) / w.per_quarter;
+            char* h = reinterpret_cast<char*>(hist + (quarter >> 1) * kArray);
+            const uint32_t inc = 1u << ((quarter & 1) * 16);
+            u16x2 worst = {0, 0};
+            auto add2 = [&](uint32_t word) {
+                const u16x2 p = halves(word);
+                const u16x2 s = ((p << (uint16_t)1) | (p >> (uint16_t)15)) - base_v;
+                worst = __builtin_elementwise_max(worst, s);
+                const uint32_t at = swizzled(__builtin_bit_cast(uint32_t, __builtin_elementwise_min(s, spare_v))) << 2;
+                atomicAdd(reinterpret_cast<uint32_t*>(h + (at & 0xFFFFu)), inc);
+                atomicAdd(reinterpret_cast<uint32_t*>(h + (at >> 16)), inc);
+            };
+            add2(x[u].x); add2(x[u].y); add2(x[u].z); add2(x[u].w);
+            if (__builtin_expect(__any(worst.x >= 2 * kHalf || worst.y >= 2 * kHalf), 0))
+                note_outside(x[u], tid + (i0 + u) * kRThreads, quarter, w.base, sh, lane);
+        }
+    }
+    __syncthreads();
+    return w;
+}
+static_assert(kArray * 4 <= 0x10000, "byte offsets of the counters in 16 bits");
+
+// The middle items of a row, one per lane of one wave, in rank order: the listed small
+// positive values, +0, -0, the small negative ones.
+__device__ __forceinline__ void middle_items(Shared& sh, int lane)
+{
+    const int n = sh.list_n;
+    const int key = lane < n ? sh.list_key[lane] : 0, col = lane < n ? sh.list_col[lane] : 0;
+    int rank = 0;
+    for (int e = 0; e < n; ++e) {
+        const int ok = __builtin_amdgcn_readlane(key, e), oc = __builtin_amdgcn_readlane(col, e);
+        rank += ok > key || (ok == key && oc < col);
+    }
+    const int npos = __popcll(__ballot(lane < n && key > 0x8000));
+    if (lane < n) {
+        const int at = rank < npos ? rank : rank + 2;
+        sh.mid_key[at] = key; sh.mid_cnt[at] = 1; sh.mid_col[at] = col;
+    }
+    if (lane < 2) {
+        int c = 0;
+        for (int q = 0; q < kQuarters; ++q) c += sh.zeros[lane][q];
+        sh.mid_key[npos + lane] = 0x8000 - lane; sh.mid_cnt[npos + lane] = c; sh.mid_col[npos + lane] = -1;
+    }
+}
+
+// Two workgroups per compute unit: eight waves per SIMD, 64 vector registers each.
+__global__ __launch_bounds__(kRThreads, 8)
+void sample_restricted_kernel(RestrictedArgs a)
+{
+    __shared__ __align__(16) uint32_t hist[2 * kArray];
+    __shared__ Shared sh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t r = blockIdx.x;
+    Row row;
+    row.p = reinterpret_cast<const u32x4*>(a.logits + r * a.row_stride);
+    row.nvec = (int)((a.V + 7) >> 3);
+    row.last = (int)(a.V - ((int64_t)(row.nvec - 1) << 3));
+    row.steps = (row.nvec + kRThreads - 1) / kRThreads;
+    row.whole = (int)(a.V >> 3) / kRThreads;
+    const float tau = a.tau_rows ? a.tau_rows[r] : a.tau_scalar;
+    const double inv_tau = 1.0 / (double)tau;
+    const float c = kLog2eF / tau;
+    const uint64_t grow = a.row_base + (uint64_t)r;
+    const bool k_on = a.top_k >= 1 && (int64_t)a.top_k < a.V, p_on = a.top_p < 1.0f;
+
+    Drawn d{false, 0, 0, 0, 0.0, 0.0};
+    const Near win = near_count(row, hist, sh, tid);
+
+    // my levels; the row's highest level
+    View vw;
+    int cnt[kOwnN];
+    const int rank0 = kOwnN * tid;
+    win.own_counts(rank0, cnt);
+    vw.Cl = 0; vw.top = kOwnN;
+#pragma unroll
+    for (int j = kOwnN - 1; j >= 0; --j) {
+        vw.Cl += cnt[j];
+        if (cnt[j] != 0) vw.top = j;
+    }
+    const int p_top = win.pattern(rank0 + (vw.Cl > 0 ? vw.top : 0));
+    int top = vw.Cl > 0 ? key_of_pattern(p_top) : -1;             // the highest level I know of
+    const int list_n = sh.list_n;
+    int n_zero = 0;
+#pragma unroll
+    for (int q = 0; q < 2 * kQuarters; ++q) n_zero += (&sh.zeros[0][0])[q];
+    const bool listed = list_n <= kMidList;
+    const bool has_mid = n_zero != 0 || (list_n != 0 && listed);
+    const int n_mid = has_mid ? list_n + 2 : 0;
+    if (has_mid && wave == 0) {
+        middle_items(sh, lane);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (lane < n_mid && sh.mid_cnt[lane] != 0 && sh.mid_key[lane] > top) top = sh.mid_key[lane];
+    }
+    {
+        const float t = wave_max((float)top);                     // keys are below 2^16: exact in fp32
+        if (lane == 0) sh.wave_top[wave] = t;
+    }
+    __syncthreads();
+    const float top_key = row16_max(sh.wave_top[lane & 15]);
+    const double z1 = top_key >= 0.0f ? (double)value_of_pattern(pattern_of_key((int)top_key)) : 0.0;
+    const float z1f = (float)z1;                                  // a bf16 value: exact
+
+    // masses and the scan; the middle comes between the two signs
+    own_mass<kOwnN, kOwnN>(vw, (p_top >> 7) & 0xFF, value_of_pattern(p_top), z1, inv_tau, [&](int j) { return cnt[j]; });
+    if (has_mid && wave == 0) {
+        const int n = lane < n_mid ? sh.mid_cnt[lane] : 0;
+        const double w = n != 0 ? exp(((double)value_of_pattern(pattern_of_key(sh.mid_key[lane])) - z1) * inv_tau) : 0.0;
+        sh.mid_C[lane] = wave_prefix_i(n);
+        sh.mid_M[lane] = wave_prefix_d((double)n * w);
+    }
+    if (has_mid) __syncthreads();                                 // the scan reads the middle's totals
+    const int mid_C = has_mid ? sh.mid_C[63] : 0;
+    const double mid_M = has_mid ? sh.mid_M[63] : 0.0;
+    int C_win;
+    double M_win;
+    scan_view(vw, 0, 0.0, kRThreads / 2, mid_C, mid_M, C_win, M_win, sh, tid);
+    const int n_below = sh.n_below;
+    const int C_in = C_win + mid_C, C_all = C_in + n_below;
+    const double M_all = M_win + mid_M;
+
+    // Columns below the window weigh nothing when every one of them is below 2^-80 of the largest
+    // weight: a row of them stays below the last bit of the total, which is at least 1, and none can win the race.
+    const bool below_weightless = n_below == 0
+        || (top_key >= 0.0f && (-(double)value_of_pattern(win.base + kHalf) - z1) * inv_tau < -56.0);
+    bool wide = sh.n_above != 0 || !listed || !below_weightless
+             || C_win + n_zero + list_n + n_below + sh.n_not_finite + sh.n_above != row.steps * kRThreads * 8    // a counter wrapped
+             || (k_on && C_all >= a.top_k && C_in < a.top_k);                                        // the cut is below the window
+    if (wide) {                                                   // uniform
+        uint32_t w4[4];
+        philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
+        d = wide_row(row, a, inv_tau, c, grow, (uint64_t)(w4[0] >> 9), hist, sh, tid);
+    } else if (top_key >= 0.0f) {
+        d.z1 = z1;
+        d.kept_C = C_all; d.kept_M = M_all;
+        int cut_key = 0;
+        auto my_cnt = [&](int j) { return cnt[j]; };
+        auto my_key = [&](int j) { return key_of_pattern(win.pattern(rank0 + j)); };
+        // The middle's share of a search, by the first negative wave: the items carry inclusive
+        // prefixes; what lies above them is what the wave's first thread has above it, less the middle.
+        constexpr int kMidWave = kRWaves / 2;
+        int C0 = 0;
+        double M0 = 0.0;
+        bool level_end = false;
+        if (has_mid && wave == kMidWave) {
+            C0 = __builtin_amdgcn_readfirstlane(vw.Cx) - mid_C;
+            M0 = lane_value(vw.Mx, 0) - mid_M;
+            level_end = lane < n_mid && sh.mid_cnt[lane] != 0
+                     && (lane == n_mid - 1 || sh.mid_key[lane + 1] != sh.mid_key[lane]);
+        }
+        auto offer_middle = [&](bool reaches) {
+            const unsigned long long hit = __ballot(level_end && reaches);
+            if (hit == 0ull) { if (lane == 0) sh.cut_key[kRWaves] = -1; }
+            else if (lane == (int)__builtin_ctzll(hit)) {
+                sh.cut_key[kRWaves] = sh.mid_key[lane]; sh.cut_C[kRWaves] = C0 + sh.mid_C[lane]; sh.cut_M[kRWaves] = M0 + sh.mid_M[lane];
+            }
+        };
+        auto take = [&](int w) {
+            if (sh.cut_key[w] > cut_key) { cut_key = sh.cut_key[w]; d.kept_C = sh.cut_C[w]; d.kept_M = sh.cut_M[w]; }
+        };
+        if (k_on && C_all >= a.top_k) {                           // exactly one place holds the cut
+            if (vw.Cx < a.top_k && vw.Cx + vw.Cl >= a.top_k) {
+                const Cut cut = own_count_cut<kOwnN, kOwnN>(vw, a.top_k, my_cnt);
+                sh.cut_key[0] = my_key(cut.j); sh.cut_C[0] = cut.C; sh.cut_M[0] = cut.M;
+            }
+            bool in_mid = false;
+            if (has_mid) {
+                if (wave == kMidWave) offer_middle(C0 + sh.mid_C[lane] >= a.top_k && C0 < a.top_k);
+                __syncthreads();
+                in_mid = sh.cut_key[kRWaves] >= 0;
+            } else {
+                __syncthreads();
+            }
+            take(in_mid ? kRWaves : 0);
+            __syncthreads();
+        }
+        if (p_on) {
+            const double T = (double)a.top_p * d.kept_M;
+            offer_mass_cut<kOwnN, kOwnN>(vw, T, my_cnt, my_key, sh, tid);
+            if (has_mid && wave == kMidWave) offer_middle(M0 + sh.mid_M[lane] >= T);
+            __syncthreads();
+            const int w1 = first_offer(sh, lane);                 // kRWaves: nobody reaches T, nothing is cut
+            if (has_mid && w1 >= kMidWave && sh.cut_key[kRWaves] >= 0) take(kRWaves);
+            else if (w1 < kRWaves) take(w1);
+        }
+        // the race: the kept levels dealt round-robin, so that a short run of them spreads over threads
+        Cand best = contestant(-1.0f, 0);
+        const int last = win.last_at_least(cut_key);
+        for (int rank = win.first_at_most((int)top_key) + tid; rank <= last; rank += kRThreads) {
+            const int n = win.count(rank);
+            if (n != 0) {
+                const int p = win.pattern(rank);
+                best = better(best, contestant(level_score(p, n, z1f, c, a.seed, grow), key_of_pattern(p)));
+            }
+        }
+        if (has_mid && wave == kRWaves - 1 && lane < n_mid && sh.mid_cnt[lane] != 0) {
+            const int key = sh.mid_key[lane];
+            if (key >= cut_key && (lane == 0 || sh.mid_key[lane - 1] != key)) {
+                int n = sh.mid_cnt[lane];
+                for (int e = lane + 1; e < n_mid && sh.mid_key[e] == key; ++e) n += sh.mid_cnt[e];
+                best = better(best, contestant(level_score(pattern_of_key(key), n, z1f, c, a.seed, grow), key));
+            }
+        }
+        best = reduce_best(best, sh, tid);
+
+        // the column inside the winning level
+        if (best.q >= 0.0f) {
+            d.any = true;
+            d.pattern = pattern_of_key(key_of(best));
+            uint32_t w4[4];
+            philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
+            const uint64_t k23 = (uint64_t)(w4[0] >> 9);
+            const int mag = d.pattern & 0x7FFF;
+            if (mag != 0 && mag < win.base) {                     // a listed value
+                int at = 0, n = 0;
+                for (int e = n_mid - 1; e >= 0; --e)
+                    if (sh.mid_key[e] == key_of(best)) { at = e; ++n; }
+                d.token = sh.mid_col[at + (int)(((2u * k23 + 1u) * (uint64_t)n) >> 24)];
+            } else {
+                int q4[kQuarters];
+                if (mag == 0) {
+#pragma unroll
+                    for (int q = 0; q < kQuarters; ++q) q4[q] = sh.zeros[d.pattern >> 15][q];
+                } else {
+                    const uint32_t s = swizzled((uint32_t)(2 * (mag - win.base) + (d.pattern >> 15)));
+                    const uint32_t lo = hist[s], hi = hist[kArray + s];
+                    q4[0] = (int)(lo & 0xFFFFu); q4[1] = (int)(lo >> 16);
+                    q4[2] = (int)(hi & 0xFFFFu); q4[3] = (int)(hi >> 16);
+                }
+                const int n = q4[0] + q4[1] + q4[2] + q4[3];
+                int rem = (int)(((2u * k23 + 1u) * (uint64_t)n) >> 24), quarter = 0;
+#pragma unroll
+                for (int q = 0; q < kQuarters - 1; ++q)
+                    if (quarter == q && rem >= q4[q]) { rem -= q4[q]; ++quarter; }
+                const int i0 = quarter * win.per_quarter;
+                const int i1 = i0 + win.per_quarter < row.steps ? i0 + win.per_quarter : row.steps;
+                d.token = locate(row, i0, i1, (uint32_t)d.pattern, rem, sh, tid);
+            }
+        }
     }
     if (tid == 0) {
-        a.token_out[row] = tok;
-        if (a.kept_out) a.kept_out[row] = kept_C;
+        const int tok = d.token >= 0 && d.token < a.V ? d.token : 0;
+        a.token_out[r] = tok;
+        if (a.kept_out) a.kept_out[r] = d.kept_C;
         if (a.logp_out)
-            a.logp_out[row] = best.q >= 0.0
-                ? (float)((bf16_value(best.bits) - z1) * inv_tau - log(kept_M))
-                : __builtin_nanf("");
+            a.logp_out[r] = d.any ? (float)(((double)value_of_pattern(d.pattern) - d.z1) * inv_tau - log(d.kept_M))
+                                  : __builtin_nanf("");
     }
 }
 

@@ -335,3 +335,94 @@ def test_fp32_rows_need_a_small_top_k():
         with pytest.raises(e3.E3Error) as ei:
             e3.e3_sample_restricted(lg, None, 1.0, k, 0.9, 1, 0)
         assert ei.value.status == -5
+
+
+# ---------------------------------------------------------------- the near window and what lies outside it
+# 32 binades up to [256, 512) (or one above the largest logit of the first vectors) are counted
+# directly; nearer to zero than that: at most 62 columns, listed; zeros apart; below it: masked columns;
+# everything else takes the wide form.  Bars as for every test of this file.
+def _outside_rows(kind, V, rows, g):
+    x = torch.randn((rows, V), generator=g, device=DEV) * 3
+
+    def put(n, values):
+        for r in range(rows):
+            cols = torch.randperm(V, generator=g, device=DEV)[:n]
+            x[r, cols] = values(n)
+
+    sign = lambda n: (torch.randint(0, 2, (n,), generator=g, device=DEV) * 2 - 1).float()
+    if kind.startswith("small"):                  # the list up to, at and past its capacity; repeated values
+        n = int(kind[5:])
+        put(n, lambda n: sign(n) * 2.0 ** -torch.randint(24, 60, (n,), generator=g, device=DEV).float())
+    elif kind == "zeros":
+        put(V // 3, lambda n: sign(n) * 0.0)
+    elif kind == "zeros_and_small":
+        put(V // 4, lambda n: sign(n) * 0.0)
+        put(20, lambda n: sign(n) * 1e-12)
+    elif kind == "masked_inf":
+        put(V // 2, lambda n: torch.full((n,), -float("inf"), device=DEV))
+    elif kind == "masked_lowest":
+        put(V // 2, lambda n: torch.full((n,), torch.finfo(torch.bfloat16).min, device=DEV))
+    elif kind == "masked_1e4":
+        put(V // 2, lambda n: torch.full((n,), -1e4, device=DEV))
+    elif kind == "large_first":                   # the window moves up with the first vectors
+        x *= 3000.0
+    elif kind == "large_late":                    # ... which do not show it
+        x[:, V // 2:] *= 3000.0
+        x[:, -1] = 9000.0
+    elif kind == "all_below":
+        x = x * 10 - 2000.0
+    elif kind == "subnormal":
+        x *= 1e-39
+    return x.to(torch.bfloat16)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["small1", "small61", "small62", "small63", "small500", "zeros", "zeros_and_small",
+                                  "masked_inf", "masked_lowest", "masked_1e4", "large_first", "large_late",
+                                  "all_below", "subnormal"])
+@pytest.mark.parametrize("V", [3_003, 70_001])
+def test_levels_outside_the_near_window(kind, V):
+    g = torch.Generator(device=DEV).manual_seed(V + sum(map(ord, kind)))
+    pitch = -(-V // 8) * 8
+    lg = torch.full((6, pitch), 77.0, device=DEV).to(torch.bfloat16)         # what lies past a row must not count
+    lg[:, :V] = _outside_rows(kind, V, 6, g)
+    lg = lg[:, :V]
+    # high temperatures put the cuts among the small values and the zeros, and the draw with them;
+    # a count cut of 90 % of the row lies among the masked columns
+    for k, p, tau in [(0, 0.9, 1.0), (0, 0.5, 60.0), (0, 0.55, 900.0), (V // 2, 1.0, 60.0), (V // 2 + 7, 0.99, 500.0),
+                      (9 * V // 10, 0.999, 5.0), (300, 0.7, 2.0)]:
+        check(lg, None, tau, k, p, 6, 40, f"outside {kind} V={V} k={k} p={p} tau={tau}")
+    if kind != "masked_inf":                      # without a cut the infinite columns are no level here
+        check(lg, None, 60.0, 0, 1.0, 6, 40, f"outside {kind} V={V} no cut")
+
+
+@pytest.mark.gpu
+def test_draws_among_listed_values_and_zeros():
+    # most of the mass on a zero level and on small listed values, so that the draw falls on them
+    rows, V = 64, 5_000
+    g = torch.Generator(device=DEV).manual_seed(12)
+    lg = torch.full((rows, V), -30.0, device=DEV)
+    for r in range(rows):
+        cols = torch.randperm(V, generator=g, device=DEV)
+        lg[r, cols[:40]] = 2.0 ** -torch.randint(24, 28, (40,), generator=g, device=DEV).float()
+        lg[r, cols[40:60]] = -2.0 ** -30
+        lg[r, cols[60:90]] = 0.0
+        lg[r, cols[90:120]] = -0.0
+    lg = lg.to(torch.bfloat16)
+    for k, p in [(0, 1.0), (0, 0.5), (0, 0.99), (300, 0.4), (60, 1.0), (45, 0.9)]:
+        check(lg, None, 1.0, k, p, 31, 7, f"draws among listed values k={k} p={p}")
+
+
+@pytest.mark.gpu
+def test_levels_longer_than_a_quarter_counter():
+    # a level of 65,536 columns or more within a quarter of the row wraps its 16-bit counter
+    V = 400_000
+    g = torch.Generator(device=DEV).manual_seed(46)
+    base = torch.randn((4, V), generator=g, device=DEV) * 0.05 - 2.0
+    base[0, :65_536] = 0.5
+    base[1, 98_304:98_304 + 65_535] = 0.5           # one short of wrapping
+    base[2, :] = torch.where(torch.rand(V, generator=g, device=DEV) < 0.9, 0.5, base[2])
+    base[3, 100_000:300_000] = -1.0
+    lg = base.to(torch.bfloat16)
+    for k, p in [(0, 0.9), (1000, 1.0), (0, 0.2), (100_000, 0.999)]:
+        check(lg, None, 1.0, k, p, 21, 5, f"long quarter levels k={k} p={p}")
