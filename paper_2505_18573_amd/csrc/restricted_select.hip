@@ -7,21 +7,23 @@
 // rows through a histogram of all 65,536 patterns; that costs one LDS atomic per column and
 // cannot hold the 2^32 patterns of fp32.  For top_k <= 256 the kept set is tiny, and this
 // file finds it by selection instead:
-//   1. one streaming read of the row leaves the maximum of every chunk of columns in LDS
-//      (plain vector maxima: about two instructions per column, no atomics) and every
-//      thread's own maximum in a register;
-//   2. theta, a value that at least k of the thread maxima reach, is a lower bound of the k-th
-//      largest column (k different threads hold a column at or above it), and a tight one:
-//      only the few chunks whose maximum reaches theta can hold kept columns;
-//   3. the columns at or above theta are read again from those chunks and listed in LDS; an
-//      exact radix select over them gives kappa, the value of the cut level, with the number
-//      of columns above it (fewer than k) and on it;
-//   4. the columns above kappa are listed, sorted by (value, column), grouped into levels
+//   1. the row is streamed once.  Every thread keeps the maximum of what it has read; a
+//      value theta that at least k of these maxima reach is a lower bound of the k-th
+//      largest column (k different threads hold a column at or above it), whatever part of
+//      the row has been read so far, and it only rises.  Vectors that hold a value at or above
+//      the current theta go into a list in LDS (the first requests, which are spread over
+//      the whole row, wait in registers for the first theta);
+//   2. the columns at or above the final theta are taken from the listed vectors into a list of
+//      (key, column); an exact radix select over them gives kappa, the value of the cut
+//      level, with the number of columns above it (fewer than k) and on it;
+//   3. the columns above kappa are listed, sorted by (value, column), grouped into levels
 //      with their fp64 masses, cut by top-p, raced and the winning level's pos-th column
 //      taken, exactly as the definition says; the cut level takes part with its count.
-// Every count is exact and every mass fp64, as in restricted.hip; a row with enormous
-// plateaus of equal values is slow (its chunks all qualify) but takes the same path.
-// Steps 3 (from the radix select on) and 4 exist twice: workgroup-wide, with a barrier after
+// A list of vectors that overflows (a row whose values climb) is made once more from a second
+// read with the final theta; if it overflows again (large plateaus of equal values), every step
+// reads the row instead of the list: slow, same results.
+// Every count is exact and every mass fp64, as in restricted.hip.
+// Steps 2 (from the radix select on) and 3 exist twice: workgroup-wide, with a barrier after
 // every short phase, and - for a list of at most 256 candidates and top_k <= 64, the usual
 // case - inside one wave with the kept columns one per lane (finish_in_one_wave below).
 #include "vocab_common.h"
@@ -30,17 +32,9 @@
 namespace e3 {
 namespace {
 
-// Threads per row.  Measured on MI355X, 512 rows x 151,936, top-k 50, workgroup-wide steps
-// throughout: 512 threads with up to 128 registers each (two workgroups per compute unit,
-// nothing spilled) 49.9 us for bf16 rows and 80 us for fp32 rows; 1024 threads held to 64
-// registers (the same two workgroups per compute unit; a dozen spilled, whose reloads queue
-// behind the streaming) 61.7 - 67 us and 82 - 112 us.
-#ifndef E3_SEL_THREADS
-#define E3_SEL_THREADS 512
-#endif
-constexpr int kSThreads = E3_SEL_THREADS;
-constexpr int kSWaves = kSThreads / 64;
-constexpr int kSBatch = 4096 / kSThreads;          // 16-byte requests a thread keeps in flight: 64 KiB per workgroup
+constexpr int kSBatch = 8;              // 16-byte requests of a thread made together; two such sets are in flight
+constexpr int kSMaxWaves = 16;
+constexpr int kSVecCap = 2048;          // vectors listed in LDS
 constexpr int kSMaxK = 256;             // top_k served here; the gt-list holds at most kSMaxK - 1 columns
 constexpr int kSEqCap = 64;             // columns of the cut level listed for a direct pick
 constexpr int kSListCap = 2048;         // candidates (columns at or above theta) listed in LDS
@@ -58,22 +52,24 @@ __device__ __forceinline__ uint32_t f32_of_key(uint32_t key)
     return (key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key;
 }
 
-// Element access for the two logit types.  A vector is 16 bytes.  Keys are 32-bit in
-// registers; bf16 rows store their chunk maxima as the upper 16 bits (the lower 16 of a bf16
-// value's key are all ones or all zeros and can be rebuilt).
+// Element access for the two logit types.  A vector is 16 bytes.  Keys are 32-bit; the lower 16
+// bits of a bf16 value's key are all ones or all zeros.
 struct SelBf16 {
-    typedef uint16_t Stored;
     static constexpr int kElems = 8;
-    static constexpr int kChunksPerThreadMax = 20 * 1024 / kSThreads;   // 40 KiB of chunk maxima
     static constexpr int kKeyBits = 16;              // significant key bits, from the top
     static __device__ __forceinline__ uint32_t elem_bits(const u32x4& v, int j)   // as binary32
     {
         const uint32_t w = j < 2 ? v.x : j < 4 ? v.y : j < 6 ? v.z : v.w;
         return (j & 1) ? (w & 0xFFFF0000u) : (w << 16);
     }
-    static __device__ __forceinline__ Stored pack(uint32_t key) { return (Stored)(key >> 16); }
-    // the largest key with these upper bits: never below the key that was packed
-    static __device__ __forceinline__ uint32_t unpack_upper(Stored s) { return ((uint32_t)s << 16) | 0xFFFFu; }
+    // columns from `n` on (1 <= n < kElems) replaced by patterns that are not numbers
+    static __device__ __forceinline__ u32x4 cut_off(const u32x4& v, int n)
+    {
+        auto word = [&](uint32_t w, int first) -> uint32_t {
+            return n <= first ? 0x7FC07FC0u : n == first + 1 ? (w & 0xFFFFu) | 0x7FC00000u : w;
+        };
+        return u32x4{word(v.x, 0), word(v.y, 2), word(v.z, 4), word(v.w, 6)};
+    }
     static __device__ __forceinline__ uint32_t pattern_of_bits(uint32_t bits) { return bits >> 16; }
     static __device__ __forceinline__ float vec_max(const u32x4& v)
     {
@@ -83,16 +79,16 @@ struct SelBf16 {
     }
 };
 struct SelF32 {
-    typedef uint32_t Stored;
     static constexpr int kElems = 4;
-    static constexpr int kChunksPerThreadMax = 10 * 1024 / kSThreads;   // 40 KiB of chunk maxima
     static constexpr int kKeyBits = 32;
     static __device__ __forceinline__ uint32_t elem_bits(const u32x4& v, int j)
     {
         return j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w;
     }
-    static __device__ __forceinline__ Stored pack(uint32_t key) { return key; }
-    static __device__ __forceinline__ uint32_t unpack_upper(Stored s) { return s; }
+    static __device__ __forceinline__ u32x4 cut_off(const u32x4& v, int n)
+    {
+        return u32x4{v.x, n <= 1 ? 0x7FC00000u : v.y, n <= 2 ? 0x7FC00000u : v.z, 0x7FC00000u};
+    }
     static __device__ __forceinline__ uint32_t pattern_of_bits(uint32_t bits) { return bits; }
     static __device__ __forceinline__ float vec_max(const u32x4& v)
     {
@@ -105,8 +101,7 @@ struct alignas(16) SelShared {
     uint32_t hist[256];
     uint32_t prefix, k_rem, n_eq_last;      // radix select state
     uint32_t n_total;                        // candidates seen by the first pass
-    int gt_n, eq_n, list_n;                  // list fills
-    int pad_;                                // keeps the arrays below on 16-byte boundaries
+    int gt_n, eq_n, list_n, vec_n;           // list fills
     int rank[kSMaxK];
     uint32_t gt_key[kSMaxK];                 // unsorted, then sorted by (key desc, col asc)
     int32_t gt_col[kSMaxK];
@@ -115,11 +110,11 @@ struct alignas(16) SelShared {
     double st_M[kSMaxK];                     // inclusive prefix mass in sorted order
     int32_t eq_col[kSEqCap];
     int cut_index;                           // last kept entry of the sorted list (-1: none), or kSMaxK: cut level kept
-    float wave_q[kSWaves];
-    int wave_lvl[kSWaves];
-    int wave_hits[kSWaves];
+    float wave_q[kSMaxWaves];
+    int wave_lvl[kSMaxWaves];
+    int wave_hits[kSMaxWaves];
     int token;
-    uint32_t tmax_wave[kSWaves];
+    uint32_t tmax_wave[kSMaxWaves];
 };
 
 static_assert(offsetof(SelShared, gt_key) % 16 == 0 && offsetof(SelShared, gt_col) % 16 == 0, "read four at a time");
@@ -182,8 +177,6 @@ struct SelArgs {
     int32_t* token_out;
     float* logp_out;
     int32_t* kept_out;
-    int group;            // vectors per chunk
-    int chunks;           // chunks per thread
 };
 
 // ---------------------------------------------------------------------------
@@ -389,14 +382,20 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
     }
 }
 
-// Two workgroups per compute unit: kSWaves / 2 waves per SIMD, which bounds the registers a
-// wave may take (512 / that many vector registers, 800 / that many scalar ones).
-template <typename T>
-__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(kSWaves / 2, kSWaves / 2)))
+// 512 threads per row, two workgroups per compute unit (one row's short phases overlap the
+// other's stream), or 1024 threads when there are fewer rows than compute units: four waves per SIMD and
+// up to 128 vector registers either way.
+template <typename T, int kSThreads>
+__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void sample_select_kernel(SelArgs a)
 {
-    extern __shared__ __align__(16) unsigned char dyn[];
-    typename T::Stored* cmax = reinterpret_cast<typename T::Stored*>(dyn);
+    constexpr int kSWaves = kSThreads / 64;
+    constexpr bool kStream = kSThreads == 512;
+    static_assert(kSWaves <= kSMaxWaves, "one slot per wave");
+    __shared__ u32x4 lvec[kSVecCap];                              // listed vectors and their indices
+    __shared__ int32_t lvec_at[kSVecCap];
+    __shared__ uint32_t lkey[kSListCap];                          // candidate columns
+    __shared__ int32_t lcol[kSListCap];
     __shared__ SelShared sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t row = blockIdx.x;
@@ -404,123 +403,161 @@ void sample_select_kernel(SelArgs a)
     const int esz = 16 / T::kElems;
     const char* rowp = static_cast<const char*>(a.logits) + row * a.row_stride * esz;
     const u32x4* rv = reinterpret_cast<const u32x4*>(rowp);
-    const int64_t nvec = (V + T::kElems - 1) / T::kElems;     // the last one may reach past V (inside the row pitch)
-    const int G = a.group, CPT = a.chunks;
+    // the last vector may reach past V (inside the row pitch)
+    const int nvec = (int)((V + T::kElems - 1) / T::kElems);
+    const int last = (int)(V - (int64_t)(nvec - 1) * T::kElems);  // its columns, 1 .. kElems
     const float tau = a.tau_rows ? a.tau_rows[row] : a.tau_scalar;
     const double inv_tau = 1.0 / (double)tau;
     const float c = kLog2eF / tau;
     const uint64_t grow = a.row_base + (uint64_t)row;
-
-    // ---- 1. chunk maxima ------------------------------------------------------------------
-    // chunk j of thread t = vectors t + kSThreads (j G + g), g < G.  Maxima are taken as floats
-    // (NaN operands drop out of v_max3); +inf is dealt with below; a maximum of zero is
-    // recorded as +0, whichever zero it was.
-    auto vec_key_max = [&](int64_t v, const u32x4& x) -> uint32_t {
-        float m = T::vec_max(x);
-        if (v == nvec - 1 && nvec * T::kElems != V) {           // columns past V do not count
-            m = -INFINITY;
-            for (int j = 0; j < T::kElems; ++j)
-                if (v * T::kElems + j < V) m = fmaxf(m, __uint_as_float(T::elem_bits(x, j)));
-        }
-        uint32_t key = m == 0.0f ? kKeyPosZero : key_of_f32(__float_as_uint(m));
-        if (m == INFINITY) {                                      // skip the non-finite ones by hand
-            key = 0u;
-            for (int j = 0; j < T::kElems; ++j)
-                if (v * T::kElems + j < V) {
-                    const uint32_t kj = key_of_f32(T::elem_bits(x, j));
-                    key = kj > key ? kj : key;
-                }
-        }
-        return key;
-    };
-    // Vector slots s = j G + g of this thread, kSBatch requests in flight at a time.
-    uint32_t tmax = 0u;
-    {
-        const int nslots = CPT * G;
-        uint32_t m = 0u;                                          // maximum of the chunk being filled
-        for (int s0 = 0; s0 < nslots; s0 += kSBatch) {
-            u32x4 x[kSBatch];
-            int64_t vv[kSBatch];
-#pragma unroll
-            for (int u = 0; u < kSBatch; ++u) {
-                vv[u] = (int64_t)tid + (int64_t)kSThreads * (s0 + u);
-                x[u] = (s0 + u < nslots && vv[u] < nvec) ? rv[vv[u]] : u32x4{0u, 0u, 0u, 0u};
-            }
-#pragma unroll
-            for (int u = 0; u < kSBatch; ++u) {
-                const int sl = s0 + u;
-                if (sl < nslots) {
-                    if (vv[u] < nvec) { const uint32_t k1 = vec_key_max(vv[u], x[u]); m = k1 > m ? k1 : m; }
-                    if ((sl + 1) % G == 0) {                      // last vector of chunk sl / G
-                        cmax[(size_t)(sl / G) * kSThreads + tid] = T::pack(m);
-                        tmax = m > tmax ? m : tmax;
-                        m = 0u;
-                    }
-                }
-            }
-        }
-    }
-
-    // ---- 2. theta: the k-th largest thread maximum ---------------------------------------------
-    const unsigned long long have_w = __ballot(tmax != 0u);
-    if (lane == 0) sh.wave_hits[wave] = __popcll(have_w);
-    if (tid == 0) { sh.gt_n = 0; sh.eq_n = 0; sh.token = 0; }
-    __syncthreads();
-    int n_threads_with = 0;
-    for (int w = 0; w < kSWaves; ++w) n_threads_with += sh.wave_hits[w];
-    __syncthreads();
-    if (n_threads_with == 0) {                                    // no finite logit in the row
-        if (tid == 0) {
-            a.token_out[row] = 0;
-            if (a.kept_out) a.kept_out[row] = 0;
-            if (a.logp_out) a.logp_out[row] = __builtin_nanf("");
-        }
-        return;
-    }
-    // Each wave takes the m-th largest of its lanes' maxima, m = ceil(k / kSWaves), bit by bit
-    // from the top with one ballot per bit (the largest value that at least m lanes reach; the
-    // bits below the significant ones stay zero, which only lowers the bound); the smallest of
-    // the waves' results has kSWaves m >= k threads at or above it.  No atomics, one barrier.
-    // (The exact k-th largest of the thread maxima would be a little tighter; it costs two to
-    // four histogram passes with their barriers.)
     const int k_req = a.top_k < kSMaxK ? a.top_k : kSMaxK;
-    uint32_t theta;
-    {
-        const int m_th = (k_req + kSWaves - 1) / kSWaves;
-        uint32_t wm = 0u;
-        for (int b = 31; b >= 32 - T::kKeyBits; --b) {
-            const uint32_t cand = wm | (1u << b);
-            if ((int)__popcll(__ballot(tmax >= cand)) >= m_th) wm = cand;
-        }
-        if (lane == 0) sh.tmax_wave[wave] = wm;
-        __syncthreads();
-        theta = 0xFFFFFFFFu;
-        for (int w = 0; w < kSWaves; ++w) theta = sh.tmax_wave[w] < theta ? sh.tmax_wave[w] : theta;
-        if (theta == 0u) theta = 1u;                                // a wave with fewer than m finite maxima: every finite value
-        // a zero maximum was recorded as +0 whichever zero it was: let -0 in as well
-        if (theta == kKeyPosZero) theta = kKeyNegZero;
-    }
 
-    // ---- 3. the candidates: every finite column whose key reaches theta ----------------------------
-    // They sit in the chunks whose maximum reaches theta.  Usually there are a few hundred: they
-    // are read once more and listed in LDS (key, column), and everything below works on the list.
-    // A row with huge plateaus of equal values overflows the list; it is then read from memory
-    // in every pass instead (slow, same results).
-    uint32_t* lkey = reinterpret_cast<uint32_t*>(dyn + (size_t)CPT * kSThreads * sizeof(typename T::Stored));
-    int32_t* lcol = reinterpret_cast<int32_t*>(lkey + kSListCap);
-    auto stream_candidates = [&](auto&& f) {
-        for (int j = 0; j < CPT; ++j) {
-            if (T::unpack_upper(cmax[(size_t)j * kSThreads + tid]) < theta) continue;
-            for (int g = 0; g < G; ++g) {
-                const int64_t v = (int64_t)tid + (int64_t)kSThreads * ((int64_t)j * G + g);
-                if (v >= nvec) break;
-                const u32x4 x = rv[v];
+    // ---- 1. the stream ----------------------------------------------------------------------
+    // Slot s of a thread is vector tid + kSThreads s; a set of requests takes every nsets-th slot, so
+    // that each set, above all the first, samples the whole row.
+    const int nslots = (nvec + kSThreads - 1) / kSThreads;
+    const int whole = (int)(V / T::kElems) / kSThreads;           // slots of nothing but complete vectors
+    const int nsets = (nslots + kSBatch - 1) / kSBatch;
+    const u32x4 none = {0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u};   // no numbers, as bf16 and as fp32
+    auto guarded = [&](int v) -> u32x4 {
+        u32x4 x = none;
+        if (v < nvec) x = rv[v];
+        if (v == nvec - 1 && last < T::kElems) x = T::cut_off(x, last);
+        return x;
+    };
+    auto request = [&](u32x4 x[kSBatch], int set) {
 #pragma unroll
-                for (int e = 0; e < T::kElems; ++e) {
-                    const int64_t col = v * T::kElems + e;
-                    const uint32_t key = key_of_f32(T::elem_bits(x, e));
-                    if (col < V && key >= theta) f(key, (int32_t)col);
-                }
+        for (int u = 0; u < kSBatch; ++u) {
+            const int s = set + u * nsets;
+            if (s < whole) x[u] = kStream ? stream_load(rv + tid + s * kSThreads) : rv[tid + s * kSThreads];   // uniform; nothing waits on these here
+            else if (s < nslots) x[u] = guarded(tid + s * kSThreads);
+            else x[u] = none;
+        }
+    };
+    float tmax = -INFINITY;                                       // maximum of the finite values I have read
+    // Maxima are taken as floats (NaN operands drop out of v_max3); a vector whose maximum is
+    // infinite is looked through by hand.
+    auto vector_max = [&](const u32x4& x) -> float {
+        const float m = T::vec_max(x);
+        if (__builtin_expect(m == INFINITY, 0)) {
+            float f = -INFINITY;
+            for (int j = 0; j < T::kElems; ++j) {
+                const float z = __uint_as_float(T::elem_bits(x, j));
+                if (z < INFINITY) f = fmaxf(f, z);
+            }
+            return f;
+        }
+        return m;
+    };
+    // The wave's m-th largest thread maximum, m = ceil(k / waves with columns), bit by bit from the
+    // top with one ballot per bit (the largest value that at least m lanes reach; only the upper 16
+    // bits, which for fp32 rows lowers the bound by less than 2^-7 of itself).  The smallest of
+    // the waves' values has waves x m >= k threads at or above it.  Values published earlier are
+    // lower bounds as well: no barrier between a refinement and its readers.
+    const int full_waves = nvec / 64 < 1 ? 1 : nvec / 64 < kSWaves ? nvec / 64 : kSWaves;
+    const int m_th = (k_req + full_waves - 1) / full_waves;
+    auto publish = [&]() {
+        if (wave >= full_waves) return;
+        const uint32_t key = tmax == 0.0f ? kKeyPosZero : key_of_f32(__float_as_uint(tmax));
+        uint32_t wm = 0u;
+        for (int b = 31; b >= 16; --b) {
+            const uint32_t cand = wm | (1u << b);
+            if ((int)__popcll(__ballot(key >= cand)) >= m_th) wm = cand;
+        }
+        if (lane == 0) __hip_atomic_store(&sh.tmax_wave[wave], wm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto current_theta = [&]() -> uint32_t {
+        uint32_t t = lane < full_waves ? __hip_atomic_load(&sh.tmax_wave[lane & (kSWaves - 1)], __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_WORKGROUP) : 0xFFFFFFFFu;
+#pragma unroll
+        for (int d = kSWaves / 2; d > 0; d >>= 1) { const uint32_t o = __shfl_xor(t, d, 64); t = o < t ? o : t; }
+        t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+        if (t == 0u) t = 1u;                                      // a wave with fewer than m finite maxima: every finite value
+        // a zero maximum was recorded as +0 whichever zero it was: let -0 in as well
+        return t == kKeyPosZero ? kKeyNegZero : t;
+    };
+    auto theta_value = [&](uint32_t t) -> float {                 // as a value to compare with (keys below the lowest finite one are no numbers)
+        return t < 0x00800000u ? -3.402823466e38f : __uint_as_float(f32_of_key(t));
+    };
+    // The vectors of a set whose maximum reaches `thf` go into the list: one reservation per wave
+    auto list_set = [&](const u32x4 x[kSBatch], const float m[kSBatch], int set, float thf) {
+        uint32_t hits = 0u;
+#pragma unroll
+        for (int u = 0; u < kSBatch; ++u) hits |= (uint32_t)(m[u] >= thf) << u;
+        if (!__any(hits != 0u)) return;
+        const int mine = __popc(hits);
+        const int inc = wave_prefix_sum(mine);
+        int base = 0;
+        if (lane == 63) base = atomicAdd(&sh.vec_n, inc);
+        int slot = __builtin_amdgcn_readlane(base, 63) + inc - mine;
+#pragma unroll
+        for (int u = 0; u < kSBatch; ++u) {
+            if (hits & (1u << u)) {
+                if (slot < kSVecCap) { lvec[slot] = x[u]; lvec_at[slot] = tid + (set + u * nsets) * kSThreads; }
+                ++slot;
+            }
+        }
+    };
+    if (tid == 0) { sh.gt_n = 0; sh.eq_n = 0; sh.token = 0; sh.list_n = 0; sh.vec_n = 0; }
+    {
+        u32x4 x[kSBatch], y[kSBatch];
+        float m[kSBatch];
+        auto maxima = [&](const u32x4 v[kSBatch]) {
+#pragma unroll
+            for (int u = 0; u < kSBatch; ++u) { m[u] = vector_max(v[u]); tmax = fmaxf(tmax, m[u]); }
+        };
+        request(x, 0);
+        if (nsets > 1) request(y, 1);
+        maxima(x);
+        publish();
+        // orders LDS only: __syncthreads() would wait for the loads in flight as well
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        float thf = theta_value(current_theta());
+        list_set(x, m, 0, thf);
+        // refined whenever what has been read has doubled, and at the end
+        auto refine = [&](int set) {
+            if (set + 1 == nsets || (set & (set + 1)) == 0) { publish(); thf = theta_value(current_theta()); }
+        };
+        for (int set = 1; set < nsets; set += 2) {
+            if (set + 1 < nsets) request(x, set + 1);
+            maxima(y);
+            list_set(y, m, set, thf);
+            refine(set);
+            if (set + 1 >= nsets) break;
+            if (set + 2 < nsets) request(y, set + 2);
+            maxima(x);
+            list_set(x, m, set + 1, thf);
+            refine(set + 1);
+        }
+    }
+    __syncthreads();
+    const uint32_t theta = current_theta();
+    if (__builtin_expect(sh.vec_n > kSVecCap, 0)) {               // uniform
+        __syncthreads();
+        if (tid == 0) sh.vec_n = 0;
+        __syncthreads();
+        const float thf = theta_value(theta);
+        for (int set = 0; set < nsets; ++set) {
+            u32x4 x[kSBatch];
+            float m[kSBatch];
+            request(x, set);
+#pragma unroll
+            for (int u = 0; u < kSBatch; ++u) m[u] = vector_max(x[u]);
+            list_set(x, m, set, thf);
+        }
+        __syncthreads();
+    }
+    const int n_vec = sh.vec_n;
+
+    // ---- 2. the candidates: every finite column whose key reaches theta ----------------------------
+    auto stream_candidates = [&](auto&& f) {
+        for (int s = 0; s < nslots; ++s) {
+            const int v = tid + s * kSThreads;
+            const u32x4 x = guarded(v);
+#pragma unroll
+            for (int e = 0; e < T::kElems; ++e) {
+                const uint32_t key = key_of_f32(T::elem_bits(x, e));
+                if (key >= theta) f(key, (int32_t)(v * T::kElems + e));
             }
         }
     };
@@ -534,70 +571,44 @@ void sample_select_kernel(SelArgs a)
         base = __shfl(base, leader, 64);
         return base + __popcll(m & ((1ull << lane) - 1ull));
     };
-    if (tid == 0) sh.list_n = 0;
-    __syncthreads();
-    {
-        // The thread's qualifying chunks as a bit mask; their vectors are then walked four at a
-        // time with fixed register slots (a register array indexed by a running count would
-        // live in scratch memory, and each of its accesses would queue behind the other rows'
-        // streaming).  All lanes of a wave take part in every round: the slot reservation is
-        // a wave-wide operation.
-        static_assert(T::kChunksPerThreadMax <= 64, "one mask bit per chunk");
-        uint64_t qmask = 0u;
-        for (int j = 0; j < CPT; ++j)
-            qmask |= (uint64_t)(T::unpack_upper(cmax[(size_t)j * kSThreads + tid]) >= theta) << j;
-        int j = qmask != 0u ? __builtin_ctzll(qmask) : -1, g = 0;
-        while (__any(j >= 0)) {
-            int64_t vq[4];
-            bool on[4];
+    if (n_vec <= kSVecCap) {
+        for (int i0 = 0; i0 < n_vec; i0 += kSThreads) {           // whole waves: the reservation is wave-wide
+            const int i = i0 + tid;
+            const u32x4 x = i < n_vec ? lvec[i] : none;
+            const int32_t col0 = i < n_vec ? lvec_at[i] * T::kElems : 0;
+            uint32_t key[T::kElems];
+            int mine = 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                vq[u] = (int64_t)tid + (int64_t)kSThreads * ((int64_t)(j < 0 ? 0 : j) * G + g);
-                on[u] = j >= 0 && vq[u] < nvec;
-                if (j >= 0 && (++g == G || !on[u])) {              // next qualifying chunk
-                    g = 0;
-                    qmask &= qmask - 1u;
-                    j = qmask != 0u ? __builtin_ctzll(qmask) : -1;
-                }
+            for (int e = 0; e < T::kElems; ++e) {
+                key[e] = key_of_f32(T::elem_bits(x, e));
+                mine += key[e] >= theta;
             }
-            u32x4 x[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = on[u] ? rv[vq[u]] : u32x4{0u, 0u, 0u, 0u};
-            // count my candidates, reserve a run of slots for the wave, write mine in order
-            uint32_t ok_mask = 0u;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-#pragma unroll
-                for (int e = 0; e < T::kElems; ++e) {
-                    const int64_t col = vq[u] * T::kElems + e;
-                    const uint32_t key = key_of_f32(T::elem_bits(x[u], e));
-                    ok_mask |= (uint32_t)(on[u] && col < V && key >= theta) << (u * T::kElems + e);
-                }
-            }
-            const int mine = __popc(ok_mask);
             const int inc = wave_prefix_sum(mine);
-            const int wave_total = __builtin_amdgcn_readlane(inc, 63);
+            if (__builtin_amdgcn_readlane(inc, 63) == 0) continue;
             int base = 0;
-            if (lane == 63 && wave_total > 0) base = atomicAdd(&sh.list_n, wave_total);
-            base = __builtin_amdgcn_readlane(base, 63);
-            int slot = base + inc - mine;
+            if (lane == 63) base = atomicAdd(&sh.list_n, inc);
+            int slot = __builtin_amdgcn_readlane(base, 63) + inc - mine;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-#pragma unroll
-                for (int e = 0; e < T::kElems; ++e) {
-                    if (ok_mask & (1u << (u * T::kElems + e))) {
-                        if (slot < kSListCap) {
-                            lkey[slot] = key_of_f32(T::elem_bits(x[u], e));
-                            lcol[slot] = (int32_t)(vq[u] * T::kElems + e);
-                        }
-                        ++slot;
-                    }
+            for (int e = 0; e < T::kElems; ++e) {
+                if (key[e] >= theta) {
+                    if (slot < kSListCap) { lkey[slot] = key[e]; lcol[slot] = col0 + e; }
+                    ++slot;
                 }
             }
         }
+    } else if (tid == 0) {
+        sh.list_n = kSListCap + 1;
     }
     __syncthreads();
     const int n_list = sh.list_n;
+    if (n_list == 0) {                                            // no finite logit in the row
+        if (tid == 0) {
+            a.token_out[row] = 0;
+            if (a.kept_out) a.kept_out[row] = 0;
+            if (a.logp_out) a.logp_out[row] = __builtin_nanf("");
+        }
+        return;
+    }
     const bool listed = n_list <= kSListCap;
     if (n_list <= kSoloList && k_req <= kSoloK) {                  // short list, small k: one wave finishes the row
         if (wave == 0) finish_in_one_wave<T>(a, sh, lkey, lcol, n_list, k_req, row, grow, inv_tau, c, lane);
@@ -611,7 +622,7 @@ void sample_select_kernel(SelArgs a)
         }
     };
 
-    // ---- 4. kappa: the k-th largest column (exact), by radix select over the candidates ---------
+    // kappa: the k-th largest column (exact), by radix select over the candidates ---------
     if (tid == 0) { sh.prefix = 0u; sh.k_rem = 0u; sh.n_total = 0u; }
     uint32_t k_col = (uint32_t)k_req;
     for (int pass = 0; pass < T::kKeyBits / 8; ++pass) {
@@ -643,7 +654,7 @@ void sample_select_kernel(SelArgs a)
     const int count_gt = (int)(k_eff - sh.k_rem);                 // columns above it (< k)
     __syncthreads();
 
-    // ---- 5. the columns above kappa, and those on it when they are few -------------------------------
+    // ---- 3. the columns above kappa, and those on it when they are few -------------------------------
     if (listed) {
         for (int e0 = 0; e0 < n_list; e0 += kSThreads) {          // whole waves: wave_slot is wave-wide
             const int e = e0 + tid;
@@ -702,7 +713,7 @@ void sample_select_kernel(SelArgs a)
     }
     __syncthreads();
 
-    // ---- 6. masses in rank order (fp64), cuts -----------------------------------------------------
+    // masses in rank order (fp64), cuts -----------------------------------------------------
     const uint32_t key1 = n > 0 ? sh.st_key[0] : kappa;           // the row's highest level
     const double z1 = (double)__uint_as_float(f32_of_key(key1));
     const double z_cut = (double)__uint_as_float(f32_of_key(kappa));
@@ -752,7 +763,7 @@ void sample_select_kernel(SelArgs a)
     const int kept_C = cut_level_kept ? n + n_cut : kept_sorted;
     const double kept_M = cut_level_kept ? M_k : sh.st_M[cut_index];
 
-    // ---- 7. race of the kept levels ------------------------------------------------------------------
+    // race of the kept levels ------------------------------------------------------------------
     // score n_j w_j / E_j, E_j from Philox stream 3 at index = the level's stored pattern; fp32
     // scores as in the unrestricted sampler; ties go to the higher level = lower sorted index.
     const float z1f = __uint_as_float(f32_of_key(key1));
@@ -796,7 +807,7 @@ void sample_select_kernel(SelArgs a)
         if (q > best_q || (q == best_q && l < best_lvl)) { best_q = q; best_lvl = l; }
     }
 
-    // ---- 8. the column inside the winning level ---------------------------------------------------------
+    // the column inside the winning level ---------------------------------------------------------
     uint32_t w4[4];
     philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
     const uint64_t k23 = (uint64_t)(w4[0] >> 9);
@@ -898,19 +909,14 @@ hipError_t launch_sample_select(const void* logits, bool is_bf16, int64_t rows, 
     a.top_k = top_k; a.top_p = top_p;
     a.seed = seed; a.row_base = row_base;
     a.token_out = token_out; a.logp_out = logp_out; a.kept_out = kept_out;
-    const int elems = is_bf16 ? SelBf16::kElems : SelF32::kElems;
-    const int cpt_max = is_bf16 ? SelBf16::kChunksPerThreadMax : SelF32::kChunksPerThreadMax;
-    const int64_t nvec = (V + elems - 1) / elems;
-    const int64_t vpt = (nvec + kSThreads - 1) / kSThreads;           // vectors per thread
-    a.group = (int)((vpt + cpt_max - 1) / cpt_max);
-    if (a.group < 1) a.group = 1;
-    a.chunks = (int)((vpt + a.group - 1) / a.group);
-    const size_t lds = (size_t)a.chunks * kSThreads * (is_bf16 ? sizeof(SelBf16::Stored) : sizeof(SelF32::Stored))
-                     + (size_t)kSListCap * 8;
-    if (is_bf16)
-        hipLaunchKernelGGL(sample_select_kernel<SelBf16>, dim3((unsigned)rows), dim3(kSThreads), lds, stream, a);
-    else
-        hipLaunchKernelGGL(sample_select_kernel<SelF32>, dim3((unsigned)rows), dim3(kSThreads), lds, stream, a);
+    const bool few = rows <= compute_units();
+    if (is_bf16) {
+        if (few) hipLaunchKernelGGL((sample_select_kernel<SelBf16, 1024>), dim3((unsigned)rows), dim3(1024), 0, stream, a);
+        else hipLaunchKernelGGL((sample_select_kernel<SelBf16, 512>), dim3((unsigned)rows), dim3(512), 0, stream, a);
+    } else {
+        if (few) hipLaunchKernelGGL((sample_select_kernel<SelF32, 1024>), dim3((unsigned)rows), dim3(1024), 0, stream, a);
+        else hipLaunchKernelGGL((sample_select_kernel<SelF32, 512>), dim3((unsigned)rows), dim3(512), 0, stream, a);
+    }
     return hipGetLastError();
 }
 

@@ -47,6 +47,9 @@ size_t vocab_pass_workspace_bytes(int64_t rows, int64_t V);
 hipError_t static_scratch(void** ptr_out, size_t* bytes_out);
 int64_t static_scratch_max_rows();
 
+// compute units of the current device (looked up once)
+int compute_units();
+
 // false when V is so large that the per-workgroup tables do not fit LDS
 bool vocab_pass_fits(int64_t V);
 

@@ -639,7 +639,7 @@ static int rows_per_group(int64_t V, bool sample)
 
 bool vocab_pass_fits(int64_t V) { return rows_per_group<8>(V, true) > 0 && rows_per_group<4>(V, true) > 0; }
 
-static int compute_units()
+int compute_units()
 {
     static int cus = 0;
     if (cus == 0) {
