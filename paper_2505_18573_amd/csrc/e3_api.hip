@@ -187,14 +187,9 @@ extern "C" int e3_logprob_entropy_gap(const void* logits, int dtype, int64_t row
             return E3_ERR_LAUNCH;
     }
     // also for rows == 0: sums and count are then written as 0
-    if (h_sum) {
-        if (e3::launch_entropy_reduce(entropy_out, row_mask, rows, entropy_sum_out, count_out,
-                                      stream, g_sum ? nullptr : stop_last) != hipSuccess)
-            return E3_ERR_LAUNCH;
-    }
-    if (g_sum) {
-        if (e3::launch_entropy_reduce(gap_out, row_mask, rows, gap_sum_out, nullptr, stream, stop_last)
-            != hipSuccess)
+    if (h_sum || g_sum) {
+        if (e3::launch_entropy_reduce(entropy_out, gap_out, row_mask, rows, entropy_sum_out, gap_sum_out,
+                                      count_out, stream, stop_last) != hipSuccess)
             return E3_ERR_LAUNCH;
     }
     return E3_OK;
@@ -235,8 +230,8 @@ extern "C" int e3_logprob_entropy_advantages(const void* logits, int dtype, int6
     if (e3::launch_vocab_pass(a, dtype == E3_BF16, false, workspace, workspace_bytes, stream) != hipSuccess)
         return E3_ERR_LAUNCH;
     if (h_sum) {
-        if (e3::launch_entropy_reduce(entropy_out, row_mask, rows, entropy_sum_out, entropy_count_out,
-                                      stream, stop_last) != hipSuccess)
+        if (e3::launch_entropy_reduce(entropy_out, nullptr, row_mask, rows, entropy_sum_out, nullptr,
+                                      entropy_count_out, stream, stop_last) != hipSuccess)
             return E3_ERR_LAUNCH;
     }
     return E3_OK;
