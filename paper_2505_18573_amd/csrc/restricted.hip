@@ -108,7 +108,7 @@ struct Row {
     int steps, whole;     // steps, and how many of them hold nothing but complete vectors
     __device__ __forceinline__ u32x4 guarded(int v) const
     {
-        constexpr uint32_t kNone = 0x7FC07FC0u;
+        constexpr uint32_t kNone = 0xFFC0FFC0u;
         u32x4 x = {kNone, kNone, kNone, kNone};
         if (v < nvec) x = p[v];
         if (v == nvec - 1) {
@@ -128,7 +128,10 @@ struct Row {
             for (int u = 0; u < kN; ++u) x[u] = p[tid + (step + u) * kRThreads];
         } else {
 #pragma unroll
-            for (int u = 0; u < kN; ++u) x[u] = guarded(step + u < end ? tid + (step + u) * kRThreads : nvec);
+            for (int u = 0; u < kN; ++u) {
+                if (step + u < (whole < end ? whole : end)) x[u] = p[tid + (step + u) * kRThreads];
+                else x[u] = guarded(step + u < end ? tid + (step + u) * kRThreads : nvec);
+            }
         }
     }
 };
@@ -205,8 +208,9 @@ __device__ __forceinline__ void scan_view(View& vw, int carry_C, double carry_M,
                                           int& Ct, double& Mt, Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
-    const int Ci = wave_prefix_i(vw.Cl);
-    const double Mi = wave_prefix_d(vw.Ml);
+    int Ci = 0;
+    double Mi = 0.0;
+    if (__any(vw.Cl > 0)) { Ci = wave_prefix_i(vw.Cl); Mi = wave_prefix_d(vw.Ml); }
     if (lane == 63) { sh.wave_C[wave] = Ci; sh.wave_M[wave] = Mi; }
     __syncthreads();
     const int tC = wave_prefix_i(lane < kRWaves ? sh.wave_C[lane] : 0);
@@ -221,9 +225,7 @@ __device__ __forceinline__ void scan_view(View& vw, int carry_C, double carry_M,
     vw.Mx = Mb + (Mi - vw.Ml);
 }
 
-// Cut searches among one thread's levels.  Count: the level whose cumulative count reaches k.
-// Mass: the first populated level whose cumulative mass reaches T, or the lowest populated one
-// if rounding lets none reach it.
+// Cut search among one thread's levels: the level whose cumulative count reaches k.
 struct Cut { int j, C; double M; };       // level j of the thread; count and mass down to it
 
 template <int kOwn, int kUnroll, typename Cnt>
@@ -243,38 +245,36 @@ __device__ __forceinline__ Cut own_count_cut(const View& vw, int k, Cnt&& cnt)
     }
     return cut;
 }
-template <int kOwn, int kUnroll, typename Cnt>
-__device__ __forceinline__ Cut own_mass_cut(const View& vw, double T, Cnt&& cnt)
-{
-    Cut cut{kOwn - 1, vw.Cx, vw.Mx};
-    double w = vw.w_top;
-    bool done = false;
-#pragma unroll kUnroll
-    for (int j = 0; j < kOwn; ++j) {
-        const int n = (int)cnt(j);
-        if (!done && n != 0) {
-            cut.j = j; cut.C += n; cut.M = fma((double)n, w, cut.M);
-            done = cut.M >= T;
-        }
-        w = next_weight(vw, w, j);
-    }
-    return cut;
-}
-
 // The mass cut of the workgroup: the owner is the first thread in rank order whose inclusive prefix
-// reaches T (the scan's prefixes may disagree in the last bit, so only threads with columns count).
-// Every wave's first such thread searches its levels and offers the result; the lowest wave's is taken.
-template <int kOwn, int kUnroll, typename Cnt, typename Key>
-__device__ __forceinline__ void offer_mass_cut(const View& vw, double T, Cnt&& cnt, Key&& key, Shared& sh, int tid)
+// reaches T (the scan's prefixes may disagree in the last bit, so only threads with columns count),
+// the cut its first populated level whose cumulative mass reaches T, or the lowest populated one
+// if rounding lets none reach it.  Every wave's first such thread is looked through by the wave, one level
+// per lane (count_at(rank) from LDS), and the result offered; the lowest wave's offer is taken.
+template <int kOwn, typename CountAt, typename KeyAt>
+__device__ __forceinline__ void offer_mass_cut(const View& vw, double T, CountAt&& count_at, KeyAt&& key_at, Shared& sh, int tid)
 {
+    static_assert(kOwn <= 16, "one row of lanes");
     const int lane = tid & 63, wave = tid >> 6;
     const unsigned long long reach = __ballot(vw.Cl > 0 && vw.Mx + vw.Ml >= T);
     if (reach == 0ull) {
         if (lane == 0) sh.cut_key[wave] = -1;
-    } else if (lane == (int)__builtin_ctzll(reach)) {
-        const Cut cut = own_mass_cut<kOwn, kUnroll>(vw, T, cnt);
-        sh.cut_key[wave] = key(cut.j); sh.cut_C[wave] = cut.C; sh.cut_M[wave] = cut.M;
+        return;
     }
+    const int owner = (int)__builtin_ctzll(reach);
+    const int rank = kOwn * (wave * 64 + owner) + lane;
+    const int n = lane < kOwn ? (int)count_at(rank) : 0;
+    const int e = lane - __builtin_amdgcn_readlane(vw.top, owner);        // lanes before the owner's top level have n == 0
+    double w = lane_value(vw.w_top, owner), r = lane_value(vw.r, owner);
+#pragma unroll
+    for (int bit = 1; bit < kOwn; bit <<= 1) {
+        if (e > 0 && (e & bit) != 0) w *= r;
+        r *= r;
+    }
+    const int C = __builtin_amdgcn_readlane(vw.Cx, owner) + wave_prefix_i(n);
+    const double M = lane_value(vw.Mx, owner) + wave_prefix_d(n != 0 ? (double)n * w : 0.0);
+    const unsigned long long have = __ballot(n != 0), enough = __ballot(n != 0 && M >= T);
+    const int at = enough != 0ull ? (int)__builtin_ctzll(enough) : 63 - (int)__builtin_clzll(have);
+    if (lane == at) { sh.cut_key[wave] = key_at(rank); sh.cut_C[wave] = C; sh.cut_M[wave] = M; }
 }
 // The first wave with an offer, or kRWaves.
 __device__ __forceinline__ int first_offer(const Shared& sh, int lane)
@@ -323,23 +323,28 @@ __device__ __forceinline__ int columns_unlike(const u32x4& x, uint32_t pat)
     return (int)n.x + (int)n.y;
 }
 
-// The rem-th column (0-based, in column order) that stores pattern `pat` within stream steps
+// Stores the rem-th column (0-based, in column order) that holds pattern `pat` within stream steps
 // [i0, i1): kBlock steps are requested at once; a (step, wave) holds 512 consecutive columns, so the
 // waves' counts per step, in that order, say where the column is, and the wave that holds it
-// finds the lane.  -1 if there are not that many.
-__device__ __forceinline__ int locate(const Row& row, int i0, int i1, uint32_t pat, int rem, Shared& sh, int tid)
+// finds the lane, which stores it.  0 if there are not that many.
+__device__ __forceinline__ void locate(const Row& row, int i0, int i1, uint32_t pat, int rem, int32_t* token,
+                                       Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) sh.token = -1;
     for (int ib = i0; ib < i1; ib += kBlock) {
         u32x4 x[kBlock];
         row.request<kBlock>(x, ib, i1, tid);
-        int inc[kBlock], own[kBlock];
+        // counts of up to 8 per lane and 512 per wave: three steps share a word of the prefix sums
+        static_assert(kBlock <= 6, "two words");
+        uint32_t own[2] = {0u, 0u}, inc[2];
 #pragma unroll
-        for (int u = 0; u < kBlock; ++u) {
-            own[u] = 8 - columns_unlike(x[u], pat);
-            inc[u] = wave_prefix_i(own[u]);
-            if (lane == 63) sh.tot[u * kRWaves + wave] = inc[u];
+        for (int u = 0; u < kBlock; ++u) own[u / 3] |= (uint32_t)(8 - columns_unlike(x[u], pat)) << (10 * (u % 3));
+        auto of = [](const uint32_t w[2], int u) -> int { return (int)(((u < 3 ? w[0] : w[1]) >> (10 * (u % 3))) & 0x3FFu); };
+#pragma unroll
+        for (int i = 0; i < 2; ++i) inc[i] = (uint32_t)wave_prefix_i((int)own[i]);
+        if (lane == 63) {
+#pragma unroll
+            for (int u = 0; u < kBlock; ++u) sh.tot[u * kRWaves + wave] = of(inc, u);
         }
         __syncthreads();
         // every wave finds the (step, wave) that holds the column: two consecutive totals per lane
@@ -356,32 +361,35 @@ __device__ __forceinline__ int locate(const Row& row, int i0, int i1, uint32_t p
             if (before + first <= rem) { before += first; ++at; }
             if (at % kRWaves == wave) {
                 const int step = at / kRWaves, want = rem - before;
+                u32x4 y = x[0];
 #pragma unroll
-                for (int u = 0; u < kBlock; ++u) {
-                    if (u == step) {
-                        if (want >= inc[u] - own[u] && want < inc[u]) {        // exactly one lane
-                            int skip = want - (inc[u] - own[u]);
-                            for_each_pattern(x[u], [&](uint32_t p, int j) {
-                                if (p == pat && skip-- == 0) sh.token = (tid + (ib + u) * kRThreads) * 8 + j;
-                            });
-                        }
-                    }
+                for (int u = 1; u < kBlock; ++u) y = u == step ? x[u] : y;
+                const int upto_me = of(inc, step), mine = of(own, step);
+                if (want >= upto_me - mine && want < upto_me) {   // exactly one lane
+                    uint32_t m = 0;
+                    for_each_pattern(y, [&](uint32_t p, int j) { m |= (uint32_t)(p == pat) << j; });
+                    for (int skip = want - (upto_me - mine); skip > 0; --skip) m &= m - 1;
+                    *token = (tid + (ib + step) * kRThreads) * 8 + (__ffs(m) - 1);
                 }
             }
-            __syncthreads();
-            return sh.token;
+            return;
         }
         rem -= __builtin_amdgcn_readlane(upto, 63);
         __syncthreads();                                          // the totals are reused
     }
-    return -1;
+    if (tid == 0) *token = 0;                                     // only with weights that are no numbers
 }
 
-struct Drawn {
-    bool any;             // a level won
-    int pattern, token, kept_C;
-    double kept_M, z1;
-};
+// The row's other outputs, by one thread.
+__device__ __forceinline__ void store_row(const RestrictedArgs& a, int64_t r, int kept_C, bool drawn, int pattern,
+                                          double z1, double kept_M, double inv_tau)
+{
+    if (a.kept_out) a.kept_out[r] = kept_C;
+    if (a.logp_out)
+        a.logp_out[r] = drawn ? (float)(((double)value_of_pattern(pattern) - z1) * inv_tau - log(kept_M))
+                              : __builtin_nanf("");
+    if (!drawn) a.token_out[r] = 0;
+}
 
 // ---------------------------------------------------------------------------
 // The wide rows: four windows of 16,384 patterns in rank order, 32-bit counters.
@@ -406,8 +414,8 @@ __device__ __forceinline__ void wide_count(const Row& row, WideWindow win, uint3
     __syncthreads();
 }
 
-__device__ __forceinline__ Drawn wide_row(const Row& row, const RestrictedArgs& a, double inv_tau, float c, uint64_t grow,
-                                          uint64_t k23, uint32_t* hist, Shared& sh, int tid)
+__device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a, int64_t r, double inv_tau, float c,
+                                         uint64_t grow, uint32_t k23, uint32_t* hist, Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
     const bool k_on = a.top_k >= 1 && (int64_t)a.top_k < a.V, p_on = a.top_p < 1.0f;
@@ -442,7 +450,6 @@ __device__ __forceinline__ Drawn wide_row(const Row& row, const RestrictedArgs& 
         scan_view(vw, C, M, kRThreads, 0, 0.0, Ct, Mt, sh, tid);
         C += Ct; M += Mt;
     };
-    Drawn d{false, 0, 0, 0, 0.0, 0.0};
     int C_all = 0;
     double M_all = 0.0;
 #pragma unroll 1
@@ -453,12 +460,14 @@ __device__ __forceinline__ Drawn wide_row(const Row& row, const RestrictedArgs& 
     }
     if (tid == 0) { sh.C_above[kWideWindows] = C_all; sh.M_above[kWideWindows] = M_all; }
     __syncthreads();
-    if (!have_z1) return d;                                       // no finite logit
-    d.z1 = z1;
-    int cut_key = 0;
-    d.kept_C = C_all; d.kept_M = M_all;
+    if (!have_z1) {                                               // no finite logit
+        if (tid == 0) store_row(a, r, 0, false, 0, 0.0, 0.0, inv_tau);
+        return;
+    }
+    int cut_key = 0, kept_C = C_all;
+    double kept_M = M_all;
     // one sweep of the window that holds a cut, then the owner's search
-    if (k_on && d.kept_C >= a.top_k) {
+    if (k_on && kept_C >= a.top_k) {
 #pragma unroll 1
         for (int w = 0; w < kWideWindows; ++w) {
             if (sh.C_above[w] < a.top_k && sh.C_above[w + 1] >= a.top_k) {
@@ -474,11 +483,11 @@ __device__ __forceinline__ Drawn wide_row(const Row& row, const RestrictedArgs& 
                 __syncthreads();
             }
         }
-        cut_key = sh.cut_key[0]; d.kept_C = sh.cut_C[0]; d.kept_M = sh.cut_M[0];
+        cut_key = sh.cut_key[0]; kept_C = sh.cut_C[0]; kept_M = sh.cut_M[0];
         __syncthreads();
     }
     if (p_on) {
-        const double T = (double)a.top_p * d.kept_M;
+        const double T = (double)a.top_p * kept_M;
         bool looked = false;
 #pragma unroll 1
         for (int w = 0; w < kWideWindows; ++w) {
@@ -489,11 +498,11 @@ __device__ __forceinline__ Drawn wide_row(const Row& row, const RestrictedArgs& 
                 int C = sh.C_above[w];
                 double M = sh.M_above[w];
                 scan(win, vw, C, M);
-                offer_mass_cut<kOwnW, 1>(vw, T, [&](int j) { return count_of(win, kOwnW * tid + j); },
-                                         [&](int j) { return key_of_pattern(win.pattern(kOwnW * tid + j)); }, sh, tid);
+                offer_mass_cut<kOwnW>(vw, T, [&](int rank) { return count_of(win, rank); },
+                                      [&](int rank) { return key_of_pattern(win.pattern(rank)); }, sh, tid);
                 __syncthreads();
                 const int w1 = first_offer(sh, lane);
-                if (w1 < kRWaves && sh.cut_key[w1] > cut_key) { cut_key = sh.cut_key[w1]; d.kept_C = sh.cut_C[w1]; d.kept_M = sh.cut_M[w1]; }
+                if (w1 < kRWaves && sh.cut_key[w1] > cut_key) { cut_key = sh.cut_key[w1]; kept_C = sh.cut_C[w1]; kept_M = sh.cut_M[w1]; }
             }
         }
     }
@@ -518,14 +527,10 @@ __device__ __forceinline__ Drawn wide_row(const Row& row, const RestrictedArgs& 
             best_n = (int)hist[pattern_of_key(key_of(mine)) & 0x3FFF];
         }
     }
-    if (best.q >= 0.0f) {
-        d.any = true;
-        d.pattern = pattern_of_key(key_of(best));
-        const int pos = (int)(((2u * k23 + 1u) * (uint64_t)best_n) >> 24);
-        __syncthreads();
-        d.token = locate(row, 0, row.steps, (uint32_t)d.pattern, pos, sh, tid);
-    }
-    return d;
+    const bool drawn = best.q >= 0.0f;
+    const int pattern = pattern_of_key(key_of(best));
+    if (tid == 0) store_row(a, r, kept_C, drawn, pattern, z1, kept_M, inv_tau);
+    if (drawn) locate(row, 0, row.steps, (uint32_t)pattern, (int)(((2ull * k23 + 1ull) * (uint64_t)best_n) >> 24), a.token_out + r, sh, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -553,25 +558,26 @@ struct Near {
     }
     static __device__ __forceinline__ int total(uint32_t a, uint32_t b)      // of the four quarters
     {
-        return (int)((a & 0xFFFFu) + (a >> 16) + (b & 0xFFFFu) + (b >> 16));
+        return (int)__builtin_amdgcn_sad_u16(b, 0u, __builtin_amdgcn_sad_u16(a, 0u, 0u));
     }
     __device__ __forceinline__ int count(int rank) const { return total(hist[slot(rank)], hist[kArray + slot(rank)]); }
     // the counts of the kOwnN levels from rank0 (a multiple of kOwnN) on
     __device__ __forceinline__ void own_counts(int rank0, int cnt[kOwnN]) const
     {
-        const bool neg = rank0 >= kHalf;
+        const bool neg = __builtin_amdgcn_readfirstlane(rank0) >= kHalf;         // a wave's levels have one sign
         const int s0 = neg ? 2 * (rank0 - kHalf) : 2 * (kHalf - kOwnN - rank0);
-        int both[2 * kOwnN];
+        uint32_t q01[kOwnN], q23[kOwnN];                          // my sign's words, in rising magnitude
 #pragma unroll
         for (int i = 0; i < kOwnN / 2; ++i) {
             const uint32_t at = swizzled((uint32_t)(s0 + 4 * i));
             const uint4 a = *reinterpret_cast<const uint4*>(hist + at);
             const uint4 b = *reinterpret_cast<const uint4*>(hist + kArray + at);
-            both[4 * i] = total(a.x, b.x); both[4 * i + 1] = total(a.y, b.y);
-            both[4 * i + 2] = total(a.z, b.z); both[4 * i + 3] = total(a.w, b.w);
+            q01[2 * i] = neg ? a.y : a.x; q01[2 * i + 1] = neg ? a.w : a.z;
+            q23[2 * i] = neg ? b.y : b.x; q23[2 * i + 1] = neg ? b.w : b.z;
         }
 #pragma unroll
-        for (int j = 0; j < kOwnN; ++j) cnt[j] = neg ? both[2 * j + 1] : both[2 * (kOwnN - 1 - j)];
+        for (int j = 0; j < kOwnN; ++j)
+            cnt[j] = neg ? total(q01[j], q23[j]) : total(q01[kOwnN - 1 - j], q23[kOwnN - 1 - j]);
     }
     // first / last rank whose key is at most / at least `key`
     __device__ __forceinline__ int first_at_most(int key) const
@@ -606,26 +612,21 @@ __device__ __forceinline__ void note_outside(const u32x4& x, int v, int quarter,
     n_odd = wave_prefix_i(n_odd);
     if (lane == 63 && n_odd != 0) atomicAdd(&sh.n_not_finite, n_odd);
     if (!__any(more)) return;
-    for_each_pattern(x, [&](uint32_t p, int j) {
-        const uint32_t mag = p & 0x7FFFu;
-        const bool out = mag < 0x7F80u && mag - (uint32_t)base >= (uint32_t)kHalf;
-        if (__ballot(out) == 0ull) return;
-        const bool neg = p >= 0x8000u;
-        auto tally = [&](bool hit, int* counter) {
-            const unsigned long long m = __ballot(hit);
-            if (m != 0ull && lane == (int)__builtin_ctzll(m)) atomicAdd(counter, (int)__popcll(m));
-        };
-        tally(out && mag == 0u && !neg, &sh.zeros[0][quarter]);
-        tally(out && mag == 0u && neg, &sh.zeros[1][quarter]);
-        const bool large = out && mag >= (uint32_t)base;
-        tally(large && !neg, &sh.n_above);
-        tally(large && neg, &sh.n_below);
-        const bool small = out && mag != 0u && mag < (uint32_t)base;
-        if (small) {
+    u32x4 rest = x;
+#pragma unroll 1
+    for (int j = 0; j < 8; ++j) {                                 // one pattern at a time: this code is rarely run, and kept small
+        const uint32_t p = rest.x & 0xFFFFu, mag = p & 0x7FFFu;
+        rest.x = rest.x >> 16 | rest.y << 16; rest.y = rest.y >> 16 | rest.z << 16;
+        rest.z = rest.z >> 16 | rest.w << 16; rest.w >>= 16;
+        const bool out = mag < 0x7F80u && mag - (uint32_t)base >= (uint32_t)kHalf, neg = p >= 0x8000u;
+        const bool zero = out && mag == 0u, large = out && mag >= (uint32_t)base;
+        if (zero) atomicAdd(&sh.zeros[neg][quarter], 1);
+        if (large) atomicAdd(neg ? &sh.n_below : &sh.n_above, 1);
+        if (out && !zero && !large) {
             const int at = atomicAdd(&sh.list_n, 1);
             if (at < kMidList) { sh.list_key[at] = key_of_pattern((int)p); sh.list_col[at] = v * 8 + j; }
         }
-    });
+    }
 }
 
 // Counts the row.  Returns the window.
@@ -666,6 +667,7 @@ __device__ __forceinline__ Near near_count(const Row& row, uint32_t* hist, Share
     const u16x2 base_v = {base2, base2}, spare_v = {spare, spare};
     for (int i0 = 0; i0 < row.steps; i0 += kAhead) {
         if (i0 > 0) row.request<kAhead>(x, i0, row.steps, tid);
+        uint32_t outside = 0u;
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
             if (i0 + u >= row.steps) break;                       // uniform
@@ -682,8 +684,15 @@ __device__ __forceinline__ Near near_count(const Row& row, uint32_t* hist, Share
                 atomicAdd(reinterpret_cast<uint32_t*>(h + (at >> 16)), inc);
             };
             add2(x[u].x); add2(x[u].y); add2(x[u].z); add2(x[u].w);
-            if (__builtin_expect(__any(worst.x >= 2 * kHalf || worst.y >= 2 * kHalf), 0))
-                note_outside(x[u], tid + (i0 + u) * kRThreads, quarter, w.base, sh, lane);
+            outside |= (uint32_t)(__any(worst.x >= 2 * kHalf || worst.y >= 2 * kHalf) != 0) << u;
+        }
+        while (__builtin_expect(outside != 0u, 0)) {              // uniform: steps with values outside the window
+            const int u = __builtin_ctz(outside);
+            outside &= outside - 1u;
+            u32x4 y = x[0];
+#pragma unroll
+            for (int i = 1; i < kAhead; ++i) y = i == u ? x[i] : y;
+            note_outside(y, tid + (i0 + u) * kRThreads, (i0 + u) / w.per_quarter, w.base, sh, lane);
         }
     }
     __syncthreads();
@@ -734,10 +743,15 @@ void sample_restricted_kernel(RestrictedArgs a)
     const uint64_t grow = a.row_base + (uint64_t)r;
     const bool k_on = a.top_k >= 1 && (int64_t)a.top_k < a.V, p_on = a.top_p < 1.0f;
 
-    Drawn d{false, 0, 0, 0, 0.0, 0.0};
+    uint32_t k23;                                                 // picks the column within the winning level
+    {
+        uint32_t w4[4];
+        philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
+        k23 = w4[0] >> 9;
+    }
     const Near win = near_count(row, hist, sh, tid);
 
-    // my levels; the row's highest level
+    // my levels
     View vw;
     int cnt[kOwnN];
     const int rank0 = kOwnN * tid;
@@ -749,20 +763,21 @@ void sample_restricted_kernel(RestrictedArgs a)
         if (cnt[j] != 0) vw.top = j;
     }
     const int p_top = win.pattern(rank0 + (vw.Cl > 0 ? vw.top : 0));
-    int top = vw.Cl > 0 ? key_of_pattern(p_top) : -1;             // the highest level I know of
     const int list_n = sh.list_n;
     int n_zero = 0;
 #pragma unroll
     for (int q = 0; q < 2 * kQuarters; ++q) n_zero += (&sh.zeros[0][0])[q];
     const bool listed = list_n <= kMidList;
-    const bool has_mid = n_zero != 0 || (list_n != 0 && listed);
+    const bool has_mid = listed && (n_zero != 0 || list_n != 0);
     const int n_mid = has_mid ? list_n + 2 : 0;
     if (has_mid && wave == 0) {
         middle_items(sh, lane);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        if (lane < n_mid && sh.mid_cnt[lane] != 0 && sh.mid_key[lane] > top) top = sh.mid_key[lane];
     }
+    // the row's highest level
+    int top = vw.Cl > 0 ? key_of_pattern(p_top) : -1;
+    if (has_mid && wave == 0 && lane < n_mid && sh.mid_cnt[lane] != 0 && sh.mid_key[lane] > top) top = sh.mid_key[lane];
     {
         const float t = wave_max((float)top);                     // keys are below 2^16: exact in fp32
         if (lane == 0) sh.wave_top[wave] = t;
@@ -794,17 +809,14 @@ void sample_restricted_kernel(RestrictedArgs a)
     // weight: a row of them stays below the last bit of the total, which is at least 1, and none can win the race.
     const bool below_weightless = n_below == 0
         || (top_key >= 0.0f && (-(double)value_of_pattern(win.base + kHalf) - z1) * inv_tau < -56.0);
-    bool wide = sh.n_above != 0 || !listed || !below_weightless
+    const bool wide = sh.n_above != 0 || !listed || !below_weightless
              || C_win + n_zero + list_n + n_below + sh.n_not_finite + sh.n_above != row.steps * kRThreads * 8    // a counter wrapped
              || (k_on && C_all >= a.top_k && C_in < a.top_k);                                        // the cut is below the window
     if (wide) {                                                   // uniform
-        uint32_t w4[4];
-        philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
-        d = wide_row(row, a, inv_tau, c, grow, (uint64_t)(w4[0] >> 9), hist, sh, tid);
+        wide_row(row, a, r, inv_tau, c, grow, k23, hist, sh, tid);
     } else if (top_key >= 0.0f) {
-        d.z1 = z1;
-        d.kept_C = C_all; d.kept_M = M_all;
-        int cut_key = 0;
+        int cut_key = 0, kept_C = C_all;
+        double kept_M = M_all;
         auto my_cnt = [&](int j) { return cnt[j]; };
         auto my_key = [&](int j) { return key_of_pattern(win.pattern(rank0 + j)); };
         // The middle's share of a search, by the first negative wave: the items carry inclusive
@@ -827,7 +839,7 @@ void sample_restricted_kernel(RestrictedArgs a)
             }
         };
         auto take = [&](int w) {
-            if (sh.cut_key[w] > cut_key) { cut_key = sh.cut_key[w]; d.kept_C = sh.cut_C[w]; d.kept_M = sh.cut_M[w]; }
+            if (sh.cut_key[w] > cut_key) { cut_key = sh.cut_key[w]; kept_C = sh.cut_C[w]; kept_M = sh.cut_M[w]; }
         };
         if (k_on && C_all >= a.top_k) {                           // exactly one place holds the cut
             if (vw.Cx < a.top_k && vw.Cx + vw.Cl >= a.top_k) {
@@ -846,8 +858,9 @@ void sample_restricted_kernel(RestrictedArgs a)
             __syncthreads();
         }
         if (p_on) {
-            const double T = (double)a.top_p * d.kept_M;
-            offer_mass_cut<kOwnN, kOwnN>(vw, T, my_cnt, my_key, sh, tid);
+            const double T = (double)a.top_p * kept_M;
+            offer_mass_cut<kOwnN>(vw, T, [&](int rank) { return win.count(rank); },
+                                  [&](int rank) { return key_of_pattern(win.pattern(rank)); }, sh, tid);
             if (has_mid && wave == kMidWave) offer_middle(M0 + sh.mid_M[lane] >= T);
             __syncthreads();
             const int w1 = first_offer(sh, lane);                 // kRWaves: nobody reaches T, nothing is cut
@@ -875,47 +888,38 @@ void sample_restricted_kernel(RestrictedArgs a)
         best = reduce_best(best, sh, tid);
 
         // the column inside the winning level
-        if (best.q >= 0.0f) {
-            d.any = true;
-            d.pattern = pattern_of_key(key_of(best));
-            uint32_t w4[4];
-            philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
-            const uint64_t k23 = (uint64_t)(w4[0] >> 9);
-            const int mag = d.pattern & 0x7FFF;
-            if (mag != 0 && mag < win.base) {                     // a listed value
+        const bool drawn = best.q >= 0.0f;
+        const int pattern = pattern_of_key(key_of(best)), mag = pattern & 0x7FFF;
+        auto pick = [&](int n) -> int { return (int)(((2ull * k23 + 1ull) * (uint64_t)n) >> 24); };
+        if (drawn && mag != 0 && mag < win.base) {                // a listed value
+            if (tid == 0) {
                 int at = 0, n = 0;
                 for (int e = n_mid - 1; e >= 0; --e)
                     if (sh.mid_key[e] == key_of(best)) { at = e; ++n; }
-                d.token = sh.mid_col[at + (int)(((2u * k23 + 1u) * (uint64_t)n) >> 24)];
-            } else {
-                int q4[kQuarters];
-                if (mag == 0) {
-#pragma unroll
-                    for (int q = 0; q < kQuarters; ++q) q4[q] = sh.zeros[d.pattern >> 15][q];
-                } else {
-                    const uint32_t s = swizzled((uint32_t)(2 * (mag - win.base) + (d.pattern >> 15)));
-                    const uint32_t lo = hist[s], hi = hist[kArray + s];
-                    q4[0] = (int)(lo & 0xFFFFu); q4[1] = (int)(lo >> 16);
-                    q4[2] = (int)(hi & 0xFFFFu); q4[3] = (int)(hi >> 16);
-                }
-                const int n = q4[0] + q4[1] + q4[2] + q4[3];
-                int rem = (int)(((2u * k23 + 1u) * (uint64_t)n) >> 24), quarter = 0;
-#pragma unroll
-                for (int q = 0; q < kQuarters - 1; ++q)
-                    if (quarter == q && rem >= q4[q]) { rem -= q4[q]; ++quarter; }
-                const int i0 = quarter * win.per_quarter;
-                const int i1 = i0 + win.per_quarter < row.steps ? i0 + win.per_quarter : row.steps;
-                d.token = locate(row, i0, i1, (uint32_t)d.pattern, rem, sh, tid);
+                a.token_out[r] = sh.mid_col[at + pick(n)];
             }
+        } else if (drawn) {
+            int q4[kQuarters];
+            if (mag == 0) {
+#pragma unroll
+                for (int q = 0; q < kQuarters; ++q) q4[q] = sh.zeros[pattern >> 15][q];
+            } else {
+                const uint32_t s = swizzled((uint32_t)(2 * (mag - win.base) + (pattern >> 15)));
+                const uint32_t lo = hist[s], hi = hist[kArray + s];
+                q4[0] = (int)(lo & 0xFFFFu); q4[1] = (int)(lo >> 16);
+                q4[2] = (int)(hi & 0xFFFFu); q4[3] = (int)(hi >> 16);
+            }
+            int rem = pick(q4[0] + q4[1] + q4[2] + q4[3]), quarter = 0;
+#pragma unroll
+            for (int q = 0; q < kQuarters - 1; ++q)
+                if (quarter == q && rem >= q4[q]) { rem -= q4[q]; ++quarter; }
+            const int i0 = quarter * win.per_quarter;
+            const int i1 = i0 + win.per_quarter < row.steps ? i0 + win.per_quarter : row.steps;
+            locate(row, i0, i1, (uint32_t)pattern, rem, a.token_out + r, sh, tid);
         }
-    }
-    if (tid == 0) {
-        const int tok = d.token >= 0 && d.token < a.V ? d.token : 0;
-        a.token_out[r] = tok;
-        if (a.kept_out) a.kept_out[r] = d.kept_C;
-        if (a.logp_out)
-            a.logp_out[r] = d.any ? (float)(((double)value_of_pattern(d.pattern) - d.z1) * inv_tau - log(d.kept_M))
-                                  : __builtin_nanf("");
+        if (tid == 0) store_row(a, r, kept_C, drawn, pattern, z1, kept_M, inv_tau);
+    } else if (tid == 0) {                                        // no finite logit
+        store_row(a, r, 0, false, 0, 0.0, 0.0, inv_tau);
     }
 }
 

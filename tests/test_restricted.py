@@ -358,6 +358,9 @@ def _outside_rows(kind, V, rows, g):
     elif kind == "zeros_and_small":
         put(V // 4, lambda n: sign(n) * 0.0)
         put(20, lambda n: sign(n) * 1e-12)
+    elif kind == "zeros_and_many_small":
+        put(V // 4, lambda n: sign(n) * 0.0)
+        put(300, lambda n: sign(n) * 1e-12)
     elif kind == "masked_inf":
         put(V // 2, lambda n: torch.full((n,), -float("inf"), device=DEV))
     elif kind == "masked_lowest":
@@ -377,7 +380,7 @@ def _outside_rows(kind, V, rows, g):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("kind", ["small1", "small61", "small62", "small63", "small500", "zeros", "zeros_and_small",
+@pytest.mark.parametrize("kind", ["small1", "small61", "small62", "small63", "small500", "zeros", "zeros_and_small", "zeros_and_many_small",
                                   "masked_inf", "masked_lowest", "masked_1e4", "large_first", "large_late",
                                   "all_below", "subnormal"])
 @pytest.mark.parametrize("V", [3_003, 70_001])
