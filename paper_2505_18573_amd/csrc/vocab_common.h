@@ -25,8 +25,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #define E3_NT_LOADS 1        // stream the logits with non-temporal loads
 #endif
 #ifndef E3_SPLIT_BELOW_NUM        // small-batch path while row-block workgroups <= CUs * NUM / DEN
-#define E3_SPLIT_BELOW_NUM 3
-#define E3_SPLIT_BELOW_DEN 8
+#define E3_SPLIT_BELOW_NUM 1
+#define E3_SPLIT_BELOW_DEN 2
 #endif
 
 constexpr int kChunk = 8;                       // columns per lane per sweep

@@ -642,9 +642,9 @@ LaunchEvents take_launch_events()
     return e;
 }
 
-// Rows per workgroup: at least two items per wave (one row of 38 super-tiles at
-// V = 151,936 gives a wave 4 or 5), and the noise table must fit LDS
-// (0 = does not fit).  Two 8-wave workgroups are resident per compute unit; what exceeds
+// Rows per workgroup of a large batch: at least two items per wave (one row of 38 super-tiles
+// at V = 151,936 gives a wave 4 or 5), and the noise table must fit LDS
+// (0 = does not fit).  launch_for takes fewer where the batch is too small for that.  Two 8-wave workgroups are resident per compute unit; what exceeds
 // that is handed out by the hardware dispatcher as workgroups finish.
 template <int kWaves>
 static int rows_per_group(int64_t V, bool sample)
@@ -673,9 +673,8 @@ int compute_units()
 }
 
 template <typename Chunk, bool kSample, int kWaves>
-static hipError_t launch_groups(const VocabPassArgs& a, hipStream_t stream)
+static hipError_t launch_groups(const VocabPassArgs& a, int rpb, hipStream_t stream)
 {
-    const int rpb = rows_per_group<kWaves>(a.V, kSample);
     if (rpb == 0) return hipErrorInvalidValue;
     const int nst = (int)((a.V + kSuperCols - 1) / kSuperCols);
     const size_t lds = lds_bytes<kWaves>(rpb, nst, kSample);
@@ -701,22 +700,33 @@ static hipError_t launch_groups(const VocabPassArgs& a, hipStream_t stream)
 template <typename Chunk, bool kSample>
 static hipError_t launch_for(const VocabPassArgs& a, hipStream_t stream)
 {
-#ifdef E3_FORCE_WAVES
-    return launch_groups<Chunk, kSample, E3_FORCE_WAVES>(a, stream);
-#else
     const int64_t cus = compute_units();
-    const int rpb8 = rows_per_group<8>(a.V, kSample);
-    const int rpb4 = rows_per_group<4>(a.V, kSample);
-    if (rpb8 == 0) return launch_groups<Chunk, kSample, 4>(a, stream);
+    // Several rows per workgroup only where that leaves a resident round of workgroups (nearly) full:
+    // 512 rows x 24,000 bf16 columns (three rows per workgroup before) 20.6 -> 11.8 us, 512 x 48,000
+    // (two) 18.7 -> 15.7 us; at 1000 rows x 32,000 two rows (18.6 us) beat one (19.6 us), hence the quarter.
+    auto spread = [&](int rpb, int64_t round) -> int {
+        const int64_t most = (a.rows + round / 4) / round;
+        return rpb > 1 && most < rpb ? (most > 1 ? (int)most : 1) : rpb;
+    };
+    const int rpb8 = spread(rows_per_group<8>(a.V, kSample), 2 * cus);
+    const int rpb4 = spread(rows_per_group<4>(a.V, kSample), 4 * cus);
+    // Rows of at most four super-tiles: four waves per workgroup and just enough rows to give each
+    // an item, while all workgroups are resident at once or nearly so (1100 x 1000 bf16: 14.1 -> 8.0 us,
+    // 1500 x 16,000: 20.4 -> 17.0 us; at 4096 x 8000 the larger groups below take the same time).
+    const int nst = (int)((a.V + kSuperCols - 1) / kSuperCols);
+    if (nst <= 4 && rpb4 > 0) {
+        const int rpb = a.rows <= 4 * cus ? 1 : (4 + nst - 1) / nst;
+        if ((a.rows + rpb - 1) / rpb <= 6 * cus) return launch_groups<Chunk, kSample, 4>(a, rpb, stream);
+    }
+    if (rpb8 == 0) return launch_groups<Chunk, kSample, 4>(a, rpb4, stream);
     const int64_t groups8 = (a.rows + rpb8 - 1) / rpb8;
-    if (groups8 > 8 * cus) return launch_groups<Chunk, kSample, 4>(a, stream);
+    if (groups8 > 8 * cus) return launch_groups<Chunk, kSample, 4>(a, rpb4, stream);
     const int64_t round8 = 2 * cus;
     const int64_t rounds = (groups8 + round8 - 1) / round8;
     if (groups8 > round8 && groups8 * 5 < rounds * round8 * 4 && rpb4 > 0
         && (a.rows + rpb4 - 1) / rpb4 <= 4 * cus)
-        return launch_groups<Chunk, kSample, 4>(a, stream);
-    return launch_groups<Chunk, kSample, 8>(a, stream);
-#endif
+        return launch_groups<Chunk, kSample, 4>(a, rpb4, stream);
+    return launch_groups<Chunk, kSample, 8>(a, rpb8, stream);
 }
 
 // Split path: used when the row-block path would leave compute units without a
@@ -725,6 +735,11 @@ static hipError_t launch_for(const VocabPassArgs& a, hipStream_t stream)
 // out by the hardware dispatcher as earlier ones finish, which balances better than
 // longer static runs), except that a row has at most 64 runs: one partial per lane
 // of the merging wave.
+// Rows of at most kNarrowTiles super-tiles are not cut: a workgroup has a wave for each of them and
+// needs no second launch (64 rows x 32,000 bf16: 10.3 -> 8.6 us; wider rows are faster cut: 64 x
+// 36,000 10.4 us cut, 11.4 us not).  Wider rows are cut while there are at most half as many row-block
+// workgroups as compute units (100 x 151,936: 15.4 us whole, 13.6 us cut; 192: 16.3 and 18.7 us).
+constexpr int kNarrowTiles = 8;
 constexpr int64_t kSplitMaxRows = 1024;          // bound used by the workspace size
 
 struct SplitPlan {
@@ -794,12 +809,8 @@ hipError_t launch_vocab_pass(const VocabPassArgs& args, bool is_bf16, bool sampl
     if (a.rows == 0) return hipSuccess;
     const int cus = compute_units();
     const int rpb8 = rows_per_group<8>(a.V, sample);
-#ifdef E3_SPLIT_ALWAYS
-    const bool few = a.rows <= kSplitMaxRows;
-#else
-    const bool few = a.rows <= kSplitMaxRows && rpb8 > 0
+    const bool few = (a.V + kSuperCols - 1) / kSuperCols > kNarrowTiles && a.rows <= kSplitMaxRows && rpb8 > 0
                   && (a.rows + rpb8 - 1) / rpb8 * E3_SPLIT_BELOW_DEN <= (int64_t)cus * E3_SPLIT_BELOW_NUM;
-#endif
     if (few && workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
         const SplitPlan plan = split_plan(a.V);
         if ((size_t)a.rows * plan.nslots * sizeof(RowPartial) <= workspace_bytes) {

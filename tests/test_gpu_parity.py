@@ -692,3 +692,32 @@ def test_parity_checks_accept_an_oracle_off_by_a_rounding_error(wrong_oracle):
     wrong_oracle("return log(st.S) - st.W / st.S;", "return (log(st.S) - st.W / st.S) * 1.000001;")
     check_logprob(lg, tgt, None, tau, 1.0, "entropy 1e-6 off")
     check_sample(lg, tau, 1.0, seed=5, row_base=1000, label="entropy 1e-6 off")
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", [(1, 1_000), (3, 4_097), (9, 16_384), (7, 16_385), (5, 32_768), (6, 32_769),
+                                    (1025, 264), (1100, 4_104), (1600, 1_000), (896, 4_200), (130, 33_000),
+                                    (260, 36_872)])
+def test_launch_shapes_of_small_batches(rows, V, dtype):
+    # narrow rows (one launch, 4 or 8 waves, one or a few rows per workgroup), the widest of them and the
+    # first that are cut, and batches around the bounds of the rows-per-workgroup rule
+    g = torch.Generator(device=DEV).manual_seed(rows * 7 + V)
+    pitch = -(-V // 8) * 8
+    lg = (torch.randn((rows, pitch), generator=g, device=DEV) * 3).to(dtype)[:, :V]
+    tau = (0.6 + 0.8 * torch.rand(rows, generator=g, device=DEV)).float()
+    check_sample(lg, tau, 1.0, seed=rows, row_base=3, label=f"small {rows}x{V} {dtype}")
+    targets = torch.randint(0, V, (rows,), generator=g, device=DEV).to(torch.int32)
+    mask = (torch.rand(rows, generator=g, device=DEV) < 0.8).to(torch.uint8)
+    check_logprob(lg, targets, mask, tau, 1.0, f"small {rows}x{V} {dtype}")
+    # groups riding along: as many as there can be workgroups, and more than that
+    for size in (1, 2, 8):
+        offsets = torch.arange(0, rows + 1, size, dtype=torch.int32, device=DEV)
+        n = int(offsets[-1])
+        if n == 0:
+            continue
+        rewards = (torch.rand(n, generator=g, device=DEV) < 0.5).float()
+        out = e3.e3_logprob_entropy_advantages(lg, targets, mask, tau, 1.0, rewards, offsets)
+        sep = e3.e3_logprob_entropy(lg, targets, mask, tau, 1.0)
+        for x, y in zip(out[:4], sep):
+            assert torch.equal(x, y)
+        assert torch.equal(out[4], e3.e3_grpo_advantages(rewards, offsets))
