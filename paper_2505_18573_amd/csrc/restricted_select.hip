@@ -425,13 +425,15 @@ void sample_select_kernel(SelArgs a)
         if (v == nvec - 1 && last < T::kElems) x = T::cut_off(x, last);
         return x;
     };
-    auto request = [&](u32x4 x[kSBatch], int set) {
+    // Requests never branch: a load on one side of a branch makes the compiler wait for it where the sides
+    // meet.  Past the row they repeat its last vector, whose maximum then does not count.
+    auto request = [&](u32x4 (&x)[kSBatch], int set) {
 #pragma unroll
         for (int u = 0; u < kSBatch; ++u) {
-            const int s = set + u * nsets;
-            if (s < whole) x[u] = kStream ? stream_load(rv + tid + s * kSThreads) : rv[tid + s * kSThreads];   // uniform; nothing waits on these here
-            else if (s < nslots) x[u] = guarded(tid + s * kSThreads);
-            else x[u] = none;
+            const int v = tid + (set + u * nsets) * kSThreads;
+            const uint32_t at = (uint32_t)(v < nvec ? v : nvec - 1) * 16u;
+            const u32x4* p = reinterpret_cast<const u32x4*>(rowp + at);
+            x[u] = kStream ? stream_load(p) : *p;
         }
     };
     float tmax = -INFINITY;                                       // maximum of the finite values I have read
@@ -448,6 +450,17 @@ void sample_select_kernel(SelArgs a)
             return f;
         }
         return m;
+    };
+    auto set_maxima = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
+#pragma unroll
+        for (int u = 0; u < kSBatch; ++u) m[u] = vector_max(x[u]);
+        if (set + (kSBatch - 1) * nsets < whole) return;          // uniform: nothing but complete vectors
+#pragma unroll
+        for (int u = 0; u < kSBatch; ++u) {
+            const int v = tid + (set + u * nsets) * kSThreads;
+            if (v >= nvec) m[u] = -INFINITY;
+            else if (v == nvec - 1 && last < T::kElems) m[u] = vector_max(T::cut_off(x[u], last));
+        }
     };
     // The wave's m-th largest thread maximum, m = ceil(k / waves with columns), bit by bit from the
     // top with one ballot per bit (the largest value that at least m lanes reach; only the upper 16
@@ -480,7 +493,7 @@ void sample_select_kernel(SelArgs a)
         return t < 0x00800000u ? -3.402823466e38f : __uint_as_float(f32_of_key(t));
     };
     // The vectors of a set whose maximum reaches `thf` go into the list: one reservation per wave
-    auto list_set = [&](const u32x4 x[kSBatch], const float m[kSBatch], int set, float thf) {
+    auto list_set = [&](const u32x4 (&x)[kSBatch], const float (&m)[kSBatch], int set, float thf) {
         uint32_t hits = 0u;
 #pragma unroll
         for (int u = 0; u < kSBatch; ++u) hits |= (uint32_t)(m[u] >= thf) << u;
@@ -502,13 +515,14 @@ void sample_select_kernel(SelArgs a)
     {
         u32x4 x[kSBatch], y[kSBatch];
         float m[kSBatch];
-        auto maxima = [&](const u32x4 v[kSBatch]) {
+        auto maxima = [&](const u32x4 (&x)[kSBatch], int set) {
+            set_maxima(x, m, set);
 #pragma unroll
-            for (int u = 0; u < kSBatch; ++u) { m[u] = vector_max(v[u]); tmax = fmaxf(tmax, m[u]); }
+            for (int u = 0; u < kSBatch; ++u) tmax = fmaxf(tmax, m[u]);
         };
         request(x, 0);
         if (nsets > 1) request(y, 1);
-        maxima(x);
+        maxima(x, 0);
         publish();
         // orders LDS only: __syncthreads() would wait for the loads in flight as well
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -520,12 +534,12 @@ void sample_select_kernel(SelArgs a)
         };
         for (int set = 1; set < nsets; set += 2) {
             if (set + 1 < nsets) request(x, set + 1);
-            maxima(y);
+            maxima(y, set);
             list_set(y, m, set, thf);
             refine(set);
             if (set + 1 >= nsets) break;
             if (set + 2 < nsets) request(y, set + 2);
-            maxima(x);
+            maxima(x, set + 1);
             list_set(x, m, set + 1, thf);
             refine(set + 1);
         }
@@ -541,8 +555,7 @@ void sample_select_kernel(SelArgs a)
             u32x4 x[kSBatch];
             float m[kSBatch];
             request(x, set);
-#pragma unroll
-            for (int u = 0; u < kSBatch; ++u) m[u] = vector_max(x[u]);
+            set_maxima(x, m, set);
             list_set(x, m, set, thf);
         }
         __syncthreads();
@@ -580,7 +593,7 @@ void sample_select_kernel(SelArgs a)
             int mine = 0;
 #pragma unroll
             for (int e = 0; e < T::kElems; ++e) {
-                key[e] = key_of_f32(T::elem_bits(x, e));
+                key[e] = col0 + e < V ? key_of_f32(T::elem_bits(x, e)) : 0u;      // the last vector may reach past the row
                 mine += key[e] >= theta;
             }
             const int inc = wave_prefix_sum(mine);
