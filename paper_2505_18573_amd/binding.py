@@ -91,35 +91,46 @@ def lib() -> C.CDLL:
     return _lib
 
 
+# A call is one or two launches of a few microseconds, so what surrounds it counts: pointers go over as
+# plain integers, the stream as torch's raw handle (no Stream object), and a check asks a tensor
+# for as little as it can.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _logits_meta(logits: torch.Tensor) -> Tuple[int, int, int, int]:
-    if logits.dim() != 2 or (logits.shape[1] > 1 and logits.stride(1) != 1):
+    shape = logits.shape
+    if len(shape) != 2:
+        raise ValueError("logits must be [rows, V] with unit column stride")
+    rows, V = shape
+    pitch, step = logits.stride()
+    if V > 1 and step != 1:
         raise ValueError("logits must be [rows, V] with unit column stride")
     if not logits.is_cuda:
         raise ValueError("logits must live on the GPU")
-    if logits.dtype == torch.bfloat16:
+    dtype = logits.dtype
+    if dtype is torch.bfloat16:
         dt = E3_BF16
-    elif logits.dtype == torch.float32:
+    elif dtype is torch.float32:
         dt = E3_F32
     else:
-        raise TypeError(f"unsupported logit dtype {logits.dtype}")
-    rows, V = logits.shape
-    stride = logits.stride(0) if rows > 1 else max(V, logits.stride(0))
-    return dt, rows, V, stride
+        raise TypeError(f"unsupported logit dtype {dtype}")
+    return dt, rows, V, pitch if rows > 1 else max(V, pitch)
 
 
 def _check(t: Optional[torch.Tensor], dtype, n: int, name: str, device):
     if t is None:
         return
-    if t.dtype != dtype or t.dim() != 1 or t.shape[0] != n or not t.is_contiguous() \
-            or t.device != device:
+    if t.dtype is not dtype or t.dim() != 1 or t.numel() != n or not t.is_contiguous() or t.device != device:
         raise ValueError(f"{name} must be a contiguous {dtype} tensor of {n} elements on {device}")
 
 
@@ -172,14 +183,17 @@ def e3_sample_entropy(logits: torch.Tensor, tau_rows: Optional[torch.Tensor], ta
     dev = logits.device
     if token_out is None:
         token_out = torch.empty(rows, dtype=torch.int32, device=dev)
+    else:
+        _check(token_out, torch.int32, rows, "token_out", dev)
     if logp_out is None:
         logp_out = torch.empty(rows, dtype=torch.float32, device=dev)
+    else:
+        _check(logp_out, torch.float32, rows, "logp_out", dev)
     if entropy_out is None:
         entropy_out = torch.empty(rows, dtype=torch.float32, device=dev)
+    else:
+        _check(entropy_out, torch.float32, rows, "entropy_out", dev)
     _check(tau_rows, torch.float32, rows, "tau_rows", dev)
-    _check(token_out, torch.int32, rows, "token_out", dev)
-    _check(logp_out, torch.float32, rows, "logp_out", dev)
-    _check(entropy_out, torch.float32, rows, "entropy_out", dev)
     ws, ws_bytes = _workspace(rows, V, workspace, dev)
     rc = lib().e3_sample_entropy(_ptr(logits), dt, rows, V, stride, _ptr(tau_rows),
                                  float(tau_scalar), int(seed), int(row_base),
@@ -220,14 +234,17 @@ def e3_sample_restricted(logits: torch.Tensor, tau_rows: Optional[torch.Tensor],
     dev = logits.device
     if token_out is None:
         token_out = torch.empty(rows, dtype=torch.int32, device=dev)
+    else:
+        _check(token_out, torch.int32, rows, "token_out", dev)
     if logp_out is None:
         logp_out = torch.empty(rows, dtype=torch.float32, device=dev)
+    else:
+        _check(logp_out, torch.float32, rows, "logp_out", dev)
     if kept_out is None:
         kept_out = torch.empty(rows, dtype=torch.int32, device=dev)
+    else:
+        _check(kept_out, torch.int32, rows, "kept_out", dev)
     _check(tau_rows, torch.float32, rows, "tau_rows", dev)
-    _check(token_out, torch.int32, rows, "token_out", dev)
-    _check(logp_out, torch.float32, rows, "logp_out", dev)
-    _check(kept_out, torch.int32, rows, "kept_out", dev)
     rc = lib().e3_sample_restricted(_ptr(logits), dt, rows, V, stride, _ptr(tau_rows),
                                     float(tau_scalar), int(top_k), float(top_p), int(seed),
                                     int(row_base), _ptr(token_out), _ptr(logp_out), _ptr(kept_out),
@@ -272,10 +289,14 @@ def e3_logprob_entropy(logits: torch.Tensor, target_ids: Optional[torch.Tensor],
     tensors are passed for them."""
     dt, rows, V, stride = _logits_meta(logits)
     dev = logits.device
-    if logp_out is None and target_ids is not None:
+    if logp_out is not None:
+        _check(logp_out, torch.float32, rows, "logp_out", dev)
+    elif target_ids is not None:
         logp_out = torch.empty(rows, dtype=torch.float32, device=dev)
     if entropy_out is None:
         entropy_out = torch.empty(rows, dtype=torch.float32, device=dev)
+    else:
+        _check(entropy_out, torch.float32, rows, "entropy_out", dev)
     if want_sum and entropy_sum_out is None:
         entropy_sum_out = torch.empty(1, dtype=torch.float64, device=dev)
     if want_sum and entropy_count_out is None:
@@ -283,8 +304,6 @@ def e3_logprob_entropy(logits: torch.Tensor, target_ids: Optional[torch.Tensor],
     _check(target_ids, torch.int32, rows, "target_ids", dev)
     _check(row_mask, torch.uint8, rows, "row_mask", dev)
     _check(tau_rows, torch.float32, rows, "tau_rows", dev)
-    _check(logp_out, torch.float32, rows, "logp_out", dev)
-    _check(entropy_out, torch.float32, rows, "entropy_out", dev)
     _check_scalar_out(entropy_sum_out, torch.float64, "entropy_sum_out", dev)
     _check_scalar_out(entropy_count_out, torch.int64, "entropy_count_out", dev)
     ws, ws_bytes = _workspace(rows, V, workspace, dev)
@@ -314,26 +333,29 @@ def e3_logprob_entropy_advantages(logits: torch.Tensor, target_ids: Optional[tor
     dev = logits.device
     n = rewards.shape[0]
     num_groups = group_offsets.shape[0] - 1
-    if logp_out is None and target_ids is not None:
+    if logp_out is not None:
+        _check(logp_out, torch.float32, rows, "logp_out", dev)
+    elif target_ids is not None:
         logp_out = torch.empty(rows, dtype=torch.float32, device=dev)
     if entropy_out is None:
         entropy_out = torch.empty(rows, dtype=torch.float32, device=dev)
+    else:
+        _check(entropy_out, torch.float32, rows, "entropy_out", dev)
     if want_sum and entropy_sum_out is None:
         entropy_sum_out = torch.empty(1, dtype=torch.float64, device=dev)
     if want_sum and entropy_count_out is None:
         entropy_count_out = torch.empty(1, dtype=torch.int64, device=dev)
     if adv_out is None:
         adv_out = torch.empty(n, dtype=torch.float32, device=dev)
+    else:
+        _check(adv_out, torch.float32, n, "adv_out", dev)
     _check(target_ids, torch.int32, rows, "target_ids", dev)
     _check(row_mask, torch.uint8, rows, "row_mask", dev)
     _check(tau_rows, torch.float32, rows, "tau_rows", dev)
-    _check(logp_out, torch.float32, rows, "logp_out", dev)
-    _check(entropy_out, torch.float32, rows, "entropy_out", dev)
     _check_scalar_out(entropy_sum_out, torch.float64, "entropy_sum_out", dev)
     _check_scalar_out(entropy_count_out, torch.int64, "entropy_count_out", dev)
     _check(rewards, torch.float32, n, "rewards", dev)
     _check(group_offsets, torch.int32, num_groups + 1, "group_offsets", dev)
-    _check(adv_out, torch.float32, n, "adv_out", dev)
     ws, ws_bytes = _workspace(rows, V, workspace, dev)
     rc = lib().e3_logprob_entropy_advantages(_ptr(logits), dt, rows, V, stride, _ptr(target_ids),
                                              _ptr(row_mask), _ptr(tau_rows), float(tau_scalar),
@@ -358,7 +380,8 @@ def e3_grpo_advantages(rewards: torch.Tensor, group_offsets: torch.Tensor, ddof:
     _check(group_offsets, torch.int32, num_groups + 1, "group_offsets", dev)
     if adv_out is None:
         adv_out = torch.empty(n, dtype=torch.float32, device=dev)
-    _check(adv_out, torch.float32, n, "adv_out", dev)
+    else:
+        _check(adv_out, torch.float32, n, "adv_out", dev)
     rc = lib().e3_grpo_advantages(_ptr(rewards), _ptr(group_offsets), num_groups, int(ddof),
                                   float(eps), _ptr(adv_out), _stream(dev))
     if rc != E3_OK:
