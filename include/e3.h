@@ -170,12 +170,12 @@ int e3_sample_entropy_noalloc(const void* logits, int dtype, int64_t rows, int64
  * Logits must be finite (inf / NaN patterns are ignored as levels; a row without any
  *   finite logit gives token 0, logp NaN, kept 0).  Other arguments, alignment rules and
  *   errors as for e3_sample_entropy; top_k < 0 or top_p not in (0, inf): E3_ERR_VALUE.
- * One workgroup of 1024 threads per row.  With 1 <= top_k <= 256 the row is read once
- * (vector maxima kept in LDS, the few vectors that can hold one of the k largest read
- * again, exact selection among those); otherwise (bf16 only) the row's stored patterns are
- * counted in LDS: one counting sweep over 32 binades of both signs, or, for the rare row
- * that does not fit them (finite logits of 512 and more that the row's beginning does not
- * show, more than 62 columns nearer to zero than 2^-23 without being zero, very long levels),
+ * One workgroup per row.  With 1 <= top_k <= 256 the row is read once (vectors that can hold
+ * one of the k largest are listed in LDS while the row streams, exact selection among those);
+ * otherwise (bf16 only) the row's stored patterns are counted in LDS: one counting sweep over
+ * 32 binades of both signs, or, for the rare row that does not fit them (finite logits of 512
+ * and more that the row's beginning does not show, more than 62 columns nearer to zero than
+ * 2^-23 without being zero, very long levels),
  * four to ten sweeps over all patterns.
  */
 int e3_sample_restricted(const void* logits, int dtype, int64_t rows, int64_t V, int64_t row_stride,
