@@ -723,7 +723,9 @@ __device__ __forceinline__ void middle_items(Shared& sh, int lane)
     }
 }
 
-// Two workgroups per compute unit: eight waves per SIMD, 64 vector registers each.
+// Two workgroups per compute unit: eight waves per SIMD, 64 vector registers each.  151,936 bf16
+// columns, top-p 0.9, all patterns in 128 KiB before / now: 8 rows 39.8 / 22.9 us, 512 rows 101 /
+// 44 us (3.5 TB/s), 1024 rows 188 / 84 us; 512 x 32,000: 59 / 27 us.
 __global__ __launch_bounds__(kRThreads, 8)
 void sample_restricted_kernel(RestrictedArgs a)
 {

@@ -382,9 +382,14 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
     }
 }
 
-// 512 threads per row, two workgroups per compute unit (one row's short phases overlap the
-// other's stream), or 1024 threads when there are fewer rows than compute units: four waves per SIMD and
-// up to 128 vector registers either way.
+// Bound by the read of the row plus ~6 us of short dependent phases after it.  512 threads per row,
+// two workgroups per compute unit (one row's short phases overlap the other's stream) and
+// non-temporal loads, or 1024 threads and plain loads for at most one row per compute unit (half the
+// stream's latency; such a batch may sit in the caches: 100 fp32 rows 24.7 us plain, 28.2 us
+// non-temporal; 300 rows x 151,936 bf16 29.7 us with 512 threads, 48 us with 1024): four waves per
+// SIMD and up to 128 vector registers either way.  151,936 bf16 columns, top-k 50 + top-p, chunk maxima
+// and a second read of the qualifying chunks before / now: 8 rows 26.0 / 18.1 us, 512 rows 45.2 /
+// 36.3 us (4.3 TB/s), 1024 rows 81.5 / 63.4 us (4.9 TB/s).
 template <typename T, int kSThreads>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void sample_select_kernel(SelArgs a)

@@ -429,3 +429,43 @@ def test_levels_longer_than_a_quarter_counter():
     lg = base.to(torch.bfloat16)
     for k, p in [(0, 0.9), (1000, 1.0), (0, 0.2), (100_000, 0.999)]:
         check(lg, None, 1.0, k, p, 21, 5, f"long quarter levels k={k} p={p}")
+
+
+# ---------------------------------------------------------------- selection: both workgroup sizes, list overflow
+# 1024 threads per row up to one row per compute unit, 512 beyond; the list of vectors holds 2048.
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", [(256, 33_001), (257, 5), (257, 4_099), (260, 16_387), (260, 33_001), (300, 70_001)])
+def test_selection_workgroup_sizes(rows, V, dtype):
+    g = torch.Generator(device=DEV).manual_seed(rows + V)
+    per = 8 if dtype == torch.bfloat16 else 4
+    pitch = -(-V // per) * per
+    lg = torch.full((rows, pitch), 77.0, device=DEV).to(dtype)               # what lies past a row must not count
+    lg[:, :V] = torch.randn((rows, V), generator=g, device=DEV) * 2.5
+    lg[3, :V] = 0.25                                                          # a plateau among ordinary rows
+    lg[4, :V] = torch.sort(lg[4, :V].float()).values.to(dtype)
+    lg[5, :V:2] = -float("inf")
+    lg = lg[:, :V]
+    for k, p in ((50, 0.95), (1, 1.0), (64, 1.0), (65, 0.9), (256, 0.9)):
+        if V == 5 and k > 1:
+            continue                              # infinite columns would reach the cut: no levels here
+        check(lg, None, 0.8, k, p, V, 3, f"select {rows}x{V} {dtype} k={k} p={p}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,threads", [(6, 1024), (258, 512)])
+def test_selection_rows_that_mislead_the_first_bound(rows, threads, dtype):
+    # the vectors that the first requests take hold small values, all others large ones: the list
+    # overflows with the first bound and is made again with the final one
+    g = torch.Generator(device=DEV).manual_seed(threads)
+    per = 8 if dtype == torch.bfloat16 else 4
+    slots = 24
+    V = slots * threads * per - 3
+    lg = torch.randn((rows, slots * threads * per), generator=g, device=DEV) + 20.0
+    nsets = -(-slots // 8)
+    for s in range(0, slots, nsets):
+        lg[:, s * threads * per:(s + 1) * threads * per] -= 40.0
+    lg = lg.to(dtype)[:, :V]
+    for k, p in ((50, 0.9), (256, 1.0)):
+        check(lg, None, 0.7, k, p, 5, 9, f"misled {threads} {dtype} k={k}")
