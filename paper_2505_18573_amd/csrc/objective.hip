@@ -65,27 +65,38 @@ void grpo_seq_terms_kernel(const float* __restrict__ logp_new, const float* __re
     if (lane == 0) seq_mean_out[i] = t1 > t0 ? acc / (double)(t1 - t0) : 0.0;
 }
 
-// Questions to the scalar, one workgroup.  Eight lanes share a question, so that the usual
-// handful of rollouts is one request deep (64 questions x 8 rollouts: 4.5 us with one lane per
-// question, 1.9 us so); a question's sum and the fold over questions have a fixed order.
+// Questions to the scalar, one workgroup, bound by the latency of its dependent requests (a
+// question's two offsets, then its rollouts' means): kLanes lanes share a question while a single round
+// of the 1024 threads takes all questions, one lane each beyond that, so that more lanes never
+// cost more rounds (a whole call with eight lanes for any number of questions / so: 512 questions x 8
+// rollouts of 300 tokens 10.9 / 8.9 us, 20,000 questions of one rollout 124 / 20 us; 64 questions x 8: the
+// fold alone 4.5 us with one lane per question, 1.9 us with eight).  A question's sum and the fold over
+// questions have an order fixed by the shape.
+template <int kLanes>
 __global__ __launch_bounds__(1024)
 void grpo_objective_reduce_kernel(const double* __restrict__ seq_mean,
                                   const int32_t* __restrict__ group_offsets, int32_t num_groups,
-                                  double* objective_out)
+                                  double* __restrict__ objective_out)
 {
+    static_assert(kLanes == 1 || kLanes == 2 || kLanes == 4 || kLanes == 8, "lanes of one row of sixteen");
     __shared__ double partial[16];
     double acc = 0.0;
-    const int sub = threadIdx.x & 7;
-    for (int32_t q0 = 0; q0 < num_groups; q0 += 1024 / 8) {        // whole waves take part in the reductions
-        const int32_t q = q0 + (int32_t)(threadIdx.x >> 3);
-        const int32_t i0 = q < num_groups ? group_offsets[q] : 0, i1 = q < num_groups ? group_offsets[q + 1] : 0;
+    const int sub = threadIdx.x & (kLanes - 1);
+    const auto offset = [&](int64_t q) -> int32_t { return group_offsets[q < num_groups ? q : num_groups]; };
+    int64_t q = threadIdx.x / kLanes;
+    int32_t i0 = 0, i1 = 0;
+    if (num_groups > 0) { i0 = offset(q); i1 = offset(q + 1); }
+    for (int64_t q0 = 0; q0 < num_groups; q0 += 1024 / kLanes) {   // whole waves take part in the reductions
+        q += 1024 / kLanes;
+        const int32_t next0 = offset(q), next1 = offset(q + 1);    // requested ahead of this round's sums
         double g = 0.0;
 #pragma unroll 4
-        for (int32_t i = i0 + sub; i < i1; i += 8) g += seq_mean[i];
-        g += dpp_d<kDppXor1>(0.0, g);
-        g += dpp_d<kDppXor2>(0.0, g);
-        g += dpp_d<kDppHalfMirror>(0.0, g);                         // the other four of the eight
+        for (int32_t i = i0 + sub; i < i1; i += kLanes) g += seq_mean[i];
+        if (kLanes >= 2) g += dpp_d<kDppXor1>(0.0, g);
+        if (kLanes >= 4) g += dpp_d<kDppXor2>(0.0, g);
+        if (kLanes >= 8) g += dpp_d<kDppHalfMirror>(0.0, g);        // the other four of the eight
         if (sub == 0 && i1 > i0) acc += g / (double)(i1 - i0);
+        i0 = next0; i1 = next1;
     }
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) partial[threadIdx.x >> 6] = acc;
@@ -123,8 +134,10 @@ hipError_t launch_grpo_objective(const float* logp_new, const float* logp_old,
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
-    hipLaunchKernelGGL(grpo_objective_reduce_kernel, dim3(1), dim3(1024), 0, stream,
-                       seq_mean_out, group_offsets, num_groups, objective_out);
+    auto reduce = num_groups <= 1024 / 8 ? grpo_objective_reduce_kernel<8>
+                : num_groups <= 1024 / 4 ? grpo_objective_reduce_kernel<4>
+                : num_groups <= 1024 / 2 ? grpo_objective_reduce_kernel<2> : grpo_objective_reduce_kernel<1>;
+    hipLaunchKernelGGL(reduce, dim3(1), dim3(1024), 0, stream, seq_mean_out, group_offsets, num_groups, objective_out);
     return hipGetLastError();
 }
 

@@ -85,3 +85,28 @@ def test_objective_parity_at_every_wave_count(num_seqs):
     assert np.allclose(terms.cpu().numpy(), want_terms, rtol=2e-6, atol=1e-7)
     assert np.allclose(seq_mean.cpu().numpy(), want_means, rtol=2e-6, atol=1e-7)
     assert J.item() == pytest.approx(want_J, rel=2e-6, abs=1e-7)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("num_groups", [0, 1, 128, 129, 256, 257, 512, 513, 1024, 1025, 2500])
+def test_objective_parity_at_every_question_count(num_groups):
+    # 8, 4, 2 and 1 lanes per question on both sides of each bound, one round of the workgroup and more;
+    # questions of 0 to 40 rollouts
+    dev = "cuda:0"
+    rng = np.random.default_rng(num_groups)
+    sizes = rng.integers(0, 5, num_groups)
+    sizes[::97] = 40
+    goff = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n = int(goff[-1])
+    soff = np.arange(n + 1, dtype=np.int32) * 2
+    old = rng.normal(-1.5, 1.0, 2 * n).astype(np.float32)
+    new = (old + rng.normal(0, 0.15, 2 * n)).astype(np.float32)
+    adv = rng.normal(0, 1, n).astype(np.float32)
+    args = [torch.from_numpy(x).to(dev) for x in (new, old, soff, adv, goff)]
+    J, seq_mean, _ = e3.e3_grpo_objective(*args, 0.2)
+    want_J, _, want_means = o.grpo_objective(new, old, soff, adv, goff, float(np.float32(0.2)))
+    assert np.allclose(seq_mean.cpu().numpy(), want_means, rtol=2e-6, atol=1e-7)
+    # the fold of the means is fp64 in another order: from the kernel's own means to 1e-12
+    own = [seq_mean[a:b].mean().item() if b > a else 0.0 for a, b in zip(goff[:-1], goff[1:])]
+    assert J.item() == pytest.approx(float(np.mean(own)) if own else 0.0, rel=1e-12, abs=1e-12)
+    assert J.item() == pytest.approx(want_J, rel=2e-6, abs=1e-7)

@@ -1,0 +1,56 @@
+"""Calls whose time must not leave that of a related call behind: inputs of the same size on which a
+kernel takes another route, or another split of the same work.  Only ratios of times taken on the same GPU in the
+same test are compared; each bound lies about half way (as a ratio) between what the sound route and the
+slow one it guards against measured.
+"""
+import pytest
+import torch
+
+import paper_2505_18573_amd as e3
+
+DEV = "cuda:0"
+pytestmark = pytest.mark.gpu
+
+
+def us(call, n=8):
+    """Microseconds per call: the best of five replays of a graph of n calls."""
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        for _ in range(n):
+            call()
+    best = float("inf")
+    for _ in range(6):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        graph.replay()
+        end.record()
+        end.synchronize()
+        best = min(best, start.elapsed_time(end) * 1000.0 / n)
+    return best
+
+
+def _objective(lens, cuts):
+    soff = torch.zeros(len(lens) + 1, dtype=torch.int64)
+    soff[1:] = torch.cumsum(lens, 0)
+    T = int(soff[-1])
+    g = torch.Generator(device=DEV).manual_seed(T)
+    old = -torch.rand(T, generator=g, device=DEV)
+    new = old + 0.1 * torch.randn(T, generator=g, device=DEV)
+    adv = torch.randn(len(lens), generator=g, device=DEV)
+    soff, goff = soff.to(torch.int32).to(DEV), cuts.to(torch.int32).to(DEV)
+    return lambda: e3.e3_grpo_objective(new, old, soff, adv, goff, 0.2)
+
+
+def test_many_questions_cost_their_rounds_only():
+    # 20,000 rollouts folded as 20,000 questions or as 1000: 18.8 and 13.7 us with one lane per question
+    # (20 rounds and one); 123 and 17.2 us when eight lanes shared every question (157 rounds and eight)
+    lens = torch.full((20_000,), 10)
+    many = us(_objective(lens, torch.arange(0, 20_001)))
+    some = us(_objective(lens, torch.arange(0, 20_001, 20)))
+    print(f"objective of 20,000 rollouts: {many:.1f} us as 20,000 questions, {some:.1f} us as 1000")
+    assert many < 3.5 * some
