@@ -2,7 +2,7 @@
 // KL term the paper drops): per token min(r A, clip(r, 1-eps, 1+eps) A) with
 // r = exp(logp_new - logp_old), averaged over the tokens of a rollout, then over the
 // rollouts of a question, then over questions.  It consumes what the vocabulary pass
-// (log-probs) and the advantage kernel (A) produce.  Two launches: one to sixteen waves per
+// (log-probs) and the advantage kernel (A) produce.  Two launches: one to eight waves per
 // rollout (fp64 sums, DPP reductions), then one workgroup that folds rollouts into questions
 // and questions into the scalar; every sum has an order fixed by the shape (bit-reproducible).
 #include "vocab_common.h"
@@ -12,9 +12,11 @@ namespace e3 {
 
 // The terms of one rollout, kWaves waves of a workgroup each.  The kernel moves 12 bytes per
 // token and is bound by latency, not by bytes: what counts is how many tokens are requested at
-// once, hence several waves per rollout and kUnroll tokens per lane requested before the first
-// is used.  512 rollouts of 77 - 8192 tokens (1.6 M tokens, 19 MB) on MI355X: one wave per
-// rollout with one token per lane at a time 44.2 us, this form 6.6 us (2.9 TB/s).
+// once, hence several waves per rollout and up to kUnroll tokens per lane requested before the
+// first is used - as many as the rollout has left, rounded up to a power of two, so that a short one
+// does not request its tokens several times.  512 rollouts of 77 - 8192 tokens (1.6 M tokens,
+// 19 MB) on MI355X: one wave per rollout with one token per lane at a time 44.2 us, this form 6.6 us
+// (2.9 TB/s).
 constexpr int kUnroll = 8;
 
 template <int kWaves, int kSeqsPerBlock>
@@ -33,16 +35,18 @@ void grpo_seq_terms_kernel(const float* __restrict__ logp_new, const float* __re
     const float A = adv[i];
     const float lo = 1.0f - clip_eps, hi = 1.0f + clip_eps;
     double acc = 0.0;
-    for (int64_t t = t0 + (kWaves == 1 ? lane : (int)threadIdx.x); t < t1; t += kStep * kUnroll) {
-        float n[kUnroll], o[kUnroll];
+    // kN steps of the rollout's waves from token t on, all requested before the first is used
+    auto terms = [&](auto steps, int64_t t) {
+        constexpr int kN = decltype(steps)::value;
+        float n[kN], o[kN];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int64_t tu = t + u * kStep < t1 ? t + u * kStep : t;
+        for (int u = 0; u < kN; ++u) {
+            const int64_t tu = t + u * kStep < t1 ? t + u * kStep : t0;
             n[u] = logp_new[tu];
             o[u] = logp_old[tu];
         }
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < kN; ++u) {
             const float r = __builtin_amdgcn_exp2f((n[u] - o[u]) * kLog2eF);
             const float rc = fminf(fmaxf(r, lo), hi);
             const float term = fminf(r * A, rc * A);
@@ -51,6 +55,13 @@ void grpo_seq_terms_kernel(const float* __restrict__ logp_new, const float* __re
                 acc += (double)term;
             }
         }
+    };
+    int64_t t = t0 + (kWaves == 1 ? lane : (int)threadIdx.x);
+    for (int64_t left = (t1 - t0 + kStep - 1) / kStep; left > 0; left -= kUnroll, t += kStep * kUnroll) {     // uniform
+        if (left > 4) terms(std::integral_constant<int, kUnroll>{}, t);
+        else if (left > 2) terms(std::integral_constant<int, 4>{}, t);
+        else if (left > 1) terms(std::integral_constant<int, 2>{}, t);
+        else terms(std::integral_constant<int, 1>{}, t);
     }
     acc = wave_sum(acc);
     if (kWaves > 1) {
@@ -124,13 +135,18 @@ hipError_t launch_grpo_objective(const float* logp_new, const float* logp_old,
                                  hipStream_t stream)
 {
     if (num_seqs > 0) {
-        // as many waves per rollout as keep all rollouts resident at once (32 waves on each of
-        // 256 compute units): few rollouts get many waves, many get one
+        // The waves per rollout: 8, 4 or 2 while all of them are resident at once (32 per compute unit),
+        // else one.  Long and very different rollouts gain from waves, short ones pay for launching
+        // idle ones: 2048 rollouts of up to 8192 tokens 27.2 us with one wave, 20.5 with two, 18.0 with four;
+        // of 100 tokens 5.8, 6.0 and 6.3 us.  3072 of up to 4096: 17.6, 14.7 and (four, not all resident)
+        // 13.6 us; of 100 tokens 4096 take 6.0, 6.5 and 7.3.  Sixteen waves for 512 and fewer are no
+        // faster than eight (7.9 and 8.0 us at up to 8192 tokens) and cost the short ones 0.3 us.
+        const int64_t resident = 32 * (int64_t)compute_units();
         const dim3 one((unsigned)num_seqs);
-        if (num_seqs <= 512) launch_terms<16, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
-        else if (num_seqs <= 1024) launch_terms<8, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
-        else if (num_seqs <= 4096) launch_terms<4, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
-        else launch_terms<1, 4>(dim3((unsigned)((num_seqs + 3) / 4)), logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
+        if (num_seqs * (int64_t)8 <= resident) launch_terms<8, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
+        else if (num_seqs * (int64_t)4 <= resident) launch_terms<4, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
+        else if (num_seqs * (int64_t)2 <= resident) launch_terms<2, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
+        else launch_terms<1, 4>(dim3((unsigned)(((int64_t)num_seqs + 3) / 4)), logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }

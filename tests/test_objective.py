@@ -59,13 +59,13 @@ def test_objective_parity_on_gpu():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("num_seqs", [1, 512, 513, 1024, 1025, 4096, 4097])
+@pytest.mark.parametrize("num_seqs", [1, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097])
 def test_objective_parity_at_every_wave_count(num_seqs):
-    # 16, 8, 4 and 1 waves per rollout, on both sides of each bound; lengths around the tokens that a
-    # wave, a workgroup of each size and one unrolled round take, and empty rollouts and questions
+    # 8, 4, 2 and 1 waves per rollout, on both sides of each bound; lengths around the tokens that a
+    # wave, a workgroup of each size and an unrolled round of 1, 2, 4 or 8 take, and empty rollouts and questions
     dev = "cuda:0"
     rng = np.random.default_rng(num_seqs)
-    edges = np.array([0, 1, 63, 64, 65, 511, 512, 513, 1023, 1024, 1025, 2047, 2049, 4095, 4097, 8191, 8192, 8193])
+    edges = np.array([0, 1, 63, 64, 65, 127, 129, 255, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2049, 4095, 4097, 8191, 8192, 8193])
     lens = np.where(np.arange(num_seqs) < edges.size, edges[np.arange(num_seqs) % edges.size],
                     rng.integers(0, 200, num_seqs))
     lens = lens[rng.permutation(num_seqs)] if num_seqs > 1 else np.array([8193])
