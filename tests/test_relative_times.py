@@ -54,3 +54,22 @@ def test_many_questions_cost_their_rounds_only():
     some = us(_objective(lens, torch.arange(0, 20_001, 20)))
     print(f"objective of 20,000 rollouts: {many:.1f} us as 20,000 questions, {some:.1f} us as 1000")
     assert many < 3.5 * some
+
+
+def _selection(lg, k=50, p=0.95):
+    rows = lg.shape[0]
+    tok = torch.empty(rows, dtype=torch.int32, device=DEV)
+    logp = torch.empty(rows, dtype=torch.float32, device=DEV)
+    kept = torch.empty(rows, dtype=torch.int32, device=DEV)
+    return lambda: e3.e3_sample_restricted(lg, None, 1.0, k, p, 7, 0, tok, logp, kept)
+
+
+@pytest.mark.parametrize("rows", [8, 300])
+def test_fp32_rows_of_nearly_equal_values_keep_their_bound(rows):
+    # values that agree in their upper 16 bits: 22 us as for ordinary rows; 124 us when the selection's bound
+    # was held in 16 bits, so that half the row reached it
+    g = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.randn((rows, 151_936), generator=g, device=DEV)
+    ordinary, narrow = us(_selection(3.0 * x)), us(_selection(100.0 + 0.3 * x))
+    print(f"{rows} fp32 rows, top-k 50: ordinary {ordinary:.1f} us, nearly equal values {narrow:.1f} us")
+    assert narrow < 2.0 * ordinary

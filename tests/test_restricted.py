@@ -469,3 +469,29 @@ def test_selection_rows_that_mislead_the_first_bound(rows, threads, dtype):
     lg = lg.to(dtype)[:, :V]
     for k, p in ((50, 0.9), (256, 1.0)):
         check(lg, None, 0.7, k, p, 5, 9, f"misled {threads} {dtype} k={k}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [6, 258])
+@pytest.mark.parametrize("kind", ["offset", "negative", "few_patterns", "one_ulp", "subnormal", "around_zero"])
+def test_selection_of_fp32_values_that_share_their_upper_bits(kind, rows):
+    # the bound of the listed vectors comes from all 32 bits: rows whose largest values differ in the lower
+    # sixteen only, repeat a few patterns of those, or lie around the two zeros
+    V = 40_003
+    g = torch.Generator(device=DEV).manual_seed(sum(map(ord, kind)) + rows)
+    x = torch.randn((rows, -(-V // 4) * 4), generator=g, device=DEV)
+    if kind == "offset":
+        x = 100.0 + 0.3 * x
+    elif kind == "negative":
+        x = -100.0 + 0.02 * x
+    elif kind == "few_patterns":
+        x = 100.0 + (x * 3).round() * 2.0 ** -14
+    elif kind == "one_ulp":
+        x = (1.0 + (torch.rand(x.shape, generator=g, device=DEV) < 0.001).float() * 2.0 ** -23) * torch.ones_like(x)
+    elif kind == "subnormal":
+        x = x * 1e-41
+    elif kind == "around_zero":
+        x = torch.where(x > 3.5, x * 1e-42, -0.0 * torch.ones_like(x))
+    lg = x[:, :V]
+    for k, p in ((1, 1.0), (20, 0.9), (50, 0.95), (200, 0.99)):
+        check(lg, None, 0.8, k, p, 3, 5, f"shared upper bits {kind} k={k} p={p}")
