@@ -73,3 +73,14 @@ def test_fp32_rows_of_nearly_equal_values_keep_their_bound(rows):
     ordinary, narrow = us(_selection(3.0 * x)), us(_selection(100.0 + 0.3 * x))
     print(f"{rows} fp32 rows, top-k 50: ordinary {ordinary:.1f} us, nearly equal values {narrow:.1f} us")
     assert narrow < 2.0 * ordinary
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_rows_that_are_mostly_a_plateau_are_listed_in_one_pass(dtype):
+    # 0.13 % of the columns stand out of zeros (bf16 / fp32: ordinary rows 18 / 22 us, these 21 / 30 us;
+    # 158 / 202 us when every vector of the plateau was listed first)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    x = torch.randn((100, 128_000), generator=g, device=DEV) * 3
+    ordinary, plateau = us(_selection(x.to(dtype))), us(_selection(torch.relu(x - 9.0).to(dtype)))
+    print(f"100 rows {dtype}, top-k 50: ordinary {ordinary:.1f} us, mostly zeros {plateau:.1f} us")
+    assert plateau < 3.0 * ordinary

@@ -495,3 +495,39 @@ def test_selection_of_fp32_values_that_share_their_upper_bits(kind, rows):
     lg = x[:, :V]
     for k, p in ((1, 1.0), (20, 0.9), (50, 0.95), (200, 0.99)):
         check(lg, None, 0.8, k, p, 3, 5, f"shared upper bits {kind} k={k} p={p}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", [(3, 140_003), (258, 70_001)])
+@pytest.mark.parametrize("kind", ["relu", "signed_zeros", "masked_1e4", "masked_lowest", "two_levels", "coarse", "climbing",
+                                  "falling", "equal"])
+def test_selection_of_rows_that_are_mostly_a_plateau(kind, rows, V, dtype):
+    # most of a row is one value and the bound starts there: with k below, at and above the number of columns
+    # that stand out of it; sorted rows, whose large columns all lie in one wave's vectors
+    g = torch.Generator(device=DEV).manual_seed(rows + sum(map(ord, kind)))
+    shape = (rows, -(-V // 8) * 8)
+    x = torch.randn(shape, generator=g, device=DEV) * 3
+    if kind == "relu":
+        x = torch.relu(x - 9.0)                       # 0.13 % stand out
+    elif kind == "signed_zeros":
+        x = torch.where(x > 10.5, x, torch.where(x > 0, 0.0, -0.0))
+    elif kind == "masked_1e4":
+        x = torch.where(torch.rand(shape, generator=g, device=DEV) < 0.9995, -1e4, x)
+    elif kind == "masked_lowest":
+        x = torch.where(torch.rand(shape, generator=g, device=DEV) < 0.9995, torch.finfo(dtype).min, x)
+    elif kind == "two_levels":
+        x = (torch.rand(shape, generator=g, device=DEV) < 0.002).float() * 2
+    elif kind == "coarse":
+        x = 100.0 + (x * 0.2).round() * 0.5           # the cut level is long, too
+    elif kind == "climbing":
+        x = torch.sort(x, 1).values
+    elif kind == "falling":
+        x = torch.sort(x, 1, descending=True).values
+    else:
+        x = torch.full(shape, 0.5, device=DEV)
+    lg = x.to(dtype).contiguous()
+    lg[:, V:] = 77.0                                  # what lies past a row must not count
+    lg = lg[:, :V]
+    for k, p in ((20, 0.9), (50, 0.95), (200, 1.0)):
+        check(lg, None, 0.8, k, p, 11, 2, f"plateau {kind} {rows}x{V} {dtype} k={k} p={p}")
