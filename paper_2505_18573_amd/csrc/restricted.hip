@@ -21,8 +21,8 @@
 //
 // THE NEAR WINDOW (every ordinary row).  The values a row really holds span few binades:
 // 32 binades of both signs, 8192 levels, are counted in 64 KiB of LDS - the 32 binades up to
-// [256, 512), or up to one above the largest logit among the first vectors read, whichever
-// is higher.  64 KiB instead of the 128 KiB all patterns need is what lets two rows share a
+// [256, 512), or up to one above the magnitude of the largest logit among the first vectors read,
+// whichever is higher.  64 KiB instead of the 128 KiB all patterns need is what lets two rows share a
 // compute unit, so that one row's short dependent phases overlap the other's stream: a 512 x
 // 151,936 batch took 100 us with one row per compute unit at a time, and the counting itself
 // is no limit then (read alone 27.2 us, read and count 31.4 us; but one row on one compute
@@ -31,13 +31,25 @@
 // the final look-up reads only the quarter that holds the column.  What lies outside the
 // window is kept exactly too: zeros are counted apart, up to 62 nearer to zero than the window are
 // listed with their columns (the MIDDLE items, ranked between the two signs), and values
-// below the window (masked columns) are counted when they are too far down to weigh anything.
+// below the window (masked columns) are counted when they are too far down to weigh anything; a
+// count cut among them keeps all of them if they are one value.
 //
-// THE WIDE ROWS.  Everything else - a value above the window, more small values than the
-// list holds, a wrapped counter (recognised because the counts no longer add up to the row's
-// width), a cut among the columns below the window - is redone over all patterns with
-// 32-bit counters, in four windows of 16,384 patterns in rank order, one sweep each; a
-// cut or the race needs its window swept again.  Slow (up to ten sweeps), exact, rare.
+// A row with values above the window, or with more small ones than the list holds, is counted once
+// more in a window raised to the former or lowered for the latter; its waves give the first count up as
+// soon as they see it.  151,936 columns, 8 / 512 rows: a logit of 9000 at the end of the row
+// 38 / 51 us, all logits around -2000 (seen by the first vectors) 37 / 67 us, all below 1e-3 48 / 84 us;
+// with all patterns in 128 KiB these took 42 / 99, 64 / 149 and 50 / 116 us, in the wide form alone
+// 108 / 117, 305 / 589 and 154 / 271 us.
+//
+// THE WIDE ROWS.  Everything else - a second window that fails too, a wrapped counter (recognised
+// because the counts no longer add up to the row's width), a count cut among several levels below the
+// window, columns below it that still weigh something (a mask of -1e4 at tau above 178) - is redone
+// over all patterns with 32-bit counters, in four windows of 16,384 patterns in rank order, one
+// sweep each; a cut or the race needs its window swept again unless it was the last.  Slow (up
+// to ten sweeps), exact, rare: ordinary logits with 500 columns of 2^-24 to 2^-60 among them 114 / 204 us (39 /
+// 99 us with all patterns in 128 KiB), half of 400,000 columns equal 515 us at 8 rows (411 us).  Its code is inlined
+// although few rows run it: as a function of its own the calling convention cost every row scratch
+// memory (8 ordinary rows 25 -> 31 us, 512 rows 45 -> 63 us).
 #include "vocab_common.h"
 #include "vocab_pass.h"
 
@@ -74,6 +86,7 @@ struct Shared {
     float sample_max[kRWaves];
     int zeros[2][kQuarters];        // +0, -0 by quarter
     int list_n, n_below, n_not_finite, n_above;
+    int below_lo, below_hi, above_hi;            // magnitude bits of the columns below the window (both ends) and above it
     int list_key[64], list_col[64]; // small values as they come
     int mid_key[64], mid_cnt[64], mid_col[64];   // the middle items in rank order
     int mid_C[64];                  // inclusive prefixes inside the middle
@@ -403,14 +416,23 @@ struct WideWindow {
     }
 };
 
-__device__ __forceinline__ void wide_count(const Row& row, WideWindow win, uint32_t* hist, int tid)
+// `resident` is the window that the counters hold already (-1: none).
+__device__ __forceinline__ void wide_count(const Row& row, WideWindow win, int& resident, uint32_t* hist, int tid)
 {
     __syncthreads();
+    if (win.w == resident) return;                                // uniform
+    resident = win.w;
     for (int i = tid; i < kWideBins + kTrash; i += kRThreads) hist[i] = 0u;
     __syncthreads();
     const uint32_t quad = win.quadrant(), trash = (uint32_t)(kWideBins + (tid & 63));
-    for (int v = tid; v < row.nvec; v += kRThreads)
-        for_each_pattern(row.guarded(v), [&](uint32_t p, int) { atomicAdd(&hist[(p >> 14) == quad ? (p & 0x3FFFu) : trash], 1u); });
+#pragma unroll 1
+    for (int i0 = 0; i0 < row.steps; i0 += 4) {
+        u32x4 x[4];
+        row.request<4>(x, i0, row.steps, tid);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            for_each_pattern(x[u], [&](uint32_t p, int) { atomicAdd(&hist[(p >> 14) == quad ? (p & 0x3FFFu) : trash], 1u); });
+    }
     __syncthreads();
 }
 
@@ -423,11 +445,12 @@ __device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a
         const int p = win.pattern(rank);
         return ((p >> 7) & 0xFF) == 0xFF ? 0u : hist[p & 0x3FFF];
     };
+    int resident = -1;
     double z1 = 0.0;
     bool have_z1 = false;
     // counts the window and scans it; (C, M) = what lies above it on entry, with it on return
     auto scan = [&](WideWindow win, View& vw, int& C, double& M) {
-        wide_count(row, win, hist, tid);
+        wide_count(row, win, resident, hist, tid);
         vw.Cl = 0; vw.top = kOwnW;
 #pragma unroll 1
         for (int j = kOwnW - 1; j >= 0; --j) {
@@ -506,15 +529,17 @@ __device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a
             }
         }
     }
-    // the race: every window down to the cut is swept once more
+    // the race: every window down to the cut once more, first the one that is counted already
     Cand best = contestant(-1.0f, 0);
     int best_n = 0;
+    const int first = resident;
 #pragma unroll 1
-    for (int w = 0; w < kWideWindows; ++w) {
-        const WideWindow win{w};
-        if (key_of_pattern(win.pattern(0)) < cut_key) break;      // uniform
-        wide_count(row, win, hist, tid);
+    for (int i = 0; i < kWideWindows; ++i) {
+        const WideWindow win{i == 0 ? first : i <= first ? i - 1 : i};
+        if (sh.C_above[win.w + 1] == sh.C_above[win.w] || key_of_pattern(win.pattern(0)) < cut_key) continue;   // uniform
+        wide_count(row, win, resident, hist, tid);
         Cand mine = contestant(-1.0f, 0);
+#pragma unroll 1
         for (int rank = tid; rank < kWideBins; rank += kRThreads) {
             const uint32_t n = count_of(win, rank);
             const int p = win.pattern(rank);
@@ -522,10 +547,9 @@ __device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a
                 mine = better(mine, contestant(level_score(p, (int)n, (float)z1, c, a.seed, grow), key_of_pattern(p)));
         }
         mine = reduce_best(mine, sh, tid);
-        if (mine.q > best.q) {                                    // an earlier window wins ties
-            best = mine;
-            best_n = (int)hist[pattern_of_key(key_of(mine)) & 0x3FFF];
-        }
+        const Cand was = best;
+        best = better(was, mine);
+        if (best.idx != was.idx || best.q != was.q) best_n = (int)hist[pattern_of_key(key_of(best)) & 0x3FFF];
     }
     const bool drawn = best.q >= 0.0f;
     const int pattern = pattern_of_key(key_of(best));
@@ -612,25 +636,62 @@ __device__ __forceinline__ void note_outside(const u32x4& x, int v, int quarter,
     n_odd = wave_prefix_i(n_odd);
     if (lane == 63 && n_odd != 0) atomicAdd(&sh.n_not_finite, n_odd);
     if (!__any(more)) return;
+    // tallies of up to 8 per lane and 512 per wave, three to a word: +0, -0, small; below and above the window
+    uint32_t n0 = 0u, n1 = 0u;
+    int lo = 0x7FFF, hi = 0, top = 0;                             // of my columns below the window and above it
     u32x4 rest = x;
+    auto next = [&]() -> uint32_t {                               // the first pattern becomes the last
+        const uint32_t p = rest.x & 0xFFFFu;
+        rest.x = rest.x >> 16 | rest.y << 16; rest.y = rest.y >> 16 | rest.z << 16;
+        rest.z = rest.z >> 16 | rest.w << 16; rest.w = rest.w >> 16 | p << 16;
+        return p;
+    };
 #pragma unroll 1
     for (int j = 0; j < 8; ++j) {                                 // one pattern at a time: this code is rarely run, and kept small
-        const uint32_t p = rest.x & 0xFFFFu, mag = p & 0x7FFFu;
-        rest.x = rest.x >> 16 | rest.y << 16; rest.y = rest.y >> 16 | rest.z << 16;
-        rest.z = rest.z >> 16 | rest.w << 16; rest.w >>= 16;
-        const bool out = mag < 0x7F80u && mag - (uint32_t)base >= (uint32_t)kHalf, neg = p >= 0x8000u;
-        const bool zero = out && mag == 0u, large = out && mag >= (uint32_t)base;
-        if (zero) atomicAdd(&sh.zeros[neg][quarter], 1);
-        if (large) atomicAdd(neg ? &sh.n_below : &sh.n_above, 1);
-        if (out && !zero && !large) {
+        const uint32_t p = next(), mag = p & 0x7FFFu, sign = p >> 15;
+        const bool large = mag >= (uint32_t)(base + kHalf) && mag < 0x7F80u;
+        n0 += mag >= (uint32_t)base ? 0u : mag == 0u ? 1u << (10u * sign) : 1u << 20;
+        n1 += large ? 1u << (10u * sign) : 0u;
+        const int m = large ? (int)mag : 0;
+        top = sign == 0u && m > top ? m : top;
+        hi = sign != 0u && m > hi ? m : hi;
+        lo = sign != 0u && m != 0 && m < lo ? m : lo;
+    }
+    auto tally = [&](uint32_t n, int* a, int* b) {
+        n = (uint32_t)wave_prefix_i((int)n);
+        if (lane == 63) {
+            atomicAdd(a, (int)(n & 0x3FFu));
+            atomicAdd(b, (int)(n >> 10 & 0x3FFu));
+        }
+    };
+    if (__any(n0 != 0u)) tally(n0, &sh.zeros[0][quarter], &sh.zeros[1][quarter]);
+    if (__any(n1 != 0u)) {
+        tally(n1, &sh.n_above, &sh.n_below);
+        if (lo < sh.below_lo) atomicMin(&sh.below_lo, lo);        // of a mask of one value the first vectors only
+        if (hi > sh.below_hi) atomicMax(&sh.below_hi, hi);
+        if (top > sh.above_hi) atomicMax(&sh.above_hi, top);
+    }
+    if (!__any(n0 >> 20 != 0u)) return;
+#pragma unroll 1
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t p = next(), mag = p & 0x7FFFu;
+        if (mag != 0u && mag < (uint32_t)base) {
             const int at = atomicAdd(&sh.list_n, 1);
             if (at < kMidList) { sh.list_key[at] = key_of_pattern((int)p); sh.list_col[at] = v * 8 + j; }
         }
     }
 }
 
-// Counts the row.  Returns the window.
-__device__ __forceinline__ Near near_count(const Row& row, uint32_t* hist, Shared& sh, int tid)
+// Columns above the window, or more small values than the list holds: the window does not hold the row.
+__device__ __forceinline__ bool near_fails(const Shared& sh)
+{
+    const volatile int* n = &sh.list_n;
+    const volatile int* m = &sh.n_above;
+    return __builtin_amdgcn_readfirstlane(*n > kMidList || *m != 0) != 0;
+}
+
+// Counts the row.  Returns the window, whose top binade is `top_exp` if that is not negative.
+__device__ __forceinline__ Near near_count(const Row& row, int top_exp, uint32_t* hist, Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
     Near w;
@@ -641,10 +702,14 @@ __device__ __forceinline__ Near near_count(const Row& row, uint32_t* hist, Share
     row.request<kAhead>(x, 0, row.steps, tid);
     for (int i = tid; i < 2 * kArray / 4; i += kRThreads) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
     if (tid < 2 * kQuarters) (&sh.zeros[0][0])[tid] = 0;
-    if (tid == 0) { sh.list_n = 0; sh.n_below = 0; sh.n_not_finite = 0; sh.n_above = 0; }
+    if (tid == 0) {
+        sh.list_n = 0; sh.n_below = 0; sh.n_not_finite = 0; sh.n_above = 0;
+        sh.below_lo = 0x7FFF; sh.below_hi = 0; sh.above_hi = 0;
+    }
     {
-        // the window's top: one binade above the largest finite logit among the first vectors
-        float m = 0.0f;
+        // the window's top: one binade above the magnitude of the largest finite logit among the first
+        // vectors (if that is negative, up to 2^20: what lies far down is a mask)
+        float m = -INFINITY;
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
             for_each_pattern(x[u], [&](uint32_t p, int) {
@@ -655,9 +720,12 @@ __device__ __forceinline__ Near near_count(const Row& row, uint32_t* hist, Share
         if (lane == 0) sh.sample_max[wave] = m;
     }
     __syncthreads();
-    const float top = row16_max(sh.sample_max[lane & 15]);
-    int top_exp = (int)(__float_as_uint(top) >> 23) + 1;
-    top_exp = top_exp < kTopExp ? kTopExp : top_exp > 254 ? 254 : top_exp;
+    if (top_exp < 0) {
+        const float top = row16_max(sh.sample_max[lane & 15]);
+        top_exp = top > -1048576.0f ? (int)(__float_as_uint(fabsf(top)) >> 23) + 1 : 0;
+        top_exp = top_exp < kTopExp ? kTopExp : top_exp;
+    }
+    top_exp = top_exp > 254 ? 254 : top_exp < kBinades - 1 ? kBinades - 1 : top_exp;
     w.base = __builtin_amdgcn_readfirstlane((top_exp - (kBinades - 1)) << 7);
 
     // Two patterns at a time: rotated left by one, (magnitude, sign) less the window's base is the
@@ -693,12 +761,42 @@ __device__ __forceinline__ Near near_count(const Row& row, uint32_t* hist, Share
 #pragma unroll
             for (int i = 1; i < kAhead; ++i) y = i == u ? x[i] : y;
             note_outside(y, tid + (i0 + u) * kRThreads, (i0 + u) / w.per_quarter, w.base, sh, lane);
+            if (near_fails(sh)) { outside = 0u; i0 = row.steps; } // the wave has counted enough
         }
     }
     __syncthreads();
     return w;
 }
 static_assert(kArray * 4 <= 0x10000, "byte offsets of the counters in 16 bits");
+
+// Counts the row, into a second window if the first had columns above it or too many small ones:
+// four binades above the largest it has seen (its waves stop at the first), or three above the
+// largest among the first vectors.
+__device__ __forceinline__ Near near_window(const Row& row, uint32_t* hist, Shared& sh, int tid)
+{
+    Near w;
+    int top_exp = -1;
+#pragma unroll 1
+    for (;;) {
+        int me = tid;
+        Row again = row;
+        // Opaque copies: otherwise the compiler holds what it can share between the two counts in
+        // registers, and the stream spills (512 rows 45 -> 51 us).
+        asm volatile("" : "+v"(me), "+s"(again.nvec), "+s"(again.last), "+s"(again.steps), "+s"(again.whole));
+        w = near_count(again, top_exp, hist, sh, me);
+        if (__builtin_expect(!near_fails(sh) || top_exp >= 0, 1)) return w;               // uniform
+        const int now = (w.base >> 7) + kBinades - 1;
+        if (sh.n_above != 0) {
+            top_exp = (sh.above_hi >> 7) + 4;
+        } else {
+            const float top = row16_max(sh.sample_max[tid & 15]);
+            top_exp = (int)((__float_as_uint(top) >> 23) & 0xFFu) + 3;
+            if (top_exp > now - 8) return w;                      // hardly lower: the small values lie below it as well
+        }
+        top_exp = __builtin_amdgcn_readfirstlane(top_exp);
+        __syncthreads();
+    }
+}
 
 // The middle items of a row, one per lane of one wave, in rank order: the listed small
 // positive values, +0, -0, the small negative ones.
@@ -751,7 +849,7 @@ void sample_restricted_kernel(RestrictedArgs a)
         philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
         k23 = w4[0] >> 9;
     }
-    const Near win = near_count(row, hist, sh, tid);
+    const Near win = near_window(row, hist, sh, tid);
 
     // my levels
     View vw;
@@ -810,10 +908,10 @@ void sample_restricted_kernel(RestrictedArgs a)
     // Columns below the window weigh nothing when every one of them is below 2^-80 of the largest
     // weight: a row of them stays below the last bit of the total, which is at least 1, and none can win the race.
     const bool below_weightless = n_below == 0
-        || (top_key >= 0.0f && (-(double)value_of_pattern(win.base + kHalf) - z1) * inv_tau < -56.0);
+        || (top_key >= 0.0f && (-(double)value_of_pattern(sh.below_lo) - z1) * inv_tau < -56.0);
     const bool wide = sh.n_above != 0 || !listed || !below_weightless
              || C_win + n_zero + list_n + n_below + sh.n_not_finite + sh.n_above != row.steps * kRThreads * 8    // a counter wrapped
-             || (k_on && C_all >= a.top_k && C_in < a.top_k);                                        // the cut is below the window
+             || (k_on && C_all >= a.top_k && C_in < a.top_k && sh.below_lo != sh.below_hi);           // the cut is below the window
     if (wide) {                                                   // uniform
         wide_row(row, a, r, inv_tau, c, grow, k23, hist, sh, tid);
     } else if (top_key >= 0.0f) {
@@ -843,7 +941,7 @@ void sample_restricted_kernel(RestrictedArgs a)
         auto take = [&](int w) {
             if (sh.cut_key[w] > cut_key) { cut_key = sh.cut_key[w]; kept_C = sh.cut_C[w]; kept_M = sh.cut_M[w]; }
         };
-        if (k_on && C_all >= a.top_k) {                           // exactly one place holds the cut
+        if (k_on && C_in >= a.top_k) {                            // exactly one place holds the cut
             if (vw.Cx < a.top_k && vw.Cx + vw.Cl >= a.top_k) {
                 const Cut cut = own_count_cut<kOwnN, kOwnN>(vw, a.top_k, my_cnt);
                 sh.cut_key[0] = my_key(cut.j); sh.cut_C[0] = cut.C; sh.cut_M[0] = cut.M;
@@ -902,7 +1000,7 @@ void sample_restricted_kernel(RestrictedArgs a)
             }
         } else if (drawn) {
             int q4[kQuarters];
-            if (mag == 0) {
+            if (mag < win.base) {                                 // a zero
 #pragma unroll
                 for (int q = 0; q < kQuarters; ++q) q4[q] = sh.zeros[pattern >> 15][q];
             } else {

@@ -84,3 +84,38 @@ def test_rows_that_are_mostly_a_plateau_are_listed_in_one_pass(dtype):
     ordinary, plateau = us(_selection(x.to(dtype))), us(_selection(torch.relu(x - 9.0).to(dtype)))
     print(f"100 rows {dtype}, top-k 50: ordinary {ordinary:.1f} us, mostly zeros {plateau:.1f} us")
     assert plateau < 3.0 * ordinary
+
+
+def _nucleus(lg, k=0, p=0.9):
+    return _selection(lg.to(torch.bfloat16), k, p)
+
+
+@pytest.mark.parametrize("rows", [8, 300])
+@pytest.mark.parametrize("kind", ["large_late", "all_below", "tiny"])
+def test_rows_outside_the_first_window_are_counted_once_more(kind, rows):
+    # 1.5 to 2 times an ordinary row (8 rows 25 us: 41, 37 and 48 us; 145, 305 and 154 us when such rows took
+    # the wide form)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.randn((rows, 151_936), generator=g, device=DEV) * 3
+    ordinary = us(_nucleus(x))
+    if kind == "large_late":
+        x[:, 75_000:] *= 3000.0
+    elif kind == "all_below":
+        x = x * 10 - 2000.0
+    else:
+        x *= 3e-5
+    outside = us(_nucleus(x))
+    print(f"{rows} rows, top-p 0.9: ordinary {ordinary:.1f} us, {kind} {outside:.1f} us")
+    assert outside < 3.0 * ordinary
+
+
+@pytest.mark.parametrize("rows", [8, 300])
+def test_a_count_cut_among_masked_columns_costs_no_sweeps(rows):
+    # 100 columns allowed, the others at -1e4: top-k 1000 takes as long as no count cut (8 rows 75 us each; 630
+    # and 149 us when the cut sent the row to the wide form)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.full((rows, 151_936), -1e4, device=DEV)
+    x[:, ::1520] = torch.randn((rows, 100), generator=g, device=DEV) * 3
+    without, with_cut = us(_nucleus(x)), us(_nucleus(x, 1000, 1.0))
+    print(f"{rows} masked rows: top-p 0.9 {without:.1f} us, top-k 1000 {with_cut:.1f} us")
+    assert with_cut < 2.0 * without

@@ -376,13 +376,36 @@ def _outside_rows(kind, V, rows, g):
         x = x * 10 - 2000.0
     elif kind == "subnormal":
         x *= 1e-39
+    elif kind == "subnormal_and_zeros":           # a window that reaches down to the zeros
+        x *= 1e-39
+        put(V // 3, lambda n: sign(n) * 0.0)
+    elif kind == "tiny":                          # the window moves down
+        x *= 3e-5
+    elif kind == "tiny_first":                    # ... and the row's rest lies above it
+        x[:, :V * 3 // 4] *= 1e-7
+    elif kind == "raised_twice":                  # larger than what the second window was made for
+        x[:, V // 2:] *= 3000.0
+        x[:, -1] = 1e30
+    elif kind == "masked_first":                  # the first vectors show nothing but a mask
+        x[:, :V * 3 // 4] = -1e4
+    elif kind == "masked_first_lowest":
+        x[:, :V * 3 // 4] = torch.finfo(torch.bfloat16).min
+    elif kind == "masked_added":                  # several levels below the window
+        put(V // 2, lambda n: -1e4 + 100 * torch.randn(n, generator=g, device=DEV))
+    elif kind == "masked_few_left":
+        x[:, torch.randperm(V, generator=g, device=DEV)[50:]] = -1e4
+    elif kind == "below_weighs":                  # columns below the window that still count
+        put(V // 2, lambda n: -520.0 - 3 * torch.rand(n, generator=g, device=DEV))
+        x -= 300.0
     return x.to(torch.bfloat16)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["small1", "small61", "small62", "small63", "small500", "zeros", "zeros_and_small", "zeros_and_many_small",
                                   "masked_inf", "masked_lowest", "masked_1e4", "large_first", "large_late",
-                                  "all_below", "subnormal"])
+                                  "all_below", "subnormal", "subnormal_and_zeros", "tiny", "tiny_first", "raised_twice",
+                                  "masked_first", "masked_first_lowest", "masked_added", "masked_few_left",
+                                  "below_weighs"])
 @pytest.mark.parametrize("V", [3_003, 70_001])
 def test_levels_outside_the_near_window(kind, V):
     g = torch.Generator(device=DEV).manual_seed(V + sum(map(ord, kind)))
@@ -393,7 +416,9 @@ def test_levels_outside_the_near_window(kind, V):
     # high temperatures put the cuts among the small values and the zeros, and the draw with them;
     # a count cut of 90 % of the row lies among the masked columns
     for k, p, tau in [(0, 0.9, 1.0), (0, 0.5, 60.0), (0, 0.55, 900.0), (V // 2, 1.0, 60.0), (V // 2 + 7, 0.99, 500.0),
-                      (9 * V // 10, 0.999, 5.0), (300, 0.7, 2.0)]:
+                      (9 * V // 10, 0.999, 5.0), (9 * V // 10, 1.0, 1.0), (300, 0.7, 2.0), (300, 1.0, 20.0)]:
+        if kind == "masked_inf" and p == 1.0 and k > V // 2:
+            continue                              # the cut would lie among the infinite columns: no levels here
         check(lg, None, tau, k, p, 6, 40, f"outside {kind} V={V} k={k} p={p} tau={tau}")
     if kind != "masked_inf":                      # without a cut the infinite columns are no level here
         check(lg, None, 60.0, 0, 1.0, 6, 40, f"outside {kind} V={V} no cut")
