@@ -171,12 +171,15 @@ int e3_sample_entropy_noalloc(const void* logits, int dtype, int64_t rows, int64
  *   finite logit gives token 0, logp NaN, kept 0).  Other arguments, alignment rules and
  *   errors as for e3_sample_entropy; top_k < 0 or top_p not in (0, inf): E3_ERR_VALUE.
  * One workgroup per row.  With 1 <= top_k <= 256 the row is read once (vectors that can hold
- * one of the k largest are listed in LDS while the row streams, exact selection among those);
- * otherwise (bf16 only) the row's stored patterns are counted in LDS: one counting sweep over
- * 32 binades of both signs, or, for the rare row that does not fit them (finite logits of 512
- * and more that the row's beginning does not show, more than 62 columns nearer to zero than
- * 2^-23 without being zero, very long levels),
- * four to ten sweeps over all patterns.
+ * one of the k largest are listed in LDS while the row streams, exact selection among those); a
+ * row with thousands of equal values at its cut is read several times.  Otherwise (bf16 only) the
+ * row's stored patterns are counted in LDS: one counting sweep over 32 binades of both signs, a second one
+ * over a higher or lower window for a row with finite logits of 512 and more that its first
+ * 32,768 columns do not show, or with more than 62 columns nearer to zero than 2^-23 without being zero.
+ * The rare rows that take four to ten more sweeps, over all patterns: a second window that
+ * does not hold them either; a level of 65,536 or more columns in a quarter of the row; columns below
+ * -512 (or below the window) that still weigh something, i.e. that are less than 56 tau below the
+ * largest logit; a count cut among columns there that are not all equal.
  */
 int e3_sample_restricted(const void* logits, int dtype, int64_t rows, int64_t V, int64_t row_stride,
                          const float* tau_rows, float tau_scalar, int32_t top_k, float top_p,
