@@ -443,14 +443,21 @@ def test_draws_among_listed_values_and_zeros():
 
 @pytest.mark.gpu
 def test_levels_longer_than_a_quarter_counter():
-    # a level of 65,536 columns or more within a quarter of the row wraps its 16-bit counter
-    V = 400_000
+    # a level of 65,536 columns or more within a quarter of the row wraps its 16-bit counter: 49 steps of 8192
+    # columns, 13 to a quarter; quarters 0 and 2 count in the low halves of the words, 1 and 3 in the high ones
+    V, quarter = 400_000, 13 * 8192
     g = torch.Generator(device=DEV).manual_seed(46)
-    base = torch.randn((4, V), generator=g, device=DEV) * 0.05 - 2.0
+    base = torch.randn((8, V), generator=g, device=DEV) * 0.05 - 2.0
     base[0, :65_536] = 0.5
-    base[1, 98_304:98_304 + 65_535] = 0.5           # one short of wrapping
+    base[1, quarter:quarter + 65_535] = 0.5         # one short of wrapping, high half
     base[2, :] = torch.where(torch.rand(V, generator=g, device=DEV) < 0.9, 0.5, base[2])
     base[3, 100_000:300_000] = -1.0
+    base[4, 2 * quarter:2 * quarter + 65_535] = 0.5  # ... low half
+    base[5, quarter:quarter + 65_536] = 0.5         # the high half wraps
+    base[6, :65_535] = 0.5                          # both halves of a word one short of wrapping
+    base[6, quarter:quarter + 65_535] = 0.5
+    base[7, quarter + 1:quarter + 1 + 65_535] = 0.5  # a full counter and one column in the next quarter
+    base[7, 2 * quarter] = 0.5
     lg = base.to(torch.bfloat16)
     for k, p in [(0, 0.9), (1000, 1.0), (0, 0.2), (100_000, 0.999)]:
         check(lg, None, 1.0, k, p, 21, 5, f"long quarter levels k={k} p={p}")
