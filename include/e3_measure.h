@@ -1,7 +1,7 @@
 /*
- * libe3 -- measurement hooks.  NOT part of the library's interface: these two entry
- * points exist so that a benchmark can time the library's own dispatches and compare
- * them with a plain read of the same memory.  They perform none of the method's
+ * libe3 -- measurement hooks.  NOT part of the library's interface: these three
+ * entry points exist so that a benchmark can time the library's own dispatches, compare
+ * them with a plain read of the same memory and see how a batch is launched.  They perform none of the method's
  * arithmetic, may change or disappear, and a product caller has no use for them.
  * Conventions (device pointers, stream, return codes) as in e3.h.
  */
@@ -41,6 +41,16 @@ int e3_time_next_launch(void* start_event, void* stop_event);
  */
 #define E3_READ_PROBE_SUMS 2048
 int e3_read_probe(const void* buf, int64_t bytes, uint32_t* sums_out, void* hip_stream);
+
+/*
+ * How the vocabulary pass launches a [rows, V] batch (sample: the sampling form) on the current
+ * device, or on 256 compute units without one; host only.  *waves, *rows_per_group and *workgroups:
+ * the launch of whole rows.  *cut: 1 if a caller that brings e3_workspace_bytes gets its rows cut
+ * over workgroups of one wave and a merging launch instead.  E3_ERR_SHAPE for a shape that
+ * the library refuses or without rows; no output may be NULL (E3_ERR_NULL).
+ */
+int e3_launch_plan(int64_t rows, int64_t V, int sample, int32_t* cut, int32_t* waves,
+                   int32_t* rows_per_group, int64_t* workgroups);
 
 #ifdef __cplusplus
 }

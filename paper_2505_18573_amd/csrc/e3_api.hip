@@ -119,6 +119,20 @@ extern "C" int e3_time_next_launch(void* start_event, void* stop_event)
     return E3_OK;
 }
 
+extern "C" int e3_launch_plan(int64_t rows, int64_t V, int sample, int32_t* cut, int32_t* waves,
+                              int32_t* rows_per_group, int64_t* workgroups)
+{
+    if (rows < 1 || rows > (int64_t)0x7FFFFFFF || V < 1 || !e3::vocab_pass_fits(V)) return E3_ERR_SHAPE;
+    if (cut == nullptr || waves == nullptr || rows_per_group == nullptr || workgroups == nullptr) return E3_ERR_NULL;
+    bool few = false;
+    const e3::LaunchPlan plan = e3::vocab_pass_plan(rows, V, sample != 0, &few);
+    *cut = few;
+    *waves = plan.waves;
+    *rows_per_group = plan.rows_per_group;
+    *workgroups = plan.workgroups;
+    return E3_OK;
+}
+
 extern "C" int e3_read_probe(const void* buf, int64_t bytes, uint32_t* sums_out, void* hip_stream)
 {
     if (bytes < 0 || (bytes & 15) != 0) return E3_ERR_SHAPE;

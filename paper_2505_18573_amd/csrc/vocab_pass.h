@@ -50,6 +50,14 @@ int64_t static_scratch_max_rows();
 // compute units of the current device (looked up once)
 int compute_units();
 
+// The launch of a batch in whole rows; *cut: its rows are cut instead if the caller brings the
+// workspace for it.
+struct LaunchPlan {
+    int waves, rows_per_group;      // of a workgroup
+    int64_t workgroups;
+};
+LaunchPlan vocab_pass_plan(int64_t rows, int64_t V, bool sample, bool* cut);
+
 // false when V is so large that the per-workgroup tables do not fit LDS
 bool vocab_pass_fits(int64_t V);
 

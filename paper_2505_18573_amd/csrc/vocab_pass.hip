@@ -690,6 +690,7 @@ static hipError_t launch_groups(const VocabPassArgs& a, int rpb, hipStream_t str
     return hipGetLastError();
 }
 
+// How a batch is launched when rows are not cut.
 // Eight waves per workgroup while the whole batch is at most eight workgroups per
 // compute unit; four waves per workgroup beyond that, where the hardware dispatcher
 // balances across many small groups (measured crossover on MI355X: between 2048 and
@@ -697,36 +698,43 @@ static hipError_t launch_groups(const VocabPassArgs& a, int rpb, hipStream_t str
 // unit: a batch that fills its last round of 2 * CUs workgroups to less than 80 %
 // (768 rows on 256 CUs: 512 + 256) runs as 4-wave workgroups if those are all resident
 // at once (measured at 768 rows: 45.0 us instead of 49.3 us).
-template <typename Chunk, bool kSample>
-static hipError_t launch_for(const VocabPassArgs& a, hipStream_t stream)
+static LaunchPlan whole_rows_plan(int64_t rows, int64_t V, bool sample)
 {
     const int64_t cus = compute_units();
+    auto plan = [&](int waves, int rpb) -> LaunchPlan {
+        return LaunchPlan{waves, rpb, rpb > 0 ? (rows + rpb - 1) / rpb : 0};
+    };
     // Several rows per workgroup only where that leaves a resident round of workgroups (nearly) full:
     // 512 rows x 24,000 bf16 columns (three rows per workgroup before) 20.6 -> 11.8 us, 512 x 48,000
     // (two) 18.7 -> 15.7 us; at 1000 rows x 32,000 two rows (18.6 us) beat one (19.6 us), hence the quarter.
     auto spread = [&](int rpb, int64_t round) -> int {
-        const int64_t most = (a.rows + round / 4) / round;
+        const int64_t most = (rows + round / 4) / round;
         return rpb > 1 && most < rpb ? (most > 1 ? (int)most : 1) : rpb;
     };
-    const int rpb8 = spread(rows_per_group<8>(a.V, kSample), 2 * cus);
-    const int rpb4 = spread(rows_per_group<4>(a.V, kSample), 4 * cus);
+    const int rpb8 = spread(rows_per_group<8>(V, sample), 2 * cus);
+    const int rpb4 = spread(rows_per_group<4>(V, sample), 4 * cus);
     // Rows of at most four super-tiles: four waves per workgroup and just enough rows to give each
     // an item, while all workgroups are resident at once or nearly so (1100 x 1000 bf16: 14.1 -> 8.0 us,
     // 1500 x 16,000: 20.4 -> 17.0 us; at 4096 x 8000 the larger groups below take the same time).
-    const int nst = (int)((a.V + kSuperCols - 1) / kSuperCols);
+    const int nst = (int)((V + kSuperCols - 1) / kSuperCols);
     if (nst <= 4 && rpb4 > 0) {
-        const int rpb = a.rows <= 4 * cus ? 1 : (4 + nst - 1) / nst;
-        if ((a.rows + rpb - 1) / rpb <= 6 * cus) return launch_groups<Chunk, kSample, 4>(a, rpb, stream);
+        const LaunchPlan narrow = plan(4, rows <= 4 * cus ? 1 : (4 + nst - 1) / nst);
+        if (narrow.workgroups <= 6 * cus) return narrow;
     }
-    if (rpb8 == 0) return launch_groups<Chunk, kSample, 4>(a, rpb4, stream);
-    const int64_t groups8 = (a.rows + rpb8 - 1) / rpb8;
-    if (groups8 > 8 * cus) return launch_groups<Chunk, kSample, 4>(a, rpb4, stream);
+    const LaunchPlan eight = plan(8, rpb8), four = plan(4, rpb4);
+    if (rpb8 == 0 || eight.workgroups > 8 * cus) return four;
     const int64_t round8 = 2 * cus;
-    const int64_t rounds = (groups8 + round8 - 1) / round8;
-    if (groups8 > round8 && groups8 * 5 < rounds * round8 * 4 && rpb4 > 0
-        && (a.rows + rpb4 - 1) / rpb4 <= 4 * cus)
-        return launch_groups<Chunk, kSample, 4>(a, rpb4, stream);
-    return launch_groups<Chunk, kSample, 8>(a, rpb8, stream);
+    const int64_t rounds = (eight.workgroups + round8 - 1) / round8;
+    if (eight.workgroups > round8 && eight.workgroups * 5 < rounds * round8 * 4 && rpb4 > 0 && four.workgroups <= 4 * cus)
+        return four;
+    return eight;
+}
+
+template <typename Chunk, bool kSample>
+static hipError_t launch_for(const VocabPassArgs& a, const LaunchPlan& plan, hipStream_t stream)
+{
+    return plan.waves == 8 ? launch_groups<Chunk, kSample, 8>(a, plan.rows_per_group, stream)
+                           : launch_groups<Chunk, kSample, 4>(a, plan.rows_per_group, stream);
 }
 
 // Split path: used when the row-block path would leave compute units without a
@@ -736,9 +744,12 @@ static hipError_t launch_for(const VocabPassArgs& a, hipStream_t stream)
 // longer static runs), except that a row has at most 64 runs: one partial per lane
 // of the merging wave.
 // Rows of at most kNarrowTiles super-tiles are not cut: a workgroup has a wave for each of them and
-// needs no second launch (64 rows x 32,000 bf16: 10.3 -> 8.6 us; wider rows are faster cut: 64 x
-// 36,000 10.4 us cut, 11.4 us not).  Wider rows are cut while there are at most half as many row-block
-// workgroups as compute units (100 x 151,936: 15.4 us whole, 13.6 us cut; 192: 16.3 and 18.7 us).
+// needs no second launch (64 rows x 32,000 bf16: 10.3 -> 8.6 us).  Wider rows are cut while whole rows
+// would make at most half as many workgroups as there are compute units.  Cut / whole in us, bf16
+// samples: 64 rows x 33,000 9.6 / 9.9, x 70,005 10.6 / 13.9, x 151,936 12.1 / 15.1; 128 rows 10.5 / 10.7,
+// 12.3 / 14.5, 15.9 / 15.8; 192 rows 11.3 / 11.1, 13.8 / 15.1, 19.0 / 16.8; x 61,000 12.6 / 12.4 at 128 rows and
+// 13.7 / 12.6 at 192.  (Rows of a whole number of super-tiles are faster whole at any count, 128 x
+// 40,960 11.0 / 9.1; x 61,441, one column into the sixteenth, from 112 rows on by 4 %.)
 constexpr int kNarrowTiles = 8;
 constexpr int64_t kSplitMaxRows = 1024;          // bound used by the workspace size
 
@@ -784,21 +795,25 @@ static hipError_t launch_split(const VocabPassArgs& a, RowPartial* ws, SplitPlan
     return hipGetLastError();
 }
 
-// Number of workgroups the row-block launch of this shape will have (both wave counts
-// give the same number when a workgroup holds one row).
-template <int kWaves>
-static int64_t row_block_groups(int64_t rows, int64_t V, bool sample)
+static bool rows_are_cut(int64_t rows, int64_t V, const LaunchPlan& whole)
 {
-    const int rpb = rows_per_group<kWaves>(V, sample);
-    return rpb > 0 ? (rows + rpb - 1) / rpb : 0;
+    return (V + kSuperCols - 1) / kSuperCols > kNarrowTiles && rows <= kSplitMaxRows && whole.workgroups > 0
+        && whole.workgroups * E3_SPLIT_BELOW_DEN <= (int64_t)compute_units() * E3_SPLIT_BELOW_NUM;
+}
+
+LaunchPlan vocab_pass_plan(int64_t rows, int64_t V, bool sample, bool* cut)
+{
+    const LaunchPlan whole = whole_rows_plan(rows, V, sample);
+    *cut = rows_are_cut(rows, V, whole);
+    return whole;
 }
 
 hipError_t launch_vocab_pass(const VocabPassArgs& args, bool is_bf16, bool sample,
                              void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     VocabPassArgs a = args;
-    // Groups ride along only in a row-block launch that has a workgroup for each of them
-    // with either wave count; otherwise they get their own launch first.
+    // Groups ride along only in a launch of whole rows that has a workgroup for each of them;
+    // otherwise they get their own launch first.
     auto separate_advantages = [&]() -> hipError_t {
         const hipError_t err = launch_grpo_advantages(a.adv_rewards, a.adv_offsets, a.adv_groups,
                                                       a.adv_ddof, a.adv_eps, a.adv_out, stream);
@@ -807,10 +822,8 @@ hipError_t launch_vocab_pass(const VocabPassArgs& args, bool is_bf16, bool sampl
     };
     if (a.adv_groups > 0 && a.rows == 0) return separate_advantages();
     if (a.rows == 0) return hipSuccess;
-    const int cus = compute_units();
-    const int rpb8 = rows_per_group<8>(a.V, sample);
-    const bool few = (a.V + kSuperCols - 1) / kSuperCols > kNarrowTiles && a.rows <= kSplitMaxRows && rpb8 > 0
-                  && (a.rows + rpb8 - 1) / rpb8 * E3_SPLIT_BELOW_DEN <= (int64_t)cus * E3_SPLIT_BELOW_NUM;
+    bool few = false;
+    const LaunchPlan whole = vocab_pass_plan(a.rows, a.V, sample, &few);
     if (few && workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
         const SplitPlan plan = split_plan(a.V);
         if ((size_t)a.rows * plan.nslots * sizeof(RowPartial) <= workspace_bytes) {
@@ -826,18 +839,15 @@ hipError_t launch_vocab_pass(const VocabPassArgs& args, bool is_bf16, bool sampl
                           : launch_split<ChunkF32, false>(a, ws, plan, stream);
         }
     }
-    if (a.adv_groups > 0) {
-        const int64_t g8 = row_block_groups<8>(a.rows, a.V, sample), g4 = row_block_groups<4>(a.rows, a.V, sample);
-        if (sample || a.adv_groups > g8 || a.adv_groups > g4) {
-            const hipError_t err = separate_advantages();
-            if (err != hipSuccess) return err;
-        }
+    if (a.adv_groups > 0 && (sample || a.adv_groups > whole.workgroups)) {
+        const hipError_t err = separate_advantages();
+        if (err != hipSuccess) return err;
     }
     if (is_bf16)
-        return sample ? launch_for<ChunkBf16, true>(a, stream)
-                      : launch_for<ChunkBf16, false>(a, stream);
-    return sample ? launch_for<ChunkF32, true>(a, stream)
-                  : launch_for<ChunkF32, false>(a, stream);
+        return sample ? launch_for<ChunkBf16, true>(a, whole, stream)
+                      : launch_for<ChunkBf16, false>(a, whole, stream);
+    return sample ? launch_for<ChunkF32, true>(a, whole, stream)
+                  : launch_for<ChunkF32, false>(a, whole, stream);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,0 +1,39 @@
+"""How the vocabulary pass launches a batch (host only; 256 compute units without a GPU, as on one)."""
+import pytest
+
+import paper_2505_18573_amd as e3
+
+CUS = 256
+TILE = 4096
+ROWS = [1, 3, 64, 96, 127, 128, 129, 160, 192, 193, 255, 256, 257, 300, 511, 512, 513, 640, 641, 768, 1000, 1024, 1025,
+        1536, 2048, 2500, 4096, 10_000, 32_768]
+WIDTHS = [1, 264, 1000, 4000, 4096, 4097, 8000, 16_384, 16_385, 24_000, 32_000, 32_768, 32_769, 40_960, 48_000, 61_440,
+          61_441, 70_005, 128_000, 151_936, 262_144, 500_000]
+
+
+@pytest.mark.parametrize("sample", [True, False])
+def test_workgroups_cover_the_rows_and_the_cut_follows_their_number(sample):
+    for V in WIDTHS:
+        for rows in ROWS:
+            cut, waves, per_group, workgroups = e3.e3_launch_plan(rows, V, sample)
+            assert waves in (4, 8) and per_group >= 1
+            assert workgroups == -(-rows // per_group), (rows, V)
+            # a workgroup never holds more rows than give each wave two items
+            assert per_group == 1 or (per_group - 1) * -(-V // TILE) < 2 * waves, (rows, V)
+            # rows are cut where whole rows leave half of the compute units without a workgroup
+            assert cut == (V > 8 * TILE and rows <= 1024 and 2 * workgroups <= CUS), (rows, V)
+            # ... which a batch with a row for more than half of them never does
+            assert not (cut and rows > CUS // 2), (rows, V)
+
+
+@pytest.mark.parametrize("rows,V,groups", [(512, 4000, 64), (1024, 4000, 128), (512, 1000, 64), (64, 1000, 8)])
+def test_small_rows_have_a_workgroup_for_every_group_of_eight(rows, V, groups):
+    # advantages ride along with the training-side pass where it has a workgroup for each group
+    assert e3.e3_launch_plan(rows, V, False)[3] >= groups
+
+
+def test_refused_shapes():
+    for rows, V in ((0, 1000), (-1, 1000), (10, 0), (10, 1 << 30)):
+        with pytest.raises(e3.E3Error) as ei:
+            e3.e3_launch_plan(rows, V)
+        assert ei.value.status == -2
