@@ -40,7 +40,6 @@ namespace {
 constexpr int kSBatch = 8;              // 16-byte requests of a thread made together; two such sets are in flight
 constexpr int kSMaxWaves = 16;
 constexpr int kSVecCap = 2048;          // vectors listed in LDS
-constexpr int kSMostHits = 128;         // of the 512 vectors a wave holds: more of them and theta is a plateau
 constexpr int kSMaxK = 256;             // top_k served here; the gt-list holds at most kSMaxK - 1 columns
 constexpr int kSEqCap = 64;             // columns of the cut level listed for a direct pick
 constexpr int kSListCap = 2048;         // candidates (columns at or above theta) listed in LDS
@@ -452,27 +451,32 @@ void sample_select_kernel(SelArgs a)
     float tmax = -INFINITY;                                       // maximum of the finite values I have read
     // Maxima are taken as floats (NaN operands drop out of v_max3); a vector whose maximum is
     // infinite is looked through by hand.
-    auto vector_max = [&](const u32x4& x) -> float {
-        const float m = T::vec_max(x);
-        if (__builtin_expect(m == INFINITY, 0)) {
-            float f = -INFINITY;
-            for (int j = 0; j < T::kElems; ++j) {
-                const float z = __uint_as_float(T::elem_bits(x, j));
-                if (z < INFINITY) f = fmaxf(f, z);
-            }
-            return f;
+    auto finite_max = [&](u32x4 x) -> float {
+        asm volatile("" : "+v"(x));                               // shares nothing with the common path, which would hold it in registers
+        float f = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < T::kElems; ++j) {
+            const float z = __uint_as_float(T::elem_bits(x, j));
+            f = z < INFINITY ? fmaxf(f, z) : f;
         }
-        return m;
+        return f;
     };
     auto set_maxima = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
+        float most = -INFINITY;
 #pragma unroll
-        for (int u = 0; u < kSBatch; ++u) m[u] = vector_max(x[u]);
-        if (set + (kSBatch - 1) * nsets < whole) return;          // uniform: nothing but complete vectors
+        for (int u = 0; u < kSBatch; ++u) { m[u] = T::vec_max(x[u]); most = fmaxf(most, m[u]); }
+        if (__builtin_expect(__any(most == INFINITY), 0)) {
+#pragma unroll
+            for (int u = 0; u < kSBatch; ++u) m[u] = finite_max(x[u]);
+        }
 #pragma unroll
         for (int u = 0; u < kSBatch; ++u) {
-            const int v = tid + (set + u * nsets) * kSThreads;
-            if (v >= nvec) m[u] = -INFINITY;
-            else if (v == nvec - 1 && last < T::kElems) m[u] = vector_max(T::cut_off(x[u], last));
+            const int slot = set + u * nsets;
+            if (slot >= whole) {                                  // uniform: holds the row's end or lies past it
+                const int v = tid + slot * kSThreads;
+                if (v >= nvec) m[u] = -INFINITY;
+                else if (v == nvec - 1 && last < T::kElems) m[u] = finite_max(T::cut_off(x[u], last));
+            }
         }
     };
     // The wave's m-th largest thread maximum, m = ceil(k / waves with columns), bit by bit from the
@@ -521,23 +525,21 @@ void sample_select_kernel(SelArgs a)
         return t < 0x00800000u ? -3.402823466e38f : __uint_as_float(T::kKeyBits == 16 ? bits & 0xFFFF0000u : bits);
     };
     // The vectors of a set whose maximum reaches theta go into the list: one reservation per wave.
-    // Where that would be most of what the wave holds, theta is a plateau so far, and only what lies above
+    // Where that would be most of most lanes' vectors, theta is a plateau so far, and only what lies above
     // it is listed (sh.skipped remembers the highest such value): enough if the final theta is higher.
     auto list_set = [&](const u32x4 (&x)[kSBatch], const float (&m)[kSBatch], int set, float thf, bool all) {
         uint32_t hits = 0u;
 #pragma unroll
         for (int u = 0; u < kSBatch; ++u) hits |= (uint32_t)(m[u] >= thf) << u;
         if (!__any(hits != 0u)) return;
-        int mine = __popc(hits);
-        int inc = wave_prefix_sum(mine);
-        if (__builtin_expect(!all && __builtin_amdgcn_readlane(inc, 63) > kSMostHits, 0)) {
+        if (__builtin_expect(!all && (int)__popcll(__ballot(__popc(hits) >= kSBatch / 2)) > 32, 0)) {
             hits = 0u;
 #pragma unroll
             for (int u = 0; u < kSBatch; ++u) hits |= (uint32_t)(m[u] > thf) << u;
-            mine = __popc(hits);
-            inc = wave_prefix_sum(mine);
             if (lane == 0) atomicMax(&sh.skipped, key_of_f32(__float_as_uint(thf)));
         }
+        const int mine = __popc(hits);
+        const int inc = wave_prefix_sum(mine);
         int base = 0;
         if (lane == 63) base = atomicAdd(&sh.vec_n, inc);
         int slot = __builtin_amdgcn_readlane(base, 63) + inc - mine;
