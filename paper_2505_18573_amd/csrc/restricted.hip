@@ -69,7 +69,11 @@ constexpr int kWideBins = 16384;                // patterns in one of the four w
 constexpr int kWideWindows = 4;
 constexpr int kOwnW = kWideBins / kRThreads;    // 16
 constexpr int kMidList = 62;                    // listed small values; with the two zeros one item per lane
-constexpr int kBlock = 5;                       // stream steps looked up at a time (a quarter of 151,936 columns)
+// Stream steps looked up at a time.  A step more in the block costs every row 0.3 us, a second block 1.8 us: 8 rows
+// of 32,000 columns with 4, 5 and 6 steps 15.4, 15.7 and 16.0 us; one block is enough for a quarter of up
+// to 131,072, 163,840 and 196,608 columns (8 x 151,936: 24.0, 23.1 and 23.5 us; 8 x 180,000: 25.5, 25.6
+// and 24.8).  Five: vocabularies of 128,000 to 160,000 columns are the common ones.
+constexpr int kBlock = 5;
 static_assert(kArray * 2 >= kWideBins + kTrash, "the wide window fits the same memory");
 static_assert(kOwnN * kRThreads == 2 * kHalf && 128 % kOwnN == 0 && 128 % kOwnW == 0, "a thread's levels share a binade");
 
@@ -87,6 +91,7 @@ struct Shared {
     int zeros[2][kQuarters];        // +0, -0 by quarter
     int list_n, n_below, n_not_finite, n_above;
     int below_lo, below_hi, above_hi;            // magnitude bits of the columns below the window (both ends) and above it
+    int fails;                      // not 0: columns above the window, or more small ones than the list holds
     int list_key[64], list_col[64]; // small values as they come
     int mid_key[64], mid_cnt[64], mid_col[64];   // the middle items in rank order
     int mid_C[64];                  // inclusive prefixes inside the middle
@@ -669,7 +674,7 @@ __device__ __forceinline__ void note_outside(const u32x4& x, int v, int quarter,
         tally(n1, &sh.n_above, &sh.n_below);
         if (lo < sh.below_lo) atomicMin(&sh.below_lo, lo);        // of a mask of one value the first vectors only
         if (hi > sh.below_hi) atomicMax(&sh.below_hi, hi);
-        if (top > sh.above_hi) atomicMax(&sh.above_hi, top);
+        if (top > sh.above_hi) { atomicMax(&sh.above_hi, top); sh.fails = 1; }
     }
     if (!__any(n0 >> 20 != 0u)) return;
 #pragma unroll 1
@@ -678,16 +683,9 @@ __device__ __forceinline__ void note_outside(const u32x4& x, int v, int quarter,
         if (mag != 0u && mag < (uint32_t)base) {
             const int at = atomicAdd(&sh.list_n, 1);
             if (at < kMidList) { sh.list_key[at] = key_of_pattern((int)p); sh.list_col[at] = v * 8 + j; }
+            else sh.fails = 1;
         }
     }
-}
-
-// Columns above the window, or more small values than the list holds: the window does not hold the row.
-__device__ __forceinline__ bool near_fails(const Shared& sh)
-{
-    const volatile int* n = &sh.list_n;
-    const volatile int* m = &sh.n_above;
-    return __builtin_amdgcn_readfirstlane(*n > kMidList || *m != 0) != 0;
 }
 
 // Counts the row.  Returns the window, whose top binade is `top_exp` if that is not negative.
@@ -704,7 +702,7 @@ __device__ __forceinline__ Near near_count(const Row& row, int top_exp, uint32_t
     if (tid < 2 * kQuarters) (&sh.zeros[0][0])[tid] = 0;
     if (tid == 0) {
         sh.list_n = 0; sh.n_below = 0; sh.n_not_finite = 0; sh.n_above = 0;
-        sh.below_lo = 0x7FFF; sh.below_hi = 0; sh.above_hi = 0;
+        sh.below_lo = 0x7FFF; sh.below_hi = 0; sh.above_hi = 0; sh.fails = 0;
     }
     {
         // the window's top: one binade above the magnitude of the largest finite logit among the first
@@ -761,7 +759,7 @@ __device__ __forceinline__ Near near_count(const Row& row, int top_exp, uint32_t
 #pragma unroll
             for (int i = 1; i < kAhead; ++i) y = i == u ? x[i] : y;
             note_outside(y, tid + (i0 + u) * kRThreads, (i0 + u) / w.per_quarter, w.base, sh, lane);
-            if (near_fails(sh)) { outside = 0u; i0 = row.steps; } // the wave has counted enough
+            if (__builtin_amdgcn_readfirstlane(*(volatile int*)&sh.fails) != 0) { outside = 0u; i0 = row.steps; }     // counted enough
         }
     }
     __syncthreads();
@@ -784,7 +782,7 @@ __device__ __forceinline__ Near near_window(const Row& row, uint32_t* hist, Shar
         // registers, and the stream spills (512 rows 45 -> 51 us).
         asm volatile("" : "+v"(me), "+s"(again.nvec), "+s"(again.last), "+s"(again.steps), "+s"(again.whole));
         w = near_count(again, top_exp, hist, sh, me);
-        if (__builtin_expect(!near_fails(sh) || top_exp >= 0, 1)) return w;               // uniform
+        if (__builtin_expect(sh.fails == 0 || top_exp >= 0, 1)) return w;                 // uniform
         const int now = (w.base >> 7) + kBinades - 1;
         if (sh.n_above != 0) {
             top_exp = (sh.above_hi >> 7) + 4;
