@@ -2,7 +2,7 @@
 // KL term the paper drops): per token min(r A, clip(r, 1-eps, 1+eps) A) with
 // r = exp(logp_new - logp_old), averaged over the tokens of a rollout, then over the
 // rollouts of a question, then over questions.  It consumes what the vocabulary pass
-// (log-probs) and the advantage kernel (A) produce.  Two launches: one to eight waves per
+// (log-probs) and the advantage kernel (A) produce.  Two launches: one to sixteen waves per
 // rollout (fp64 sums, DPP reductions), then one workgroup that folds rollouts into questions
 // and questions into the scalar; every sum has an order fixed by the shape (bit-reproducible).
 #include "vocab_common.h"
@@ -15,8 +15,8 @@ namespace e3 {
 // once, hence several waves per rollout and up to kUnroll tokens per lane requested before the
 // first is used - as many as the rollout has left, rounded up to a power of two, so that a short one
 // does not request its tokens several times.  512 rollouts of 77 - 8192 tokens (1.6 M tokens,
-// 19 MB) on MI355X: one wave per rollout with one token per lane at a time 44.2 us, this form 6.6 us
-// (2.9 TB/s).
+// 19 MB) on MI355X: one wave per rollout with one token per lane at a time 44.2 us, this form 6.8 us
+// (2.8 TB/s).
 constexpr int kUnroll = 8;
 
 template <int kWaves, int kSeqsPerBlock>
@@ -135,15 +135,16 @@ hipError_t launch_grpo_objective(const float* logp_new, const float* logp_old,
                                  hipStream_t stream)
 {
     if (num_seqs > 0) {
-        // The waves per rollout: 8, 4 or 2 while all of them are resident at once (32 per compute unit),
-        // else one.  Long and very different rollouts gain from waves, short ones pay for launching
-        // idle ones: 2048 rollouts of up to 8192 tokens 27.2 us with one wave, 20.5 with two, 18.0 with four;
-        // of 100 tokens 5.8, 6.0 and 6.3 us.  3072 of up to 4096: 17.6, 14.7 and (four, not all resident)
-        // 13.6 us; of 100 tokens 4096 take 6.0, 6.5 and 7.3.  Sixteen waves for 512 and fewer are no
-        // faster than eight (7.9 and 8.0 us at up to 8192 tokens) and cost the short ones 0.3 us.
+        // The waves per rollout: 16, 8, 4 or 2 while all of them are resident at once (32 per compute
+        // unit), else one.  Long and very different rollouts gain from waves, short ones pay for launching
+        // idle ones.  512 rollouts of up to 8192 tokens 9.0 us with eight waves, 8.3 with sixteen, of up to 2048 4.9
+        // and 5.3; 2048 of up to 8192 27.2 us with one wave, 20.5 with two, 18.0 with four, of 100 tokens
+        // 5.8, 6.0 and 6.3; 3072 of up to 4096 17.6, 14.7 and (four, not all resident) 13.6 us; 4096 of 100
+        // tokens 6.0, 6.5 and 7.3.
         const int64_t resident = 32 * (int64_t)compute_units();
         const dim3 one((unsigned)num_seqs);
-        if (num_seqs * (int64_t)8 <= resident) launch_terms<8, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
+        if (num_seqs * (int64_t)16 <= resident) launch_terms<16, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
+        else if (num_seqs * (int64_t)8 <= resident) launch_terms<8, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
         else if (num_seqs * (int64_t)4 <= resident) launch_terms<4, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
         else if (num_seqs * (int64_t)2 <= resident) launch_terms<2, 1>(one, logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);
         else launch_terms<1, 4>(dim3((unsigned)(((int64_t)num_seqs + 3) / 4)), logp_new, logp_old, seq_offsets, adv, num_seqs, clip_eps, token_term_out, seq_mean_out, stream);

@@ -61,7 +61,7 @@ def test_objective_parity_on_gpu():
 @pytest.mark.gpu
 @pytest.mark.parametrize("num_seqs", [1, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097])
 def test_objective_parity_at_every_wave_count(num_seqs):
-    # 8, 4, 2 and 1 waves per rollout, on both sides of each bound; lengths around the tokens that a
+    # 16, 8, 4, 2 and 1 waves per rollout, on both sides of each bound; lengths around the tokens that a
     # wave, a workgroup of each size and an unrolled round of 1, 2, 4 or 8 take, and empty rollouts and questions
     dev = "cuda:0"
     rng = np.random.default_rng(num_seqs)
