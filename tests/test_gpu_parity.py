@@ -721,3 +721,24 @@ def test_launch_shapes_of_small_batches(rows, V, dtype):
         for x, y in zip(out[:4], sep):
             assert torch.equal(x, y)
         assert torch.equal(out[4], e3.e3_grpo_advantages(rewards, offsets))
+
+
+def test_streams_without_the_raw_handle(monkeypatch):
+    # the binding takes torch's raw stream handle where there is one and a Stream object otherwise: the same
+    # results on a stream of the caller's own either way, ordered behind what that stream did before
+    g = torch.Generator(device=DEV).manual_seed(8)
+    source = (torch.randn((64, 40_000), generator=g, device=DEV) * 3).to(torch.bfloat16)
+    want = e3.e3_sample_entropy(source, None, 0.9, 3, 0)
+    torch.cuda.synchronize()
+    assert e3.binding._raw_stream is not None
+    for raw in (e3.binding._raw_stream, None):
+        monkeypatch.setattr(e3.binding, "_raw_stream", raw)
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            assert e3.binding._stream(source.device) == stream.cuda_stream
+            lg = torch.zeros_like(source)
+            lg.copy_(source)
+            got = e3.e3_sample_entropy(lg, None, 0.9, 3, 0)
+        stream.synchronize()
+        for x, y in zip(got, want):
+            assert torch.equal(x, y)

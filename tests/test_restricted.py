@@ -338,9 +338,10 @@ def test_fp32_rows_need_a_small_top_k():
 
 
 # ---------------------------------------------------------------- the near window and what lies outside it
-# 32 binades up to [256, 512) (or one above the largest logit of the first vectors) are counted
-# directly; nearer to zero than that: at most 62 columns, listed; zeros apart; below it: masked columns;
-# everything else takes the wide form.  Bars as for every test of this file.
+# 32 binades up to [256, 512) (or one above the magnitude of the largest logit of the first vectors) are
+# counted directly; nearer to zero than that: at most 62 columns, listed; zeros apart; below it: masked columns.
+# A row that this does not hold is counted once more in a window raised or lowered for it; everything else
+# takes the wide form.  Bars as for every test of this file.
 def _outside_rows(kind, V, rows, g):
     x = torch.randn((rows, V), generator=g, device=DEV) * 3
 
