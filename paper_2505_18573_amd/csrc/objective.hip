@@ -99,7 +99,7 @@ void grpo_objective_reduce_kernel(const double* __restrict__ seq_mean,
     if (num_groups > 0) { i0 = offset(q); i1 = offset(q + 1); }
     for (int64_t q0 = 0; q0 < num_groups; q0 += 1024 / kLanes) {   // whole waves take part in the reductions
         q += 1024 / kLanes;
-        const int32_t next0 = offset(q), next1 = offset(q + 1);    // requested ahead of this round's sums
+        const int32_t next0 = offset(q), next1 = offset(q + 1);    // requested ahead of these sums
         double g = 0.0;
 #pragma unroll 4
         for (int32_t i = i0 + sub; i < i1; i += kLanes) g += seq_mean[i];
