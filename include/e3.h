@@ -173,9 +173,9 @@ int e3_sample_entropy_noalloc(const void* logits, int dtype, int64_t rows, int64
  * One workgroup per row.  With 1 <= top_k <= 256 the row is read once (vectors that can hold
  * one of the k largest are listed in LDS while the row streams, exact selection among those); a
  * row with thousands of equal values at its cut is read several times.  Otherwise (bf16 only) the
- * row's stored patterns are counted in LDS: one counting sweep over 32 binades of both signs, a second one
+ * row's stored patterns are counted in LDS: one counting sweep over 31.5 binades of both signs, a second one
  * over a higher or lower window for a row with finite logits of 512 and more that its first
- * 32,768 columns do not show, or with more than 62 columns nearer to zero than 2^-23 without being zero.
+ * 16,384 columns do not show, or with more than 62 columns nearer to zero than 1.5 x 2^-23 without being zero.
  * The rare rows that take four to ten more sweeps, over all patterns: a second window that
  * does not hold them either; a level of 65,536 or more columns in a quarter of the row; columns below
  * -512 (or below the window) that still weigh something, i.e. that are less than 56 tau below the

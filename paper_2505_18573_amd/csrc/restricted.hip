@@ -8,7 +8,7 @@
 // over the kept levels followed by a uniform choice among the winning level's columns.
 //
 // bf16 has only 65,536 bit patterns, so the whole value distribution of a row is a count
-// histogram.  One workgroup of 16 waves owns one row:
+// histogram.  One workgroup owns one row:
 //   1. stream the row once, counting with LDS atomics;
 //   2. every thread owns a run of consecutive levels of one binade, i.e. equally spaced
 //      values whose weights exp((z - z_1)/tau) form a geometric sequence: two
@@ -19,14 +19,11 @@
 //      pos-th column of the winning level is looked up in the row.
 // Counts are integers; masses and the cuts are fp64.
 //
-// THE NEAR WINDOW (every ordinary row).  The values a row really holds span few binades:
-// 32 binades of both signs, 8192 levels, are counted in 64 KiB of LDS - the 32 binades up to
-// [256, 512), or up to one above the magnitude of the largest logit among the first vectors read,
-// whichever is higher.  64 KiB instead of the 128 KiB all patterns need is what lets two rows share a
-// compute unit, so that one row's short dependent phases overlap the other's stream: a 512 x
-// 151,936 batch took 100 us with one row per compute unit at a time, and the counting itself
-// is no limit then (read alone 27.2 us, read and count 31.4 us; but one row on one compute
-// unit 4.2 and 12.2 us: there the LDS atomics are).  Each level has four 16-bit counters, one
+// THE NEAR WINDOW (every ordinary row).  The values a row really holds span few binades: 31.5 binades of
+// both signs, 8064 levels, are counted in 64 KiB of LDS - those up to [256, 512), or up to one above the
+// magnitude of the largest logit among the first vectors read, whichever is higher.  64 KiB instead of
+// the 128 KiB all patterns need is what lets two rows share a compute unit, so that one row's short
+// dependent phases overlap the other's stream.  Each level has four 16-bit counters, one
 // per quarter of the row (the quarter is uniform per step of the stream, so it costs nothing), and
 // the final look-up reads only the quarter that holds the column.  What lies outside the
 // window is kept exactly too: zeros are counted apart, up to 62 nearer to zero than the window are
@@ -34,20 +31,33 @@
 // below the window (masked columns) are counted when they are too far down to weigh anything; a
 // count cut among them keeps all of them if they are one value.
 //
+// What bounds it.  The counting: an LDS atomic on 64 random counters takes 7.7 cycles (4 without a bank
+// conflict), 7.6 us for the 151,936 columns of a row alone on its compute unit, and five vector
+// instructions go with it; two rows together sit between that, the issue of those instructions and HBM.
+// Then five short phases per row (levels and scan 2.2 us, cuts 1.2, race 0.9, look-up 2.2 to 3), chains of
+// LDS, barriers and dependent instructions that the last rows of a launch have nothing to overlap with.
+// Hence workgroups of eight waves (per-wave work of the phases is done half as often as with sixteen:
+// 100 rows x 1000 columns 14.6 us with sixteen waves and 64 registers each, 10.7 now), two sets of requests in
+// flight, and nothing in the stream but the count: spare words for what lies outside, one check per set.
+// Sixteen waves still stream a single row faster: with at most one row per compute unit they win from
+// about 114,688 columns on (eight / sixteen waves in us: 100 rows x 70,000 15.3 / 15.5, x 100,000 17.5 / 17.6, x 130,000 20.3 /
+// 19.5, x 400,000 45.3 / 39.4; 256 rows x 40,000 13.6 / 15.1, x 100,000 19.0 / 19.4, x 130,000 21.6 / 21.5).
+// Captured launches, top-p 0.9, sixteen waves with a burst of four requests / now: 8 x 151,936 23.0 /
+// 19.4 us, 256 rows 26.2 / 23.4, 512 rows 43.2 / 37.9 (4.1 TB/s), 1024 rows 82.6 / 73.5; 512 x 32,000 26.7 / 17.6,
+// 300 x 70,000 30.8 / 21.8, 512 x 5000 22.6 / 13.3.
+//
 // A row with values above the window, or with more small ones than the list holds, is counted once
 // more in a window raised to the former or lowered for the latter; its waves give the first count up as
-// soon as they see it.  151,936 columns, 8 / 512 rows: a logit of 9000 at the end of the row
-// 38 / 51 us, all logits around -2000 (seen by the first vectors) 37 / 67 us, all below 1e-3 48 / 84 us;
-// with all patterns in 128 KiB these took 42 / 99, 64 / 149 and 50 / 116 us, in the wide form alone
-// 108 / 117, 305 / 589 and 154 / 271 us.
+// soon as they see it (151,936 columns, 8 / 512 rows: a logit of 9000 at the end of the row 37 / 46 us, all logits
+// around -2000, seen by the first vectors, 34 / 61 us, all below 1e-3 38 / 58 us).
 //
 // THE WIDE ROWS.  Everything else - a second window that fails too, a wrapped counter (recognised
 // because the counts no longer add up to the row's width), a count cut among several levels below the
 // window, columns below it that still weigh something (a mask of -1e4 at tau above 178) - is redone
 // over all patterns with 32-bit counters, in four windows of 16,384 patterns in rank order, one
 // sweep each; a cut or the race needs its window swept again unless it was the last.  Slow (up
-// to ten sweeps), exact, rare: ordinary logits with 500 columns of 2^-24 to 2^-60 among them 114 / 204 us (39 /
-// 99 us with all patterns in 128 KiB), half of 400,000 columns equal 515 us at 8 rows (411 us).  Its code is inlined
+// to ten sweeps), exact, rare: ordinary logits with 500 columns of 2^-24 to 2^-60 among them 110 / 216 us at 8 /
+// 512 rows, half of 400,000 columns equal 519 us at 8 rows.  Its code is inlined
 // although few rows run it: as a function of its own the calling convention cost every row scratch
 // memory (8 ordinary rows 25 -> 31 us, 512 rows 45 -> 63 us).
 #include "vocab_common.h"
@@ -56,31 +66,49 @@
 namespace e3 {
 namespace {
 
-constexpr int kRThreads = 1024;
-constexpr int kRWaves = kRThreads / 64;
 constexpr int kBinades = 32;                    // of each sign in the near window
-constexpr int kHalf = kBinades * 128;           // its levels of one sign
+constexpr int kHalf = kBinades * 128;           // its words of one sign
 constexpr int kTopExp = 135;                    // exponent field of the lowest top binade, [256, 512)
 constexpr int kQuarters = 4;
-constexpr int kOwnN = 2 * kHalf / kRThreads;    // near window: 8 levels per thread
-constexpr int kTrash = 64;                      // words behind a counter array, one per lane
-constexpr int kArray = 2 * kHalf + kTrash;      // two quarters' counters in each word
+constexpr int kTrash = 64;                      // spare words, one per lane
+constexpr int kLevels = kHalf - kTrash;         // levels of one sign that are counted
+constexpr int kArray = 2 * kHalf;               // words of two quarters' counters
 constexpr int kWideBins = 16384;                // patterns in one of the four wide windows
 constexpr int kWideWindows = 4;
-constexpr int kOwnW = kWideBins / kRThreads;    // 16
 constexpr int kMidList = 62;                    // listed small values; with the two zeros one item per lane
-// Stream steps looked up at a time.  A step more in the block costs every row 0.3 us, a second block 1.8 us: 8 rows
-// of 32,000 columns with 4, 5 and 6 steps 15.4, 15.7 and 16.0 us; one block is enough for a quarter of up
-// to 131,072, 163,840 and 196,608 columns (8 x 151,936: 24.0, 23.1 and 23.5 us; 8 x 180,000: 25.5, 25.6
-// and 24.8).  Five: vocabularies of 128,000 to 160,000 columns are the common ones.
-constexpr int kBlock = 5;
-static_assert(kArray * 2 >= kWideBins + kTrash, "the wide window fits the same memory");
-static_assert(kOwnN * kRThreads == 2 * kHalf && 128 % kOwnN == 0 && 128 % kOwnW == 0, "a thread's levels share a binade");
+// Stream steps of one set of requests, two sets being in flight: 512 x 151,936 37.7, 38.8 and 39.7 us with 2, 3 and 4
+// (the first values arrive later the more are asked for), 8 x 151,936 20.0, 19.9 and 20.1.
+constexpr int kSet = 2;
+static_assert(kArray * 2 >= kWideBins, "the wide window fits the same memory");
 
 // Rank key of a pattern: ascending in value, -0 just below +0.
 __device__ __forceinline__ int key_of_pattern(int p) { return p < 0x8000 ? p + 0x8000 : 0xFFFF - p; }
 __device__ __forceinline__ int pattern_of_key(int key) { return key >= 0x8000 ? key - 0x8000 : 0xFFFF - key; }
 __device__ __forceinline__ float value_of_pattern(int p) { return __uint_as_float((uint32_t)p << 16); }
+
+struct RestrictedArgs {
+    const uint16_t* logits;
+    int64_t rows, V, row_stride;
+    const float* tau_rows;
+    float tau_scalar;
+    int32_t top_k;
+    float top_p;
+    uint64_t seed, row_base;
+    int32_t* token_out;
+    float* logp_out;
+    int32_t* kept_out;
+};
+
+// A row's sampling by one workgroup of kRThreads threads.
+template <int kRThreads>
+struct Sampler {
+static constexpr int kRWaves = kRThreads / 64;
+static constexpr int kOwnN = 2 * kHalf / kRThreads;    // near window: a thread's levels
+static constexpr int kOwnW = kWideBins / kRThreads;
+static constexpr int kWide = 4096 / kRThreads;         // wide rows: stream steps requested together
+// Stream steps looked up at a time: one block is enough for a quarter of up to 163,840 columns.
+static constexpr int kBlock = 5120 / kRThreads;
+static_assert(kOwnN * kRThreads == 2 * kHalf && 128 % kOwnN == 0 && 128 % kOwnW == 0, "a thread's levels share a binade");
 
 struct Shared {
     float wave_top[kRWaves];
@@ -99,22 +127,8 @@ struct Shared {
     int cut_key[kRWaves + 1], cut_C[kRWaves + 1];      // what each wave (and the middle) offers as the cut
     double cut_M[kRWaves + 1];
     int tot[kBlock * kRWaves];
-    int token;
     int C_above[kWideWindows + 1];  // wide rows: count and mass above each window
     double M_above[kWideWindows + 1];
-};
-
-struct RestrictedArgs {
-    const uint16_t* logits;
-    int64_t rows, V, row_stride;
-    const float* tau_rows;
-    float tau_scalar;
-    int32_t top_k;
-    float top_p;
-    uint64_t seed, row_base;
-    int32_t* token_out;
-    float* logp_out;
-    int32_t* kept_out;
 };
 
 // The row as 16-byte vectors, kRThreads of them per step.  The last vector may reach past the row's
@@ -123,19 +137,32 @@ struct RestrictedArgs {
 struct Row {
     const u32x4* p;
     int nvec, last;       // vectors; columns in the last one, 1 .. 8
+    int complete;         // vectors of eight columns
     int steps, whole;     // steps, and how many of them hold nothing but complete vectors
     __device__ __forceinline__ u32x4 guarded(int v) const
     {
+        return counted(v < nvec ? p[v] : u32x4{0u, 0u, 0u, 0u}, v);
+    }
+    // vector v without what is not the row's
+    __device__ __forceinline__ u32x4 counted(const u32x4& x, int v) const
+    {
         constexpr uint32_t kNone = 0xFFC0FFC0u;
-        u32x4 x = {kNone, kNone, kNone, kNone};
-        if (v < nvec) x = p[v];
-        if (v == nvec - 1) {
-            auto fill = [&](uint32_t word, int first) -> uint32_t {
-                return last <= first ? kNone : last == first + 1 ? (word & 0xFFFFu) | (kNone & 0xFFFF0000u) : word;
-            };
-            x = u32x4{fill(x.x, 0), fill(x.y, 2), fill(x.z, 4), fill(x.w, 6)};
+        const int n = v < nvec - 1 ? 8 : v == nvec - 1 ? last : 0;
+        auto fill = [&](uint32_t word, int first) -> uint32_t {
+            return n <= first ? kNone : n == first + 1 ? (word & 0xFFFFu) | (kNone & 0xFFFF0000u) : word;
+        };
+        return u32x4{fill(x.x, 0), fill(x.y, 2), fill(x.z, 4), fill(x.w, 6)};
+    }
+    // kN steps from `step` on, requested together and without a branch (where two sides of one meet, the
+    // compiler waits for the loads of both): past the row they repeat its last vector, for `counted` to drop
+    template <int kN>
+    __device__ __forceinline__ void request_ahead(u32x4 x[kN], int step, int tid) const
+    {
+#pragma unroll
+        for (int u = 0; u < kN; ++u) {
+            const int v = tid + (step + u) * kRThreads;
+            x[u] = p[v < nvec ? v : nvec - 1];
         }
-        return x;
     }
     // kN steps from `step` on, requested together; those at or past `end` read as nothing
     template <int kN>
@@ -155,7 +182,7 @@ struct Row {
 };
 
 template <typename F>
-__device__ __forceinline__ void for_each_pattern(const u32x4& v, F&& f)
+static __device__ __forceinline__ void for_each_pattern(const u32x4& v, F&& f)
 {
     f(v.x & 0xFFFFu, 0); f(v.x >> 16, 1); f(v.y & 0xFFFFu, 2); f(v.y >> 16, 3);
     f(v.z & 0xFFFFu, 4); f(v.z >> 16, 5); f(v.w & 0xFFFFu, 6); f(v.w >> 16, 7);
@@ -163,7 +190,7 @@ __device__ __forceinline__ void for_each_pattern(const u32x4& v, F&& f)
 
 // Inclusive prefix sums over the lanes of a wave (see wave_max for the steps).
 template <typename T, typename Step>
-__device__ __forceinline__ T wave_prefix(T v, Step&& step)
+static __device__ __forceinline__ T wave_prefix(T v, Step&& step)
 {
     v += step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{}, v);    // row_shr 1, 2, 4, 8
     v += step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{}, v);
@@ -173,16 +200,16 @@ __device__ __forceinline__ T wave_prefix(T v, Step&& step)
     v += step(std::integral_constant<int, kDppBcast31>{}, std::integral_constant<int, 0xC>{}, v);
     return v;
 }
-__device__ __forceinline__ int wave_prefix_i(int v)
+static __device__ __forceinline__ int wave_prefix_i(int v)
 {
     return wave_prefix(v, [](auto c, auto m, int x) { return dpp_i<decltype(c)::value, decltype(m)::value>(0, x); });
 }
-__device__ __forceinline__ double wave_prefix_d(double v)
+static __device__ __forceinline__ double wave_prefix_d(double v)
 {
     return wave_prefix(v, [](auto c, auto m, double x) { return dpp_d<decltype(c)::value, decltype(m)::value>(0.0, x); });
 }
 
-__device__ __forceinline__ double lane_value(double v, int lane)
+static __device__ __forceinline__ double lane_value(double v, int lane)
 {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
                             __builtin_amdgcn_readlane(__double2loint(v), lane));
@@ -199,12 +226,12 @@ struct View {
 
 // The weight after level j's: levels before `top` have no columns and keep w_top (their own weight
 // may lie beyond fp64 when the thread holds levels above the row's highest).
-__device__ __forceinline__ double next_weight(const View& vw, double w, int j) { return j < vw.top ? w : w * vw.r; }
+static __device__ __forceinline__ double next_weight(const View& vw, double w, int j) { return j < vw.top ? w : w * vw.r; }
 
 // Weights and mass of a thread's levels: cnt(j) columns on level j, z_top the value of level `top`,
 // e the binade's exponent field.
 template <int kOwn, int kUnroll, typename Cnt>
-__device__ __forceinline__ void own_mass(View& vw, int e, float z_top, double z1, double inv_tau, Cnt&& cnt)
+static __device__ __forceinline__ void own_mass(View& vw, int e, float z_top, double z1, double inv_tau, Cnt&& cnt)
 {
     vw.w_top = 0.0; vw.r = 0.0; vw.Ml = 0.0;
     if (vw.Cl > 0) {
@@ -221,8 +248,8 @@ __device__ __forceinline__ void own_mass(View& vw, int e, float z_top, double z1
 }
 
 // Exclusive scan of counts and masses in thread order = rank order; threads from `mid_at` on
-// also have (mid_C, mid_M) before them.  Returns the totals of the scanned levels.
-__device__ __forceinline__ void scan_view(View& vw, int carry_C, double carry_M, int mid_at, int mid_C, double mid_M,
+// also have the middle's totals before them, which one wave has left in LDS.  Returns the totals of the scanned levels.
+static __device__ __forceinline__ void scan_view(View& vw, int carry_C, double carry_M, int mid_at,
                                           int& Ct, double& Mt, Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
@@ -238,7 +265,7 @@ __device__ __forceinline__ void scan_view(View& vw, int carry_C, double carry_M,
     int Cb = carry_C;
     double Mb = carry_M;
     if (wave > 0) { Cb += __builtin_amdgcn_readlane(tC, wave - 1); Mb += lane_value(tM, wave - 1); }
-    if (tid >= mid_at) { Cb += mid_C; Mb += mid_M; }
+    if (tid >= mid_at) { Cb += sh.mid_C[63]; Mb += sh.mid_M[63]; }
     vw.Cx = Cb + Ci - vw.Cl;
     vw.Mx = Mb + (Mi - vw.Ml);
 }
@@ -247,7 +274,7 @@ __device__ __forceinline__ void scan_view(View& vw, int carry_C, double carry_M,
 struct Cut { int j, C; double M; };       // level j of the thread; count and mass down to it
 
 template <int kOwn, int kUnroll, typename Cnt>
-__device__ __forceinline__ Cut own_count_cut(const View& vw, int k, Cnt&& cnt)
+static __device__ __forceinline__ Cut own_count_cut(const View& vw, int k, Cnt&& cnt)
 {
     Cut cut{kOwn - 1, vw.Cx, vw.Mx};
     double w = vw.w_top;
@@ -269,12 +296,13 @@ __device__ __forceinline__ Cut own_count_cut(const View& vw, int k, Cnt&& cnt)
 // if rounding lets none reach it.  Every wave's first such thread is looked through by the wave, one level
 // per lane (count_at(rank) from LDS), and the result offered; the lowest wave's offer is taken.
 template <int kOwn, typename CountAt, typename KeyAt>
-__device__ __forceinline__ void offer_mass_cut(const View& vw, double T, CountAt&& count_at, KeyAt&& key_at, Shared& sh, int tid)
+static __device__ __forceinline__ void offer_mass_cut(const View& vw, double T, CountAt&& count_at, KeyAt&& key_at, Shared& sh, int tid)
 {
-    static_assert(kOwn <= 16, "one row of lanes");
+    static_assert(kOwn <= 64, "a lane per level");
     const int lane = tid & 63, wave = tid >> 6;
     const unsigned long long reach = __ballot(vw.Cl > 0 && vw.Mx + vw.Ml >= T);
-    if (reach == 0ull) {
+    // (a wave with clearly more than T above it cannot be the lowest)
+    if (reach == 0ull || lane_value(vw.Mx, 0) > T * (1.0 + 1e-9)) {
         if (lane == 0) sh.cut_key[wave] = -1;
         return;
     }
@@ -295,21 +323,21 @@ __device__ __forceinline__ void offer_mass_cut(const View& vw, double T, CountAt
     if (lane == at) { sh.cut_key[wave] = key_at(rank); sh.cut_C[wave] = C; sh.cut_M[wave] = M; }
 }
 // The first wave with an offer, or kRWaves.
-__device__ __forceinline__ int first_offer(const Shared& sh, int lane)
+static __device__ __forceinline__ int first_offer(const Shared& sh, int lane)
 {
-    const unsigned long long have = __ballot(lane < kRWaves && sh.cut_key[lane & 15] >= 0);
+    const unsigned long long have = __ballot(lane < kRWaves && sh.cut_key[lane & (kRWaves - 1)] >= 0);
     return have != 0ull ? (int)__builtin_ctzll(have) : kRWaves;
 }
 
 // A contestant of the race: score n w / E and a label that is lower for a higher level (ties go
 // to the higher level, as Cand's go to the lower label).
-__device__ __forceinline__ Cand contestant(float q, int key) { return Cand{q, 0xFFFF - key}; }
-__device__ __forceinline__ int key_of(const Cand& c) { return 0xFFFF - c.idx; }
+static __device__ __forceinline__ Cand contestant(float q, int key) { return Cand{q, 0xFFFF - key}; }
+static __device__ __forceinline__ int key_of(const Cand& c) { return 0xFFFF - c.idx; }
 
 // Score of the level with pattern p and n columns: n 2^{(z - z_1) c} / E, E = -ln u from Philox
 // stream 3 at index = the pattern.  fp32, as in the unrestricted sampler; decisions closer than
 // fp32 resolves are the near-ties the parity rule exempts.
-__device__ __forceinline__ float level_score(int p, int n, float z1f, float c, uint64_t seed, uint64_t grow)
+static __device__ __forceinline__ float level_score(int p, int n, float z1f, float c, uint64_t seed, uint64_t grow)
 {
     uint32_t w4[4];
     philox4x32_10((uint32_t)p >> 2, (uint32_t)grow, (uint32_t)(grow >> 32), 3u, (uint32_t)seed, (uint32_t)(seed >> 32), w4);
@@ -319,50 +347,53 @@ __device__ __forceinline__ float level_score(int p, int n, float z1f, float c, u
 }
 
 // The workgroup's best contestant.
-__device__ __forceinline__ Cand reduce_best(Cand b, Shared& sh, int tid)
+static __device__ __forceinline__ Cand reduce_best(Cand b, Shared& sh, int tid)
 {
     const int lane = tid & 63;
     b = wave_best(b);
     if (lane == 0) sh.best[tid >> 6] = b;
     __syncthreads();
-    static_assert(kRWaves == 16, "one lane of a sixteen-lane row per wave");
-    return row16_best(sh.best[lane & 15]);
+    static_assert(kRWaves <= 16, "one lane of a sixteen-lane row per wave");
+    return row16_best(sh.best[lane & (kRWaves - 1)]);
 }
 
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u16x2 halves(uint32_t w) { return __builtin_bit_cast(u16x2, w); }
-
-// How many of the vector's eight patterns are not `pat`.
-__device__ __forceinline__ int columns_unlike(const u32x4& x, uint32_t pat)
-{
-    const u16x2 p2 = halves(pat | pat << 16), one = {1, 1};
-    const u16x2 n = __builtin_elementwise_min(halves(x.x) ^ p2, one) + __builtin_elementwise_min(halves(x.y) ^ p2, one)
-                  + __builtin_elementwise_min(halves(x.z) ^ p2, one) + __builtin_elementwise_min(halves(x.w) ^ p2, one);
-    return (int)n.x + (int)n.y;
-}
+typedef int16_t s16x2 __attribute__((ext_vector_type(2)));
+static __device__ __forceinline__ u16x2 halves(uint32_t w) { return __builtin_bit_cast(u16x2, w); }
+static __device__ __forceinline__ s16x2 signed_halves(uint32_t w) { return __builtin_bit_cast(s16x2, w); }
 
 // Stores the rem-th column (0-based, in column order) that holds pattern `pat` within stream steps
 // [i0, i1): kBlock steps are requested at once; a (step, wave) holds 512 consecutive columns, so the
 // waves' counts per step, in that order, say where the column is, and the wave that holds it
-// finds the lane, which stores it.  0 if there are not that many.
-__device__ __forceinline__ void locate(const Row& row, int i0, int i1, uint32_t pat, int rem, int32_t* token,
+// finds the lane, which stores it.  0 if there are not that many.  Most (step, wave) hold no such column.
+static __device__ __forceinline__ void locate(const Row& row, int i0, int i1, uint32_t pat, int rem, int32_t* token,
                                        Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
+    const u16x2 p2 = halves(pat | pat << 16);
+#pragma unroll 1
     for (int ib = i0; ib < i1; ib += kBlock) {
         u32x4 x[kBlock];
-        row.request<kBlock>(x, ib, i1, tid);
-        // counts of up to 8 per lane and 512 per wave: three steps share a word of the prefix sums
-        static_assert(kBlock <= 6, "two words");
-        uint32_t own[2] = {0u, 0u}, inc[2];
+        row.template request_ahead<kBlock>(x, ib, tid);
+        uint32_t found[kBlock];                                   // my columns (bits 0..7) and how many my wave has up to me
 #pragma unroll
-        for (int u = 0; u < kBlock; ++u) own[u / 3] |= (uint32_t)(8 - columns_unlike(x[u], pat)) << (10 * (u % 3));
-        auto of = [](const uint32_t w[2], int u) -> int { return (int)(((u < 3 ? w[0] : w[1]) >> (10 * (u % 3))) & 0x3FFu); };
-#pragma unroll
-        for (int i = 0; i < 2; ++i) inc[i] = (uint32_t)wave_prefix_i((int)own[i]);
-        if (lane == 63) {
-#pragma unroll
-            for (int u = 0; u < kBlock; ++u) sh.tot[u * kRWaves + wave] = of(inc, u);
+        for (int u = 0; u < kBlock; ++u) {
+            const u16x2 d = __builtin_elementwise_min(
+                __builtin_elementwise_min(halves(x[u].x) ^ p2, halves(x[u].y) ^ p2),
+                __builtin_elementwise_min(halves(x[u].z) ^ p2, halves(x[u].w) ^ p2));
+            const int step = ib + u;
+            found[u] = 0u;
+            int total = 0;
+            if (__any(d.x == 0 || d.y == 0) && step < i1) {       // uniform
+                const int v = tid + step * kRThreads;
+                uint32_t m = 0u;
+                for_each_pattern(x[u], [&](uint32_t p, int j) { m |= (uint32_t)(p == pat) << j; });
+                if (step >= row.whole) m = v < row.nvec - 1 ? m : v == row.nvec - 1 ? m & (0xFFu >> (8 - row.last)) : 0u;
+                const int upto = wave_prefix_i(__popc(m));
+                found[u] = (uint32_t)upto << 8 | m;
+                total = __builtin_amdgcn_readlane(upto, 63);
+            }
+            if (lane == 0) sh.tot[u * kRWaves + wave] = total;
         }
         __syncthreads();
         // every wave finds the (step, wave) that holds the column: two consecutive totals per lane
@@ -379,14 +410,13 @@ __device__ __forceinline__ void locate(const Row& row, int i0, int i1, uint32_t 
             if (before + first <= rem) { before += first; ++at; }
             if (at % kRWaves == wave) {
                 const int step = at / kRWaves, want = rem - before;
-                u32x4 y = x[0];
+                uint32_t mine = found[0];
 #pragma unroll
-                for (int u = 1; u < kBlock; ++u) y = u == step ? x[u] : y;
-                const int upto_me = of(inc, step), mine = of(own, step);
-                if (want >= upto_me - mine && want < upto_me) {   // exactly one lane
-                    uint32_t m = 0;
-                    for_each_pattern(y, [&](uint32_t p, int j) { m |= (uint32_t)(p == pat) << j; });
-                    for (int skip = want - (upto_me - mine); skip > 0; --skip) m &= m - 1;
+                for (int u = 1; u < kBlock; ++u) mine = u == step ? found[u] : mine;
+                uint32_t m = mine & 0xFFu;
+                const int skip = want - ((int)(mine >> 8) - __popc(m));
+                if (skip >= 0 && skip < __popc(m)) {              // exactly one lane
+                    for (int i = 0; i < skip; ++i) m &= m - 1;
                     *token = (tid + (ib + step) * kRThreads) * 8 + (__ffs(m) - 1);
                 }
             }
@@ -398,13 +428,13 @@ __device__ __forceinline__ void locate(const Row& row, int i0, int i1, uint32_t 
     if (tid == 0) *token = 0;                                     // only with weights that are no numbers
 }
 
-// The row's other outputs, by one thread.
-__device__ __forceinline__ void store_row(const RestrictedArgs& a, int64_t r, int kept_C, bool drawn, int pattern,
-                                          double z1, double kept_M, double inv_tau)
+// The row's other outputs, by one thread; ln_M: the kept levels' mass relative to the weight of z_ref.
+static __device__ __forceinline__ void store_row(const RestrictedArgs& a, int64_t r, int kept_C, bool drawn, int pattern,
+                                          double z_ref, double ln_M, double inv_tau)
 {
     if (a.kept_out) a.kept_out[r] = kept_C;
     if (a.logp_out)
-        a.logp_out[r] = drawn ? (float)(((double)value_of_pattern(pattern) - z1) * inv_tau - log(kept_M))
+        a.logp_out[r] = drawn ? (float)(((double)value_of_pattern(pattern) - z_ref) * inv_tau - ln_M)
                               : __builtin_nanf("");
     if (!drawn) a.token_out[r] = 0;
 }
@@ -421,8 +451,11 @@ struct WideWindow {
     }
 };
 
+// A pattern's counter in its window: neighbouring threads' runs of kOwnW start in different banks.
+static __device__ __forceinline__ uint32_t wide_place(uint32_t p) { return (p & 0x3FFFu) ^ (p / kOwnW & 31u); }
+
 // `resident` is the window that the counters hold already (-1: none).
-__device__ __forceinline__ void wide_count(const Row& row, WideWindow win, int& resident, uint32_t* hist, int tid)
+static __device__ __forceinline__ void wide_count(const Row& row, WideWindow win, int& resident, uint32_t* hist, int tid)
 {
     __syncthreads();
     if (win.w == resident) return;                                // uniform
@@ -431,24 +464,24 @@ __device__ __forceinline__ void wide_count(const Row& row, WideWindow win, int& 
     __syncthreads();
     const uint32_t quad = win.quadrant(), trash = (uint32_t)(kWideBins + (tid & 63));
 #pragma unroll 1
-    for (int i0 = 0; i0 < row.steps; i0 += 4) {
-        u32x4 x[4];
-        row.request<4>(x, i0, row.steps, tid);
+    for (int i0 = 0; i0 < row.steps; i0 += kWide) {
+        u32x4 x[kWide];
+        row.template request<kWide>(x, i0, row.steps, tid);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            for_each_pattern(x[u], [&](uint32_t p, int) { atomicAdd(&hist[(p >> 14) == quad ? (p & 0x3FFFu) : trash], 1u); });
+        for (int u = 0; u < kWide; ++u)
+            for_each_pattern(x[u], [&](uint32_t p, int) { atomicAdd(&hist[(p >> 14) == quad ? wide_place(p) : trash], 1u); });
     }
     __syncthreads();
 }
 
-__device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a, int64_t r, double inv_tau, float c,
+static __device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a, int64_t r, double inv_tau, float c,
                                          uint64_t grow, uint32_t k23, uint32_t* hist, Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
     const bool k_on = a.top_k >= 1 && (int64_t)a.top_k < a.V, p_on = a.top_p < 1.0f;
     auto count_of = [&](WideWindow win, int rank) -> uint32_t {
         const int p = win.pattern(rank);
-        return ((p >> 7) & 0xFF) == 0xFF ? 0u : hist[p & 0x3FFF];
+        return ((p >> 7) & 0xFF) == 0xFF ? 0u : hist[wide_place((uint32_t)p)];
     };
     int resident = -1;
     double z1 = 0.0;
@@ -457,7 +490,7 @@ __device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a
     auto scan = [&](WideWindow win, View& vw, int& C, double& M) {
         wide_count(row, win, resident, hist, tid);
         vw.Cl = 0; vw.top = kOwnW;
-#pragma unroll 1
+#pragma unroll 8
         for (int j = kOwnW - 1; j >= 0; --j) {
             const uint32_t n = count_of(win, kOwnW * tid + j);
             vw.Cl += (int)n;
@@ -468,14 +501,14 @@ __device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a
             const float t = wave_max(vw.Cl > 0 ? (float)key_of_pattern(p_top) : -1.0f);
             if (lane == 0) sh.wave_top[wave] = t;
             __syncthreads();
-            const float best = row16_max(sh.wave_top[lane & 15]);
+            const float best = row16_max(sh.wave_top[lane & (kRWaves - 1)]);
             if (best >= 0.0f) { have_z1 = true; z1 = (double)value_of_pattern(pattern_of_key((int)best)); }
         }
-        own_mass<kOwnW, 1>(vw, (p_top >> 7) & 0xFF, value_of_pattern(p_top), z1, inv_tau,
+        own_mass<kOwnW, 8>(vw, (p_top >> 7) & 0xFF, value_of_pattern(p_top), z1, inv_tau,
                         [&](int j) { return count_of(win, kOwnW * tid + j); });
         int Ct;
         double Mt;
-        scan_view(vw, C, M, kRThreads, 0, 0.0, Ct, Mt, sh, tid);
+        scan_view(vw, C, M, kRThreads, Ct, Mt, sh, tid);
         C += Ct; M += Mt;
     };
     int C_all = 0;
@@ -544,7 +577,7 @@ __device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a
         if (sh.C_above[win.w + 1] == sh.C_above[win.w] || key_of_pattern(win.pattern(0)) < cut_key) continue;   // uniform
         wide_count(row, win, resident, hist, tid);
         Cand mine = contestant(-1.0f, 0);
-#pragma unroll 1
+#pragma unroll 4
         for (int rank = tid; rank < kWideBins; rank += kRThreads) {
             const uint32_t n = count_of(win, rank);
             const int p = win.pattern(rank);
@@ -554,33 +587,27 @@ __device__ __forceinline__ void wide_row(const Row& row, const RestrictedArgs& a
         mine = reduce_best(mine, sh, tid);
         const Cand was = best;
         best = better(was, mine);
-        if (best.idx != was.idx || best.q != was.q) best_n = (int)hist[pattern_of_key(key_of(best)) & 0x3FFF];
+        if (best.idx != was.idx || best.q != was.q) best_n = (int)hist[wide_place((uint32_t)pattern_of_key(key_of(best)))];
     }
     const bool drawn = best.q >= 0.0f;
     const int pattern = pattern_of_key(key_of(best));
-    if (tid == 0) store_row(a, r, kept_C, drawn, pattern, z1, kept_M, inv_tau);
+    if (tid == 0) store_row(a, r, kept_C, drawn, pattern, z1, log(kept_M), inv_tau);
     if (drawn) locate(row, 0, row.steps, (uint32_t)pattern, (int)(((2ull * k23 + 1ull) * (uint64_t)best_n) >> 24), a.token_out + r, sh, tid);
 }
 
 // ---------------------------------------------------------------------------
 // The near window.
 // ---------------------------------------------------------------------------
-// Counter places (13 bits, or two of them in a word's halves) to words of LDS: groups of four words
-// change places within sixteen by the place's bits 6 and 7, so that the threads of a wave, each
-// reading its own sixteen consecutive places as four 16-byte pieces, meet no bank conflict (4.7 us
-// without, the whole read 2 us with).
-__device__ __forceinline__ uint32_t swizzled(uint32_t place) { return place ^ ((place >> 4) & 0x000C000Cu); }
-
 struct Near {
     int base;             // magnitude bits of the window's lowest level
     int per_quarter;      // stream steps per quarter
+    float first_top;      // the largest finite value among the first vectors (-inf: none)
     const uint32_t* hist;
-    // rank 0 .. kHalf - 1: non-negative levels from the top, then the negative ones; the counters
-    // of z and -z are neighbours (place 2 (magnitude - base) + sign, swizzled)
-    __device__ __forceinline__ int slot(int rank) const
-    {
-        return (int)swizzled((uint32_t)(rank < kHalf ? 2 * (kHalf - 1 - rank) : 2 * (rank - kHalf) + 1));
-    }
+    // rank 0 .. kHalf - 1: non-negative levels from the top, then the negative ones.  A word holds two
+    // quarters' counters of a level; each sign's words lie in rising magnitude, the highest kTrash of them
+    // being the spare ones.
+    __device__ __forceinline__ int slot(int rank) const { return rank < kHalf ? kHalf - 1 - rank : rank; }
+    __device__ __forceinline__ int slot_of_pattern(int p) const { return (p & 0x7FFF) - base + (p >> 15) * kHalf; }
     __device__ __forceinline__ int pattern(int rank) const
     {
         return rank < kHalf ? base + kHalf - 1 - rank : 0x8000 + base + rank - kHalf;
@@ -594,19 +621,24 @@ struct Near {
     __device__ __forceinline__ void own_counts(int rank0, int cnt[kOwnN]) const
     {
         const bool neg = __builtin_amdgcn_readfirstlane(rank0) >= kHalf;         // a wave's levels have one sign
-        const int s0 = neg ? 2 * (rank0 - kHalf) : 2 * (kHalf - kOwnN - rank0);
-        uint32_t q01[kOwnN], q23[kOwnN];                          // my sign's words, in rising magnitude
+        const uint32_t* h = hist + (neg ? rank0 : kHalf - kOwnN - rank0);
+        uint32_t q01[kOwnN], q23[kOwnN];                          // in rising magnitude
 #pragma unroll
-        for (int i = 0; i < kOwnN / 2; ++i) {
-            const uint32_t at = swizzled((uint32_t)(s0 + 4 * i));
-            const uint4 a = *reinterpret_cast<const uint4*>(hist + at);
-            const uint4 b = *reinterpret_cast<const uint4*>(hist + kArray + at);
-            q01[2 * i] = neg ? a.y : a.x; q01[2 * i + 1] = neg ? a.w : a.z;
-            q23[2 * i] = neg ? b.y : b.x; q23[2 * i + 1] = neg ? b.w : b.z;
+        for (int i = 0; i < kOwnN; i += 4) {
+            const uint4 a = *reinterpret_cast<const uint4*>(h + i);
+            const uint4 b = *reinterpret_cast<const uint4*>(h + kArray + i);
+            q01[i] = a.x; q01[i + 1] = a.y; q01[i + 2] = a.z; q01[i + 3] = a.w;
+            q23[i] = b.x; q23[i + 1] = b.y; q23[i + 2] = b.z; q23[i + 3] = b.w;
         }
 #pragma unroll
-        for (int j = 0; j < kOwnN; ++j)
-            cnt[j] = neg ? total(q01[j], q23[j]) : total(q01[kOwnN - 1 - j], q23[kOwnN - 1 - j]);
+        for (int j = 0; j < kOwnN; ++j) q01[j] = (uint32_t)total(q01[j], q23[j]);
+#pragma unroll
+        for (int j = 0; j < kOwnN; ++j) cnt[j] = (int)(neg ? q01[j] : q01[kOwnN - 1 - j]);
+        static_assert(kTrash % kOwnN == 0, "a thread's words are levels or spare ones");
+        if (rank0 < kTrash || rank0 >= 2 * kHalf - kTrash) {
+#pragma unroll
+            for (int j = 0; j < kOwnN; ++j) cnt[j] = 0;
+        }
     }
     // first / last rank whose key is at most / at least `key`
     __device__ __forceinline__ int first_at_most(int key) const
@@ -622,82 +654,158 @@ struct Near {
         if (key >= 0x8000 + base) return 0x8000 + base + kHalf - 1 - key;
         if (key > 0x7FFF - base) return kHalf - 1;
         const int r = kHalf + (0x7FFF - base) - key;
-        return r < 2 * kHalf ? r : 2 * kHalf - 1;
+        return r < kHalf + kLevels ? r : kHalf + kLevels - 1;
     }
 };
 
-// A vector that holds patterns outside the window (rare): all lanes of the wave take part.
-__device__ __forceinline__ void note_outside(const u32x4& x, int v, int quarter, int base, Shared& sh, int lane)
+// What of a lane's columns lies outside the window, by kind: two 16-bit counts to a word (a lane has at most
+// 8 x 2032 columns of the widest row).
+struct Tally {
+    uint32_t zeros;       // +0, -0, of the current quarter
+    uint32_t far;         // columns below the window, above it
+    uint32_t odd;         // no numbers
+    u16x2 lowest, highest, top;     // (magnitude - window's end) of the columns below the window, wrapped down by one, and as it is; of those above
+};
+
+// Patterns of a word at or above c (as unsigned numbers), 0 or 1 in each half.
+static __device__ __forceinline__ u16x2 at_least(u16x2 w, uint32_t c)
 {
-    // what is no number (masked columns, what lies past the row) is only counted
-    int n_odd = 0;
-    bool more = false;
-    for_each_pattern(x, [&](uint32_t p, int) {
-        const uint32_t mag = p & 0x7FFFu;
-        const bool odd = mag >= 0x7F80u;
-        n_odd += odd;
-        more |= !odd && mag - (uint32_t)base >= (uint32_t)kHalf;
+    const uint16_t c1 = (uint16_t)(c - 1u);
+    const u16x2 less = {c1, c1}, one = {1, 1};
+    return __builtin_elementwise_min(__builtin_elementwise_sub_sat(w, less), one);
+}
+
+// A vector step that may hold patterns outside the window (rare): all lanes of the wave take part, a lane with its
+// vector, the columns col0, col0 + 1, ..., if `mine`.
+static __device__ __forceinline__ void note_outside(const u32x4& x, int col0, bool mine, int quarter, int base, Tally& t, Shared& sh)
+{
+    const u16x2 base_v = {(uint16_t)base, (uint16_t)base};
+    auto level = [&](uint32_t w) -> u16x2 { return halves(__builtin_bit_cast(uint32_t, halves(w) - base_v) & 0x7FFF7FFFu); };
+    const u16x2 worst = __builtin_elementwise_max(__builtin_elementwise_max(level(x.x), level(x.y)),
+                                                  __builtin_elementwise_max(level(x.z), level(x.w)));
+    const bool out = mine && (worst.x >= kLevels || worst.y >= kLevels);
+    if (!__any(out)) return;
+    auto both = [](u16x2 n) -> int { return (int)n.x + (int)n.y; };
+    auto each = [&](auto&& f) { f(x.x); f(x.y); f(x.z); f(x.w); };
+    // what is no number (masked columns) is only counted
+    u16x2 outside = {0, 0}, odd = {0, 0}, near = {0, 0};          // near: as a count of what is not
+    each([&](uint32_t word) {
+        outside += at_least(level(word), (uint32_t)kLevels);
+        odd += at_least(halves(word & 0x7FFF7FFFu), 0x7F80u);
     });
-    n_odd = wave_prefix_i(n_odd);
-    if (lane == 63 && n_odd != 0) atomicAdd(&sh.n_not_finite, n_odd);
-    if (!__any(more)) return;
-    // tallies of up to 8 per lane and 512 per wave, three to a word: +0, -0, small; below and above the window
-    uint32_t n0 = 0u, n1 = 0u;
-    int lo = 0x7FFF, hi = 0, top = 0;                             // of my columns below the window and above it
-    u32x4 rest = x;
-    auto next = [&]() -> uint32_t {                               // the first pattern becomes the last
-        const uint32_t p = rest.x & 0xFFFFu;
-        rest.x = rest.x >> 16 | rest.y << 16; rest.y = rest.y >> 16 | rest.z << 16;
-        rest.z = rest.z >> 16 | rest.w << 16; rest.w = rest.w >> 16 | p << 16;
-        return p;
-    };
-#pragma unroll 1
-    for (int j = 0; j < 8; ++j) {                                 // one pattern at a time: this code is rarely run, and kept small
-        const uint32_t p = next(), mag = p & 0x7FFFu, sign = p >> 15;
-        const bool large = mag >= (uint32_t)(base + kHalf) && mag < 0x7F80u;
-        n0 += mag >= (uint32_t)base ? 0u : mag == 0u ? 1u << (10u * sign) : 1u << 20;
-        n1 += large ? 1u << (10u * sign) : 0u;
-        const int m = large ? (int)mag : 0;
-        top = sign == 0u && m > top ? m : top;
-        hi = sign != 0u && m > hi ? m : hi;
-        lo = sign != 0u && m != 0 && m < lo ? m : lo;
-    }
-    auto tally = [&](uint32_t n, int* a, int* b) {
-        n = (uint32_t)wave_prefix_i((int)n);
-        if (lane == 63) {
-            atomicAdd(a, (int)(n & 0x3FFu));
-            atomicAdd(b, (int)(n >> 10 & 0x3FFu));
+    const int n_odd = both(odd);
+    if (out) t.odd += (uint32_t)n_odd;
+    if (!__any(out && both(outside) > n_odd)) return;
+    each([&](uint32_t word) { near += at_least(halves(word & 0x7FFF7FFFu), (uint32_t)base); });
+    const int n_near = out && base > 0 ? 8 - both(near) : 0;      // base 0: zeros are levels
+    if (__any(out && both(outside) > n_odd + n_near)) {
+        const uint32_t end = (uint32_t)(base + kLevels);
+        const uint16_t end1 = (uint16_t)(end - 1u), neg1 = (uint16_t)(0x8000u + end - 1u);
+        const u16x2 e1 = {end1, end1}, n1 = {neg1, neg1}, one = {1, 1};
+        u16x2 above = {0, 0}, below = {0, 0};
+        if (out) {
+            each([&](uint32_t word) {
+                const u16x2 w = halves(word);
+                const u16x2 is_above = at_least(w, end) - at_least(w, 0x7F80u), is_below = at_least(w, 0x8000u + end) - at_least(w, 0xFF80u);
+                above += is_above;
+                below += is_below;
+                t.top = __builtin_elementwise_max(t.top, __builtin_elementwise_sub_sat(w, e1) * is_above);
+                const u16x2 far = __builtin_elementwise_sub_sat(w, n1) * is_below;
+                t.highest = __builtin_elementwise_max(t.highest, far);
+                t.lowest = __builtin_elementwise_min(t.lowest, far - one);
+            });
+            t.far += (uint32_t)(both(below) | both(above) << 16);
+            if (both(above) != 0) sh.fails = 1;
         }
-    };
-    if (__any(n0 != 0u)) tally(n0, &sh.zeros[0][quarter], &sh.zeros[1][quarter]);
-    if (__any(n1 != 0u)) {
-        tally(n1, &sh.n_above, &sh.n_below);
-        if (lo < sh.below_lo) atomicMin(&sh.below_lo, lo);        // of a mask of one value the first vectors only
-        if (hi > sh.below_hi) atomicMax(&sh.below_hi, hi);
-        if (top > sh.above_hi) { atomicMax(&sh.above_hi, top); sh.fails = 1; }
     }
-    if (!__any(n0 >> 20 != 0u)) return;
+    if (__any(n_near != 0) && n_near != 0) {
+        const u16x2 one = {1, 1};
+        u16x2 zero_p = {0, 0}, zero_n = {0, 0};
+        each([&](uint32_t word) {
+            zero_p += one - at_least(halves(word), 1u);
+            zero_n += one - at_least(halves(word ^ 0x80008000u), 1u);
+        });
+        t.zeros += (uint32_t)(both(zero_p) | both(zero_n) << 16);
+        if (n_near != both(zero_p) + both(zero_n)) {              // small values are listed one by one
+            u32x4 rest = x;
 #pragma unroll 1
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t p = next(), mag = p & 0x7FFFu;
-        if (mag != 0u && mag < (uint32_t)base) {
-            const int at = atomicAdd(&sh.list_n, 1);
-            if (at < kMidList) { sh.list_key[at] = key_of_pattern((int)p); sh.list_col[at] = v * 8 + j; }
-            else sh.fails = 1;
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t p = rest.x & 0xFFFFu, mag = p & 0x7FFFu;
+                if (mag != 0u && mag < (uint32_t)base) {
+                    const int at = atomicAdd(&sh.list_n, 1);
+                    if (at < kMidList) { sh.list_key[at] = key_of_pattern((int)p); sh.list_col[at] = col0 + j; }
+                    else sh.fails = 1;
+                }
+                rest.x = rest.x >> 16 | rest.y << 16; rest.y = rest.y >> 16 | rest.z << 16;
+                rest.z = rest.z >> 16 | rest.w << 16; rest.w >>= 16;
+            }
         }
     }
 }
 
-// Counts the row.  Returns the window, whose top binade is `top_exp` if that is not negative.
-__device__ __forceinline__ Near near_count(const Row& row, int top_exp, uint32_t* hist, Shared& sh, int tid)
+// The zeros of a quarter, and at the end the rest, to the workgroup.
+static __device__ __forceinline__ void hand_zeros(Tally& t, int quarter, Shared& sh, int lane)
+{
+    if (!__any(t.zeros != 0u)) return;
+    const uint32_t p = (uint32_t)wave_prefix_i((int)(t.zeros & 0xFFFFu)), n = (uint32_t)wave_prefix_i((int)(t.zeros >> 16));
+    if (lane == 63) { atomicAdd(&sh.zeros[0][quarter], (int)p); atomicAdd(&sh.zeros[1][quarter], (int)n); }
+    t.zeros = 0u;
+}
+static __device__ __forceinline__ void hand_rest(const Tally& t, int base, Shared& sh, int lane)
+{
+    if (!__any((t.far | t.odd) != 0u)) return;
+    const int below = wave_prefix_i((int)(t.far & 0xFFFFu)), above = wave_prefix_i((int)(t.far >> 16)), odd = wave_prefix_i((int)t.odd);
+    if (lane == 63) { atomicAdd(&sh.n_below, below); atomicAdd(&sh.n_above, above); atomicAdd(&sh.n_not_finite, odd); }
+    const int end1 = base + kLevels - 1;
+    auto most = [](u16x2 a) -> float { return (float)(a.x > a.y ? a.x : a.y); };
+    const float top = wave_max(most(t.top)), hi = wave_max(most(t.highest));
+    const float lo = -wave_max(-(float)(t.lowest.x < t.lowest.y ? t.lowest.x : t.lowest.y));
+    if (lane == 0) {
+        if (top > 0.0f) atomicMax(&sh.above_hi, end1 + (int)top);
+        if (hi > 0.0f) { atomicMax(&sh.below_hi, end1 + (int)hi); atomicMin(&sh.below_lo, end1 + 1 + (int)lo); }
+    }
+}
+
+// The largest finite value among a wave's first vectors, -inf if there is none.  As signed 16-bit integers
+// the patterns of non-negative values are in value order above all others; a wave without any, or with an
+// infinity or a NaN on top, looks through its values one by one.
+static __device__ __forceinline__ float wave_top_value(const Row& row, const u32x4 x[kSet], const u32x4 y[kSet], int tid)
+{
+    s16x2 m = {-32768, -32768};
+    auto each = [&](auto&& f) {
+#pragma unroll
+        for (int u = 0; u < 2 * kSet; ++u) f(u < row.whole ? u < kSet ? x[u % kSet] : y[u % kSet]
+                                                           : row.counted(u < kSet ? x[u % kSet] : y[u % kSet], tid + u * kRThreads));
+    };
+    each([&](const u32x4& v) {
+        m = __builtin_elementwise_max(m, __builtin_elementwise_max(signed_halves(v.x), signed_halves(v.y)));
+        m = __builtin_elementwise_max(m, __builtin_elementwise_max(signed_halves(v.z), signed_halves(v.w)));
+    });
+    const float best = wave_max((float)(m.x > m.y ? m.x : m.y));
+    if (__builtin_expect(best >= 0.0f && best < (float)0x7F80, 1)) return value_of_pattern((int)best);     // uniform
+    float f = -INFINITY;
+    each([&](const u32x4& v) {
+        for_each_pattern(v, [&](uint32_t p, int) {
+            const float z = value_of_pattern((int)p);
+            f = z < INFINITY ? fmaxf(f, z) : f;
+        });
+    });
+    return wave_max(f);
+}
+
+// Counts the row.  Returns the window, whose top binade is `top_exp` if that is not negative.  Two sets of
+// requests are in flight: a set is asked for as soon as the one before it in its registers is counted.
+static __device__ __forceinline__ Near near_count(const Row& row, int top_exp, uint32_t* hist, Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
     Near w;
     w.hist = hist;
     w.per_quarter = (row.steps + kQuarters - 1) / kQuarters;
-    constexpr int kAhead = 4;
-    u32x4 x[kAhead];
-    row.request<kAhead>(x, 0, row.steps, tid);
+    u32x4 x[kSet], y[kSet];
+    row.template request_ahead<kSet>(x, 0, tid);
+    row.template request_ahead<kSet>(y, kSet, tid);
+    uint32_t tail = 0u;                                           // the columns behind the last complete vector
+    if (row.last < 8 && tid < row.last) tail = reinterpret_cast<const uint16_t*>(row.p + row.complete)[tid];
     for (int i = tid; i < 2 * kArray / 4; i += kRThreads) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
     if (tid < 2 * kQuarters) (&sh.zeros[0][0])[tid] = 0;
     if (tid == 0) {
@@ -705,72 +813,95 @@ __device__ __forceinline__ Near near_count(const Row& row, int top_exp, uint32_t
         sh.below_lo = 0x7FFF; sh.below_hi = 0; sh.above_hi = 0; sh.fails = 0;
     }
     {
-        // the window's top: one binade above the magnitude of the largest finite logit among the first
-        // vectors (if that is negative, up to 2^20: what lies far down is a mask)
-        float m = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u)
-            for_each_pattern(x[u], [&](uint32_t p, int) {
-                const float z = value_of_pattern((int)p);
-                m = z < INFINITY ? fmaxf(m, z) : m;
-            });
-        m = wave_max(m);
+        const float m = wave_top_value(row, x, y, tid);
         if (lane == 0) sh.sample_max[wave] = m;
     }
-    __syncthreads();
+    // orders LDS only: __syncthreads() would wait for the loads in flight as well
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    w.first_top = row16_max(sh.sample_max[lane & (kRWaves - 1)]);
+    // the window's top: one binade above the magnitude of the largest finite logit among the first
+    // vectors (if that is negative, up to 2^20: what lies far down is a mask)
     if (top_exp < 0) {
-        const float top = row16_max(sh.sample_max[lane & 15]);
-        top_exp = top > -1048576.0f ? (int)(__float_as_uint(fabsf(top)) >> 23) + 1 : 0;
+        top_exp = w.first_top > -1048576.0f ? (int)(__float_as_uint(fabsf(w.first_top)) >> 23) + 1 : 0;
         top_exp = top_exp < kTopExp ? kTopExp : top_exp;
     }
     top_exp = top_exp > 254 ? 254 : top_exp < kBinades - 1 ? kBinades - 1 : top_exp;
-    w.base = __builtin_amdgcn_readfirstlane((top_exp - (kBinades - 1)) << 7);
+    w.base = __builtin_amdgcn_readfirstlane(top_exp > kBinades - 1 ? ((top_exp - (kBinades - 1)) << 7) + kTrash : 0);
 
-    // Two patterns at a time: rotated left by one, (magnitude, sign) less the window's base is the
-    // slot, and anything outside the window (wrapped around or past the end) is a large number
-    // that a minimum sends to the lane's own spare word.
-    const uint16_t base2 = (uint16_t)(2 * w.base), spare = (uint16_t)(2 * kHalf + lane);
-    const u16x2 base_v = {base2, base2}, spare_v = {spare, spare};
-    for (int i0 = 0; i0 < row.steps; i0 += kAhead) {
-        if (i0 > 0) row.request<kAhead>(x, i0, row.steps, tid);
-        uint32_t outside = 0u;
+    // Two patterns at a time: less the window's base, and without the sign, the magnitude is the level, and
+    // anything outside the window (wrapped around or past the end) is a large number that a minimum
+    // sends to the lane's own spare word; the sign goes next to the twelve bits of the level.  Five packed
+    // or plain instructions per column with the two addresses.
+    static_assert(kHalf == 4096 && kArray * 4 == 0x8000, "places of 13 bits, the array next to them");
+    const uint16_t base1 = (uint16_t)w.base, spare = (uint16_t)(kLevels + lane);
+    const u16x2 base_v = {base1, base1}, spare_v = {spare, spare};
+    u16x2 worst = {0, 0};
+    auto add8 = [&](const u32x4& x, int step) {
+        const int quarter = step / w.per_quarter;
+        const uint32_t array = (uint32_t)(quarter >> 1) << 15, inc = 1u << ((quarter & 1) * 16);
+        char* h = reinterpret_cast<char*>(hist);
+        auto add2 = [&](uint32_t word) {
+            const uint32_t s = __builtin_bit_cast(uint32_t, halves(word) - base_v);
+            const u16x2 level = halves(s & 0x7FFF7FFFu);
+            worst = __builtin_elementwise_max(worst, level);
+            const uint32_t at = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(level, spare_v)) | (s >> 3 & 0x10001000u);
+            atomicAdd(reinterpret_cast<uint32_t*>(h + ((at << 2 & 0x7FFCu) | array)), inc);
+            atomicAdd(reinterpret_cast<uint32_t*>(h + ((at >> 14 & 0x7FFCu) | array)), inc);
+        };
+        add2(x.x); add2(x.y); add2(x.z); add2(x.w);
+    };
+    Tally t{0u, 0u, 0u, {0xFFFF, 0xFFFF}, {0, 0}, {0, 0}};
+    int noted = 0;                                                // the quarter of t.zeros
+    auto note = [&](const u32x4& y, int step, int col0, bool mine) {
+        const int quarter = step / w.per_quarter;
+        if (quarter != noted) { hand_zeros(t, noted, sh, lane); noted = quarter; }
+        note_outside(y, col0, mine, quarter, w.base, t, sh);
+    };
+    auto count = [&](const u32x4 (&x)[kSet], int i0) -> bool {
+        worst = u16x2{0, 0};
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            if (i0 + u >= row.steps) break;                       // uniform
-            const int quarter = (i0 + u) / w.per_quarter;
-            char* h = reinterpret_cast<char*>(hist + (quarter >> 1) * kArray);
-            const uint32_t inc = 1u << ((quarter & 1) * 16);
-            u16x2 worst = {0, 0};
-            auto add2 = [&](uint32_t word) {
-                const u16x2 p = halves(word);
-                const u16x2 s = ((p << (uint16_t)1) | (p >> (uint16_t)15)) - base_v;
-                worst = __builtin_elementwise_max(worst, s);
-                const uint32_t at = swizzled(__builtin_bit_cast(uint32_t, __builtin_elementwise_min(s, spare_v))) << 2;
-                atomicAdd(reinterpret_cast<uint32_t*>(h + (at & 0xFFFFu)), inc);
-                atomicAdd(reinterpret_cast<uint32_t*>(h + (at >> 16)), inc);
-            };
-            add2(x[u].x); add2(x[u].y); add2(x[u].z); add2(x[u].w);
-            outside |= (uint32_t)(__any(worst.x >= 2 * kHalf || worst.y >= 2 * kHalf) != 0) << u;
+        for (int u = 0; u < kSet; ++u) {
+            if (tid + (i0 + u) * kRThreads < row.complete) add8(x[u], i0 + u);
         }
-        while (__builtin_expect(outside != 0u, 0)) {              // uniform: steps with values outside the window
-            const int u = __builtin_ctz(outside);
-            outside &= outside - 1u;
+        if (__builtin_expect(!__any(worst.x >= kLevels || worst.y >= kLevels), 1)) return false;
+#pragma unroll 1
+        for (int u = 0; u < kSet; ++u) {
             u32x4 y = x[0];
 #pragma unroll
-            for (int i = 1; i < kAhead; ++i) y = i == u ? x[i] : y;
-            note_outside(y, tid + (i0 + u) * kRThreads, (i0 + u) / w.per_quarter, w.base, sh, lane);
-            if (__builtin_amdgcn_readfirstlane(*(volatile int*)&sh.fails) != 0) { outside = 0u; i0 = row.steps; }     // counted enough
+            for (int i = 1; i < kSet; ++i) {
+                const uint32_t is = i == u ? 0xFFFFFFFFu : 0u;
+                y = (y & ~is) | (x[i] & is);
+            }
+            const int v = tid + (i0 + u) * kRThreads;
+            note(y, i0 + u, v * 8, v < row.complete);
         }
+        return __builtin_amdgcn_readfirstlane(*(volatile int*)&sh.fails) != 0;             // counted enough
+    };
+    for (int i0 = 0;; i0 += 2 * kSet) {
+        if (count(x, i0) || i0 + kSet >= row.steps) break;
+        row.template request_ahead<kSet>(x, i0 + 2 * kSet, tid);
+        if (count(y, i0 + kSet) || i0 + 2 * kSet >= row.steps) break;
+        row.template request_ahead<kSet>(y, i0 + 3 * kSet, tid);
     }
+    if (row.last < 8 && wave == 0) {                              // the row's last columns, one per lane
+        const bool mine = lane < row.last;
+        const uint32_t level = (tail & 0x7FFFu) - (uint32_t)w.base, inside = (uint32_t)w.base * 0x10001u;
+        const int quarter = (row.steps - 1) / w.per_quarter;
+        if (mine && level < (uint32_t)kLevels)
+            atomicAdd(&hist[(quarter >> 1) * kArray + level + (tail >> 15) * kHalf], 1u << ((quarter & 1) * 16));
+        if (__any(mine && level >= (uint32_t)kLevels))
+            note(u32x4{tail | (inside & 0xFFFF0000u), inside, inside, inside}, row.steps - 1, row.complete * 8 + lane, mine);
+    }
+    hand_zeros(t, noted, sh, lane);
+    hand_rest(t, w.base, sh, lane);
     __syncthreads();
     return w;
 }
-static_assert(kArray * 4 <= 0x10000, "byte offsets of the counters in 16 bits");
 
 // Counts the row, into a second window if the first had columns above it or too many small ones:
 // four binades above the largest it has seen (its waves stop at the first), or three above the
 // largest among the first vectors.
-__device__ __forceinline__ Near near_window(const Row& row, uint32_t* hist, Shared& sh, int tid)
+static __device__ __forceinline__ Near near_window(const Row& row, uint32_t* hist, Shared& sh, int tid)
 {
     Near w;
     int top_exp = -1;
@@ -780,15 +911,14 @@ __device__ __forceinline__ Near near_window(const Row& row, uint32_t* hist, Shar
         Row again = row;
         // Opaque copies: otherwise the compiler holds what it can share between the two counts in
         // registers, and the stream spills (512 rows 45 -> 51 us).
-        asm volatile("" : "+v"(me), "+s"(again.nvec), "+s"(again.last), "+s"(again.steps), "+s"(again.whole));
+        asm volatile("" : "+v"(me), "+s"(again.nvec), "+s"(again.last), "+s"(again.steps), "+s"(again.whole), "+s"(again.complete));
         w = near_count(again, top_exp, hist, sh, me);
         if (__builtin_expect(sh.fails == 0 || top_exp >= 0, 1)) return w;                 // uniform
         const int now = (w.base >> 7) + kBinades - 1;
         if (sh.n_above != 0) {
             top_exp = (sh.above_hi >> 7) + 4;
         } else {
-            const float top = row16_max(sh.sample_max[tid & 15]);
-            top_exp = (int)((__float_as_uint(top) >> 23) & 0xFFu) + 3;
+            top_exp = (int)((__float_as_uint(w.first_top) >> 23) & 0xFFu) + 3;
             if (top_exp > now - 8) return w;                      // hardly lower: the small values lie below it as well
         }
         top_exp = __builtin_amdgcn_readfirstlane(top_exp);
@@ -798,7 +928,7 @@ __device__ __forceinline__ Near near_window(const Row& row, uint32_t* hist, Shar
 
 // The middle items of a row, one per lane of one wave, in rank order: the listed small
 // positive values, +0, -0, the small negative ones.
-__device__ __forceinline__ void middle_items(Shared& sh, int lane)
+static __device__ __forceinline__ void middle_items(Shared& sh, int lane)
 {
     const int n = sh.list_n;
     const int key = lane < n ? sh.list_key[lane] : 0, col = lane < n ? sh.list_col[lane] : 0;
@@ -819,14 +949,8 @@ __device__ __forceinline__ void middle_items(Shared& sh, int lane)
     }
 }
 
-// Two workgroups per compute unit: eight waves per SIMD, 64 vector registers each.  151,936 bf16
-// columns, top-p 0.9, all patterns in 128 KiB before / now: 8 rows 39.8 / 22.9 us, 512 rows 101 /
-// 44 us (3.5 TB/s), 1024 rows 188 / 84 us; 512 x 32,000: 59 / 27 us.
-__global__ __launch_bounds__(kRThreads, 8)
-void sample_restricted_kernel(RestrictedArgs a)
+static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hist, Shared& sh)
 {
-    __shared__ __align__(16) uint32_t hist[2 * kArray];
-    __shared__ Shared sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t r = blockIdx.x;
     Row row;
@@ -834,7 +958,8 @@ void sample_restricted_kernel(RestrictedArgs a)
     row.nvec = (int)((a.V + 7) >> 3);
     row.last = (int)(a.V - ((int64_t)(row.nvec - 1) << 3));
     row.steps = (row.nvec + kRThreads - 1) / kRThreads;
-    row.whole = (int)(a.V >> 3) / kRThreads;
+    row.complete = (int)(a.V >> 3);
+    row.whole = row.complete / kRThreads;
     const float tau = a.tau_rows ? a.tau_rows[r] : a.tau_scalar;
     const double inv_tau = 1.0 / (double)tau;
     const float c = kLog2eF / tau;
@@ -849,18 +974,6 @@ void sample_restricted_kernel(RestrictedArgs a)
     }
     const Near win = near_window(row, hist, sh, tid);
 
-    // my levels
-    View vw;
-    int cnt[kOwnN];
-    const int rank0 = kOwnN * tid;
-    win.own_counts(rank0, cnt);
-    vw.Cl = 0; vw.top = kOwnN;
-#pragma unroll
-    for (int j = kOwnN - 1; j >= 0; --j) {
-        vw.Cl += cnt[j];
-        if (cnt[j] != 0) vw.top = j;
-    }
-    const int p_top = win.pattern(rank0 + (vw.Cl > 0 ? vw.top : 0));
     const int list_n = sh.list_n;
     int n_zero = 0;
 #pragma unroll
@@ -873,32 +986,49 @@ void sample_restricted_kernel(RestrictedArgs a)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
-    // the row's highest level
-    int top = vw.Cl > 0 ? key_of_pattern(p_top) : -1;
-    if (has_mid && wave == 0 && lane < n_mid && sh.mid_cnt[lane] != 0 && sh.mid_key[lane] > top) top = sh.mid_key[lane];
-    {
-        const float t = wave_max((float)top);                     // keys are below 2^16: exact in fp32
-        if (lane == 0) sh.wave_top[wave] = t;
+    // Masses and the scan; the middle comes between the two signs.  The weights are relative to the first
+    // vectors' largest value, so that the row's largest needs no barrier of its own; if that is so much
+    // larger that they could overflow, once more relative to it.
+    View vw;
+    const int rank0 = kOwnN * tid;
+    double z_ref = (double)win.first_top, z1, M_win;
+    float top_key;
+    int C_win;
+    bool again = false;
+#pragma unroll 1
+    for (;;) {
+        // my levels, and the row's highest one
+        int cnt[kOwnN];
+        win.own_counts(rank0, cnt);
+        vw.Cl = 0; vw.top = kOwnN;
+#pragma unroll
+        for (int j = kOwnN - 1; j >= 0; --j) {
+            vw.Cl += cnt[j];
+            if (cnt[j] != 0) vw.top = j;
+        }
+        const int p_top = win.pattern(rank0 + (vw.Cl > 0 ? vw.top : 0));
+        int top = vw.Cl > 0 ? key_of_pattern(p_top) : -1;
+        if (has_mid && wave == 0 && lane < n_mid && sh.mid_cnt[lane] != 0 && sh.mid_key[lane] > top) top = sh.mid_key[lane];
+        const float wave_top = wave_max((float)top);              // keys are below 2^16: exact in fp32
+        if (lane == 0) sh.wave_top[wave] = wave_top;
+        own_mass<kOwnN, kOwnN>(vw, (p_top >> 7) & 0xFF, value_of_pattern(p_top), z_ref, inv_tau, [&](int j) { return cnt[j]; });
+        if (has_mid && wave == 0) {
+            const int n = lane < n_mid ? sh.mid_cnt[lane] : 0;
+            const double w = n != 0 ? exp(((double)value_of_pattern(pattern_of_key(sh.mid_key[lane])) - z_ref) * inv_tau) : 0.0;
+            sh.mid_C[lane] = wave_prefix_i(n);
+            sh.mid_M[lane] = wave_prefix_d((double)n * w);
+        }
+        scan_view(vw, 0, 0.0, has_mid ? kRThreads / 2 : kRThreads, C_win, M_win, sh, tid);
+        top_key = row16_max(sh.wave_top[lane & (kRWaves - 1)]);
+        z1 = top_key >= 0.0f ? (double)value_of_pattern(pattern_of_key((int)top_key)) : 0.0;
+        if (again || fabs((z1 - z_ref) * inv_tau) < 256.0) break;                // uniform
+        __syncthreads();
+        again = true;
+        z_ref = z1;
     }
-    __syncthreads();
-    const float top_key = row16_max(sh.wave_top[lane & 15]);
-    const double z1 = top_key >= 0.0f ? (double)value_of_pattern(pattern_of_key((int)top_key)) : 0.0;
     const float z1f = (float)z1;                                  // a bf16 value: exact
-
-    // masses and the scan; the middle comes between the two signs
-    own_mass<kOwnN, kOwnN>(vw, (p_top >> 7) & 0xFF, value_of_pattern(p_top), z1, inv_tau, [&](int j) { return cnt[j]; });
-    if (has_mid && wave == 0) {
-        const int n = lane < n_mid ? sh.mid_cnt[lane] : 0;
-        const double w = n != 0 ? exp(((double)value_of_pattern(pattern_of_key(sh.mid_key[lane])) - z1) * inv_tau) : 0.0;
-        sh.mid_C[lane] = wave_prefix_i(n);
-        sh.mid_M[lane] = wave_prefix_d((double)n * w);
-    }
-    if (has_mid) __syncthreads();                                 // the scan reads the middle's totals
     const int mid_C = has_mid ? sh.mid_C[63] : 0;
     const double mid_M = has_mid ? sh.mid_M[63] : 0.0;
-    int C_win;
-    double M_win;
-    scan_view(vw, 0, 0.0, kRThreads / 2, mid_C, mid_M, C_win, M_win, sh, tid);
     const int n_below = sh.n_below;
     const int C_in = C_win + mid_C, C_all = C_in + n_below;
     const double M_all = M_win + mid_M;
@@ -908,14 +1038,14 @@ void sample_restricted_kernel(RestrictedArgs a)
     const bool below_weightless = n_below == 0
         || (top_key >= 0.0f && (-(double)value_of_pattern(sh.below_lo) - z1) * inv_tau < -56.0);
     const bool wide = sh.n_above != 0 || !listed || !below_weightless
-             || C_win + n_zero + list_n + n_below + sh.n_not_finite + sh.n_above != row.steps * kRThreads * 8    // a counter wrapped
+             || C_win + n_zero + list_n + n_below + sh.n_not_finite + sh.n_above != (int)a.V                       // a counter wrapped
              || (k_on && C_all >= a.top_k && C_in < a.top_k && sh.below_lo != sh.below_hi);           // the cut is below the window
     if (wide) {                                                   // uniform
         wide_row(row, a, r, inv_tau, c, grow, k23, hist, sh, tid);
     } else if (top_key >= 0.0f) {
         int cut_key = 0, kept_C = C_all;
         double kept_M = M_all;
-        auto my_cnt = [&](int j) { return cnt[j]; };
+        auto my_cnt = [&](int j) { return win.count(rank0 + j); };
         auto my_key = [&](int j) { return key_of_pattern(win.pattern(rank0 + j)); };
         // The middle's share of a search, by the first negative wave: the items carry inclusive
         // prefixes; what lies above them is what the wave's first thread has above it, less the middle.
@@ -941,7 +1071,7 @@ void sample_restricted_kernel(RestrictedArgs a)
         };
         if (k_on && C_in >= a.top_k) {                            // exactly one place holds the cut
             if (vw.Cx < a.top_k && vw.Cx + vw.Cl >= a.top_k) {
-                const Cut cut = own_count_cut<kOwnN, kOwnN>(vw, a.top_k, my_cnt);
+                const Cut cut = own_count_cut<kOwnN, 1>(vw, a.top_k, my_cnt);
                 sh.cut_key[0] = my_key(cut.j); sh.cut_C[0] = cut.C; sh.cut_M[0] = cut.M;
             }
             bool in_mid = false;
@@ -967,6 +1097,7 @@ void sample_restricted_kernel(RestrictedArgs a)
         }
         // the race: the kept levels dealt round-robin, so that a short run of them spreads over threads
         Cand best = contestant(-1.0f, 0);
+        const double ln_M = wave == kRWaves - 1 ? log(kept_M) : 0.0;         // the wave with the least of the race
         const int last = win.last_at_least(cut_key);
         for (int rank = win.first_at_most((int)top_key) + tid; rank <= last; rank += kRThreads) {
             const int n = win.count(rank);
@@ -988,6 +1119,7 @@ void sample_restricted_kernel(RestrictedArgs a)
         // the column inside the winning level
         const bool drawn = best.q >= 0.0f;
         const int pattern = pattern_of_key(key_of(best)), mag = pattern & 0x7FFF;
+        if (tid == kRThreads - 64) store_row(a, r, kept_C, drawn, pattern, z_ref, ln_M, inv_tau);
         auto pick = [&](int n) -> int { return (int)(((2ull * k23 + 1ull) * (uint64_t)n) >> 24); };
         if (drawn && mag != 0 && mag < win.base) {                // a listed value
             if (tid == 0) {
@@ -1002,7 +1134,7 @@ void sample_restricted_kernel(RestrictedArgs a)
 #pragma unroll
                 for (int q = 0; q < kQuarters; ++q) q4[q] = sh.zeros[pattern >> 15][q];
             } else {
-                const uint32_t s = swizzled((uint32_t)(2 * (mag - win.base) + (pattern >> 15)));
+                const int s = win.slot_of_pattern(pattern);
                 const uint32_t lo = hist[s], hi = hist[kArray + s];
                 q4[0] = (int)(lo & 0xFFFFu); q4[1] = (int)(lo >> 16);
                 q4[2] = (int)(hi & 0xFFFFu); q4[3] = (int)(hi >> 16);
@@ -1015,13 +1147,26 @@ void sample_restricted_kernel(RestrictedArgs a)
             const int i1 = i0 + win.per_quarter < row.steps ? i0 + win.per_quarter : row.steps;
             locate(row, i0, i1, (uint32_t)pattern, rem, a.token_out + r, sh, tid);
         }
-        if (tid == 0) store_row(a, r, kept_C, drawn, pattern, z1, kept_M, inv_tau);
     } else if (tid == 0) {                                        // no finite logit
         store_row(a, r, 0, false, 0, 0.0, 0.0, inv_tau);
     }
 }
+};
+
+// Two workgroups of 512 threads per compute unit, or one of 1024: four waves per SIMD, 128 vector registers each.
+template <int kRThreads>
+__global__ __launch_bounds__(kRThreads, 4)
+void sample_restricted_kernel(RestrictedArgs a)
+{
+    __shared__ __align__(16) uint32_t hist[2 * kArray + kTrash];
+    __shared__ typename Sampler<kRThreads>::Shared sh;
+    Sampler<kRThreads>::run(a, hist, sh);
+}
 
 }  // namespace
+
+// From this width on a row alone on its compute unit is streamed by sixteen waves (figures: top of this file).
+constexpr int64_t kFewWide = 114'688;
 
 hipError_t launch_sample_restricted(const void* logits, int64_t rows, int64_t V, int64_t row_stride,
                                     const float* tau_rows, float tau_scalar, int32_t top_k, float top_p,
@@ -1036,7 +1181,10 @@ hipError_t launch_sample_restricted(const void* logits, int64_t rows, int64_t V,
     a.top_k = top_k; a.top_p = top_p;
     a.seed = seed; a.row_base = row_base;
     a.token_out = token_out; a.logp_out = logp_out; a.kept_out = kept_out;
-    hipLaunchKernelGGL(sample_restricted_kernel, dim3((unsigned)rows), dim3(kRThreads), 0, stream, a);
+    if (rows <= compute_units() && V >= kFewWide)
+        hipLaunchKernelGGL((sample_restricted_kernel<1024>), dim3((unsigned)rows), dim3(1024), 0, stream, a);
+    else
+        hipLaunchKernelGGL((sample_restricted_kernel<512>), dim3((unsigned)rows), dim3(512), 0, stream, a);
     return hipGetLastError();
 }
 

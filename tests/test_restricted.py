@@ -425,6 +425,34 @@ def test_levels_outside_the_near_window(kind, V):
         check(lg, None, 60.0, 0, 1.0, 6, 40, f"outside {kind} V={V} no cut")
 
 
+# Eight waves per row, or sixteen for few rows of 114,688 columns and more; a vector holds 8 columns, a stream step 4096
+# or 8192, the first 4 steps choose the window.
+@pytest.mark.gpu
+@pytest.mark.parametrize("V", [7, 9, 4_095, 4_097, 16_383, 16_390, 114_687, 114_689, 131_075])
+def test_edges_of_the_near_window_and_of_the_row(V):
+    g = torch.Generator(device=DEV).manual_seed(V)
+    rows, pitch = 6, -(-V // 8) * 8 + 8
+    tail = V - V // 8 * 8                             # the columns behind the last complete vector
+    x = torch.randn((rows, pitch), generator=g, device=DEV) * 3
+    edges = torch.tensor([511.9, 510.0, 384.0, 256.0, -511.9, -384.0, 2.0 ** -23, 1.5 * 2.0 ** -23, 1.49 * 2.0 ** -23,
+                          -1.5 * 2.0 ** -23, -1.25 * 2.0 ** -23, 0.0, -0.0], device=DEV)
+    for r in range(rows):                             # levels at both ends of the window, anywhere in the row
+        n = min(V, edges.numel() * 2)
+        x[r, torch.randperm(V, generator=g, device=DEV)[:n]] = edges[torch.randint(0, edges.numel(), (n,), generator=g, device=DEV)]
+    if tail:                                          # ... and in its last columns
+        x[1, V - tail:V] = torch.tensor([512.0, 0.0, -0.0, 1e-12, -1e4, -float("inf"), 3.0], device=DEV)[:tail]
+        x[2, V - tail:V] = -1e4
+    x[3, :min(V - 1, 20_000)] = -300.0                # nothing but negative values at first
+    x[4, :V] -= 3000.0
+    x[4, V - 1] = 400.0                               # far above everything that the first vectors show
+    lg = x.to(torch.bfloat16)
+    lg[:, V:] = 77.0                                  # what lies past a row must not count
+    lg = lg[:, :V]
+    for k, p, tau in [(0, 0.9, 1.0), (0, 0.999, 0.5), (0, 0.6, 400.0), (0, 0.9, 0.02), (V // 2 + 1, 0.99, 300.0), (300, 0.7, 2.0)]:
+        if (k > 256 or k == 0) and k <= V - 3:        # an infinite column is no level: no cut may reach it
+            check(lg, None, tau, k, p, 6, 40, f"edges V={V} k={k} p={p} tau={tau}")
+
+
 @pytest.mark.gpu
 def test_draws_among_listed_values_and_zeros():
     # most of the mass on a zero level and on small listed values, so that the draw falls on them
