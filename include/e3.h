@@ -187,6 +187,21 @@ int e3_sample_restricted(const void* logits, int dtype, int64_t rows, int64_t V,
                          int32_t* token_out, float* logp_out, int32_t* kept_out, void* hip_stream);
 
 /*
+ * e3_sample_restricted with an optional workspace (device, 16-byte aligned, contents on entry ignored, no
+ * state between calls, to be used by one call at a time): with e3_restricted_workspace_bytes of it a small batch is
+ * cut into slices of columns that many workgroups read, and a second launch on the same stream
+ * finishes the rows.  Without it, or with less, every row is read by one workgroup as in
+ * e3_sample_restricted.  Same tokens (but for the near-ties above), counts and log-probs up to rounding in either form.
+ * e3_restricted_workspace_bytes: host only; 0 where a workspace would not be used.
+ */
+size_t e3_restricted_workspace_bytes(int dtype, int64_t rows, int64_t V, int32_t top_k);
+int e3_sample_restricted_ws(const void* logits, int dtype, int64_t rows, int64_t V, int64_t row_stride,
+                            const float* tau_rows, float tau_scalar, int32_t top_k, float top_p,
+                            uint64_t seed, uint64_t row_base,
+                            int32_t* token_out, float* logp_out, int32_t* kept_out,
+                            void* workspace, size_t workspace_bytes, void* hip_stream);
+
+/*
  * Training side: log-probability of a given token and the entropy of each row,
  * with the logits divided by the temperature as in the policy forward pass (end
  * of the "Temperature Scheduler" paragraph of Section 4.2), plus the two numbers

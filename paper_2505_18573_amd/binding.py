@@ -22,7 +22,7 @@ E3_TILE_CHUNK, E3_TILE_LANES, E3_TILE_DEPTH = 8, 64, 8
 E3_NOALLOC_MAX_ROWS = 1024
 
 EXPORTS = ("e3_strerror", "e3_workspace_bytes", "e3_sample_entropy", "e3_sample_entropy_noalloc",
-           "e3_sample_restricted",
+           "e3_sample_restricted", "e3_sample_restricted_ws", "e3_restricted_workspace_bytes",
            "e3_logprob_entropy", "e3_logprob_entropy_advantages",
            "e3_grpo_advantages", "e3_temperature_update", "e3_difficulty_ranks",
            "e3_allocate_budgets", "e3_budget_bounds", "e3_logprob_entropy_gap",
@@ -59,6 +59,11 @@ def lib() -> C.CDLL:
         L.e3_sample_restricted.argtypes = [vp, C.c_int, i64, i64, i64, vp, f32, i32, f32, u64, u64,
                                            vp, vp, vp, vp]
         L.e3_sample_restricted.restype = C.c_int
+        L.e3_sample_restricted_ws.argtypes = [vp, C.c_int, i64, i64, i64, vp, f32, i32, f32, u64, u64,
+                                              vp, vp, vp, vp, C.c_size_t, vp]
+        L.e3_sample_restricted_ws.restype = C.c_int
+        L.e3_restricted_workspace_bytes.argtypes = [C.c_int, i64, i64, i32]
+        L.e3_restricted_workspace_bytes.restype = C.c_size_t
         L.e3_time_next_launch.argtypes = [vp, vp]
         L.e3_time_next_launch.restype = C.c_int
         L.e3_launch_plan.argtypes = [i64, i64, C.c_int, vp, vp, vp, vp]
@@ -247,10 +252,13 @@ def e3_sample_restricted(logits: torch.Tensor, tau_rows: Optional[torch.Tensor],
     else:
         _check(kept_out, torch.int32, rows, "kept_out", dev)
     _check(tau_rows, torch.float32, rows, "tau_rows", dev)
-    rc = lib().e3_sample_restricted(_ptr(logits), dt, rows, V, stride, _ptr(tau_rows),
-                                    float(tau_scalar), int(top_k), float(top_p), int(seed),
-                                    int(row_base), _ptr(token_out), _ptr(logp_out), _ptr(kept_out),
-                                    _stream(dev))
+    L, top_k = lib(), int(top_k)
+    ws_bytes = L.e3_restricted_workspace_bytes(dt, rows, V, top_k)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev) if ws_bytes else None
+    rc = L.e3_sample_restricted_ws(_ptr(logits), dt, rows, V, stride, _ptr(tau_rows),
+                                   float(tau_scalar), top_k, float(top_p), int(seed),
+                                   int(row_base), _ptr(token_out), _ptr(logp_out), _ptr(kept_out),
+                                   _ptr(ws), ws_bytes, _stream(dev))
     if rc != E3_OK:
         raise E3Error(rc, "e3_sample_restricted")
     return token_out, logp_out, kept_out

@@ -142,11 +142,27 @@ extern "C" int e3_read_probe(const void* buf, int64_t bytes, uint32_t* sums_out,
     return err == hipSuccess ? E3_OK : E3_ERR_LAUNCH;
 }
 
+extern "C" size_t e3_restricted_workspace_bytes(int dtype, int64_t rows, int64_t V, int32_t top_k)
+{
+    if (dtype != E3_BF16 || rows <= 0 || V <= 0 || e3::sample_select_serves(top_k)) return 0;
+    return e3::sample_restricted_workspace_bytes(rows, V);
+}
+
 extern "C" int e3_sample_restricted(const void* logits, int dtype, int64_t rows, int64_t V,
                                     int64_t row_stride, const float* tau_rows, float tau_scalar,
                                     int32_t top_k, float top_p, uint64_t seed, uint64_t row_base,
                                     int32_t* token_out, float* logp_out, int32_t* kept_out,
                                     void* hip_stream)
+{
+    return e3_sample_restricted_ws(logits, dtype, rows, V, row_stride, tau_rows, tau_scalar, top_k, top_p, seed, row_base,
+                                   token_out, logp_out, kept_out, nullptr, 0, hip_stream);
+}
+
+extern "C" int e3_sample_restricted_ws(const void* logits, int dtype, int64_t rows, int64_t V,
+                                       int64_t row_stride, const float* tau_rows, float tau_scalar,
+                                       int32_t top_k, float top_p, uint64_t seed, uint64_t row_base,
+                                       int32_t* token_out, float* logp_out, int32_t* kept_out,
+                                       void* workspace, size_t workspace_bytes, void* hip_stream)
 {
     int rc = check_logits(logits, dtype, rows, V, row_stride);
     if (rc != E3_OK) return rc;
@@ -164,7 +180,7 @@ extern "C" int e3_sample_restricted(const void* logits, int dtype, int64_t rows,
         ? e3::launch_sample_select(logits, dtype == E3_BF16, rows, V, row_stride, tau_rows, tau_scalar,
                                    top_k, top_p, seed, row_base, token_out, logp_out, kept_out, stream)
         : e3::launch_sample_restricted(logits, rows, V, row_stride, tau_rows, tau_scalar, top_k, top_p,
-                                       seed, row_base, token_out, logp_out, kept_out, stream);
+                                       seed, row_base, token_out, logp_out, kept_out, workspace, workspace_bytes, stream);
     return err == hipSuccess ? E3_OK : E3_ERR_LAUNCH;
 }
 

@@ -46,6 +46,12 @@
 // 19.4 us, 256 rows 26.2 / 23.4, 512 rows 43.2 / 37.9 (4.1 TB/s), 1024 rows 82.6 / 73.5; 512 x 32,000 26.7 / 17.6,
 // 300 x 70,000 30.8 / 21.8, 512 x 5000 22.6 / 13.3.
 //
+// FEW ROWS, given a workspace.  A row alone on its compute unit is bound by that unit's LDS while the others idle.
+// Such rows are cut into eight slices, each counted by a workgroup of its own in the window that 64 vectors spread over the row
+// choose for all of them; 16 KiB of counters and some notes per slice go to memory (5 us), and the second launch
+// adds the slices up (a quarter is two of them), runs the phases, and looks the column up in one slice (10 us).
+// 8 x 151,936, top-p 0.9: 19.4 us whole, 14.9 cut; with 100 columns allowed and -1e4 elsewhere 57 and 23 us.
+//
 // A row with values above the window, or with more small ones than the list holds, is counted once
 // more in a window raised to the former or lowered for the latter; its waves give the first count up as
 // soon as they see it (151,936 columns, 8 / 512 rows: a logit of 9000 at the end of the row 37 / 46 us, all logits
@@ -97,6 +103,20 @@ struct RestrictedArgs {
     int32_t* token_out;
     float* logp_out;
     int32_t* kept_out;
+    // rows cut into slices (few rows): how many, their counters and what they found outside the window
+    int32_t nslices;
+    uint16_t* slice_counts;         // [rows][nslices][2 kHalf]
+    struct SliceNotes* slice_notes; // [rows][nslices]
+};
+
+// What a slice of a row passes on besides its counters.  The window is the same for all slices of a row.
+struct alignas(16) SliceNotes {
+    int zeros[2];                   // +0, -0
+    int list_n, n_below, n_not_finite, below_lo, below_hi;
+    int above_hi;                   // not 0: the largest of the columns above the window (of those seen, the count stops then)
+    int base;
+    float first_top;
+    int list_key[kMidList], list_col[kMidList];
 };
 
 // A row's sampling by one workgroup of kRThreads threads.
@@ -139,6 +159,20 @@ struct Row {
     int nvec, last;       // vectors; columns in the last one, 1 .. 8
     int complete;         // vectors of eight columns
     int steps, whole;     // steps, and how many of them hold nothing but complete vectors
+    // vectors [v0, v1) of the row
+    __device__ __forceinline__ Row part(int v0, int v1) const
+    {
+        Row q;
+        q.p = p + v0;
+        q.nvec = v1 - v0;
+        q.last = v1 == nvec ? last : 8;
+        q.complete = q.nvec - (q.last < 8);
+        q.steps = (q.nvec + kRThreads - 1) / kRThreads;
+        q.whole = q.complete / kRThreads;
+        return q;
+    }
+    // slice s of n
+    __device__ __forceinline__ int slice_begin(int s, int n) const { return (int)((int64_t)nvec * s / n); }
     __device__ __forceinline__ u32x4 guarded(int v) const
     {
         return counted(v < nvec ? p[v] : u32x4{0u, 0u, 0u, 0u}, v);
@@ -180,6 +214,18 @@ struct Row {
         }
     }
 };
+
+static __device__ __forceinline__ Row whole_row(const RestrictedArgs& a, int64_t r)
+{
+    Row row;
+    row.p = reinterpret_cast<const u32x4*>(a.logits + r * a.row_stride);
+    row.nvec = (int)((a.V + 7) >> 3);
+    row.last = (int)(a.V - ((int64_t)(row.nvec - 1) << 3));
+    row.steps = (row.nvec + kRThreads - 1) / kRThreads;
+    row.complete = (int)(a.V >> 3);
+    row.whole = row.complete / kRThreads;
+    return row;
+}
 
 template <typename F>
 static __device__ __forceinline__ void for_each_pattern(const u32x4& v, F&& f)
@@ -365,8 +411,9 @@ static __device__ __forceinline__ s16x2 signed_halves(uint32_t w) { return __bui
 // Stores the rem-th column (0-based, in column order) that holds pattern `pat` within stream steps
 // [i0, i1): kBlock steps are requested at once; a (step, wave) holds 512 consecutive columns, so the
 // waves' counts per step, in that order, say where the column is, and the wave that holds it
-// finds the lane, which stores it.  0 if there are not that many.  Most (step, wave) hold no such column.
-static __device__ __forceinline__ void locate(const Row& row, int i0, int i1, uint32_t pat, int rem, int32_t* token,
+// finds the lane, which stores it (`row` starts at column col0).  0 if there are not that many.  Most (step, wave) hold no such column.
+template <int kBlock>
+static __device__ __forceinline__ void locate(const Row& row, int col0, int i0, int i1, uint32_t pat, int rem, int32_t* token,
                                        Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
@@ -417,7 +464,7 @@ static __device__ __forceinline__ void locate(const Row& row, int i0, int i1, ui
                 const int skip = want - ((int)(mine >> 8) - __popc(m));
                 if (skip >= 0 && skip < __popc(m)) {              // exactly one lane
                     for (int i = 0; i < skip; ++i) m &= m - 1;
-                    *token = (tid + (ib + step) * kRThreads) * 8 + (__ffs(m) - 1);
+                    *token = col0 + (tid + (ib + step) * kRThreads) * 8 + (__ffs(m) - 1);
                 }
             }
             return;
@@ -592,7 +639,7 @@ static __device__ __forceinline__ void wide_row(const Row& row, const Restricted
     const bool drawn = best.q >= 0.0f;
     const int pattern = pattern_of_key(key_of(best));
     if (tid == 0) store_row(a, r, kept_C, drawn, pattern, z1, log(kept_M), inv_tau);
-    if (drawn) locate(row, 0, row.steps, (uint32_t)pattern, (int)(((2ull * k23 + 1ull) * (uint64_t)best_n) >> 24), a.token_out + r, sh, tid);
+    if (drawn) locate<kBlock>(row, 0, 0, row.steps, (uint32_t)pattern, (int)(((2ull * k23 + 1ull) * (uint64_t)best_n) >> 24), a.token_out + r, sh, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -769,51 +816,60 @@ static __device__ __forceinline__ void hand_rest(const Tally& t, int base, Share
 // The largest finite value among a wave's first vectors, -inf if there is none.  As signed 16-bit integers
 // the patterns of non-negative values are in value order above all others; a wave without any, or with an
 // infinity or a NaN on top, looks through its values one by one.
-static __device__ __forceinline__ float wave_top_value(const Row& row, const u32x4 x[kSet], const u32x4 y[kSet], int tid)
+template <int kN, typename Get>
+static __device__ __forceinline__ float wave_top_value(Get&& get)
 {
     s16x2 m = {-32768, -32768};
-    auto each = [&](auto&& f) {
 #pragma unroll
-        for (int u = 0; u < 2 * kSet; ++u) f(u < row.whole ? u < kSet ? x[u % kSet] : y[u % kSet]
-                                                           : row.counted(u < kSet ? x[u % kSet] : y[u % kSet], tid + u * kRThreads));
-    };
-    each([&](const u32x4& v) {
+    for (int u = 0; u < kN; ++u) {
+        const u32x4 v = get(u);
         m = __builtin_elementwise_max(m, __builtin_elementwise_max(signed_halves(v.x), signed_halves(v.y)));
         m = __builtin_elementwise_max(m, __builtin_elementwise_max(signed_halves(v.z), signed_halves(v.w)));
-    });
+    }
     const float best = wave_max((float)(m.x > m.y ? m.x : m.y));
     if (__builtin_expect(best >= 0.0f && best < (float)0x7F80, 1)) return value_of_pattern((int)best);     // uniform
     float f = -INFINITY;
-    each([&](const u32x4& v) {
-        for_each_pattern(v, [&](uint32_t p, int) {
+#pragma unroll
+    for (int u = 0; u < kN; ++u)
+        for_each_pattern(get(u), [&](uint32_t p, int) {
             const float z = value_of_pattern((int)p);
             f = z < INFINITY ? fmaxf(f, z) : f;
         });
-    });
     return wave_max(f);
 }
 
 // Counts the row.  Returns the window, whose top binade is `top_exp` if that is not negative.  Two sets of
 // requests are in flight: a set is asked for as soon as the one before it in its registers is counted.
-static __device__ __forceinline__ Near near_count(const Row& row, int top_exp, uint32_t* hist, Shared& sh, int tid)
+// kSlice: `row` is a slice, from column col0 on, of `whole`, and counts as one quarter; the window then follows from 64
+// vectors spread over the whole row, the same ones for all its slices, and is lowered where they are small.
+template <bool kSlice>
+static __device__ __forceinline__ Near near_count(const Row& row, const Row& whole, int col0, int top_exp, uint32_t* hist,
+                                                  Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
     Near w;
     w.hist = hist;
-    w.per_quarter = (row.steps + kQuarters - 1) / kQuarters;
-    u32x4 x[kSet], y[kSet];
+    w.per_quarter = kSlice ? 1 << 30 : (row.steps + kQuarters - 1) / kQuarters;
+    u32x4 x[kSet], y[kSet], spread{0u, 0u, 0u, 0u};
+    const int spread_at = kSlice ? (int)((int64_t)whole.nvec * lane / 64) : 0;
+    if (kSlice && wave == 0) spread = whole.p[spread_at];
     row.template request_ahead<kSet>(x, 0, tid);
     row.template request_ahead<kSet>(y, kSet, tid);
     uint32_t tail = 0u;                                           // the columns behind the last complete vector
     if (row.last < 8 && tid < row.last) tail = reinterpret_cast<const uint16_t*>(row.p + row.complete)[tid];
-    for (int i = tid; i < 2 * kArray / 4; i += kRThreads) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
+    for (int i = tid; i < (kSlice ? 1 : 2) * kArray / 4; i += kRThreads) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
     if (tid < 2 * kQuarters) (&sh.zeros[0][0])[tid] = 0;
     if (tid == 0) {
         sh.list_n = 0; sh.n_below = 0; sh.n_not_finite = 0; sh.n_above = 0;
         sh.below_lo = 0x7FFF; sh.below_hi = 0; sh.above_hi = 0; sh.fails = 0;
     }
     {
-        const float m = wave_top_value(row, x, y, tid);
+        const float m = kSlice
+            ? wave == 0 ? wave_top_value<1>([&](int) { return whole.counted(spread, spread_at); }) : -INFINITY
+            : wave_top_value<2 * kSet>([&](int u) {
+                  const u32x4 v = u < kSet ? x[u % kSet] : y[u % kSet];
+                  return u < row.whole ? v : row.counted(v, tid + u * kRThreads);
+              });
         if (lane == 0) sh.sample_max[wave] = m;
     }
     // orders LDS only: __syncthreads() would wait for the loads in flight as well
@@ -823,7 +879,9 @@ static __device__ __forceinline__ Near near_count(const Row& row, int top_exp, u
     // vectors (if that is negative, up to 2^20: what lies far down is a mask)
     if (top_exp < 0) {
         top_exp = w.first_top > -1048576.0f ? (int)(__float_as_uint(fabsf(w.first_top)) >> 23) + 1 : 0;
-        top_exp = top_exp < kTopExp ? kTopExp : top_exp;
+        // (lowered only for a non-negative value, and to eleven binades above it)
+        const int least = !kSlice || w.first_top < 0.0f || top_exp + 11 > kTopExp ? kTopExp : top_exp + 11;
+        top_exp = top_exp < least ? least : top_exp;
     }
     top_exp = top_exp > 254 ? 254 : top_exp < kBinades - 1 ? kBinades - 1 : top_exp;
     w.base = __builtin_amdgcn_readfirstlane(top_exp > kBinades - 1 ? ((top_exp - (kBinades - 1)) << 7) + kTrash : 0);
@@ -873,7 +931,7 @@ static __device__ __forceinline__ Near near_count(const Row& row, int top_exp, u
                 y = (y & ~is) | (x[i] & is);
             }
             const int v = tid + (i0 + u) * kRThreads;
-            note(y, i0 + u, v * 8, v < row.complete);
+            note(y, i0 + u, col0 + v * 8, v < row.complete);
         }
         return __builtin_amdgcn_readfirstlane(*(volatile int*)&sh.fails) != 0;             // counted enough
     };
@@ -890,7 +948,7 @@ static __device__ __forceinline__ Near near_count(const Row& row, int top_exp, u
         if (mine && level < (uint32_t)kLevels)
             atomicAdd(&hist[(quarter >> 1) * kArray + level + (tail >> 15) * kHalf], 1u << ((quarter & 1) * 16));
         if (__any(mine && level >= (uint32_t)kLevels))
-            note(u32x4{tail | (inside & 0xFFFF0000u), inside, inside, inside}, row.steps - 1, row.complete * 8 + lane, mine);
+            note(u32x4{tail | (inside & 0xFFFF0000u), inside, inside, inside}, row.steps - 1, col0 + row.complete * 8 + lane, mine);
     }
     hand_zeros(t, noted, sh, lane);
     hand_rest(t, w.base, sh, lane);
@@ -900,11 +958,10 @@ static __device__ __forceinline__ Near near_count(const Row& row, int top_exp, u
 
 // Counts the row, into a second window if the first had columns above it or too many small ones:
 // four binades above the largest it has seen (its waves stop at the first), or three above the
-// largest among the first vectors.
-static __device__ __forceinline__ Near near_window(const Row& row, uint32_t* hist, Shared& sh, int tid)
+// largest among the first vectors.  top_exp: the window's top binade where it is known already, or -1.
+static __device__ __forceinline__ Near near_window(const Row& row, int top_exp, uint32_t* hist, Shared& sh, int tid)
 {
     Near w;
-    int top_exp = -1;
 #pragma unroll 1
     for (;;) {
         int me = tid;
@@ -912,7 +969,7 @@ static __device__ __forceinline__ Near near_window(const Row& row, uint32_t* his
         // Opaque copies: otherwise the compiler holds what it can share between the two counts in
         // registers, and the stream spills (512 rows 45 -> 51 us).
         asm volatile("" : "+v"(me), "+s"(again.nvec), "+s"(again.last), "+s"(again.steps), "+s"(again.whole), "+s"(again.complete));
-        w = near_count(again, top_exp, hist, sh, me);
+        w = near_count<false>(again, again, 0, top_exp, hist, sh, me);
         if (__builtin_expect(sh.fails == 0 || top_exp >= 0, 1)) return w;                 // uniform
         const int now = (w.base >> 7) + kBinades - 1;
         if (sh.n_above != 0) {
@@ -924,6 +981,109 @@ static __device__ __forceinline__ Near near_window(const Row& row, uint32_t* his
         top_exp = __builtin_amdgcn_readfirstlane(top_exp);
         __syncthreads();
     }
+}
+
+// One slice of a row: its counters, 16 bits each, and its notes go to memory.
+static __device__ __forceinline__ void count_slice(const RestrictedArgs& a, uint32_t* hist, Shared& sh)
+{
+    const int tid = threadIdx.x;
+    const int64_t r = blockIdx.x / a.nslices;
+    const int s = blockIdx.x - (int)r * a.nslices;
+    const Row row = whole_row(a, r);
+    const int v0 = row.slice_begin(s, a.nslices);
+    const Near w = near_count<true>(row.part(v0, row.slice_begin(s + 1, a.nslices)), row, v0 * 8, -1, hist, sh, tid);
+    uint32_t packed[kOwnN / 2];
+#pragma unroll
+    for (int i = 0; i < kOwnN; i += 4) {
+        const uint4 c = *reinterpret_cast<const uint4*>(hist + kOwnN * tid + i);
+        packed[i / 2] = c.x | c.y << 16;
+        packed[i / 2 + 1] = c.z | c.w << 16;
+    }
+    uint32_t* out = reinterpret_cast<uint32_t*>(a.slice_counts + (size_t)blockIdx.x * kArray + kOwnN * tid);
+#pragma unroll
+    for (int i = 0; i < kOwnN / 2; i += 4)
+        *reinterpret_cast<uint4*>(out + i) = uint4{packed[i], packed[i + 1], packed[i + 2], packed[i + 3]};
+    SliceNotes& n = a.slice_notes[blockIdx.x];
+    const int listed = sh.list_n < kMidList ? sh.list_n : kMidList;
+    if (tid == 0) {
+        n.zeros[0] = sh.zeros[0][0]; n.zeros[1] = sh.zeros[1][0];
+        n.list_n = sh.list_n; n.n_below = sh.n_below; n.n_not_finite = sh.n_not_finite;
+        n.below_lo = sh.below_lo; n.below_hi = sh.below_hi; n.above_hi = sh.above_hi;
+        n.base = w.base; n.first_top = w.first_top;
+    }
+    if (tid < listed) { n.list_key[tid] = sh.list_key[tid]; n.list_col[tid] = sh.list_col[tid]; }
+}
+
+// The counters and notes of a row's slices, as near_window leaves those of a row it has counted itself, and -1; or the top
+// binade of the window that the row is to be counted in instead, by the rules of near_window.
+static __device__ __forceinline__ int gather_slices(const RestrictedArgs& a, int64_t r, Near& w, uint32_t* hist, Shared& sh, int tid)
+{
+    const int lane = tid & 63, wave = tid >> 6, per = a.nslices / kQuarters;
+    const uint16_t* counts = a.slice_counts + (size_t)r * a.nslices * kArray + kOwnN * tid;
+    w.hist = hist;
+    w.per_quarter = 0;
+    // a quarter is `per` slices; a thread sums the two quarters of one array at a time, two levels per word (a sum past
+    // 16 bits reaches the next level, and the counts no longer add up to the row's width)
+#pragma unroll 1
+    for (int array = 0; array < 2; ++array) {
+        uint32_t sum[2][kOwnN / 2] = {};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s >= per) break;                                  // uniform
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const uint4* from = reinterpret_cast<const uint4*>(counts + (size_t)((2 * array + q) * per + s) * kArray);
+#pragma unroll
+                for (int i = 0; i < kOwnN / 8; ++i) {
+                    const uint4 c = from[i];
+                    sum[q][4 * i] += c.x; sum[q][4 * i + 1] += c.y; sum[q][4 * i + 2] += c.z; sum[q][4 * i + 3] += c.w;
+                }
+            }
+        }
+        uint32_t* to = hist + array * kArray + kOwnN * tid;
+#pragma unroll
+        for (int i = 0; i < kOwnN / 2; i += 2) {
+            uint4 c;
+            c.x = (sum[0][i] & 0xFFFFu) | sum[1][i] << 16; c.y = sum[0][i] >> 16 | (sum[1][i] & 0xFFFF0000u);
+            c.z = (sum[0][i + 1] & 0xFFFFu) | sum[1][i + 1] << 16; c.w = sum[0][i + 1] >> 16 | (sum[1][i + 1] & 0xFFFF0000u);
+            *reinterpret_cast<uint4*>(to + 2 * i) = c;
+        }
+    }
+    if (wave == 0) {
+        const SliceNotes* n = a.slice_notes + r * a.nslices + (lane < a.nslices ? lane : 0);
+        const bool mine = lane < a.nslices;
+        const int list_n = mine ? n->list_n : 0;
+        const int lists = wave_prefix_i(list_n);
+        const int zero_p = wave_prefix_i(mine ? n->zeros[0] : 0), zero_n = wave_prefix_i(mine ? n->zeros[1] : 0);
+        const int below = wave_prefix_i(mine ? n->n_below : 0), odd = wave_prefix_i(mine ? n->n_not_finite : 0);
+        const float lo = -wave_max(mine ? -(float)n->below_lo : -32767.0f), hi = wave_max(mine ? (float)n->below_hi : 0.0f);
+        const int above = (int)wave_max(mine ? (float)n->above_hi : 0.0f), all_listed = __builtin_amdgcn_readlane(lists, 63);
+        if (lane == 63) {
+            sh.zeros[0][0] = zero_p; sh.zeros[1][0] = zero_n;
+            sh.list_n = lists; sh.n_below = below; sh.n_not_finite = odd; sh.n_above = 0;
+            sh.below_lo = (int)lo; sh.below_hi = (int)hi; sh.above_hi = above;
+        }
+        if (lane > 0 && lane < kQuarters) { sh.zeros[0][lane] = 0; sh.zeros[1][lane] = 0; }
+        if (all_listed <= kMidList) {
+            for (int i = 0; i < list_n; ++i) {
+                sh.list_key[lists - list_n + i] = n->list_key[i];
+                sh.list_col[lists - list_n + i] = n->list_col[i];
+            }
+        }
+    }
+    const SliceNotes& first = a.slice_notes[r * a.nslices];
+    w.base = __builtin_amdgcn_readfirstlane(first.base);
+    w.first_top = uniform_f(first.first_top);
+    __syncthreads();
+    int top_exp = -1;
+    if (sh.above_hi != 0) {
+        top_exp = (sh.above_hi >> 7) + 4;
+    } else if (sh.list_n > kMidList) {                            // (not lower: such a row takes the wide form)
+        const int lower = (int)((__float_as_uint(w.first_top) >> 23) & 0xFFu) + 3;
+        if (lower <= (w.base >> 7) + kBinades - 1 - 8) top_exp = lower;
+    }
+    __syncthreads();                                              // what was read here may be counted anew
+    return __builtin_amdgcn_readfirstlane(top_exp);
 }
 
 // The middle items of a row, one per lane of one wave, in rank order: the listed small
@@ -949,17 +1109,13 @@ static __device__ __forceinline__ void middle_items(Shared& sh, int lane)
     }
 }
 
+// kCut: the row's slices have been counted.
+template <bool kCut>
 static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hist, Shared& sh)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t r = blockIdx.x;
-    Row row;
-    row.p = reinterpret_cast<const u32x4*>(a.logits + r * a.row_stride);
-    row.nvec = (int)((a.V + 7) >> 3);
-    row.last = (int)(a.V - ((int64_t)(row.nvec - 1) << 3));
-    row.steps = (row.nvec + kRThreads - 1) / kRThreads;
-    row.complete = (int)(a.V >> 3);
-    row.whole = row.complete / kRThreads;
+    const Row row = whole_row(a, r);
     const float tau = a.tau_rows ? a.tau_rows[r] : a.tau_scalar;
     const double inv_tau = 1.0 / (double)tau;
     const float c = kLog2eF / tau;
@@ -972,7 +1128,10 @@ static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hi
         philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
         k23 = w4[0] >> 9;
     }
-    const Near win = near_window(row, hist, sh, tid);
+    Near win;
+    const int anew = kCut ? gather_slices(a, r, win, hist, sh, tid) : -1;
+    const bool sliced = kCut && anew < 0;                         // uniform
+    if (!sliced) win = near_window(row, anew, hist, sh, tid);
 
     const int list_n = sh.list_n;
     int n_zero = 0;
@@ -1128,6 +1287,19 @@ static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hi
                     if (sh.mid_key[e] == key_of(best)) { at = e; ++n; }
                 a.token_out[r] = sh.mid_col[at + pick(n)];
             }
+        } else if (kCut && sliced && drawn) {
+            // the slice that holds the column: a lane has a slice's count of the level
+            int n = 0;
+            if (lane < a.nslices)
+                n = mag < win.base ? a.slice_notes[r * a.nslices + lane].zeros[pattern >> 15]
+                                   : a.slice_counts[((size_t)r * a.nslices + lane) * kArray + win.slot_of_pattern(pattern)];
+            const int upto = wave_prefix_i(n);
+            const int rem = pick(__builtin_amdgcn_readlane(upto, 63));
+            const unsigned long long past = __ballot(upto > rem);
+            const int s = past != 0ull ? (int)__builtin_ctzll(past) : 0;
+            const int v0 = row.slice_begin(s, a.nslices);
+            const Row part = row.part(v0, row.slice_begin(s + 1, a.nslices));
+            locate<2048 / kRThreads>(part, v0 * 8, 0, part.steps, (uint32_t)pattern, rem - __builtin_amdgcn_readlane(upto - n, s), a.token_out + r, sh, tid);
         } else if (drawn) {
             int q4[kQuarters];
             if (mag < win.base) {                                 // a zero
@@ -1145,7 +1317,7 @@ static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hi
                 if (quarter == q && rem >= q4[q]) { rem -= q4[q]; ++quarter; }
             const int i0 = quarter * win.per_quarter;
             const int i1 = i0 + win.per_quarter < row.steps ? i0 + win.per_quarter : row.steps;
-            locate(row, i0, i1, (uint32_t)pattern, rem, a.token_out + r, sh, tid);
+            locate<kBlock>(row, 0, i0, i1, (uint32_t)pattern, rem, a.token_out + r, sh, tid);
         }
     } else if (tid == 0) {                                        // no finite logit
         store_row(a, r, 0, false, 0, 0.0, 0.0, inv_tau);
@@ -1154,13 +1326,22 @@ static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hi
 };
 
 // Two workgroups of 512 threads per compute unit, or one of 1024: four waves per SIMD, 128 vector registers each.
-template <int kRThreads>
+template <int kRThreads, bool kCut>
 __global__ __launch_bounds__(kRThreads, 4)
 void sample_restricted_kernel(RestrictedArgs a)
 {
     __shared__ __align__(16) uint32_t hist[2 * kArray + kTrash];
     __shared__ typename Sampler<kRThreads>::Shared sh;
-    Sampler<kRThreads>::run(a, hist, sh);
+    Sampler<kRThreads>::template run<kCut>(a, hist, sh);
+}
+
+constexpr int kSliceThreads = 512;
+__global__ __launch_bounds__(kSliceThreads, 4)
+void count_slices_kernel(RestrictedArgs a)
+{
+    __shared__ __align__(16) uint32_t hist[kArray];
+    __shared__ Sampler<kSliceThreads>::Shared sh;
+    Sampler<kSliceThreads>::count_slice(a, hist, sh);
 }
 
 }  // namespace
@@ -1168,10 +1349,28 @@ void sample_restricted_kernel(RestrictedArgs a)
 // From this width on a row alone on its compute unit is streamed by sixteen waves (figures: top of this file).
 constexpr int64_t kFewWide = 114'688;
 
+// Slices of a row, 0: not cut.  Eight (sixteen where the columns of an eighth would not fit 16-bit counters) for rows of at
+// least kSliceMinV columns and 4096 columns per row of the batch, up to twice as many slices as compute units: what
+// a cut row saves is its stream, what it costs is a launch and 16 KiB of counters per slice.  Whole / eight
+// slices / sixteen / four in us: 8 x 151,936 19.4 / 14.9 / 15.9 / 16.6, 32 x 151,936 19.9 / 17.6 / 20.7 / 18.2, 64 x 151,936
+// 20.3 / 20.5; 16 x 70,000 15.0 / 14.3, 32 x 70,000 14.9 / 15.6; 64 x 260,000 28.1 / 22.6.
+constexpr int64_t kSliceMinV = 65'536;
+static int slices_of(int64_t rows, int64_t V)
+{
+    if (rows < 1 || V < kSliceMinV || rows * 4096 > V || rows * 8 > 2 * (int64_t)compute_units()) return 0;
+    return V <= 8 * 65'528 ? 8 : 16;
+}
+
+size_t sample_restricted_workspace_bytes(int64_t rows, int64_t V)
+{
+    return (size_t)rows * slices_of(rows, V) * (kArray * sizeof(uint16_t) + sizeof(SliceNotes));
+}
+
 hipError_t launch_sample_restricted(const void* logits, int64_t rows, int64_t V, int64_t row_stride,
                                     const float* tau_rows, float tau_scalar, int32_t top_k, float top_p,
                                     uint64_t seed, uint64_t row_base, int32_t* token_out,
-                                    float* logp_out, int32_t* kept_out, hipStream_t stream)
+                                    float* logp_out, int32_t* kept_out, void* workspace, size_t workspace_bytes,
+                                    hipStream_t stream)
 {
     if (rows == 0) return hipSuccess;
     RestrictedArgs a;
@@ -1181,10 +1380,21 @@ hipError_t launch_sample_restricted(const void* logits, int64_t rows, int64_t V,
     a.top_k = top_k; a.top_p = top_p;
     a.seed = seed; a.row_base = row_base;
     a.token_out = token_out; a.logp_out = logp_out; a.kept_out = kept_out;
-    if (rows <= compute_units() && V >= kFewWide)
-        hipLaunchKernelGGL((sample_restricted_kernel<1024>), dim3((unsigned)rows), dim3(1024), 0, stream, a);
-    else
-        hipLaunchKernelGGL((sample_restricted_kernel<512>), dim3((unsigned)rows), dim3(512), 0, stream, a);
+    a.nslices = 0; a.slice_counts = nullptr; a.slice_notes = nullptr;
+    const size_t need = sample_restricted_workspace_bytes(rows, V);
+    if (need > 0 && workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0 && workspace_bytes >= need) {
+        a.nslices = slices_of(rows, V);
+        a.slice_counts = static_cast<uint16_t*>(workspace);
+        a.slice_notes = reinterpret_cast<SliceNotes*>(a.slice_counts + (size_t)rows * a.nslices * kArray);
+        hipLaunchKernelGGL(count_slices_kernel, dim3((unsigned)(rows * a.nslices)), dim3(kSliceThreads), 0, stream, a);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL((sample_restricted_kernel<512, true>), dim3((unsigned)rows), dim3(512), 0, stream, a);
+    } else if (rows <= compute_units() && V >= kFewWide) {
+        hipLaunchKernelGGL((sample_restricted_kernel<1024, false>), dim3((unsigned)rows), dim3(1024), 0, stream, a);
+    } else {
+        hipLaunchKernelGGL((sample_restricted_kernel<512, false>), dim3((unsigned)rows), dim3(512), 0, stream, a);
+    }
     return hipGetLastError();
 }
 

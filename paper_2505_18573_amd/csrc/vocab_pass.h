@@ -67,11 +67,15 @@ hipError_t launch_entropy_reduce(const float* entropy, const float* gap, const u
                                  double* sum_out, double* gap_sum_out, int64_t* count_out,
                                  hipStream_t stream, hipEvent_t stop_event = nullptr);
 
-// top-k / top-p restricted sampling of bf16 rows (one workgroup per row)
+// top-k / top-p restricted sampling of bf16 rows: one workgroup per row, or, when the caller brings
+// sample_restricted_workspace_bytes (0: no use for it), few rows cut into slices and a second launch that
+// finishes them
+size_t sample_restricted_workspace_bytes(int64_t rows, int64_t V);
 hipError_t launch_sample_restricted(const void* logits, int64_t rows, int64_t V, int64_t row_stride,
                                     const float* tau_rows, float tau_scalar, int32_t top_k, float top_p,
                                     uint64_t seed, uint64_t row_base, int32_t* token_out,
-                                    float* logp_out, int32_t* kept_out, hipStream_t stream);
+                                    float* logp_out, int32_t* kept_out, void* workspace, size_t workspace_bytes,
+                                    hipStream_t stream);
 
 // top-k (<= 256, see sample_select_serves) / top-p restricted sampling by selection, bf16 and
 // fp32 rows (one workgroup per row)

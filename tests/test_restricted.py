@@ -453,6 +453,63 @@ def test_edges_of_the_near_window_and_of_the_row(V):
             check(lg, None, tau, k, p, 6, 40, f"edges V={V} k={k} p={p} tau={tau}")
 
 
+def _by_c_call(lg, tau, k, p, seed, ws, ws_bytes):
+    rows, V = lg.shape
+    out = [torch.empty(rows, dtype=t, device=DEV) for t in (torch.int32, torch.float32, torch.int32)]
+    rc = e3.lib().e3_sample_restricted_ws(lg.data_ptr(), e3.E3_BF16, rows, V, lg.stride(0), None, tau, k, p, seed, 9,
+                                          out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(),
+                                          ws, ws_bytes, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    return out
+
+
+# Few rows of 65,536 columns and more are cut into eight slices (sixteen from 524,225 columns on) given a workspace:
+# slices of equal and unequal length, with and without columns behind the last complete vector.
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,V", [(1, 65_536), (16, 65_543), (5, 131_071), (3, 524_224), (2, 524_232), (2, 1_040_384)])
+def test_cut_rows_give_what_whole_rows_give(rows, V):
+    need = e3.lib().e3_restricted_workspace_bytes(e3.E3_BF16, rows, V, 0)
+    assert need == rows * (8 if V <= 524_224 else 16) * (16_384 + 544)
+    g = torch.Generator(device=DEV).manual_seed(V)
+    pitch = -(-V // 8) * 8
+    for kind in ("plain", "late", "small", "masked", "zeros", "wide"):
+        x = torch.randn((rows, pitch), generator=g, device=DEV) * 3
+        if kind == "late":
+            x[0, V - 1] = 9000.0                      # above the window: counted anew by the second launch
+        elif kind == "small":                         # listed by several slices; row 0 more than the list holds
+            x[:, 5:V:V // 50] = 2.0 ** -30
+            x[0, 3:V:V // 90] = -(2.0 ** -28)
+        elif kind == "masked":
+            x = torch.where(torch.rand(x.shape, generator=g, device=DEV) < 0.999, -1e4, x)
+            x[0, :V // 3] = -float("inf")
+        elif kind == "zeros":
+            x = torch.relu(x)
+            x[:, 1:V:2] *= -1.0
+        elif kind == "wide":
+            x[0] = 0.5                                # one level longer than a quarter's counters
+            x[rows - 1] = -600.0 - x[rows - 1]        # columns below the window that weigh
+            x[rows - 1, 7] = -590.0
+        lg = x.to(torch.bfloat16)
+        lg[:, V:] = 77.0                              # what lies past a row must not count
+        lg = lg[:, :V]
+        ws = torch.randint(0, 256, (need,), generator=g, device=DEV, dtype=torch.uint8)      # its contents do not matter
+        for k, p, tau in [(0, 0.9, 1.0), (300, 0.95, 0.7), (V // 2, 0.999, 40.0), (0, 0.7, 500.0)]:
+            want = _by_c_call(lg, tau, k, p, 3, None, 0)
+            for got in (_by_c_call(lg, tau, k, p, 3, ws.data_ptr(), need), _by_c_call(lg, tau, k, p, 3, ws.data_ptr(), need - 1)):
+                assert torch.equal(got[2], want[2]), (kind, k, p, tau)
+                assert torch.equal(got[0], want[0]), (kind, k, p, tau)
+                assert torch.allclose(got[1], want[1], rtol=1e-6, atol=1e-7, equal_nan=True), (kind, k, p, tau)
+    check(lg, None, 1.0, 0, 0.9, 3, 9, f"cut rows {rows}x{V}")
+
+
+def test_workspace_of_cut_rows_needs_no_gpu():
+    need = e3.lib().e3_restricted_workspace_bytes
+    assert need(e3.E3_BF16, 8, 151_936, 0) == 8 * 8 * (16_384 + 544)
+    assert need(e3.E3_BF16, 8, 151_936, 50) == 0 and need(e3.E3_F32, 8, 151_936, 0) == 0
+    assert need(e3.E3_BF16, 8, 65_535, 0) == 0 and need(e3.E3_BF16, 512, 151_936, 0) == 0
+    assert need(e3.E3_BF16, 0, 151_936, 0) == 0 and need(e3.E3_BF16, -1, 151_936, 0) == 0 and need(7, 8, 151_936, 0) == 0
+
+
 @pytest.mark.gpu
 def test_draws_among_listed_values_and_zeros():
     # most of the mass on a zero level and on small listed values, so that the draw falls on them
