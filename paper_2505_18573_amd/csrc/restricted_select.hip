@@ -39,7 +39,7 @@ namespace {
 
 constexpr int kSBatch = 8;              // 16-byte requests of a thread made together; two such sets are in flight
 constexpr int kSMaxWaves = 16;
-constexpr int kSVecCap = 2048;          // vectors listed in LDS
+constexpr int kSVecCap = 2688;          // vectors listed in LDS (what two workgroups per compute unit leave room for)
 constexpr int kSMaxK = 256;             // top_k served here; the gt-list holds at most kSMaxK - 1 columns
 constexpr int kSEqCap = 64;             // columns of the cut level listed for a direct pick
 constexpr int kSListCap = 2048;         // candidates (columns at or above theta) listed in LDS
@@ -126,6 +126,32 @@ struct alignas(16) SelShared {
 
 static_assert(offsetof(SelShared, gt_key) % 16 == 0 && offsetof(SelShared, gt_col) % 16 == 0, "read four at a time");
 
+// Inclusive prefix sum over the lanes of a wave: four shifts inside each row of sixteen lanes,
+// then lane 15 of a row into the next row and lane 31 into the upper half (lanes a shift does
+// not reach read zero).
+__device__ __forceinline__ int wave_prefix_sum(int v)
+{
+    v += dpp_i<0x111>(0, v);               // row_shr:1
+    v += dpp_i<0x112>(0, v);               // row_shr:2
+    v += dpp_i<0x114>(0, v);               // row_shr:4
+    v += dpp_i<0x118>(0, v);               // row_shr:8
+    v += dpp_i<kDppBcast15, 0xA>(0, v);
+    v += dpp_i<kDppBcast31, 0xC>(0, v);
+    return v;
+}
+
+// Inclusive prefix sum in fp64, by the same steps as wave_prefix_sum.
+__device__ __forceinline__ double wave_prefix_sum_f64(double v)
+{
+    v += dpp_d<0x111>(0.0, v);
+    v += dpp_d<0x112>(0.0, v);
+    v += dpp_d<0x114>(0.0, v);
+    v += dpp_d<0x118>(0.0, v);
+    v += dpp_d<kDppBcast15, 0xA>(0.0, v);
+    v += dpp_d<kDppBcast31, 0xC>(0.0, v);
+    return v;
+}
+
 // One 8-bit pass of a radix select for the k-th largest: every thread has added its keys
 // that match `prefix` above `shift + 8` to hist; wave 0 finds the digit that holds rank k_rem.
 __device__ __forceinline__ void select_digit(SelShared& sh, int tid)
@@ -135,12 +161,7 @@ __device__ __forceinline__ void select_digit(SelShared& sh, int tid)
         uint32_t c[4], sum = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) { c[j] = sh.hist[255 - 4 * tid - j]; sum += c[j]; }
-        uint32_t inc = sum;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t o = __shfl_up(inc, d, 64);
-            if (tid >= d) inc += o;
-        }
+        const uint32_t inc = (uint32_t)wave_prefix_sum((int)sum);
         uint32_t before = inc - sum;                       // counts in higher bins
         const uint32_t k = sh.k_rem;
         if (before < k && k <= inc) {                       // exactly one lane
@@ -157,20 +178,6 @@ __device__ __forceinline__ void select_digit(SelShared& sh, int tid)
             }
         }
     }
-}
-
-// Inclusive prefix sum over the lanes of a wave: four shifts inside each row of sixteen lanes,
-// then lane 15 of a row into the next row and lane 31 into the upper half (lanes a shift does
-// not reach read zero).
-__device__ __forceinline__ int wave_prefix_sum(int v)
-{
-    v += dpp_i<0x111>(0, v);               // row_shr:1
-    v += dpp_i<0x112>(0, v);               // row_shr:2
-    v += dpp_i<0x114>(0, v);               // row_shr:4
-    v += dpp_i<0x118>(0, v);               // row_shr:8
-    v += dpp_i<kDppBcast15, 0xA>(0, v);
-    v += dpp_i<kDppBcast31, 0xC>(0, v);
-    return v;
 }
 
 struct SelArgs {
@@ -202,10 +209,8 @@ constexpr int kSoloK = 64;
 
 __device__ __forceinline__ double read_lane_f64(double v, int src_lane)
 {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFFll), src_lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src_lane);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(uint32_t)lo);
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src_lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), src_lane));
 }
 
 template <typename T>
@@ -233,8 +238,28 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
     // least k keys reach (one ballot per register and bit; the keys' low bits follow the sign
     // when only the upper kKeyBits are significant)
     const int k_eff = n_list < k_req ? n_list : k_req;              // fewer than k finite columns: all of them
-    uint32_t kappa = 0u;
-    for (int b = 31; b >= 32 - T::kKeyBits; --b) {
+    // (from the highest bit that not all of them share)
+    uint32_t all = 0xFFFFFFFFu, any = 0u;
+#pragma unroll
+    for (int j = 0; j < kPerLane; ++j) {
+        if (lane + 64 * j < n_list) { all &= lk[j]; any |= lk[j]; }
+    }
+    {
+        auto fold = [&](auto c, auto m) {
+            all &= (uint32_t)dpp_i<decltype(c)::value, decltype(m)::value>((int)all, (int)all);
+            any |= (uint32_t)dpp_i<decltype(c)::value, decltype(m)::value>((int)any, (int)any);
+        };
+        std::integral_constant<int, 0xF> every;
+        fold(std::integral_constant<int, kDppXor1>{}, every); fold(std::integral_constant<int, kDppXor2>{}, every);
+        fold(std::integral_constant<int, kDppHalfMirror>{}, every); fold(std::integral_constant<int, kDppMirror>{}, every);
+        fold(std::integral_constant<int, kDppBcast15>{}, std::integral_constant<int, 0xA>{});
+        fold(std::integral_constant<int, kDppBcast31>{}, std::integral_constant<int, 0xC>{});
+    }
+    all = (uint32_t)__builtin_amdgcn_readlane((int)all, 63);
+    const uint32_t differ = all ^ (uint32_t)__builtin_amdgcn_readlane((int)any, 63);
+    const int high = differ != 0u ? 31 - (int)__builtin_clz(differ) : -1;       // bits above it are those of every key
+    uint32_t kappa = high < 0 ? all : all & ~(0xFFFFFFFFu >> (31 - high));
+    for (int b = high; b >= 32 - T::kKeyBits; --b) {
         const uint32_t cand = kappa | (1u << b);
         int reach = 0;
 #pragma unroll
@@ -289,17 +314,13 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
     const double z1 = (double)__uint_as_float(f32_of_key(key1));
     const double z_cut = (double)__uint_as_float(f32_of_key(kappa));
     const double w = have ? exp(((double)__uint_as_float(f32_of_key(skey)) - z1) * inv_tau) : 0.0;
-    double M = w;                                                   // inclusive prefix mass
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const double o = __shfl_up(M, d, 64);
-        if (lane >= d) M += o;
-    }
+    const double M = wave_prefix_sum_f64(w);                        // inclusive prefix mass
     const double M_gt = n > 0 ? read_lane_f64(M, n - 1) : 0.0;
     const double w_cut = exp((z_cut - z1) * inv_tau);
     const double M_k = M_gt + (double)n_cut * w_cut;               // mass of the top-k set
-    const uint32_t next_key = (uint32_t)__shfl_down((int)skey, 1, 64);
-    const uint32_t prev_key = (uint32_t)__shfl_up((int)skey, 1, 64);
+    constexpr int kNextLane = 0x130, kPrevLane = 0x138;             // wave_shl:1, wave_shr:1
+    const uint32_t next_key = (uint32_t)dpp_i<kNextLane>(0, (int)skey);
+    const uint32_t prev_key = (uint32_t)dpp_i<kPrevLane>(0, (int)skey);
     int cut_index = kSMaxK;                                          // default: everything down to the cut level
     if (a.top_p < 1.0f) {
         // top-p on the renormalised top-k set: first level end whose cumulative mass reaches the target
@@ -311,7 +332,7 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
     const bool cut_level_kept = cut_index == kSMaxK;
     const int kept_sorted = cut_level_kept ? n : cut_index + 1;    // sorted entries kept
     const int kept_C = cut_level_kept ? n + n_cut : kept_sorted;
-    const double kept_M = cut_level_kept ? M_k : read_lane_f64(M, cut_index);
+    const double ln_M = log(cut_level_kept ? M_k : read_lane_f64(M, cut_index));
 
     // race of the kept levels: a level's first lane scores it, lane 63 scores the cut level
     const bool level_start = have && (lane == 0 || prev_key != skey);
@@ -334,14 +355,9 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
              * inv_exp_variate(word);
         my_lvl = for_cut ? kSMaxK : lane;
     }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        const float oq = __shfl_xor(my_q, d, 64);
-        const int ol = __shfl_xor(my_lvl, d, 64);
-        if (oq > my_q || (oq == my_q && ol < my_lvl)) { my_q = oq; my_lvl = ol; }   // ties: the higher level
-    }
-    const float best_q = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, my_q)));
-    const int best_lvl = __builtin_amdgcn_readfirstlane(my_lvl);
+    const Cand winner = wave_best(Cand{my_q, my_lvl});               // ties: the higher level
+    const float best_q = winner.q;
+    const int best_lvl = winner.idx;
 
     // the column inside the winning level
     uint32_t w4[4];
@@ -384,7 +400,7 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
         if (a.kept_out) a.kept_out[row] = kept_C;
         if (a.logp_out)
             a.logp_out[row] = best_q >= 0.0f
-                ? (float)(((double)__uint_as_float(f32_of_key(tok_key)) - z1) * inv_tau - log(kept_M))
+                ? (float)(((double)__uint_as_float(f32_of_key(tok_key)) - z1) * inv_tau - ln_M)
                 : __builtin_nanf("");
     }
 }
@@ -394,9 +410,9 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
 // non-temporal loads, or 1024 threads and plain loads for at most one row per compute unit (half the
 // stream's latency; such a batch may sit in the caches: 100 fp32 rows 24.7 us plain, 28.2 us
 // non-temporal; 300 rows x 151,936 bf16 29.7 us with 512 threads, 48 us with 1024): four waves per
-// SIMD and up to 128 vector registers either way.  151,936 bf16 columns, top-k 50 + top-p, chunk maxima
-// and a second read of the qualifying chunks before / now: 8 rows 26.0 / 18.1 us, 512 rows 45.2 /
-// 36.3 us (4.3 TB/s), 1024 rows 81.5 / 63.4 us (4.9 TB/s).
+// SIMD and up to 128 vector registers either way.  151,936 bf16 columns, top-k 50 + top-p 0.95: 8 rows 16.5 us,
+// 512 rows 33.6 us (4.6 TB/s), 1024 rows 58.6 us (5.3 TB/s); with the one-wave finish's scans and reductions through
+// LDS permutes instead of DPP, the cut searched over all 16 or 32 bits and the logarithm taken last 17.6, 34.6 and 61.1.
 template <typename T, int kSThreads>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void sample_select_kernel(SelArgs a)
@@ -513,8 +529,10 @@ void sample_select_kernel(SelArgs a)
     auto current_theta = [&]() -> uint32_t {
         uint32_t t = lane < full_waves ? __hip_atomic_load(&sh.tmax_wave[lane & (kSWaves - 1)], __ATOMIC_RELAXED,
                                                         __HIP_MEMORY_SCOPE_WORKGROUP) : 0xFFFFFFFFu;
-#pragma unroll
-        for (int d = kSWaves / 2; d > 0; d >>= 1) { const uint32_t o = __shfl_xor(t, d, 64); t = o < t ? o : t; }
+        // sixteen lanes hold them
+        auto least = [&](auto c) { const uint32_t o = (uint32_t)dpp_i<decltype(c)::value>((int)t, (int)t); t = o < t ? o : t; };
+        least(std::integral_constant<int, kDppXor1>{}); least(std::integral_constant<int, kDppXor2>{});
+        least(std::integral_constant<int, kDppHalfMirror>{}); least(std::integral_constant<int, kDppMirror>{});
         t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
         if (t == 0u) t = 1u;                                      // a wave with fewer than m finite maxima: every finite value
         // a zero maximum was recorded as +0 whichever zero it was: let -0 in as well
@@ -568,9 +586,12 @@ void sample_select_kernel(SelArgs a)
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         float thf = theta_value(current_theta());
         list_set(x, m, 0, thf, nsets == 1);
-        // refined whenever what has been read has doubled, and at the end
+        // refined whenever what has been read has doubled, and at the end; after every set for a large k, whose list
+        // would overflow otherwise (512 x 151,936, top-k 256, a list of 2048 / of 2688 / and refined so: fp32 108 / 89 / 73 us,
+        // bf16 54 / 48 / 48; at k = 100 it would cost 0.5 us)
+        const bool often = k_req > (kSThreads == 512 ? 160 : 224);
         auto refine = [&](int set) {
-            if (set + 1 == nsets || (set & (set + 1)) == 0) { publish(); thf = theta_value(current_theta()); }
+            if (set + 1 == nsets || (set & (set + 1)) == 0 || often) { publish(); thf = theta_value(current_theta()); }
         };
         for (int set = 1; set < nsets; set += 2) {
             if (set + 1 < nsets) request(x, set + 1);
@@ -728,10 +749,8 @@ void sample_select_kernel(SelArgs a)
         if (pass == 0) {
             // number of candidates; fewer than k finite columns in the row: the cut is the lowest level
             if (tid < 64) {
-                uint32_t t = sh.hist[tid] + sh.hist[tid + 64] + sh.hist[tid + 128] + sh.hist[tid + 192];
-#pragma unroll
-                for (int d = 32; d > 0; d >>= 1) t += __shfl_xor(t, d, 64);
-                if (tid == 0) { sh.n_total = t; sh.k_rem = t < k_col ? t : k_col; }
+                const uint32_t t = (uint32_t)wave_prefix_sum((int)(sh.hist[tid] + sh.hist[tid + 64] + sh.hist[tid + 128] + sh.hist[tid + 192]));
+                if (tid == 63) { sh.n_total = t; sh.k_rem = t < k_col ? t : k_col; }
             }
             __syncthreads();
         }
@@ -819,13 +838,7 @@ void sample_select_kernel(SelArgs a)
             w[j] = i < n ? sh.st_M[i] : 0.0;
             loc += w[j];
         }
-        double inc = loc;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const double o = __shfl_up(inc, d, 64);
-            if (tid >= d) inc += o;
-        }
-        double run = inc - loc;
+        double run = wave_prefix_sum_f64(loc) - loc;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int i = 4 * tid + j;
@@ -852,7 +865,7 @@ void sample_select_kernel(SelArgs a)
     const bool cut_level_kept = cut_index == kSMaxK;
     const int kept_sorted = cut_level_kept ? n : cut_index + 1;    // sorted entries kept
     const int kept_C = cut_level_kept ? n + n_cut : kept_sorted;
-    const double kept_M = cut_level_kept ? M_k : sh.st_M[cut_index];
+    const double ln_M = wave == kSWaves - 1 ? log(cut_level_kept ? M_k : sh.st_M[cut_index]) : 0.0;      // the wave with the least of the race
 
     // race of the kept levels ------------------------------------------------------------------
     // score n_j w_j / E_j, E_j from Philox stream 3 at index = the level's stored pattern; fp32
@@ -882,21 +895,12 @@ void sample_select_kernel(SelArgs a)
         my_q = level_score(kappa, n_cut);
         my_lvl = kSMaxK;
     }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        const float oq = __shfl_xor(my_q, d, 64);
-        const int ol = __shfl_xor(my_lvl, d, 64);
-        if (oq > my_q || (oq == my_q && ol < my_lvl)) { my_q = oq; my_lvl = ol; }
-    }
-    if (lane == 0) { sh.wave_q[wave] = my_q; sh.wave_lvl[wave] = my_lvl; }
+    const Cand of_wave = wave_best(Cand{my_q, my_lvl});
+    if (lane == 0) { sh.wave_q[wave] = of_wave.q; sh.wave_lvl[wave] = of_wave.idx; }
     __syncthreads();
-    float best_q = -1.0f;
-    int best_lvl = 0x7FFFFFFF;
-    for (int w = 0; w < kSWaves; ++w) {
-        const float q = sh.wave_q[w];
-        const int l = sh.wave_lvl[w];
-        if (q > best_q || (q == best_q && l < best_lvl)) { best_q = q; best_lvl = l; }
-    }
+    const Cand winner = row16_best(Cand{sh.wave_q[lane & (kSWaves - 1)], sh.wave_lvl[lane & (kSWaves - 1)]});
+    const float best_q = winner.q;
+    const int best_lvl = winner.idx;
 
     // the column inside the winning level ---------------------------------------------------------
     uint32_t w4[4];
@@ -973,13 +977,13 @@ void sample_select_kernel(SelArgs a)
             tok = sh.token;
         }
     }
-    if (tid == 0) {
+    if (tid == kSThreads - 64) {
         if (tok < 0 || tok >= V) tok = 0;
         a.token_out[row] = tok;
         if (a.kept_out) a.kept_out[row] = kept_C;
         if (a.logp_out)
             a.logp_out[row] = best_q >= 0.0f
-                ? (float)(((double)__uint_as_float(f32_of_key(tok_key)) - z1) * inv_tau - log(kept_M))
+                ? (float)(((double)__uint_as_float(f32_of_key(tok_key)) - z1) * inv_tau - ln_M)
                 : __builtin_nanf("");
     }
 }

@@ -550,7 +550,7 @@ def test_levels_longer_than_a_quarter_counter():
 
 
 # ---------------------------------------------------------------- selection: both workgroup sizes, list overflow
-# 1024 threads per row up to one row per compute unit, 512 beyond; the list of vectors holds 2048.
+# 1024 threads per row up to one row per compute unit, 512 beyond; the list of vectors holds 2688.
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("rows,V", [(256, 33_001), (257, 5), (257, 4_099), (260, 16_387), (260, 33_001), (300, 70_001)])
