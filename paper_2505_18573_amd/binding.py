@@ -4,10 +4,15 @@ Every function has the name and the arguments of the C entry point it calls
 (include/e3.h).  Tensors are torch tensors used as device memory; the current
 torch stream is handed over as the hipStream_t.  Nothing is computed here, and
 there is no fallback: without the built library the import of `lib()` raises.
+The calls that a step consists of go through _native (csrc/native_binding.cpp) as long as their
+arguments are plain tensors, ints and floats of the right shape; everything else, errors above all,
+is treated here.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional, Tuple
 
@@ -15,6 +20,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libe3.so")
+NATIVE_PATH = os.path.join(HERE, "_native.so")
 
 E3_F32, E3_BF16 = 0, 1
 E3_OK = 0
@@ -29,7 +35,18 @@ EXPORTS = ("e3_strerror", "e3_workspace_bytes", "e3_sample_entropy", "e3_sample_
            "e3_temperature_update_gap", "e3_grpo_objective", "e3_read_probe",
            "e3_time_next_launch", "e3_launch_plan")
 
+_NATIVE_CALLS = ("e3_grpo_advantages", "e3_grpo_objective", "e3_workspace_bytes", "e3_sample_entropy",
+                 "e3_restricted_workspace_bytes", "e3_sample_restricted_ws", "e3_logprob_entropy_advantages",
+                 "e3_temperature_update")
+
 _lib: Optional[C.CDLL] = None
+_native = None                     # the native calls, once they are bound to the loaded library
+
+
+# A call is one or two launches of a few microseconds, so what surrounds it counts: pointers go over as
+# plain integers, the stream as torch's raw handle (no Stream object), and a check asks a tensor
+# for as little as it can.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 class E3Error(RuntimeError):
@@ -95,13 +112,42 @@ def lib() -> C.CDLL:
         L.e3_budget_bounds.argtypes = [i32, i32, i32, i32, i32, vp, vp]
         L.e3_budget_bounds.restype = C.c_int
         _lib = L
+        _bind_native(L)
     return _lib
 
 
-# A call is one or two launches of a few microseconds, so what surrounds it counts: pointers go over as
-# plain integers, the stream as torch's raw handle (no Stream object), and a check asks a tensor
-# for as little as it can.
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+def _bind_native(L: C.CDLL) -> None:
+    """Loads the native calls (built beside the library) and points them at L's entry points."""
+    global _native
+    if _raw_stream is None:                       # a torch without the raw stream handle: no native calls
+        return
+    if not os.path.exists(NATIVE_PATH):
+        raise ImportError(f"{NATIVE_PATH} is missing: run `python -m paper_2505_18573_amd.build`")
+    if _native is None:
+        loader = importlib.machinery.ExtensionFileLoader("_native", NATIVE_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_native", loader))
+        loader.exec_module(module)
+    else:
+        module = _native
+    module.bind({n: C.cast(getattr(L, n), C.c_void_p).value for n in _NATIVE_CALLS}, _raw_stream)
+    _native = module
+
+
+def _ordinary(name: str, *args):
+    """The outputs of native call `name` (of the entry point e3_...), or None if its arguments are not ordinary."""
+    if _lib is None:
+        lib()
+    if _native is None:
+        return None
+    out = getattr(_native, name)(*args)
+    if type(out) is int:
+        raise E3Error(out, _ENTRY[name])
+    return out
+
+
+_ENTRY = {"advantages": "e3_grpo_advantages", "objective": "e3_grpo_objective", "sample": "e3_sample_entropy",
+          "restricted": "e3_sample_restricted", "logprob": "e3_logprob_entropy",
+          "logprob_advantages": "e3_logprob_entropy_advantages", "temperature": "e3_temperature_update"}
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -186,6 +232,9 @@ def e3_sample_entropy(logits: torch.Tensor, tau_rows: Optional[torch.Tensor], ta
                       entropy_out: Optional[torch.Tensor] = None,
                       workspace=None):
     """Returns (token int32 [rows], logp fp32 [rows], entropy fp32 [rows])."""
+    out = _ordinary("sample", logits, tau_rows, tau_scalar, seed, row_base, token_out, logp_out, entropy_out, workspace)
+    if out is not None:
+        return out
     dt, rows, V, stride = _logits_meta(logits)
     dev = logits.device
     if token_out is None:
@@ -237,6 +286,9 @@ def e3_sample_restricted(logits: torch.Tensor, tau_rows: Optional[torch.Tensor],
                          kept_out: Optional[torch.Tensor] = None):
     """Returns (token int32 [rows], logp fp32 [rows], kept int32 [rows]).  bf16 rows: any
     top_k / top_p; fp32 rows: 1 <= top_k <= 256 (E3_ERR_VALUE otherwise)."""
+    out = _ordinary("restricted", logits, tau_rows, tau_scalar, top_k, top_p, seed, row_base, token_out, logp_out, kept_out)
+    if out is not None:
+        return out
     dt, rows, V, stride = _logits_meta(logits)
     dev = logits.device
     if token_out is None:
@@ -308,6 +360,10 @@ def e3_logprob_entropy(logits: torch.Tensor, target_ids: Optional[torch.Tensor],
     """Returns (logp fp32 [rows] or None, entropy fp32 [rows], entropy_sum fp64 [1] or None,
     entropy_count int64 [1] or None); the sum and count stay on the device unless pinned host
     tensors are passed for them."""
+    out = _ordinary("logprob", logits, target_ids, row_mask, tau_rows, tau_scalar, None, None, 0, 0.0, logp_out,
+                    entropy_out, entropy_sum_out, entropy_count_out, None, workspace, want_sum)
+    if out is not None:
+        return out
     dt, rows, V, stride = _logits_meta(logits)
     dev = logits.device
     if logp_out is not None:
@@ -350,6 +406,11 @@ def e3_logprob_entropy_advantages(logits: torch.Tensor, target_ids: Optional[tor
                                   workspace=None, want_sum: bool = True):
     """e3_logprob_entropy and e3_grpo_advantages in one call.  Returns (logp, entropy,
     entropy_sum, entropy_count, adv)."""
+    if rewards is not None:
+        out = _ordinary("logprob_advantages", logits, target_ids, row_mask, tau_rows, tau_scalar, rewards, group_offsets, ddof,
+                        eps, logp_out, entropy_out, entropy_sum_out, entropy_count_out, adv_out, workspace, want_sum)
+        if out is not None:
+            return out
     dt, rows, V, stride = _logits_meta(logits)
     dev = logits.device
     n = rewards.shape[0]
@@ -392,6 +453,9 @@ def e3_logprob_entropy_advantages(logits: torch.Tensor, target_ids: Optional[tor
 def e3_grpo_advantages(rewards: torch.Tensor, group_offsets: torch.Tensor, ddof: int = 0,
                        eps: float = 0.0, adv_out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Returns adv fp32 [N].  group_offsets is int32 [B+1] on the same device."""
+    out = _ordinary("advantages", rewards, group_offsets, ddof, eps, adv_out)
+    if out is not None:
+        return out
     dev = rewards.device
     if not rewards.is_cuda:
         raise ValueError("rewards must live on the GPU")
@@ -414,6 +478,9 @@ def e3_temperature_update(tau_t: float, H_t: float, H_init: float, vocab: int, t
                           t_anneal: int = -1, t_max: int = 0, eta: float = 1.0,
                           tau_min: float = 0.0, tau_max: float = float("inf")):
     """Host-only scheduler step.  Returns (tau_next, H_target)."""
+    out = _ordinary("temperature", tau_t, H_t, H_init, vocab, t, t_anneal, t_max, eta, tau_min, tau_max)
+    if out is not None:
+        return out
     nxt, tgt = C.c_double(float("nan")), C.c_double(float("nan"))
     rc = lib().e3_temperature_update(float(tau_t), float(H_t), float(H_init), int(vocab), int(t),
                                      int(t_anneal), int(t_max), float(eta), float(tau_min),
@@ -504,6 +571,9 @@ def e3_grpo_objective(logp_new: torch.Tensor, logp_old: torch.Tensor, seq_offset
                       adv: torch.Tensor, group_offsets: torch.Tensor, clip_eps: float,
                       want_token_terms: bool = False):
     """Returns (objective fp64 [1], seq_mean fp64 [N], token_terms fp32 [T] or None), on the device."""
+    out = _ordinary("objective", logp_new, logp_old, seq_offsets, adv, group_offsets, clip_eps, want_token_terms)
+    if out is not None:
+        return out
     dev = logp_new.device
     if not logp_new.is_cuda:
         raise ValueError("logp_new must live on the GPU")

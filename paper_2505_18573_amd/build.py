@@ -1,12 +1,14 @@
-"""Build libe3.so (HIP, gfx950) in-tree with hipcc."""
+"""Build libe3.so (HIP, gfx950) with hipcc and the binding's native calls (host only) with g++, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libe3.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["e3_api.hip", "vocab_pass.hip", "restricted.hip", "restricted_select.hip", "probe.hip", "advantages.hip", "objective.hip",
            "scheduler.cpp", "budget.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -33,7 +35,22 @@ def build(verbose: bool = False, extra=()) -> str:
         print(err)
     if res.returncode != 0:
         raise RuntimeError(f"hipcc failed with status {res.returncode}")
+    build_native(verbose)
     return LIB
+
+
+def build_native(verbose: bool = False) -> str:
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], "-o", NATIVE, os.path.join(CSRC, "native_binding.cpp"),
+           "-L" + os.path.join(root, "lib"), "-lc10", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
+    return NATIVE
 
 
 if __name__ == "__main__":

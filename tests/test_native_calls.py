@@ -1,0 +1,123 @@
+"""The binding's native calls against its Python path: the same outputs bit for bit, the same errors, and arguments
+that are not plain tensors, ints and floats are left to the Python path."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_18573_amd as e3
+
+DEV = "cuda:0"
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+def _calls(dev, rows=6, V=40_000, groups=3):
+    g = torch.Generator(device=dev).manual_seed(1)
+    lg = (torch.randn((rows, V), generator=g, device=dev) * 3).to(torch.bfloat16)
+    tau = (0.5 + torch.rand(rows, generator=g, device=dev)).float()
+    tgt = torch.randint(0, V, (rows,), generator=g, device=dev).to(torch.int32)
+    mask = torch.tensor([1, 0] * (rows // 2), dtype=torch.uint8, device=dev)
+    off = torch.arange(0, rows + 1, rows // groups, dtype=torch.int32, device=dev)
+    rew = torch.rand(rows, generator=g, device=dev)
+    T = 100
+    new, old = -torch.rand(T, generator=g, device=dev), -torch.rand(T, generator=g, device=dev)
+    soff = torch.tensor([0, 10, 10, 40, 77, 90, T], dtype=torch.int32, device=dev)
+    f32 = lambda n: torch.empty(n, dtype=torch.float32, device=dev)
+    return {
+        "sample": (e3.e3_sample_entropy, dict(logits=lg, tau_rows=tau, tau_scalar=1.0, seed=7, row_base=1 << 40)),
+        "sample_into": (e3.e3_sample_entropy, dict(logits=lg, tau_rows=None, tau_scalar=1, seed=-3, logp_out=f32(rows), workspace=False)),
+        "restricted": (e3.e3_sample_restricted, dict(logits=lg, tau_rows=tau, tau_scalar=1.0, top_k=0, top_p=0.9, seed=3)),
+        "restricted_k": (e3.e3_sample_restricted, dict(logits=lg.float(), tau_rows=None, tau_scalar=0.7, top_k=20, top_p=1, seed=3)),
+        "logprob": (e3.e3_logprob_entropy, dict(logits=lg, target_ids=tgt, row_mask=mask, tau_rows=tau, tau_scalar=1.0)),
+        "logprob_plain": (e3.e3_logprob_entropy, dict(logits=lg, target_ids=None, row_mask=None, tau_rows=None, tau_scalar=0.8, want_sum=False)),
+        "both": (e3.e3_logprob_entropy_advantages, dict(logits=lg, target_ids=tgt, row_mask=None, tau_rows=None, tau_scalar=1.0, rewards=rew,
+                                                       group_offsets=off, ddof=1, eps=1e-6)),
+        "advantages": (e3.e3_grpo_advantages, dict(rewards=rew, group_offsets=off, eps=0.5)),
+        "objective": (e3.e3_grpo_objective, dict(logp_new=new, logp_old=old, seq_offsets=soff, adv=rew, group_offsets=off, clip_eps=0.2,
+                                                 want_token_terms=True)),
+        "objective_plain": (e3.e3_grpo_objective, dict(logp_new=new, logp_old=old, seq_offsets=soff, adv=rew, group_offsets=off, clip_eps=0)),
+        "temperature": (e3.e3_temperature_update, dict(tau_t=1.0, H_t=0.5, H_init=0.6, vocab=1000, t=3, t_anneal=1, t_max=9, eta=0.5)),
+    }
+
+
+def _outcome(f, kw, monkeypatch, native):
+    e3.lib()
+    with monkeypatch.context() as m:
+        if not native:
+            m.setattr(e3.binding, "_native", None)
+        try:
+            out = f(**kw)
+        except Exception as e:                        # the error is what is compared
+            return type(e), str(e)
+    if torch.cuda.is_available():
+        torch.cuda.synchronize()
+    return out if isinstance(out, tuple) else (out,)
+
+
+NAMES = list(_calls("cpu", V=64))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", NAMES)
+def test_same_outputs_as_the_python_path(name, monkeypatch):
+    f, kw = _calls(DEV)[name]
+    odd = dict(kw)                                    # values of types that the native calls leave alone
+    for key, cast in (("seed", np.int64), ("tau_scalar", torch.tensor), ("ddof", np.int32), ("clip_eps", np.float64), ("tau_t", np.float64)):
+        if key in odd:
+            odd[key] = cast(odd[key])
+    want = [x.clone() if torch.is_tensor(x) else x for x in _outcome(f, kw, monkeypatch, native=False)]
+    for got in (_outcome(f, kw, monkeypatch, native=True), _outcome(f, odd, monkeypatch, native=True)):
+        assert len(got) == len(want)
+        for a, b in zip(got, want):
+            if torch.is_tensor(b):
+                assert a.dtype == b.dtype and a.device == b.device and torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+            else:
+                assert a == b
+
+
+def _spoilt(kw):
+    """One argument at a time replaced by what the call must refuse."""
+    for key, v in kw.items():
+        if torch.is_tensor(v):
+            yield dict(kw, **{key: v.to(torch.float64)})
+            yield dict(kw, **{key: v[:-1]})
+            yield dict(kw, **{key: v.repeat_interleave(2, -1)[..., ::2]})
+            yield dict(kw, **{key: v.cpu()})
+            yield dict(kw, **{key: 5})
+            yield dict(kw, **{key: v.as_subclass(Sub)[:-1]})
+        elif key in ("tau_scalar", "eps", "clip_eps", "top_p", "H_t", "tau_t"):
+            yield dict(kw, **{key: -1.0})
+            yield dict(kw, **{key: float("nan")})
+            yield dict(kw, **{key: "x"})
+        elif key in ("ddof", "top_k", "vocab"):
+            yield dict(kw, **{key: -1})
+
+
+def _same_errors(f, kw, monkeypatch):
+    for bad in _spoilt(kw):
+        want, got = (_outcome(f, bad, monkeypatch, native=n) for n in (False, True))
+        if isinstance(want[0], type):
+            assert got == want, bad
+        else:                                         # not refused (a short reward list, say): not refused either way
+            assert not isinstance(got[0], type), bad
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_same_errors_without_a_gpu(name, monkeypatch):
+    if torch.cuda.is_available():
+        pytest.skip("tensors on the CPU, all of them refused")
+    f, kw = _calls("cpu", V=64)[name]
+    if name != "temperature":
+        with pytest.raises(ValueError):
+            f(**kw)
+    _same_errors(f, kw, monkeypatch)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["sample", "restricted", "logprob", "temperature"])
+def test_same_errors(name, monkeypatch):
+    # (calls whose shortened offsets or targets would be read out of bounds are not made here)
+    f, kw = _calls(DEV)[name]
+    _same_errors(f, kw, monkeypatch)
