@@ -37,14 +37,14 @@
 // Then five short phases per row (levels and scan 2.2 us, cuts 1.2, race 0.9, look-up 2.2 to 3), chains of
 // LDS, barriers and dependent instructions that the last rows of a launch have nothing to overlap with.
 // Hence workgroups of eight waves (per-wave work of the phases is done half as often as with sixteen:
-// 100 rows x 1000 columns 14.6 us with sixteen waves and 64 registers each, 10.7 now), two sets of requests in
+// 100 rows x 1000 columns 14.6 us with sixteen waves and 64 registers each, 9.8 now), two sets of requests in
 // flight, and nothing in the stream but the count: spare words for what lies outside, one check per set.
 // Sixteen waves still stream a single row faster: with at most one row per compute unit they win from
 // about 114,688 columns on (eight / sixteen waves in us: 100 rows x 70,000 15.3 / 15.5, x 100,000 17.5 / 17.6, x 130,000 20.3 /
 // 19.5, x 400,000 45.3 / 39.4; 256 rows x 40,000 13.6 / 15.1, x 100,000 19.0 / 19.4, x 130,000 21.6 / 21.5).
 // Captured launches, top-p 0.9, sixteen waves with a burst of four requests / now: 8 x 151,936 23.0 /
-// 19.4 us, 256 rows 26.2 / 23.4, 512 rows 43.2 / 37.9 (4.1 TB/s), 1024 rows 82.6 / 73.5; 512 x 32,000 26.7 / 17.6,
-// 300 x 70,000 30.8 / 21.8, 512 x 5000 22.6 / 13.3.
+// 19.4 us, 256 rows 26.2 / 23.4, 512 rows 43.2 / 37.9 (4.1 TB/s), 1024 rows 82.6 / 73.5; 512 x 32,000 26.7 / 16.4,
+// 300 x 70,000 30.8 / 21.4, 512 x 5000 22.6 / 12.0.
 //
 // FEW ROWS, given a workspace.  A row alone on its compute unit is bound by that unit's LDS while the others idle.
 // Such rows are cut into eight slices, each counted by a workgroup of its own in the window that 64 vectors spread over the row
@@ -128,6 +128,7 @@ static constexpr int kOwnW = kWideBins / kRThreads;
 static constexpr int kWide = 4096 / kRThreads;         // wide rows: stream steps requested together
 // Stream steps looked up at a time: one block is enough for a quarter of up to 163,840 columns.
 static constexpr int kBlock = 5120 / kRThreads;
+static constexpr int kShortBlock = 3;
 static_assert(kOwnN * kRThreads == 2 * kHalf && 128 % kOwnN == 0 && 128 % kOwnW == 0, "a thread's levels share a binade");
 
 struct Shared {
@@ -422,6 +423,7 @@ static __device__ __forceinline__ void locate(const Row& row, int col0, int i0, 
     for (int ib = i0; ib < i1; ib += kBlock) {
         u32x4 x[kBlock];
         row.template request_ahead<kBlock>(x, ib, tid);
+        int totals = 0;                                           // lane u: the wave's columns of step u
         uint32_t found[kBlock];                                   // my columns (bits 0..7) and how many my wave has up to me
 #pragma unroll
         for (int u = 0; u < kBlock; ++u) {
@@ -440,8 +442,9 @@ static __device__ __forceinline__ void locate(const Row& row, int col0, int i0, 
                 found[u] = (uint32_t)upto << 8 | m;
                 total = __builtin_amdgcn_readlane(upto, 63);
             }
-            if (lane == 0) sh.tot[u * kRWaves + wave] = total;
+            totals = lane == u ? total : totals;
         }
+        if (lane < kBlock) sh.tot[lane * kRWaves + wave] = totals;
         __syncthreads();
         // every wave finds the (step, wave) that holds the column: two consecutive totals per lane
         static_assert(kBlock * kRWaves <= 128 && kBlock * kRWaves % 2 == 0, "two totals per lane");
@@ -1317,7 +1320,13 @@ static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hi
                 if (quarter == q && rem >= q4[q]) { rem -= q4[q]; ++quarter; }
             const int i0 = quarter * win.per_quarter;
             const int i1 = i0 + win.per_quarter < row.steps ? i0 + win.per_quarter : row.steps;
-            locate<kBlock>(row, 0, i0, i1, (uint32_t)pattern, rem, a.token_out + r, sh, tid);
+            // A block that lies past the quarter for the most part costs its requests and comparisons all the same: 512 x
+            // 32,000 17.6 us with the one block, 16.4 so.  (A third of half the block: 200 x 60,000 14.8 -> 14.3, but its code
+            // cost other widths 0.1 to 0.2 us.)
+            if (kRThreads == 512 && i1 - i0 <= kShortBlock)
+                locate<kShortBlock>(row, 0, i0, i1, (uint32_t)pattern, rem, a.token_out + r, sh, tid);
+            else
+                locate<kBlock>(row, 0, i0, i1, (uint32_t)pattern, rem, a.token_out + r, sh, tid);
         }
     } else if (tid == 0) {                                        // no finite logit
         store_row(a, r, 0, false, 0, 0.0, 0.0, inv_tau);
