@@ -40,9 +40,12 @@ def build(verbose: bool = False, extra=()) -> str:
 
 
 def build_native(verbose: bool = False) -> str:
+    # NDEBUG: otherwise the headers bring a thread-local variable (pybind11's reference counter).  A library with
+    # thread-local storage of its own that is loaded late and never touches it makes glibc (before 2.39) take the slow way
+    # to every other library's: each torch call of the process 0.3 us longer, an allocated output 1.33 instead of 1.06 us.
     import torch
     root = os.path.dirname(torch.__file__)
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-shared", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-I" + sysconfig.get_paths()["include"], "-o", NATIVE, os.path.join(CSRC, "native_binding.cpp"),

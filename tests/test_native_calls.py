@@ -1,5 +1,7 @@
 """The binding's native calls against its Python path: the same outputs bit for bit, the same errors, and arguments
 that are not plain tensors, ints and floats are left to the Python path."""
+import struct
+
 import numpy as np
 import pytest
 import torch
@@ -121,3 +123,13 @@ def test_same_errors(name, monkeypatch):
     # (calls whose shortened offsets or targets would be read out of bounds are not made here)
     f, kw = _calls(DEV)[name]
     _same_errors(f, kw, monkeypatch)
+
+
+def test_the_module_brings_no_thread_local_storage():
+    # loaded after torch's libraries, it would make their own thread-local variables slower to reach (see build_native)
+    elf = open(e3.binding.NATIVE_PATH, "rb").read()
+    assert elf[:6] == b"\x7fELF\x02\x01"
+    at, = struct.unpack_from("<Q", elf, 32)
+    size, n = struct.unpack_from("<HH", elf, 54)
+    kinds = [struct.unpack_from("<I", elf, at + i * size)[0] for i in range(n)]
+    assert 1 in kinds and 7 not in kinds                  # PT_LOAD, PT_TLS
