@@ -111,8 +111,8 @@ def lib() -> C.CDLL:
         L.e3_allocate_budgets.restype = C.c_int
         L.e3_budget_bounds.argtypes = [i32, i32, i32, i32, i32, vp, vp]
         L.e3_budget_bounds.restype = C.c_int
+        _bind_native(L)                           # may raise: nothing is loaded then
         _lib = L
-        _bind_native(L)
     return _lib
 
 
@@ -123,12 +123,9 @@ def _bind_native(L: C.CDLL) -> None:
         return
     if not os.path.exists(NATIVE_PATH):
         raise ImportError(f"{NATIVE_PATH} is missing: run `python -m paper_2505_18573_amd.build`")
-    if _native is None:
-        loader = importlib.machinery.ExtensionFileLoader("_native", NATIVE_PATH)
-        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_native", loader))
-        loader.exec_module(module)
-    else:
-        module = _native
+    loader = importlib.machinery.ExtensionFileLoader("_native", NATIVE_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_native", loader))
+    loader.exec_module(module)
     module.bind({n: C.cast(getattr(L, n), C.c_void_p).value for n in _NATIVE_CALLS}, _raw_stream)
     _native = module
 

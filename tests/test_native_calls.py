@@ -133,3 +133,16 @@ def test_the_module_brings_no_thread_local_storage():
     size, n = struct.unpack_from("<HH", elf, 54)
     kinds = [struct.unpack_from("<I", elf, at + i * size)[0] for i in range(n)]
     assert 1 in kinds and 7 not in kinds                  # PT_LOAD, PT_TLS
+
+
+def test_every_load_raises_while_a_library_is_missing(monkeypatch, tmp_path):
+    b = e3.binding
+    with monkeypatch.context() as m:
+        m.setattr(b, "_lib", None)
+        m.setattr(b, "_native", None)
+        m.setattr(b, "NATIVE_PATH", str(tmp_path / "_native.so"))
+        for _ in range(2):
+            with pytest.raises(ImportError):
+                e3.lib()
+            with pytest.raises(ImportError):
+                e3.e3_temperature_update(1.0, 0.5, 0.6, 1000)
