@@ -50,6 +50,10 @@
 // Such rows are cut into eight slices, each counted by a workgroup of its own in the window that 64 vectors spread over the row
 // choose for all of them; 16 KiB of counters and some notes per slice go to memory (5 us), and the second launch
 // adds the slices up (a quarter is two of them), runs the phases, and looks the column up in one slice (10 us).
+// Where that sample holds neither large values nor negative ones of ordinary size, the window is lowered to the values it
+// does hold, so that a row of small ones needs no list; if a slice then meets others, the second launch counts the
+// row anew (8 x 151,936 clamped to at most 0: 268 us when the window followed the largest value alone, and the
+// negative columns lay below it, 23 so; 3e-4 x ordinary with 30 columns at -30: 150 and 24).
 // 8 x 151,936, top-p 0.9: 19.4 us whole, 14.9 cut; with 100 columns allowed and -1e4 elsewhere 57 and 23 us.
 //
 // A row with values above the window, or with more small ones than the list holds, is counted once
@@ -75,6 +79,7 @@ namespace {
 constexpr int kBinades = 32;                    // of each sign in the near window
 constexpr int kHalf = kBinades * 128;           // its words of one sign
 constexpr int kTopExp = 135;                    // exponent field of the lowest top binade, [256, 512)
+constexpr int kTopEnd = (kTopExp + 1) << 7;     // the first magnitude above it
 constexpr int kQuarters = 4;
 constexpr int kTrash = 64;                      // spare words, one per lane
 constexpr int kLevels = kHalf - kTrash;         // levels of one sign that are counted
@@ -137,6 +142,7 @@ struct Shared {
     int wave_C[kRWaves];
     Cand best[kRWaves];
     float sample_max[kRWaves];
+    float sample_mag;               // slices: the largest magnitude in the sample that the ordinary window holds
     int zeros[2][kQuarters];        // +0, -0 by quarter
     int list_n, n_below, n_not_finite, n_above;
     int below_lo, below_hi, above_hi;            // magnitude bits of the columns below the window (both ends) and above it
@@ -841,6 +847,9 @@ static __device__ __forceinline__ float wave_top_value(Get&& get)
     return wave_max(f);
 }
 
+// The top binade of a window lowered for a row of which `mag` is the largest magnitude seen.
+static __device__ __forceinline__ int lowered_top(float mag) { return (int)(__float_as_uint(mag) >> 23) + 12; }
+
 // Counts the row.  Returns the window, whose top binade is `top_exp` if that is not negative.  Two sets of
 // requests are in flight: a set is asked for as soon as the one before it in its registers is counted.
 // kSlice: `row` is a slice, from column col0 on, of `whole`, and counts as one quarter; the window then follows from 64
@@ -874,6 +883,18 @@ static __device__ __forceinline__ Near near_count(const Row& row, const Row& who
                   return u < row.whole ? v : row.counted(v, tid + u * kRThreads);
               });
         if (lane == 0) sh.sample_max[wave] = m;
+        if (kSlice && wave == 0 && m >= 0.0f && lowered_top(m) < kTopExp) {                // uniform, rare
+            const u32x4 v = whole.counted(spread, spread_at);
+            const u16x2 one = {1, 1};
+            auto held = [&](uint32_t word) -> u16x2 {
+                const u16x2 mag = halves(word & 0x7FFF7FFFu);
+                return mag * (one - at_least(mag, (uint32_t)kTopEnd));
+            };
+            const u16x2 most = __builtin_elementwise_max(__builtin_elementwise_max(held(v.x), held(v.y)),
+                                                         __builtin_elementwise_max(held(v.z), held(v.w)));
+            const float mag = wave_max((float)(most.x > most.y ? most.x : most.y));
+            if (lane == 0) sh.sample_mag = value_of_pattern((int)mag);
+        }
     }
     // orders LDS only: __syncthreads() would wait for the loads in flight as well
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -882,8 +903,13 @@ static __device__ __forceinline__ Near near_count(const Row& row, const Row& who
     // vectors (if that is negative, up to 2^20: what lies far down is a mask)
     if (top_exp < 0) {
         top_exp = w.first_top > -1048576.0f ? (int)(__float_as_uint(fabsf(w.first_top)) >> 23) + 1 : 0;
-        // (lowered only for a non-negative value, and to eleven binades above it)
-        const int least = !kSlice || w.first_top < 0.0f || top_exp + 11 > kTopExp ? kTopExp : top_exp + 11;
+        // (lowered only for a non-negative value, and to eleven binades above all that the sample holds of either
+        // sign: half of a row at zero and the others negative is an ordinary row)
+        int least = kTopExp;
+        if (kSlice && w.first_top >= 0.0f && lowered_top(w.first_top) < kTopExp) {
+            const int lower = lowered_top(sh.sample_mag);
+            least = lower < kTopExp ? lower : kTopExp;
+        }
         top_exp = top_exp < least ? least : top_exp;
     }
     top_exp = top_exp > 254 ? 254 : top_exp < kBinades - 1 ? kBinades - 1 : top_exp;
@@ -1084,6 +1110,11 @@ static __device__ __forceinline__ int gather_slices(const RestrictedArgs& a, int
     } else if (sh.list_n > kMidList) {                            // (not lower: such a row takes the wide form)
         const int lower = (int)((__float_as_uint(w.first_top) >> 23) & 0xFFu) + 3;
         if (lower <= (w.base >> 7) + kBinades - 1 - 8) top_exp = lower;
+    }
+    // columns below a lowered window that the ordinary one holds (the sample had none of them): the lowest window that does
+    if (sh.n_below != 0 && sh.below_lo < kTopEnd) {
+        const int reach = sh.below_hi < kTopEnd ? sh.below_hi >> 7 : kTopExp;
+        top_exp = top_exp < reach ? reach : top_exp;
     }
     __syncthreads();                                              // what was read here may be counted anew
     return __builtin_amdgcn_readfirstlane(top_exp);

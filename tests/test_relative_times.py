@@ -119,3 +119,22 @@ def test_a_count_cut_among_masked_columns_costs_no_sweeps(rows):
     without, with_cut = us(_nucleus(x)), us(_nucleus(x, 1000, 1.0))
     print(f"{rows} masked rows: top-p 0.9 {without:.1f} us, top-k 1000 {with_cut:.1f} us")
     assert with_cut < 2.0 * without
+
+
+@pytest.mark.parametrize("kind", ["at_most_zero", "tiny_positive", "few_negative"])
+def test_few_rows_without_large_positive_values_cost_no_sweeps(kind):
+    # 8 rows cut into slices, an ordinary one 16 us: 22, 26 and 24 us (the last counted once more); 268, 154 and 150 us when the
+    # slices' window was chosen by the largest value of a sample alone, so that the negative columns lay below it
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.randn((8, 151_936), generator=g, device=DEV) * 3
+    ordinary = us(_nucleus(x))
+    if kind == "at_most_zero":
+        x = x.clamp(max=0)
+    elif kind == "tiny_positive":
+        x = torch.where(x < 0, x, x * 1e-4)
+    else:
+        x *= 3e-4
+        x[:, 3::5000] = -30.0
+    other = us(_nucleus(x))
+    print(f"8 rows, top-p 0.9: ordinary {ordinary:.1f} us, {kind} {other:.1f} us")
+    assert other < 3.0 * ordinary

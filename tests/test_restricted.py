@@ -472,7 +472,7 @@ def test_cut_rows_give_what_whole_rows_give(rows, V):
     assert need == rows * (8 if V <= 524_224 else 16) * (16_384 + 544)
     g = torch.Generator(device=DEV).manual_seed(V)
     pitch = -(-V // 8) * 8
-    for kind in ("plain", "late", "small", "masked", "zeros", "wide"):
+    for kind in ("plain", "late", "small", "masked", "zeros", "wide", "at_most_zero", "tiny_positive", "few_negative", "few_larger"):
         x = torch.randn((rows, pitch), generator=g, device=DEV) * 3
         if kind == "late":
             x[0, V - 1] = 9000.0                      # above the window: counted anew by the second launch
@@ -489,6 +489,17 @@ def test_cut_rows_give_what_whole_rows_give(rows, V):
             x[0] = 0.5                                # one level longer than a quarter's counters
             x[rows - 1] = -600.0 - x[rows - 1]        # columns below the window that weigh
             x[rows - 1, 7] = -590.0
+        elif kind == "at_most_zero":                  # nothing positive: the columns that matter are zeros and negative ones
+            x = x.clamp(max=0)
+        elif kind == "tiny_positive":
+            x = torch.where(x < 0, x, x * 1e-4)
+        elif kind == "few_negative":                  # ordinary negative values that a sample hardly meets
+            x *= 1e-4
+            x[:, 3:V:V // 30] = -20.0
+        elif kind == "few_larger":                    # ... and positive ones
+            x *= 1e-4
+            x[:, 3:V:V // 30] = -300.0
+            x[:, 5:V:V // 20] = 6.0
         lg = x.to(torch.bfloat16)
         lg[:, V:] = 77.0                              # what lies past a row must not count
         lg = lg[:, :V]
