@@ -130,7 +130,7 @@ struct Sampler {
 static constexpr int kRWaves = kRThreads / 64;
 static constexpr int kOwnN = 2 * kHalf / kRThreads;    // near window: a thread's levels
 static constexpr int kOwnW = kWideBins / kRThreads;
-static constexpr int kWide = 4096 / kRThreads;         // wide rows: stream steps requested together
+static constexpr int kWideSet = 2048 / kRThreads;      // wide rows: stream steps of one set of requests
 // Stream steps looked up at a time: one block is enough for a quarter of up to 163,840 columns.
 static constexpr int kBlock = 5120 / kRThreads;
 static constexpr int kShortBlock = 3;
@@ -180,10 +180,6 @@ struct Row {
     }
     // slice s of n
     __device__ __forceinline__ int slice_begin(int s, int n) const { return (int)((int64_t)nvec * s / n); }
-    __device__ __forceinline__ u32x4 guarded(int v) const
-    {
-        return counted(v < nvec ? p[v] : u32x4{0u, 0u, 0u, 0u}, v);
-    }
     // vector v without what is not the row's
     __device__ __forceinline__ u32x4 counted(const u32x4& x, int v) const
     {
@@ -203,21 +199,6 @@ struct Row {
         for (int u = 0; u < kN; ++u) {
             const int v = tid + (step + u) * kRThreads;
             x[u] = p[v < nvec ? v : nvec - 1];
-        }
-    }
-    // kN steps from `step` on, requested together; those at or past `end` read as nothing
-    template <int kN>
-    __device__ __forceinline__ void request(u32x4 x[kN], int step, int end, int tid) const
-    {
-        if (step + kN <= (whole < end ? whole : end)) {           // uniform: plain loads, nothing waits on them here
-#pragma unroll
-            for (int u = 0; u < kN; ++u) x[u] = p[tid + (step + u) * kRThreads];
-        } else {
-#pragma unroll
-            for (int u = 0; u < kN; ++u) {
-                if (step + u < (whole < end ? whole : end)) x[u] = p[tid + (step + u) * kRThreads];
-                else x[u] = guarded(step + u < end ? tid + (step + u) * kRThreads : nvec);
-            }
         }
     }
 };
@@ -510,22 +491,45 @@ struct WideWindow {
 // A pattern's counter in its window: neighbouring threads' runs of kOwnW start in different banks.
 static __device__ __forceinline__ uint32_t wide_place(uint32_t p) { return (p & 0x3FFFu) ^ (p / kOwnW & 31u); }
 
-// `resident` is the window that the counters hold already (-1: none).
+// `resident` is the window that the counters hold already (-1: none).  Two sets of requests in flight and two patterns
+// at a time, as in near_count: relative to the window's quadrant its own patterns have no high bits, and a minimum sends all
+// others to the lane's spare word (8 x 151,936, 500 small columns: XXX).
 static __device__ __forceinline__ void wide_count(const Row& row, WideWindow win, int& resident, uint32_t* hist, int tid)
 {
     __syncthreads();
     if (win.w == resident) return;                                // uniform
     resident = win.w;
-    for (int i = tid; i < kWideBins + kTrash; i += kRThreads) hist[i] = 0u;
-    __syncthreads();
-    const uint32_t quad = win.quadrant(), trash = (uint32_t)(kWideBins + (tid & 63));
-#pragma unroll 1
-    for (int i0 = 0; i0 < row.steps; i0 += kWide) {
-        u32x4 x[kWide];
-        row.template request<kWide>(x, i0, row.steps, tid);
+    u32x4 x[kWideSet], y[kWideSet];
+    row.template request_ahead<kWideSet>(x, 0, tid);
+    row.template request_ahead<kWideSet>(y, kWideSet, tid);
+    for (int i = tid; i < (kWideBins + kTrash) / 4; i += kRThreads) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
+    // orders LDS only: __syncthreads() would wait for the loads in flight as well
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const uint32_t quad = win.quadrant() * 0x40004000u;
+    const uint16_t spare = (uint16_t)(kWideBins + (tid & 63));
+    const u16x2 spare_v = {spare, spare};
+    static_assert(kWideBins == 0x4000 && kTrash == 64, "what exceeds a place is a spare word or above all of them");
+    auto add2 = [&](uint32_t word) {
+        const uint32_t t = word ^ quad;
+        const uint32_t at = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(halves(t ^ (t / kOwnW & 0x001F001Fu)), spare_v));
+        atomicAdd(&hist[at & 0xFFFFu], 1u);
+        atomicAdd(&hist[at >> 16], 1u);
+    };
+    auto count = [&](const u32x4 (&x)[kWideSet], int i0) {
 #pragma unroll
-        for (int u = 0; u < kWide; ++u)
-            for_each_pattern(x[u], [&](uint32_t p, int) { atomicAdd(&hist[(p >> 14) == quad ? wide_place(p) : trash], 1u); });
+        for (int u = 0; u < kWideSet; ++u) {
+            const int step = i0 + u;
+            if (step >= row.steps) break;                         // uniform
+            const u32x4 v = step < row.whole ? x[u] : row.counted(x[u], tid + step * kRThreads);
+            add2(v.x); add2(v.y); add2(v.z); add2(v.w);
+        }
+    };
+#pragma unroll 1
+    for (int i0 = 0; i0 < row.steps; i0 += 2 * kWideSet) {
+        count(x, i0);
+        row.template request_ahead<kWideSet>(x, i0 + 2 * kWideSet, tid);
+        count(y, i0 + kWideSet);
+        row.template request_ahead<kWideSet>(y, i0 + 3 * kWideSet, tid);
     }
     __syncthreads();
 }
@@ -545,12 +549,19 @@ static __device__ __forceinline__ void wide_row(const Row& row, const Restricted
     // counts the window and scans it; (C, M) = what lies above it on entry, with it on return
     auto scan = [&](WideWindow win, View& vw, int& C, double& M) {
         wide_count(row, win, resident, hist, tid);
+        // my levels: one binade, and one aligned run of words up to the exchange in wide_place
+        uint32_t cnt[kOwnW];
+        const int p0 = win.pattern(kOwnW * tid), run = p0 & 0x3FFF & ~(kOwnW - 1);
+        const int exchange = run / kOwnW % 32 ^ (win.w < 2 ? kOwnW - 1 : 0);
+        const bool numbers = ((p0 >> 7) & 0xFF) != 0xFF;
+#pragma unroll
+        for (int j = 0; j < kOwnW; ++j) cnt[j] = hist[run ^ exchange ^ j];
         vw.Cl = 0; vw.top = kOwnW;
-#pragma unroll 8
+#pragma unroll
         for (int j = kOwnW - 1; j >= 0; --j) {
-            const uint32_t n = count_of(win, kOwnW * tid + j);
-            vw.Cl += (int)n;
-            if (n != 0u) vw.top = j;
+            if (!numbers) cnt[j] = 0u;
+            vw.Cl += (int)cnt[j];
+            if (cnt[j] != 0u) vw.top = j;
         }
         const int p_top = win.pattern(kOwnW * tid + (vw.Cl > 0 ? vw.top : 0));
         if (!have_z1) {
@@ -560,8 +571,7 @@ static __device__ __forceinline__ void wide_row(const Row& row, const Restricted
             const float best = row16_max(sh.wave_top[lane & (kRWaves - 1)]);
             if (best >= 0.0f) { have_z1 = true; z1 = (double)value_of_pattern(pattern_of_key((int)best)); }
         }
-        own_mass<kOwnW, 8>(vw, (p_top >> 7) & 0xFF, value_of_pattern(p_top), z1, inv_tau,
-                        [&](int j) { return count_of(win, kOwnW * tid + j); });
+        own_mass<kOwnW, kOwnW>(vw, (p_top >> 7) & 0xFF, value_of_pattern(p_top), z1, inv_tau, [&](int j) { return cnt[j]; });
         int Ct;
         double Mt;
         scan_view(vw, C, M, kRThreads, Ct, Mt, sh, tid);

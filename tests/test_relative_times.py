@@ -138,3 +138,18 @@ def test_few_rows_without_large_positive_values_cost_no_sweeps(kind):
     other = us(_nucleus(x))
     print(f"8 rows, top-p 0.9: ordinary {ordinary:.1f} us, {kind} {other:.1f} us")
     assert other < 3.0 * ordinary
+
+
+@pytest.mark.parametrize("rows,V,most", [(8, 32_000, 4.9), (100, 70_000, 5.4)])
+def test_rows_that_are_swept_over_all_patterns(rows, V, most):
+    # 500 columns of 2^-24 to 2^-60: 42 and 60 us (ordinary rows 11.5 and 15.7); 76 and 124 when a sweep waited for its own
+    # requests and every level's counter was looked up twice by half as many threads as before (70 and 108)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.randn((rows, V), generator=g, device=DEV) * 3
+    ordinary = us(_nucleus(x))
+    for row in x:
+        cols = torch.randperm(V, generator=g, device=DEV)[:500]
+        row[cols] = 2.0 ** -torch.randint(24, 60, (500,), generator=g, device=DEV).float()
+    small = us(_nucleus(x))
+    print(f"{rows} x {V}, top-p 0.9: ordinary {ordinary:.1f} us, 500 small columns {small:.1f} us")
+    assert small < most * ordinary
