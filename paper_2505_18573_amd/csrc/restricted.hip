@@ -66,8 +66,8 @@
 // window, columns below it that still weigh something (a mask of -1e4 at tau above 178) - is redone
 // over all patterns with 32-bit counters, in four windows of 16,384 patterns in rank order, one
 // sweep each; a cut or the race needs its window swept again unless it was the last.  Slow (up
-// to ten sweeps), exact, rare: ordinary logits with 500 columns of 2^-24 to 2^-60 among them 110 / 216 us at 8 /
-// 512 rows, half of 400,000 columns equal 519 us at 8 rows.  Its code is inlined
+// to ten sweeps), exact, rare: ordinary logits with 500 columns of 2^-24 to 2^-60 among them 86 / 148 us at 8 /
+// 512 rows, the first half of 400,000 columns equal 345 us at 8 rows.  Its code is inlined
 // although few rows run it: as a function of its own the calling convention cost every row scratch
 // memory (8 ordinary rows 25 -> 31 us, 512 rows 45 -> 63 us).
 #include "vocab_common.h"
@@ -493,7 +493,8 @@ static __device__ __forceinline__ uint32_t wide_place(uint32_t p) { return (p & 
 
 // `resident` is the window that the counters hold already (-1: none).  Two sets of requests in flight and two patterns
 // at a time, as in near_count: relative to the window's quadrant its own patterns have no high bits, and a minimum sends all
-// others to the lane's spare word (8 x 151,936, 500 small columns: XXX).
+// others to the lane's spare word (8 x 151,936, top-p 0.9, with 500 small columns: 137 us when eight requests were waited for
+// and then counted, 118 so).
 static __device__ __forceinline__ void wide_count(const Row& row, WideWindow win, int& resident, uint32_t* hist, int tid)
 {
     __syncthreads();
@@ -549,7 +550,9 @@ static __device__ __forceinline__ void wide_row(const Row& row, const Restricted
     // counts the window and scans it; (C, M) = what lies above it on entry, with it on return
     auto scan = [&](WideWindow win, View& vw, int& C, double& M) {
         wide_count(row, win, resident, hist, tid);
-        // my levels: one binade, and one aligned run of words up to the exchange in wide_place
+        // My levels, read once: one binade, and one aligned run of words up to the exchange in wide_place.  (Each one's place
+        // and exponent worked out anew, for the count and for the mass, in a loop of eight: the 118 us above, 86 so; one copy of
+        // this code for all sweeps instead of three: 5 us more.)
         uint32_t cnt[kOwnW];
         const int p0 = win.pattern(kOwnW * tid), run = p0 & 0x3FFF & ~(kOwnW - 1);
         const int exchange = run / kOwnW % 32 ^ (win.w < 2 ? kOwnW - 1 : 0);
