@@ -202,6 +202,11 @@ def e3_workspace_bytes(rows: int, V: int) -> int:
     return int(lib().e3_workspace_bytes(rows, V))
 
 
+def e3_restricted_workspace_bytes(dtype: int, rows: int, V: int, top_k: int) -> int:
+    """Host-only.  dtype: E3_BF16 or E3_F32.  0: e3_sample_restricted has no use for a workspace."""
+    return int(lib().e3_restricted_workspace_bytes(dtype, rows, V, top_k))
+
+
 def new_workspace(rows: int, V: int, device) -> Optional[torch.Tensor]:
     """Allocate a workspace for a [rows, V] problem (None when none is needed)."""
     need = e3_workspace_bytes(rows, V)
@@ -280,14 +285,21 @@ def e3_sample_restricted(logits: torch.Tensor, tau_rows: Optional[torch.Tensor],
                          top_k: int, top_p: float, seed: int, row_base: int = 0,
                          token_out: Optional[torch.Tensor] = None,
                          logp_out: Optional[torch.Tensor] = None,
-                         kept_out: Optional[torch.Tensor] = None):
+                         kept_out: Optional[torch.Tensor] = None,
+                         workspace=None):
     """Returns (token int32 [rows], logp fp32 [rows], kept int32 [rows]).  bf16 rows: any
-    top_k / top_p; fp32 rows: 1 <= top_k <= 256 (E3_ERR_VALUE otherwise)."""
-    out = _ordinary("restricted", logits, tau_rows, tau_scalar, top_k, top_p, seed, row_base, token_out, logp_out, kept_out)
+    top_k / top_p; fp32 rows: 1 <= top_k <= 256 (E3_ERR_VALUE otherwise).
+
+    workspace: a tensor of e3_restricted_workspace_bytes() to use, with which few wide rows are spread over
+    workgroups, or False for none (a row then stays in one workgroup).  None: a call that allocates outputs allocates it
+    too, if there is memory; a call that is given all of its outputs allocates nothing."""
+    out = _ordinary("restricted", logits, tau_rows, tau_scalar, top_k, top_p, seed, row_base, token_out, logp_out, kept_out,
+                    workspace)
     if out is not None:
         return out
     dt, rows, V, stride = _logits_meta(logits)
     dev = logits.device
+    may_allocate = token_out is None or logp_out is None or kept_out is None
     if token_out is None:
         token_out = torch.empty(rows, dtype=torch.int32, device=dev)
     else:
@@ -302,8 +314,17 @@ def e3_sample_restricted(logits: torch.Tensor, tau_rows: Optional[torch.Tensor],
         _check(kept_out, torch.int32, rows, "kept_out", dev)
     _check(tau_rows, torch.float32, rows, "tau_rows", dev)
     L, top_k = lib(), int(top_k)
-    ws_bytes = L.e3_restricted_workspace_bytes(dt, rows, V, top_k)
-    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev) if ws_bytes else None
+    if workspace is None and may_allocate:
+        need = L.e3_restricted_workspace_bytes(dt, rows, V, top_k)
+        try:
+            workspace = torch.empty(need, dtype=torch.uint8, device=dev) if need else False
+        except torch.OutOfMemoryError:
+            workspace = False
+    elif workspace is None:
+        workspace = False
+    elif workspace is not False and (workspace.device != dev or not workspace.is_contiguous()):
+        raise ValueError(f"workspace must be a contiguous tensor on {dev}")
+    ws, ws_bytes = _workspace(rows, V, workspace, dev)
     rc = L.e3_sample_restricted_ws(_ptr(logits), dt, rows, V, stride, _ptr(tau_rows),
                                    float(tau_scalar), top_k, float(top_p), int(seed),
                                    int(row_base), _ptr(token_out), _ptr(logp_out), _ptr(kept_out),

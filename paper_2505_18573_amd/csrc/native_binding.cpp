@@ -11,6 +11,7 @@
 
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <c10/util/Exception.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/e3.h"
@@ -167,7 +168,20 @@ struct Workspace {
         p = t->data_ptr();
         bytes = (size_t)t->numel() * t->element_size();
     }
-    Workspace(Reader& r, size_t need) { make(r, need); }
+    // The restricted sampler's: None allocates what is needed where `may_allocate`, and goes without where the memory is not there.
+    Workspace(Reader& r, PyObject* o, size_t need, bool may_allocate)
+    {
+        if (o == Py_False) return;
+        if (o == Py_None) {
+            if (!may_allocate) return;
+            try { make(r, need); } catch (const c10::OutOfMemoryError&) { own = at::Tensor(); p = nullptr; bytes = 0; }
+            return;
+        }
+        const at::Tensor* t = r.plain(o);
+        if (t == nullptr || t->device() != r.dev || !t->is_contiguous()) { r.ok = false; return; }
+        p = t->data_ptr();
+        bytes = (size_t)t->numel() * t->element_size();
+    }
 };
 
 PyObject* unusual() { Py_RETURN_NONE; }
@@ -268,10 +282,10 @@ PyObject* sample(PyObject*, PyObject* const* a, Py_ssize_t n_args)
     });
 }
 
-// logits, tau_rows, tau_scalar, top_k, top_p, seed, row_base, token_out, logp_out, kept_out
+// logits, tau_rows, tau_scalar, top_k, top_p, seed, row_base, token_out, logp_out, kept_out, workspace
 PyObject* restricted(PyObject*, PyObject* const* a, Py_ssize_t n_args)
 {
-    if (n_args != 10) return unusual();
+    if (n_args != 11) return unusual();
     return guarded([&]() -> PyObject* {
         Reader r;
         const Logits l(r, a[0]);
@@ -285,7 +299,8 @@ PyObject* restricted(PyObject*, PyObject* const* a, Py_ssize_t n_args)
         token.take_or_make(r, a[7], at::kInt, l.rows);
         logp.take_or_make(r, a[8], at::kFloat, l.rows);
         kept.take_or_make(r, a[9], at::kInt, l.rows);
-        const Workspace ws(r, p_restricted_bytes(l.dtype, l.rows, l.V, top_k));
+        const bool may_allocate = a[7] == Py_None || a[8] == Py_None || a[9] == Py_None;
+        const Workspace ws(r, a[10], p_restricted_bytes(l.dtype, l.rows, l.V, top_k), may_allocate);
         return run(r, [&](void* s) {
                        return p_restricted(l.p, l.dtype, l.rows, l.V, l.pitch, (const float*)tau, (float)tau_scalar, top_k, (float)top_p, seed,
                                            row_base, (int32_t*)token.p, (float*)logp.p, (int32_t*)kept.p, ws.p, ws.bytes, s);

@@ -64,3 +64,35 @@ def test_replays_match_eager(rows_per_prompt):
         torch.cuda.synchronize()
         for name in eager:
             assert torch.equal(out[name], eager[name]), (replay, name)
+
+
+@pytest.mark.parametrize("held", [True, False])
+def test_replays_of_rows_cut_into_slices(held):
+    # two launches that share a workspace: the caller's, or one that torch allocates within the capture
+    g = torch.Generator(device=DEV).manual_seed(3)
+    lg = (torch.randn((8, 65_536), generator=g, device=DEV) * 3).to(torch.bfloat16)
+    need = e3.e3_restricted_workspace_bytes(e3.E3_BF16, 8, 65_536, 0)
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV) if held else None
+    out = [torch.empty(8, dtype=t, device=DEV) for t in (torch.int32, torch.float32, torch.int32)] if held else [None] * 3
+    run = lambda: e3.e3_sample_restricted(lg, None, 1.0, 0, 0.9, 4, 9, *out, workspace=ws)
+    want = [x.clone() for x in run()]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        run()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        got = run()
+    for replay in range(4):
+        for t in got:
+            t.zero_()
+        if held:
+            ws.fill_(0xA5)                            # what it holds on entry does not matter
+        other = torch.full((1 << 20,), 7, dtype=torch.int32, device=DEV)          # memory that the replay must leave alone
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (other == 7).all()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b), replay

@@ -57,11 +57,13 @@ def test_many_questions_cost_their_rounds_only():
 
 
 def _selection(lg, k=50, p=0.95):
-    rows = lg.shape[0]
+    rows, V = lg.shape
+    need = e3.e3_restricted_workspace_bytes(e3.E3_BF16 if lg.dtype == torch.bfloat16 else e3.E3_F32, rows, V, k)
+    workspace = torch.empty(need, dtype=torch.uint8, device=DEV) if need else False
     tok = torch.empty(rows, dtype=torch.int32, device=DEV)
     logp = torch.empty(rows, dtype=torch.float32, device=DEV)
     kept = torch.empty(rows, dtype=torch.int32, device=DEV)
-    return lambda: e3.e3_sample_restricted(lg, None, 1.0, k, p, 7, 0, tok, logp, kept)
+    return lambda: e3.e3_sample_restricted(lg, None, 1.0, k, p, 7, 0, tok, logp, kept, workspace)
 
 
 @pytest.mark.parametrize("rows", [8, 300])

@@ -513,6 +513,79 @@ def test_cut_rows_give_what_whole_rows_give(rows, V):
     check(lg, None, 1.0, 0, 0.9, 3, 9, f"cut rows {rows}x{V}")
 
 
+def _held(rows):
+    return [torch.empty(rows, dtype=t, device=DEV) for t in (torch.int32, torch.float32, torch.int32)]
+
+
+def _few_rows(rows=8, V=65_536, seed=1):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    return (torch.randn((rows, V), generator=g, device=DEV) * 3).to(torch.bfloat16)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_a_call_that_is_given_its_outputs_allocates_nothing(native, monkeypatch):
+    e3.lib()
+    if not native:
+        monkeypatch.setattr(e3.binding, "_native", None)
+    lg = _few_rows()
+    need = e3.e3_restricted_workspace_bytes(e3.E3_BF16, *lg.shape, 0)
+    want = e3.e3_sample_restricted(lg, None, 1.0, 0, 0.9, 3)
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    allocations = lambda: torch.cuda.memory_stats()["allocation.all.allocated"]
+    for workspace in (None, False, ws):
+        out = _held(8)
+        before = allocations()
+        got = e3.e3_sample_restricted(lg, None, 1.0, 0, 0.9, 3, 0, *out, workspace=workspace)
+        assert allocations() == before
+        assert all(a is b for a, b in zip(got, out))
+        assert torch.equal(got[0], want[0]) and torch.equal(got[2], want[2])
+        assert torch.allclose(got[1], want[1], rtol=1e-6, atol=1e-7)
+    for bad in (ws.cpu(), ws[::2]):                   # a workspace that the launch could not use
+        with pytest.raises(ValueError):
+            e3.e3_sample_restricted(lg, None, 1.0, 0, 0.9, 3, workspace=bad)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_few_rows_without_memory_for_a_workspace(native, monkeypatch):
+    e3.lib()
+    if not native:
+        monkeypatch.setattr(e3.binding, "_native", None)
+    lg = _few_rows(64, 262_144)
+    need = e3.e3_restricted_workspace_bytes(e3.E3_BF16, 64, 262_144, 0)
+    want = [x.clone() for x in e3.e3_sample_restricted(lg, None, 1.0, 0, 0.9, 3, 0, *_held(64))]
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-9)          # torch's allocator gets no further memory
+    held = []
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            for _ in range(1000):                             # what it has left in large pieces
+                held.append(torch.empty(need, dtype=torch.uint8, device=DEV))
+        got = e3.e3_sample_restricted(lg, None, 1.0, 0, 0.9, 3, 0, *_held(64)[:2])       # allocates one small output
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)                              # whole rows either way
+
+
+@pytest.mark.gpu
+def test_cut_rows_on_two_streams():
+    # each call with a workspace of its own, from torch: many calls in flight on both streams give what single ones do
+    batches = [_few_rows(8, 70_001 // 8 * 8, seed) for seed in range(4)]
+    want = [[x.clone() for x in e3.e3_sample_restricted(lg, None, 1.0, 0, 0.9, 3)] for lg in batches]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    got = []
+    for i in range(40):
+        with torch.cuda.stream(streams[i % 2]):
+            got.append(e3.e3_sample_restricted(batches[i % 4], None, 1.0, 0, 0.9, 3))
+    torch.cuda.synchronize()
+    for i, out in enumerate(got):
+        for a, b in zip(out, want[i % 4]):
+            assert torch.equal(a, b), i
+
+
 def test_workspace_of_cut_rows_needs_no_gpu():
     need = e3.lib().e3_restricted_workspace_bytes
     assert need(e3.E3_BF16, 8, 151_936, 0) == 8 * 8 * (16_384 + 544)
