@@ -146,3 +146,72 @@ def test_every_load_raises_while_a_library_is_missing(monkeypatch, tmp_path):
                 e3.lib()
             with pytest.raises(ImportError):
                 e3.e3_temperature_update(1.0, 0.5, 0.6, 1000)
+
+
+# Every output and workspace given by the caller; the names are those of _ENTRY's calls.
+HELD = ["sample", "restricted", "logprob", "both", "advantages", "objective"]
+
+
+def _held_calls(name, dev):
+    f, kw = _calls(dev)[name]
+    rows, V = kw["logits"].shape if "logits" in kw else (6, 0)
+    f32 = lambda: torch.empty(rows, dtype=torch.float32, device=dev)
+    i32 = lambda: torch.empty(rows, dtype=torch.int32, device=dev)
+    if name == "sample":
+        kw.update(token_out=i32(), logp_out=f32(), entropy_out=f32(), workspace=e3.new_workspace(rows, V, dev))
+    elif name == "restricted":
+        kw.update(logits=torch.cat([kw["logits"], kw["logits"]], 1), token_out=i32(), logp_out=f32(), kept_out=i32())
+        need = e3.e3_restricted_workspace_bytes(e3.E3_BF16, rows, 2 * V, kw["top_k"])
+        assert need > 0
+        kw.update(workspace=torch.empty(need, dtype=torch.uint8, device=dev))
+    elif name == "logprob":
+        kw.update(logp_out=f32(), entropy_out=f32(), entropy_sum_out=torch.empty(1, dtype=torch.float64, device=dev),
+                  entropy_count_out=torch.empty(1, dtype=torch.int64, device=dev), workspace=e3.new_workspace(rows, V, dev))
+    elif name == "both":
+        kw.update(logp_out=f32(), entropy_out=f32(), adv_out=f32(), row_mask=torch.ones(rows, dtype=torch.uint8, device=dev),
+                  tau_rows=f32().fill_(0.8), entropy_sum_out=torch.empty(1, dtype=torch.float64, pin_memory=True),
+                  entropy_count_out=torch.empty(1, dtype=torch.int64, pin_memory=True), workspace=e3.new_workspace(rows, V, dev))
+    elif name == "advantages":
+        kw.update(adv_out=f32())
+    return f, kw
+
+
+def _refused(name, kw):
+    """One tensor at a time replaced by one that the checks on the host refuse."""
+    for key, v in kw.items():
+        if not torch.is_tensor(v):
+            continue
+        if key == "workspace":
+            if name == "restricted":                  # (elsewhere any tensor is taken)
+                yield dict(kw, workspace=v.cpu())
+                yield dict(kw, workspace=v.repeat_interleave(2)[::2])
+            continue
+        yield dict(kw, **{key: v.to(torch.float16)})
+        if v.numel() > 1:
+            yield dict(kw, **{key: v.repeat_interleave(2, -1)[..., ::2]})
+        yield dict(kw, **{key: v.cpu()} if v.is_cuda else {key: v.clone()})          # on the host, and not pinned
+        yield dict(kw, **{key: 5})
+        yield dict(kw, **{key: torch.cat([v, v], -1)} if v.dim() == 1 and key not in ("rewards", "group_offsets") else {key: v[None]})
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", HELD)
+def test_given_outputs_and_what_the_checks_refuse(name, monkeypatch):
+    f, kw = _held_calls(name, DEV)
+    given = [v for k, v in kw.items() if k.endswith("_out")]
+    want = [x if x is None else x.clone() for x in _outcome(f, kw, monkeypatch, native=False)]
+    for t in given:
+        t.zero_()
+    got = _outcome(f, kw, monkeypatch, native=True)
+    assert not isinstance(got[0], type) and all(any(t is x for x in got) for t in given)
+    for a, b in zip(got, want):
+        assert b is None or torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    sub = dict(kw, **{k: v.as_subclass(Sub) for k, v in kw.items() if torch.is_tensor(v) and not k.endswith("_out")})
+    for a, b in zip(_outcome(f, sub, monkeypatch, native=True), want):
+        assert b is None or torch.equal(a.as_subclass(torch.Tensor).view(torch.uint8), b.view(torch.uint8))
+    n = 0
+    for bad in _refused(name, kw):
+        refused, native = (_outcome(f, bad, monkeypatch, native=x) for x in (False, True))
+        assert isinstance(refused[0], type) and native == refused, (bad, refused, native)
+        n += 1
+    assert n >= 8
