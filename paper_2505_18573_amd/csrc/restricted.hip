@@ -72,6 +72,7 @@
 // memory (8 ordinary rows 25 -> 31 us, 512 rows 45 -> 63 us).
 #include "vocab_common.h"
 #include "vocab_pass.h"
+#include "wave_scan.h"
 
 namespace e3 {
 namespace {
@@ -222,33 +223,6 @@ static __device__ __forceinline__ void for_each_pattern(const u32x4& v, F&& f)
     f(v.z & 0xFFFFu, 4); f(v.z >> 16, 5); f(v.w & 0xFFFFu, 6); f(v.w >> 16, 7);
 }
 
-// Inclusive prefix sums over the lanes of a wave (see wave_max for the steps).
-template <typename T, typename Step>
-static __device__ __forceinline__ T wave_prefix(T v, Step&& step)
-{
-    v += step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{}, v);    // row_shr 1, 2, 4, 8
-    v += step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{}, v);
-    v += step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{}, v);
-    v += step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{}, v);
-    v += step(std::integral_constant<int, kDppBcast15>{}, std::integral_constant<int, 0xA>{}, v);
-    v += step(std::integral_constant<int, kDppBcast31>{}, std::integral_constant<int, 0xC>{}, v);
-    return v;
-}
-static __device__ __forceinline__ int wave_prefix_i(int v)
-{
-    return wave_prefix(v, [](auto c, auto m, int x) { return dpp_i<decltype(c)::value, decltype(m)::value>(0, x); });
-}
-static __device__ __forceinline__ double wave_prefix_d(double v)
-{
-    return wave_prefix(v, [](auto c, auto m, double x) { return dpp_d<decltype(c)::value, decltype(m)::value>(0.0, x); });
-}
-
-static __device__ __forceinline__ double lane_value(double v, int lane)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                            __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-
 // A thread's levels after the scan: levels of one binade in falling rank order, `top` the first
 // with columns (weight w_top, at most 1), each later one `r` times the weight of the one before.
 struct View {
@@ -289,16 +263,16 @@ static __device__ __forceinline__ void scan_view(View& vw, int carry_C, double c
     const int lane = tid & 63, wave = tid >> 6;
     int Ci = 0;
     double Mi = 0.0;
-    if (__any(vw.Cl > 0)) { Ci = wave_prefix_i(vw.Cl); Mi = wave_prefix_d(vw.Ml); }
+    if (__any(vw.Cl > 0)) { Ci = wave_prefix_sum(vw.Cl); Mi = wave_prefix_sum(vw.Ml); }
     if (lane == 63) { sh.wave_C[wave] = Ci; sh.wave_M[wave] = Mi; }
     __syncthreads();
-    const int tC = wave_prefix_i(lane < kRWaves ? sh.wave_C[lane] : 0);
-    const double tM = wave_prefix_d(lane < kRWaves ? sh.wave_M[lane] : 0.0);
+    const int tC = wave_prefix_sum(lane < kRWaves ? sh.wave_C[lane] : 0);
+    const double tM = wave_prefix_sum(lane < kRWaves ? sh.wave_M[lane] : 0.0);
     Ct = __builtin_amdgcn_readlane(tC, kRWaves - 1);
-    Mt = lane_value(tM, kRWaves - 1);
+    Mt = read_lane(tM, kRWaves - 1);
     int Cb = carry_C;
     double Mb = carry_M;
-    if (wave > 0) { Cb += __builtin_amdgcn_readlane(tC, wave - 1); Mb += lane_value(tM, wave - 1); }
+    if (wave > 0) { Cb += __builtin_amdgcn_readlane(tC, wave - 1); Mb += read_lane(tM, wave - 1); }
     if (tid >= mid_at) { Cb += sh.mid_C[63]; Mb += sh.mid_M[63]; }
     vw.Cx = Cb + Ci - vw.Cl;
     vw.Mx = Mb + (Mi - vw.Ml);
@@ -336,7 +310,7 @@ static __device__ __forceinline__ void offer_mass_cut(const View& vw, double T, 
     const int lane = tid & 63, wave = tid >> 6;
     const unsigned long long reach = __ballot(vw.Cl > 0 && vw.Mx + vw.Ml >= T);
     // (a wave with clearly more than T above it cannot be the lowest)
-    if (reach == 0ull || lane_value(vw.Mx, 0) > T * (1.0 + 1e-9)) {
+    if (reach == 0ull || read_lane(vw.Mx, 0) > T * (1.0 + 1e-9)) {
         if (lane == 0) sh.cut_key[wave] = -1;
         return;
     }
@@ -344,14 +318,14 @@ static __device__ __forceinline__ void offer_mass_cut(const View& vw, double T, 
     const int rank = kOwn * (wave * 64 + owner) + lane;
     const int n = lane < kOwn ? (int)count_at(rank) : 0;
     const int e = lane - __builtin_amdgcn_readlane(vw.top, owner);        // lanes before the owner's top level have n == 0
-    double w = lane_value(vw.w_top, owner), r = lane_value(vw.r, owner);
+    double w = read_lane(vw.w_top, owner), r = read_lane(vw.r, owner);
 #pragma unroll
     for (int bit = 1; bit < kOwn; bit <<= 1) {
         if (e > 0 && (e & bit) != 0) w *= r;
         r *= r;
     }
-    const int C = __builtin_amdgcn_readlane(vw.Cx, owner) + wave_prefix_i(n);
-    const double M = lane_value(vw.Mx, owner) + wave_prefix_d(n != 0 ? (double)n * w : 0.0);
+    const int C = __builtin_amdgcn_readlane(vw.Cx, owner) + wave_prefix_sum(n);
+    const double M = read_lane(vw.Mx, owner) + wave_prefix_sum(n != 0 ? (double)n * w : 0.0);
     const unsigned long long have = __ballot(n != 0), enough = __ballot(n != 0 && M >= T);
     const int at = enough != 0ull ? (int)__builtin_ctzll(enough) : 63 - (int)__builtin_clzll(have);
     if (lane == at) { sh.cut_key[wave] = key_at(rank); sh.cut_C[wave] = C; sh.cut_M[wave] = M; }
@@ -425,7 +399,7 @@ static __device__ __forceinline__ void locate(const Row& row, int col0, int i0, 
                 uint32_t m = 0u;
                 for_each_pattern(x[u], [&](uint32_t p, int j) { m |= (uint32_t)(p == pat) << j; });
                 if (step >= row.whole) m = v < row.nvec - 1 ? m : v == row.nvec - 1 ? m & (0xFFu >> (8 - row.last)) : 0u;
-                const int upto = wave_prefix_i(__popc(m));
+                const int upto = wave_prefix_sum((int)__popc(m));
                 found[u] = (uint32_t)upto << 8 | m;
                 total = __builtin_amdgcn_readlane(upto, 63);
             }
@@ -437,7 +411,7 @@ static __device__ __forceinline__ void locate(const Row& row, int col0, int i0, 
         static_assert(kBlock * kRWaves <= 128 && kBlock * kRWaves % 2 == 0, "two totals per lane");
         const bool some = 2 * lane < kBlock * kRWaves;
         const int t0 = some ? sh.tot[2 * lane] : 0, t1 = some ? sh.tot[2 * lane + 1] : 0;
-        const int upto = wave_prefix_i(t0 + t1);
+        const int upto = wave_prefix_sum(t0 + t1);
         const unsigned long long past = __ballot(upto > rem);
         if (past != 0ull) {                                       // uniform over the workgroup
             const int l = (int)__builtin_ctzll(past);
@@ -816,14 +790,14 @@ static __device__ __forceinline__ void note_outside(const u32x4& x, int col0, bo
 static __device__ __forceinline__ void hand_zeros(Tally& t, int quarter, Shared& sh, int lane)
 {
     if (!__any(t.zeros != 0u)) return;
-    const uint32_t p = (uint32_t)wave_prefix_i((int)(t.zeros & 0xFFFFu)), n = (uint32_t)wave_prefix_i((int)(t.zeros >> 16));
+    const uint32_t p = (uint32_t)wave_prefix_sum((int)(t.zeros & 0xFFFFu)), n = (uint32_t)wave_prefix_sum((int)(t.zeros >> 16));
     if (lane == 63) { atomicAdd(&sh.zeros[0][quarter], (int)p); atomicAdd(&sh.zeros[1][quarter], (int)n); }
     t.zeros = 0u;
 }
 static __device__ __forceinline__ void hand_rest(const Tally& t, int base, Shared& sh, int lane)
 {
     if (!__any((t.far | t.odd) != 0u)) return;
-    const int below = wave_prefix_i((int)(t.far & 0xFFFFu)), above = wave_prefix_i((int)(t.far >> 16)), odd = wave_prefix_i((int)t.odd);
+    const int below = wave_prefix_sum((int)(t.far & 0xFFFFu)), above = wave_prefix_sum((int)(t.far >> 16)), odd = wave_prefix_sum((int)t.odd);
     if (lane == 63) { atomicAdd(&sh.n_below, below); atomicAdd(&sh.n_above, above); atomicAdd(&sh.n_not_finite, odd); }
     const int end1 = base + kLevels - 1;
     auto most = [](u16x2 a) -> float { return (float)(a.x > a.y ? a.x : a.y); };
@@ -1095,9 +1069,9 @@ static __device__ __forceinline__ int gather_slices(const RestrictedArgs& a, int
         const SliceNotes* n = a.slice_notes + r * a.nslices + (lane < a.nslices ? lane : 0);
         const bool mine = lane < a.nslices;
         const int list_n = mine ? n->list_n : 0;
-        const int lists = wave_prefix_i(list_n);
-        const int zero_p = wave_prefix_i(mine ? n->zeros[0] : 0), zero_n = wave_prefix_i(mine ? n->zeros[1] : 0);
-        const int below = wave_prefix_i(mine ? n->n_below : 0), odd = wave_prefix_i(mine ? n->n_not_finite : 0);
+        const int lists = wave_prefix_sum(list_n);
+        const int zero_p = wave_prefix_sum(mine ? n->zeros[0] : 0), zero_n = wave_prefix_sum(mine ? n->zeros[1] : 0);
+        const int below = wave_prefix_sum(mine ? n->n_below : 0), odd = wave_prefix_sum(mine ? n->n_not_finite : 0);
         const float lo = -wave_max(mine ? -(float)n->below_lo : -32767.0f), hi = wave_max(mine ? (float)n->below_hi : 0.0f);
         const int above = (int)wave_max(mine ? (float)n->above_hi : 0.0f), all_listed = __builtin_amdgcn_readlane(lists, 63);
         if (lane == 63) {
@@ -1221,8 +1195,8 @@ static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hi
         if (has_mid && wave == 0) {
             const int n = lane < n_mid ? sh.mid_cnt[lane] : 0;
             const double w = n != 0 ? exp(((double)value_of_pattern(pattern_of_key(sh.mid_key[lane])) - z_ref) * inv_tau) : 0.0;
-            sh.mid_C[lane] = wave_prefix_i(n);
-            sh.mid_M[lane] = wave_prefix_d((double)n * w);
+            sh.mid_C[lane] = wave_prefix_sum(n);
+            sh.mid_M[lane] = wave_prefix_sum((double)n * w);
         }
         scan_view(vw, 0, 0.0, has_mid ? kRThreads / 2 : kRThreads, C_win, M_win, sh, tid);
         top_key = row16_max(sh.wave_top[lane & (kRWaves - 1)]);
@@ -1261,7 +1235,7 @@ static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hi
         bool level_end = false;
         if (has_mid && wave == kMidWave) {
             C0 = __builtin_amdgcn_readfirstlane(vw.Cx) - mid_C;
-            M0 = lane_value(vw.Mx, 0) - mid_M;
+            M0 = read_lane(vw.Mx, 0) - mid_M;
             level_end = lane < n_mid && sh.mid_cnt[lane] != 0
                      && (lane == n_mid - 1 || sh.mid_key[lane + 1] != sh.mid_key[lane]);
         }
@@ -1340,7 +1314,7 @@ static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hi
             if (lane < a.nslices)
                 n = mag < win.base ? a.slice_notes[r * a.nslices + lane].zeros[pattern >> 15]
                                    : a.slice_counts[((size_t)r * a.nslices + lane) * kArray + win.slot_of_pattern(pattern)];
-            const int upto = wave_prefix_i(n);
+            const int upto = wave_prefix_sum(n);
             const int rem = pick(__builtin_amdgcn_readlane(upto, 63));
             const unsigned long long past = __ballot(upto > rem);
             const int s = past != 0ull ? (int)__builtin_ctzll(past) : 0;

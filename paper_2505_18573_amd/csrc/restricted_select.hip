@@ -33,6 +33,7 @@
 // case - inside one wave with the kept columns one per lane (finish_in_one_wave below).
 #include "vocab_common.h"
 #include "vocab_pass.h"
+#include "wave_scan.h"
 
 namespace e3 {
 namespace {
@@ -126,32 +127,6 @@ struct alignas(16) SelShared {
 
 static_assert(offsetof(SelShared, gt_key) % 16 == 0 && offsetof(SelShared, gt_col) % 16 == 0, "read four at a time");
 
-// Inclusive prefix sum over the lanes of a wave: four shifts inside each row of sixteen lanes,
-// then lane 15 of a row into the next row and lane 31 into the upper half (lanes a shift does
-// not reach read zero).
-__device__ __forceinline__ int wave_prefix_sum(int v)
-{
-    v += dpp_i<0x111>(0, v);               // row_shr:1
-    v += dpp_i<0x112>(0, v);               // row_shr:2
-    v += dpp_i<0x114>(0, v);               // row_shr:4
-    v += dpp_i<0x118>(0, v);               // row_shr:8
-    v += dpp_i<kDppBcast15, 0xA>(0, v);
-    v += dpp_i<kDppBcast31, 0xC>(0, v);
-    return v;
-}
-
-// Inclusive prefix sum in fp64, by the same steps as wave_prefix_sum.
-__device__ __forceinline__ double wave_prefix_sum_f64(double v)
-{
-    v += dpp_d<0x111>(0.0, v);
-    v += dpp_d<0x112>(0.0, v);
-    v += dpp_d<0x114>(0.0, v);
-    v += dpp_d<0x118>(0.0, v);
-    v += dpp_d<kDppBcast15, 0xA>(0.0, v);
-    v += dpp_d<kDppBcast31, 0xC>(0.0, v);
-    return v;
-}
-
 // One 8-bit pass of a radix select for the k-th largest: every thread has added its keys
 // that match `prefix` above `shift + 8` to hist; wave 0 finds the digit that holds rank k_rem.
 __device__ __forceinline__ void select_digit(SelShared& sh, int tid)
@@ -206,12 +181,6 @@ struct SelArgs {
 // ---------------------------------------------------------------------------
 constexpr int kSoloList = 256;
 constexpr int kSoloK = 64;
-
-__device__ __forceinline__ double read_lane_f64(double v, int src_lane)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src_lane),
-                            __builtin_amdgcn_readlane(__double2loint(v), src_lane));
-}
 
 template <typename T>
 __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& sh, const uint32_t* lkey,
@@ -314,8 +283,8 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
     const double z1 = (double)__uint_as_float(f32_of_key(key1));
     const double z_cut = (double)__uint_as_float(f32_of_key(kappa));
     const double w = have ? exp(((double)__uint_as_float(f32_of_key(skey)) - z1) * inv_tau) : 0.0;
-    const double M = wave_prefix_sum_f64(w);                        // inclusive prefix mass
-    const double M_gt = n > 0 ? read_lane_f64(M, n - 1) : 0.0;
+    const double M = wave_prefix_sum(w);                            // inclusive prefix mass
+    const double M_gt = n > 0 ? read_lane(M, n - 1) : 0.0;
     const double w_cut = exp((z_cut - z1) * inv_tau);
     const double M_k = M_gt + (double)n_cut * w_cut;               // mass of the top-k set
     constexpr int kNextLane = 0x130, kPrevLane = 0x138;             // wave_shl:1, wave_shr:1
@@ -332,7 +301,7 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
     const bool cut_level_kept = cut_index == kSMaxK;
     const int kept_sorted = cut_level_kept ? n : cut_index + 1;    // sorted entries kept
     const int kept_C = cut_level_kept ? n + n_cut : kept_sorted;
-    const double ln_M = log(cut_level_kept ? M_k : read_lane_f64(M, cut_index));
+    const double ln_M = log(cut_level_kept ? M_k : read_lane(M, cut_index));
 
     // race of the kept levels: a level's first lane scores it, lane 63 scores the cut level
     const bool level_start = have && (lane == 0 || prev_key != skey);
@@ -838,7 +807,7 @@ void sample_select_kernel(SelArgs a)
             w[j] = i < n ? sh.st_M[i] : 0.0;
             loc += w[j];
         }
-        double run = wave_prefix_sum_f64(loc) - loc;
+        double run = wave_prefix_sum(loc) - loc;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int i = 4 * tid + j;
