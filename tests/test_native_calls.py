@@ -215,3 +215,35 @@ def test_given_outputs_and_what_the_checks_refuse(name, monkeypatch):
         assert isinstance(refused[0], type) and native == refused, (bad, refused, native)
         n += 1
     assert n >= 8
+
+
+# Logits in every layout that the checks let through, and two that they do not.
+LAYOUTS = {
+    "no rows": lambda x: x[:0],
+    "one column": lambda x: x.as_strided((6, 1), (40_000, 8)),
+    "one row, short pitch": lambda x: x.as_strided((1, 40_000), (8, 1)),
+    "wide pitch": lambda x: x.repeat(1, 2)[:, :39_991],
+    "few wide rows": lambda x: x.repeat(1, 4)[:, :159_997],
+    "expanded": lambda x: x[:1].expand(6, -1),
+    "misaligned pitch": lambda x: x.as_strided((5, 30_001), (30_001, 1)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("layout", list(LAYOUTS))
+def test_layouts_of_the_logits(layout, dtype, monkeypatch):
+    lg = LAYOUTS[layout](_calls(DEV)["sample"][1]["logits"].to(dtype))
+    rows = lg.shape[0]
+    tgt, mask = torch.zeros(rows, dtype=torch.int32, device=DEV), torch.ones(rows, dtype=torch.uint8, device=DEV)
+    refused = layout in ("expanded", "misaligned pitch")
+    for f, kw in [(e3.e3_sample_entropy, dict(tau_rows=None, tau_scalar=0.8, seed=5)),
+                  (e3.e3_sample_restricted, dict(tau_rows=None, tau_scalar=0.8, top_k=0, top_p=0.9, seed=5)),
+                  (e3.e3_sample_restricted, dict(tau_rows=None, tau_scalar=0.8, top_k=7, top_p=0.9, seed=5)),
+                  (e3.e3_logprob_entropy, dict(target_ids=tgt, row_mask=mask, tau_rows=None, tau_scalar=0.8))]:
+        want, got = (_outcome(f, dict(kw, logits=lg), monkeypatch, native=n) for n in (False, True))
+        if refused or (dtype == torch.float32 and kw.get("top_k") == 0):
+            assert isinstance(want[0], type) and got == want
+            continue
+        for a, b in zip(got, want):
+            assert a.shape == b.shape and torch.equal(a.view(torch.uint8), b.view(torch.uint8)), (f, kw)
