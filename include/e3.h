@@ -173,9 +173,11 @@ int e3_sample_entropy_noalloc(const void* logits, int dtype, int64_t rows, int64
  * One workgroup per row.  With 1 <= top_k <= 256 the row is read once (vectors that can hold
  * one of the k largest are listed in LDS while the row streams, exact selection among those); a
  * row with thousands of equal values at its cut is read several times.  Otherwise (bf16 only) the
- * row's stored patterns are counted in LDS: one counting sweep over 31.5 binades of both signs, a second one
- * over a higher or lower window for a row with finite logits of 512 and more that its first
- * 16,384 columns do not show, or with more than 62 columns nearer to zero than 1.5 x 2^-23 without being zero.
+ * row's stored patterns are counted in LDS: one counting sweep over a window of 31.5 binades of both signs, which ends at
+ * 512 or at one binade above what a sample of the row shows, whichever is higher.  The sample is the row's first 16,384 columns,
+ * or 32,768 where sixteen waves stream a row (at least 114,688 columns, at most one row per compute unit).  A second sweep over
+ * a higher or lower window follows for a row with finite logits above the first one, or with more than 62 columns
+ * nearer to zero than the window reaches (1.5 x 2^-23 in the usual one) without being zero.
  * The rare rows that take four to ten more sweeps, over all patterns: a second window that
  * does not hold them either; a level of 65,536 or more columns in a quarter of the row; columns below
  * -512 (or below the window) that still weigh something, i.e. that are less than 56 tau below the
@@ -192,6 +194,8 @@ int e3_sample_restricted(const void* logits, int dtype, int64_t rows, int64_t V,
  * cut into slices of columns that many workgroups read, and a second launch on the same stream
  * finishes the rows.  Without it, or with less, every row is read by one workgroup as in
  * e3_sample_restricted.  Same tokens (but for the near-ties above), counts and log-probs up to rounding in either form.
+ * The window of cut rows is chosen by 512 columns spread over the row, and also lies lower than the usual one where these
+ * hold small values only; a row that does not fit it is swept once more by one workgroup.
  * e3_restricted_workspace_bytes: host only; 0 where a workspace would not be used.
  */
 size_t e3_restricted_workspace_bytes(int dtype, int64_t rows, int64_t V, int32_t top_k);

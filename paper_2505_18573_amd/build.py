@@ -40,9 +40,10 @@ def build(verbose: bool = False, extra=()) -> str:
 
 
 def build_native(verbose: bool = False) -> str:
-    # NDEBUG: otherwise the headers bring a thread-local variable (pybind11's reference counter).  A library with
-    # thread-local storage of its own that is loaded late and never touches it makes glibc (before 2.39) take the slow way
-    # to every other library's: each torch call of the process 0.3 us longer, an allocated output 1.33 instead of 1.06 us.
+    # NDEBUG: otherwise the headers bring a thread-local variable (pybind11's reference counter).  While the library with
+    # thread-local storage that was loaded last has not touched it, glibc (before 2.39) takes the slow way to every other
+    # library's.  A vocabulary pass touches libe3.so's and ends that; with a variable here that nothing touches, each torch
+    # call of the process stayed 0.3 us longer, an allocated output 1.33 instead of 1.06 us.
     import torch
     root = os.path.dirname(torch.__file__)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-shared", "-Wall",

@@ -1,6 +1,6 @@
 // The binding's hot calls without Python between the tensors and libe3.so.  A call of a few microseconds on the GPU took as
 // long in Python: about 0.7 us per checked tensor, 0.8 to 1.4 us per foreign call, 1.1 us per allocated output.
-// One pass among others, in Python / here: 64 x 8 advantages 5.7 / 3.6 us (the kernel 3.4), the objective of 512
+// One pass among others, in Python / here: 64 x 8 advantages 5.7 / 3.6 us (the kernel 2.9), the objective of 512
 // rollouts 11.6 / 9.4 us (its kernels 8.9), a step of 512 rows, whose host work lies between two launches, 72.9 / 69.8 us.
 //
 // Every function takes the arguments of the Python function it serves, and does what that does when they are ordinary: plain

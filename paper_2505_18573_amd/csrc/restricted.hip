@@ -1377,10 +1377,11 @@ void count_slices_kernel(RestrictedArgs a)
 constexpr int64_t kFewWide = 114'688;
 
 // Slices of a row, 0: not cut.  Eight (sixteen where the columns of an eighth would not fit 16-bit counters) for rows of at
-// least kSliceMinV columns and 4096 columns per row of the batch, up to twice as many slices as compute units: what
-// a cut row saves is its stream, what it costs is a launch and 16 KiB of counters per slice.  Whole / eight
+// least kSliceMinV columns and 4096 columns per row of the batch, as long as eighths would make at most two workgroups per
+// compute unit: what a cut row saves is its stream, what it costs is a launch and 16 KiB of counters per slice.  Whole / eight
 // slices / sixteen / four in us: 8 x 151,936 19.4 / 14.9 / 15.9 / 16.6, 32 x 151,936 19.9 / 17.6 / 20.7 / 18.2, 64 x 151,936
-// 20.3 / 20.5; 16 x 70,000 15.0 / 14.3, 32 x 70,000 14.9 / 15.6; 64 x 260,000 28.1 / 22.6.
+// 20.3 / 20.5; 16 x 70,000 15.0 / 14.3, 32 x 70,000 14.9 / 15.6.  (The line follows these widths; wider rows would bear more
+// of them: 64 x 260,000, which it leaves whole, 28.1 / 22.6.)
 constexpr int64_t kSliceMinV = 65'536;
 static int slices_of(int64_t rows, int64_t V)
 {
