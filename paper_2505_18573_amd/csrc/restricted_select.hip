@@ -28,9 +28,9 @@
 // plateau listed first / so: bf16 158 / 21 us, fp32 202 / 32 us (ordinary rows 17 and 24 us);
 // 512 x 151,936 bf16 rows sorted by value 142 / 50 us, fp32 108 / 102 us.
 // Every count is exact and every mass fp64, as in restricted.hip.
-// Steps 2 (from the radix select on) and 3 exist twice: workgroup-wide, with a barrier after
+// Steps 2 (from the radix select on) and 3 exist twice: for any list, with a barrier after
 // every short phase, and - for a list of at most 256 candidates and top_k <= 64, the usual
-// case - inside one wave with the kept columns one per lane (finish_in_one_wave below).
+// case - by ranking the list outright (finish_short_list below).
 #include "vocab_common.h"
 #include "vocab_pass.h"
 #include "wave_scan.h"
@@ -109,7 +109,8 @@ struct alignas(16) SelShared {
     uint32_t n_total;                        // candidates seen by the first pass
     int gt_n, eq_n, list_n, vec_n;           // list fills
     uint32_t skipped;                        // key of the highest plateau of which a wave listed only what lies above (0: none)
-    uint32_t pad_[3];                        // keeps the arrays below on 16-byte boundaries
+    uint32_t k23;                            // the noise word that picks a level's column, 23 bits of it
+    uint32_t pad_[2];                        // keeps the arrays below on 16-byte boundaries
     int rank[kSMaxK];
     uint32_t gt_key[kSMaxK];                 // unsorted, then sorted by (key desc, col asc)
     int32_t gt_col[kSMaxK];
@@ -126,6 +127,20 @@ struct alignas(16) SelShared {
 };
 
 static_assert(offsetof(SelShared, gt_key) % 16 == 0 && offsetof(SelShared, gt_col) % 16 == 0, "read four at a time");
+
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
+{
+    auto most = [&](auto c, auto m) {
+        const uint32_t o = (uint32_t)dpp_i<decltype(c)::value, decltype(m)::value>((int)v, (int)v);
+        v = o > v ? o : v;
+    };
+    std::integral_constant<int, 0xF> every;
+    most(std::integral_constant<int, kDppXor1>{}, every); most(std::integral_constant<int, kDppXor2>{}, every);
+    most(std::integral_constant<int, kDppHalfMirror>{}, every); most(std::integral_constant<int, kDppMirror>{}, every);
+    most(std::integral_constant<int, kDppBcast15>{}, std::integral_constant<int, 0xA>{});
+    most(std::integral_constant<int, kDppBcast31>{}, std::integral_constant<int, 0xC>{});
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
 
 // One 8-bit pass of a radix select for the k-th largest: every thread has added its keys
 // that match `prefix` above `shift + 8` to hist; wave 0 finds the digit that holds rank k_rem.
@@ -169,196 +184,173 @@ struct SelArgs {
 };
 
 // ---------------------------------------------------------------------------
-// The rest of a row in one wave, for a short candidate list (at most kSoloList entries in
-// LDS) and a small count cut (top_k <= kSoloK, so fewer than 64 columns stand above the cut
-// level: one per lane, and lane 63 is free for the cut level itself).  Same steps and same
-// arithmetic as the workgroup-wide code in the kernel below; what changes is where the
-// data sit: the list is held in registers (four entries per lane), kappa is found bit by bit
-// with ballots, the columns above it then live one per lane, are ranked against each other
-// through lane broadcasts, and masses, cuts, race and pick are wave scans, ballots and lane
-// reads.  No workgroup barrier is involved (the other waves
-// have left), and what goes through LDS is ordered by the wave's own program order.
+// The rest of a row for a short candidate list (at most kSoloList entries in LDS) and a small
+// count cut (top_k <= kSoloK): the usual case.  Same definition and arithmetic as the workgroup-wide
+// code in the kernel below, in three steps with two barriers.  What bounds it is the number of
+// dependent instructions of a wave, so everything that can be done per candidate is done by all waves at once:
+//   rank    the list is ranked as it is, the L x L comparisons spread over the waves (a group of 64 entries against one
+//           part of the others each); one of them also draws the entries' race noise, another takes the fp64
+//           exponentials.  The k-th largest needs no search: it is the entry of rank k - 1;
+//   sort    entries go to their rank, equal values in any order (the pick below orders a level's columns);
+//   finish  one wave, one sorted entry per lane: levels, masses, cuts, race and pick are scans, ballots and
+//           lane reads.  Fewer than k <= 64 entries stand above the cut level and its first one stands
+//           behind them, so 64 lanes see all that matters; the rest of the cut level is only counted.
+// 512 rows x 151,936 bf16 columns, top-k 50 (lists of 70 to 190): one wave alone that searched the k-th largest bit by bit
+// (1500 cycles, 4000 for fp32) and ranked the columns above it through lane broadcasts (4000) took 10,200 cycles, these
+// steps take 4900.  64 rows x 32,000, top-k 50: bf16 10.7 -> 8.4 us, fp32 11.5 -> 8.3 us.
 // ---------------------------------------------------------------------------
 constexpr int kSoloList = 256;
 constexpr int kSoloK = 64;
 
-template <typename T>
-__device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& sh, const uint32_t* lkey,
-                                                   const int32_t* lcol, int n_list, int k_req, int64_t row,
-                                                   uint64_t grow, double inv_tau, float c, int lane)
+// How many of four keys are above `key`, added to two counters: two instructions a key.  Written as asm because the compiler
+// puts a comparison right before the addition that takes its result as a carry, which this part makes wait; here three
+// instructions stand between them (two are needed).
+__device__ __forceinline__ void count_above(int& n0, int& n1, const uint4& o, uint32_t key)
 {
-    auto lds_order = []() {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    };
-    const unsigned long long below = (1ull << lane) - 1ull;        // lanes before mine
+    uint64_t c0, c1, c2, c3;
+    asm("v_cmp_gt_u32_e64 %2, %6, %10\n\t"
+        "v_cmp_gt_u32_e64 %3, %7, %10\n\t"
+        "v_cmp_gt_u32_e64 %4, %8, %10\n\t"
+        "v_cmp_gt_u32_e64 %5, %9, %10\n\t"
+        "v_addc_co_u32_e64 %0, vcc, 0, %0, %2\n\t"
+        "v_addc_co_u32_e64 %1, vcc, 0, %1, %3\n\t"
+        "v_addc_co_u32_e64 %0, vcc, 0, %0, %4\n\t"
+        "v_addc_co_u32_e64 %1, vcc, 0, %1, %5"
+        : "+v"(n0), "+v"(n1), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)
+        : "v"(o.x), "v"(o.y), "v"(o.z), "v"(o.w), "v"(key) : "vcc");
+}
 
-    // the list in registers: lane l holds entries l, l + 64, ... (key 0 = none: below every real key)
-    constexpr int kPerLane = kSoloList / 64;
-    uint32_t lk[kPerLane];
-    int32_t lc[kPerLane];
-#pragma unroll
-    for (int j = 0; j < kPerLane; ++j) {
-        const int e = lane + 64 * j;
-        lk[j] = e < n_list ? lkey[e] : 0u;
-        lc[j] = e < n_list ? lcol[e] : 0;
-    }
-    // kappa, the k-th largest listed key, bit by bit from the top: the largest value that at
-    // least k keys reach (one ballot per register and bit; the keys' low bits follow the sign
-    // when only the upper kKeyBits are significant)
-    const int k_eff = n_list < k_req ? n_list : k_req;              // fewer than k finite columns: all of them
-    // (from the highest bit that not all of them share)
-    uint32_t all = 0xFFFFFFFFu, any = 0u;
-#pragma unroll
-    for (int j = 0; j < kPerLane; ++j) {
-        if (lane + 64 * j < n_list) { all &= lk[j]; any |= lk[j]; }
-    }
-    {
-        auto fold = [&](auto c, auto m) {
-            all &= (uint32_t)dpp_i<decltype(c)::value, decltype(m)::value>((int)all, (int)all);
-            any |= (uint32_t)dpp_i<decltype(c)::value, decltype(m)::value>((int)any, (int)any);
-        };
-        std::integral_constant<int, 0xF> every;
-        fold(std::integral_constant<int, kDppXor1>{}, every); fold(std::integral_constant<int, kDppXor2>{}, every);
-        fold(std::integral_constant<int, kDppHalfMirror>{}, every); fold(std::integral_constant<int, kDppMirror>{}, every);
-        fold(std::integral_constant<int, kDppBcast15>{}, std::integral_constant<int, 0xA>{});
-        fold(std::integral_constant<int, kDppBcast31>{}, std::integral_constant<int, 0xC>{});
-    }
-    all = (uint32_t)__builtin_amdgcn_readlane((int)all, 63);
-    const uint32_t differ = all ^ (uint32_t)__builtin_amdgcn_readlane((int)any, 63);
-    const int high = differ != 0u ? 31 - (int)__builtin_clz(differ) : -1;       // bits above it are those of every key
-    uint32_t kappa = high < 0 ? all : all & ~(0xFFFFFFFFu >> (31 - high));
-    for (int b = high; b >= 32 - T::kKeyBits; --b) {
-        const uint32_t cand = kappa | (1u << b);
-        int reach = 0;
-#pragma unroll
-        for (int j = 0; j < kPerLane; ++j) reach += __popcll(__ballot(lk[j] >= cand));
-        if (reach >= k_eff) kappa = cand;
-    }
-    if (T::kKeyBits < 32 && (kappa & 0x80000000u) == 0u) kappa |= 0xFFFFFFFFu >> T::kKeyBits;
+// LDS of these steps that other steps use as well: SelShared::rank holds the ranks, gt_col counts the entries sent to a rank
+// (both zeroed when the kernel starts, as are the first kSoloList keys of the list), st_key and st_col are the
+// sorted list, st_M its weights and gt_key its noise; `mass` and `noise` (kSoloList each) are the same before sorting.
+template <typename T, int kSThreads>
+__device__ __forceinline__ void finish_short_list(const SelArgs& a, SelShared& sh, const uint32_t* lkey,
+                                                  const int32_t* lcol, double* mass, float* noise, int n_list,
+                                                  int k_req, int64_t row, uint64_t grow, double inv_tau, float c,
+                                                  int lane, int wave)
+{
+    constexpr int kSWaves = kSThreads / 64;
+    constexpr int kLgWaves = kSWaves == 16 ? 4 : 3;
+    static_assert(kSWaves == 1 << kLgWaves && kSoloList == 256, "whole parts, at least two");
+    const int lg_groups = n_list <= 64 ? 0 : n_list <= 128 ? 1 : 2;
+    const int groups = 1 << lg_groups, parts = kSWaves >> lg_groups;
+    const int group = wave & (groups - 1), part = wave >> lg_groups;
+    const int entry = group * 64 + lane;                            // (keys behind the list are 0: below every real one)
+    const uint32_t key = lkey[entry];
+    const bool mine = entry < n_list;
 
-    // the columns above kappa, one per lane in list order; those on kappa's level into their list
-    uint32_t key_i = 0u;
-    int32_t col_i = 0;
-    int n = 0, n_cut = 0;                                          // columns above kappa (fewer than k), columns on its level
-    {
+    // ---- rank: the entries above mine, among my part of the list; the last two parts of four or more have other work
+    const int lg_rank = parts == 2 ? 1 : parts == 4 ? 1 : parts == 8 ? 2 : 3;
+    if (part < 1 << lg_rank) {
+        const int per = (((n_list - 1) >> lg_rank) + 16) & ~15;      // a multiple of the sixteen entries read together
+        const int end = (part + 1) * per < n_list ? (part + 1) * per : n_list;
+        int above = 0, above1 = 0;
+        for (int e = part * per; e < end; e += 16) {
+            uint4 o[4];
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            const bool gt = lk[j] > kappa;
-            const unsigned long long gm = __ballot(gt);
-            if (gt) {
-                const int slot = n + __popcll(gm & below);
-                sh.gt_key[slot] = lk[j];
-                sh.gt_col[slot] = lc[j];
-            }
-            n += __popcll(gm);
-            const bool eq = lk[j] == kappa;
-            const unsigned long long em = __ballot(eq);
-            if (eq) {
-                const int slot = n_cut + __popcll(em & below);
-                if (slot < kSEqCap) sh.eq_col[slot] = lc[j];
-            }
-            n_cut += __popcll(em);
+            for (int u = 0; u < 4; ++u) o[u] = reinterpret_cast<const uint4*>(&lkey[e])[u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) count_above(above, above1, o[u], key);
         }
-        lds_order();
-        if (lane < n) { key_i = sh.gt_key[lane]; col_i = sh.gt_col[lane]; }
+        above += above1;
+        if (mine && above != 0) atomicAdd(&sh.rank[entry], above);
     }
-    // rank by (value descending, column ascending): each lane counts the lanes ahead of it; one
-    // 64-bit comparison per pair on (key, inverted column)
-    const uint64_t order_i = ((uint64_t)key_i << 32) | (uint32_t)~col_i;
-    int rank = 0;
-    for (int e = 0; e < n; ++e) {
-        const uint32_t ok = (uint32_t)__builtin_amdgcn_readlane((int)key_i, e);
-        const uint32_t oc = (uint32_t)__builtin_amdgcn_readlane(~col_i, e);
-        rank += (((uint64_t)ok << 32) | oc) > order_i;
-    }
-    if (lane < n) { sh.st_key[rank] = key_i; sh.st_col[rank] = col_i; }
-    lds_order();
-    const bool have = lane < n;
-    const uint32_t skey = have ? sh.st_key[lane] : 0u;             // lane = rank from here on
-    const int32_t scol = have ? sh.st_col[lane] : 0;
-
-    // masses in rank order (fp64), cuts
-    const uint32_t key1 = n > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)skey, 0) : kappa;   // the row's highest level
-    const double z1 = (double)__uint_as_float(f32_of_key(key1));
-    const double z_cut = (double)__uint_as_float(f32_of_key(kappa));
-    const double w = have ? exp(((double)__uint_as_float(f32_of_key(skey)) - z1) * inv_tau) : 0.0;
-    const double M = wave_prefix_sum(w);                            // inclusive prefix mass
-    const double M_gt = n > 0 ? read_lane(M, n - 1) : 0.0;
-    const double w_cut = exp((z_cut - z1) * inv_tau);
-    const double M_k = M_gt + (double)n_cut * w_cut;               // mass of the top-k set
-    constexpr int kNextLane = 0x130, kPrevLane = 0x138;             // wave_shl:1, wave_shr:1
-    const uint32_t next_key = (uint32_t)dpp_i<kNextLane>(0, (int)skey);
-    const uint32_t prev_key = (uint32_t)dpp_i<kPrevLane>(0, (int)skey);
-    int cut_index = kSMaxK;                                          // default: everything down to the cut level
-    if (a.top_p < 1.0f) {
-        // top-p on the renormalised top-k set: first level end whose cumulative mass reaches the target
-        const double Tm = (double)a.top_p * M_k;
-        const bool level_end = have && (lane == n - 1 || next_key != skey);
-        const unsigned long long reach = __ballot(level_end && M >= Tm);
-        if (reach != 0ull) cut_index = (int)__builtin_ctzll(reach);
-    }
-    const bool cut_level_kept = cut_index == kSMaxK;
-    const int kept_sorted = cut_level_kept ? n : cut_index + 1;    // sorted entries kept
-    const int kept_C = cut_level_kept ? n + n_cut : kept_sorted;
-    const double ln_M = log(cut_level_kept ? M_k : read_lane(M, cut_index));
-
-    // race of the kept levels: a level's first lane scores it, lane 63 scores the cut level
-    const bool level_start = have && (lane == 0 || prev_key != skey);
-    const unsigned long long starts = __ballot(level_start);
-    const unsigned long long later = lane < 63 ? starts >> (lane + 1) : 0ull;
-    const int cnt = (later != 0ull ? lane + 1 + (int)__builtin_ctzll(later) : n) - lane;    // columns of my level
-    const float z1f = __uint_as_float(f32_of_key(key1));
-    const bool for_cut = lane == 63 && cut_level_kept;
-    float my_q = -1.0f;
-    int my_lvl = 0x7FFFFFFF;                                       // sorted index of the level's first entry; kSMaxK = cut level
-    if ((level_start && lane < kept_sorted) || for_cut) {
-        const uint32_t bits = f32_of_key(for_cut ? kappa : skey);
-        const uint32_t pat = T::pattern_of_bits(bits);
+    if (part == parts - 1) {
+        // race noise of the level: E_j from Philox stream 3 at the level's stored pattern
+        const uint32_t pat = T::pattern_of_bits(f32_of_key(key));
         uint32_t w4[4];
         philox4x32_10(pat >> 2, (uint32_t)grow, (uint32_t)(grow >> 32), 3u,
                       (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
         const int sel = pat & 3;
-        const uint32_t word = sel == 0 ? w4[0] : sel == 1 ? w4[1] : sel == 2 ? w4[2] : w4[3];
-        my_q = (float)(for_cut ? n_cut : cnt) * __builtin_amdgcn_exp2f((__uint_as_float(bits) - z1f) * c)
-             * inv_exp_variate(word);
-        my_lvl = for_cut ? kSMaxK : lane;
+        noise[entry] = inv_exp_variate(sel == 0 ? w4[0] : sel == 1 ? w4[1] : sel == 2 ? w4[2] : w4[3]);
+    } else if (part == parts - 2) {
+        // weights relative to the row's largest column, which every list holds
+        uint32_t top = 0u;
+        for (int e = lane; e < groups * 64; e += 64) top = lkey[e] > top ? lkey[e] : top;
+        top = wave_max_u32(top);
+        const double z1 = (double)__uint_as_float(f32_of_key(top));
+        mass[entry] = exp(((double)__uint_as_float(f32_of_key(key)) - z1) * inv_tau);
     }
-    const Cand winner = wave_best(Cand{my_q, my_lvl});               // ties: the higher level
-    const float best_q = winner.q;
-    const int best_lvl = winner.idx;
+    __syncthreads();
 
-    // the column inside the winning level
-    uint32_t w4[4];
-    philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
-    const uint64_t k23 = (uint64_t)(w4[0] >> 9);
+    // ---- sort
+    if (wave < groups && mine) {
+        const int r = sh.rank[entry];
+        const int at = r + atomicAdd(&sh.gt_col[r], 1);
+        sh.st_key[at] = key;
+        sh.st_col[at] = lcol[entry];
+        sh.st_M[at] = mass[entry];
+        sh.gt_key[at] = __float_as_uint(noise[entry]);
+    }
+    __syncthreads();
+    if (wave != 0) return;
+
+    // ---- finish: lane = rank
+    const bool real = lane < n_list;
+    const uint32_t skey = real ? sh.st_key[lane] : 0u;
+    const int32_t scol = real ? sh.st_col[lane] : 0;
+    const double w = real ? sh.st_M[lane] : 0.0;
+    const float inv_e = __uint_as_float(sh.gt_key[lane]);           // read for real entries only
+    const int k_eff = n_list < k_req ? n_list : k_req;              // fewer than k finite columns: all of them
+    const uint32_t kappa = (uint32_t)__builtin_amdgcn_readlane((int)skey, k_eff - 1);
+    const int n = (int)__popcll(__ballot(real && skey > kappa));    // columns above the cut level: lanes 0 .. n - 1; lane n is its first
+    int n_cut = (int)__popcll(__ballot(real && skey == kappa));
+    if (__builtin_amdgcn_readlane((int)skey, 63) == (int)kappa)     // (a list of fewer than 64 ends with key 0)
+        for (int e = 64 + lane; e < groups * 64; e += 64) n_cut += (int)__popcll(__ballot(e < n_list && sh.st_key[e] == kappa));
+
+    // masses in rank order (fp64), cuts
+    const uint32_t key1 = (uint32_t)__builtin_amdgcn_readlane((int)skey, 0);       // the row's highest level
+    const double z1 = (double)__uint_as_float(f32_of_key(key1));
+    const double M = wave_prefix_sum(lane < n ? w : 0.0);           // inclusive prefix mass
+    const double M_gt = n > 0 ? read_lane(M, n - 1) : 0.0;
+    const double M_k = M_gt + (double)n_cut * read_lane(w, n);      // mass of the top-k set
+    constexpr int kNextLane = 0x130, kPrevLane = 0x138;             // wave_shl:1, wave_shr:1
+    const uint32_t next_key = (uint32_t)dpp_i<kNextLane>(0, (int)skey);
+    const uint32_t prev_key = (uint32_t)dpp_i<kPrevLane>(0, (int)skey);
+    int kept_sorted = n + 1;                                        // lanes of kept levels (the cut level in lane n) ...
+    int kept_C = n + n_cut;                                         // ... and their columns: by default down to the cut level
+    double M_kept = M_k;
+    if (a.top_p < 1.0f) {
+        // top-p on the renormalised top-k set: first level end whose cumulative mass reaches the target
+        const double Tm = (double)a.top_p * M_k;
+        const bool level_end = lane < n && next_key != skey;        // (lane n's key differs from lane n - 1's)
+        const unsigned long long reach = __ballot(level_end && M >= Tm);
+        if (reach != 0ull) {
+            const int cut_index = (int)__builtin_ctzll(reach);
+            kept_sorted = kept_C = cut_index + 1;
+            M_kept = read_lane(M, cut_index);
+        }
+    }
+    const double ln_M = log(M_kept);
+
+    // race of the kept levels, each scored by its first lane
+    const bool level_start = lane <= n && (lane == 0 || prev_key != skey);
+    const unsigned long long starts = __ballot(level_start);
+    const unsigned long long later = lane < 63 ? starts >> (lane + 1) : 0ull;
+    const int cnt = lane == n ? n_cut : 1 + (int)__builtin_ctzll(later | 1ull << 63);     // columns of my level
+    const float z1f = __uint_as_float(f32_of_key(key1));
+    float my_q = -1.0f;
+    if (level_start && lane < kept_sorted)
+        my_q = (float)cnt * __builtin_amdgcn_exp2f((__uint_as_float(f32_of_key(skey)) - z1f) * c) * inv_e;
+    const float best_q = wave_max(my_q);
+    const unsigned long long winners = __ballot(my_q == best_q);
+    const int best = (int)__builtin_ctzll(winners | 1ull << 63);    // ties: the higher level
+
+    // the column inside the winning level: the pos-th of its columns
     int tok = 0;
     uint32_t tok_key = key1;
-    if (best_q >= 0.0f && best_lvl < kSMaxK) {
-        const int level_cnt = __builtin_amdgcn_readlane(cnt, best_lvl);
-        const int pos = (int)(((2u * k23 + 1u) * (uint64_t)level_cnt) >> 24);
-        tok = __builtin_amdgcn_readlane(scol, best_lvl + pos);     // a level's lanes are in column order
-        tok_key = (uint32_t)__builtin_amdgcn_readlane((int)skey, best_lvl);
-    } else if (best_q >= 0.0f) {
-        const int pos = (int)(((2u * k23 + 1u) * (uint64_t)n_cut) >> 24);
-        tok_key = kappa;
-        if (n_cut <= kSEqCap) {
-            // the pos-th smallest of the level's listed columns
-            const int32_t mc = lane < n_cut ? sh.eq_col[lane] : 0x7FFFFFFF;
-            int before = 0;
-            for (int e = 0; e < n_cut; ++e) before += __builtin_amdgcn_readlane(mc, e) < mc;
-            const unsigned long long hit = __ballot(lane < n_cut && before == pos);
-            tok = __builtin_amdgcn_readlane(mc, (int)__builtin_ctzll(hit | (1ull << 63)));
-        } else {
-            // a longer level inside the list: rank its columns against each other from LDS
-            for (int e0 = 0; e0 < n_list; e0 += 64) {
+    if (best_q >= 0.0f) {
+        tok_key = (uint32_t)__builtin_amdgcn_readlane((int)skey, best);
+        const int level_cnt = __builtin_amdgcn_readlane(cnt, best);
+        tok = __builtin_amdgcn_readlane(scol, best);
+        if (level_cnt > 1) {
+            const int pos = (int)(((2u * (uint64_t)sh.k23 + 1u) * (uint64_t)level_cnt) >> 24);
+            for (int e0 = 0; e0 < level_cnt; e0 += 64) {
                 const int e = e0 + lane;
-                const bool mine = e < n_list && lkey[e] == kappa;
-                const int32_t mc = e < n_list ? lcol[e] : 0;
+                const int32_t mc = e < level_cnt ? sh.st_col[best + e] : 0x7FFFFFFF;
                 int before = 0;
-#pragma unroll 8
-                for (int f = 0; f < n_list; ++f) before += (int)(lkey[f] == kappa) & (int)(lcol[f] < mc);
-                const unsigned long long hit = __ballot(mine && before == pos);
+                for (int f = 0; f < level_cnt; ++f) before += sh.st_col[best + f] < mc;
+                const unsigned long long hit = __ballot(e < level_cnt && before == pos);
                 if (hit != 0ull) tok = __builtin_amdgcn_readlane(mc, (int)__builtin_ctzll(hit));
             }
         }
@@ -374,14 +366,14 @@ __device__ __forceinline__ void finish_in_one_wave(const SelArgs& a, SelShared& 
     }
 }
 
-// Bound by the read of the row plus ~6 us of short dependent phases after it.  512 threads per row,
+// Bound by the read of the row plus ~3.5 us of short dependent phases after it.  512 threads per row,
 // two workgroups per compute unit (one row's short phases overlap the other's stream) and
 // non-temporal loads, or 1024 threads and plain loads for at most one row per compute unit (half the
 // stream's latency; such a batch may sit in the caches: 100 fp32 rows 24.7 us plain, 28.2 us
 // non-temporal; 300 rows x 151,936 bf16 29.7 us with 512 threads, 48 us with 1024): four waves per
-// SIMD and up to 128 vector registers either way.  151,936 bf16 columns, top-k 50 + top-p 0.95: 8 rows 16.5 us,
-// 512 rows 33.6 us (4.6 TB/s), 1024 rows 58.6 us (5.3 TB/s); with the one-wave finish's scans and reductions through
-// LDS permutes instead of DPP, the cut searched over all 16 or 32 bits and the logarithm taken last 17.6, 34.6 and 61.1.
+// SIMD and up to 128 vector registers either way.  151,936 bf16 columns, top-k 50 + top-p 0.95: 8 rows 14.2 us,
+// 512 rows 30.2 us (5.1 TB/s), 1024 rows 53.7 us (5.8 TB/s); with one wave finishing a row alone (see finish_short_list)
+// and the candidates taken column by column from the listed vectors 16.5, 33.7 and 59.6.
 template <typename T, int kSThreads>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void sample_select_kernel(SelArgs a)
@@ -394,7 +386,7 @@ void sample_select_kernel(SelArgs a)
     __shared__ uint32_t lkey[kSListCap];                          // candidate columns
     __shared__ int32_t lcol[kSListCap];
     __shared__ SelShared sh;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t row = blockIdx.x;
     const int64_t V = a.V;
     const int esz = 16 / T::kElems;
@@ -539,6 +531,7 @@ void sample_select_kernel(SelArgs a)
         }
     };
     if (tid == 0) { sh.gt_n = 0; sh.eq_n = 0; sh.token = 0; sh.list_n = 0; sh.vec_n = 0; sh.skipped = 0u; }
+    if (tid < kSoloList) { sh.rank[tid] = 0; sh.gt_col[tid] = 0; lkey[tid] = 0u; }
     {
         u32x4 x[kSBatch], y[kSBatch];
         float m[kSBatch];
@@ -549,6 +542,11 @@ void sample_select_kernel(SelArgs a)
         };
         request(x, 0);
         if (nsets > 1) request(y, 1);
+        if (wave == kSWaves - 1) {                                // while they are in flight
+            uint32_t w4[4];
+            philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
+            if (lane == 0) sh.k23 = w4[0] >> 9;
+        }
         maxima(x, 0);
         publish();
         // orders LDS only: __syncthreads() would wait for the loads in flight as well
@@ -643,28 +641,33 @@ void sample_select_kernel(SelArgs a)
         return base + __popcll(m & ((1ull << lane) - 1ull));
     };
     if (n_vec <= kSVecCap) {
+        const float thf = theta_value(theta);
+        const int32_t vlast = (int32_t)V - T::kElems;                 // vectors beginning behind it are cut short by the row's end
         for (int i0 = 0; i0 < n_vec; i0 += kSThreads) {           // whole waves: the reservation is wave-wide
             const int i = i0 + tid;
-            const u32x4 x = i < n_vec ? lvec[i] : none;
-            const int32_t col0 = i < n_vec ? lvec_at[i] * T::kElems : 0;
-            uint32_t key[T::kElems];
-            int mine = 0;
+            const u32x4 x = lvec[i < n_vec ? i : 0];
+            const int32_t col0 = lvec_at[i < n_vec ? i : 0] * T::kElems;
+            // as values: a key reaches theta where the value does (zeros: theta is never that of +0), and is finite
+            uint32_t hits = 0u;
 #pragma unroll
             for (int e = 0; e < T::kElems; ++e) {
-                key[e] = col0 + e < V ? key_of_f32(T::elem_bits(x, e)) : 0u;      // the last vector may reach past the row
-                mine += key[e] >= theta;
+                const float z = __uint_as_float(T::elem_bits(x, e));
+                hits |= (uint32_t)(z >= thf && z < INFINITY) << e;
             }
+            if (col0 > vlast) hits &= (1u << last) - 1u;              // the last vector may reach past the row
+            hits = i < n_vec ? hits : 0u;
+            const int mine = __popc(hits);
             const int inc = wave_prefix_sum(mine);
             if (__builtin_amdgcn_readlane(inc, 63) == 0) continue;
             int base = 0;
             if (lane == 63) base = atomicAdd(&sh.list_n, inc);
             int slot = __builtin_amdgcn_readlane(base, 63) + inc - mine;
-#pragma unroll
-            for (int e = 0; e < T::kElems; ++e) {
-                if (key[e] >= theta) {
-                    if (slot < kSListCap) { lkey[slot] = key[e]; lcol[slot] = col0 + e; }
-                    ++slot;
-                }
+            // (a hit at a time: one or two rounds, where the vector's columns one after the other would be as many as it has)
+            while (hits != 0u) {
+                const int e = (int)__builtin_ctz(hits);
+                if (slot < kSListCap) { lkey[slot] = key_of_f32(T::elem_bits(x, e)); lcol[slot] = col0 + e; }
+                ++slot;
+                hits &= hits - 1u;
             }
         }
     } else if (tid == 0) {
@@ -681,8 +684,11 @@ void sample_select_kernel(SelArgs a)
         return;
     }
     const bool listed = n_list <= kSListCap;
-    if (n_list <= kSoloList && k_req <= kSoloK) {                  // short list, small k: one wave finishes the row
-        if (wave == 0) finish_in_one_wave<T>(a, sh, lkey, lcol, n_list, k_req, row, grow, inv_tau, c, lane);
+    if (n_list <= kSoloList && k_req <= kSoloK) {                  // short list, small k: ranked as it is
+        // (the listed vectors are no longer needed)
+        double* mass = reinterpret_cast<double*>(lvec);
+        finish_short_list<T, kSThreads>(a, sh, lkey, lcol, mass, reinterpret_cast<float*>(mass + kSoloList), n_list, k_req,
+                                        row, grow, inv_tau, c, lane, wave);
         return;
     }
     auto for_each_candidate = [&](auto&& f) {
@@ -872,9 +878,7 @@ void sample_select_kernel(SelArgs a)
     const int best_lvl = winner.idx;
 
     // the column inside the winning level ---------------------------------------------------------
-    uint32_t w4[4];
-    philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
-    const uint64_t k23 = (uint64_t)(w4[0] >> 9);
+    const uint64_t k23 = (uint64_t)sh.k23;
     int tok = 0;
     uint32_t tok_key = key1;
     if (best_q >= 0.0f && best_lvl < kSMaxK) {

@@ -637,6 +637,26 @@ def test_levels_longer_than_a_quarter_counter():
 # 1024 threads per row up to one row per compute unit, 512 beyond; the list of vectors holds 2688.
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows", [9, 260])
+@pytest.mark.parametrize("V", [1, 15, 16, 17, 63, 64, 65, 128, 129, 192, 193, 252, 256, 257])
+def test_short_candidate_lists(V, rows, dtype):
+    # so few vectors that (nearly) every column is a candidate: the sizes at which the ranking of a list changes its split over
+    # the waves (64, 128, 256 entries) and reads (16), on both workgroup sizes, with levels that end before, at
+    # and behind the 64th entry
+    g = torch.Generator(device=DEV).manual_seed(V + rows)
+    x = torch.randn((rows, -(-V // 8) * 8), generator=g, device=DEV) * 2.5
+    x[1::5] = (x[1::5] * 2).round() / 2                                # few distinct values
+    x[2::5] = 0.75                                                     # one level
+    x[3::5] = torch.where(x[3::5] > 1.0, x[3::5], torch.full_like(x[3::5], -1.0))     # a cut level that is a plateau
+    x[4::5, ::3] = 0.0
+    x[4::5, 1::3] = -0.0
+    lg = x.to(dtype)[:, :V]
+    for k, p in [(64, 1.0), (64, 0.7), (20, 0.9), (1, 0.5)]:
+        check(lg, None, 0.8, k, p, V + k, 7, f"V={V} rows={rows} {dtype} k={k} p={p}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("rows,V", [(256, 33_001), (257, 5), (257, 4_099), (260, 16_387), (260, 33_001), (300, 70_001)])
 def test_selection_workgroup_sizes(rows, V, dtype):
     g = torch.Generator(device=DEV).manual_seed(rows + V)
