@@ -60,6 +60,14 @@ __device__ __forceinline__ float dpp_f(float old, float v)
 {
     return __int_as_float(dpp_i<kCtrl, kRowMask>(__float_as_int(old), __float_as_int(v)));
 }
+// Steps that reach every lane: no register has to be prepared for lanes without a source.
+template <int kCtrl>
+__device__ __forceinline__ double dpp_all(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
 template <int kCtrl, int kRowMask = 0xF>
 __device__ __forceinline__ double dpp_d(double old, double v)
 {
@@ -113,29 +121,91 @@ __device__ __forceinline__ float row16_max(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
 }
 
-__device__ __forceinline__ double row16_sum(double v)
+// Two maxima at once: each fills the wait states of the other.
+__device__ __forceinline__ void wave_max2(float& a, float& b)
 {
-    v += dpp_d<kDppXor1>(0.0, v);
-    v += dpp_d<kDppXor2>(0.0, v);
-    v += dpp_d<kDppHalfMirror>(0.0, v);
-    v += dpp_d<kDppMirror>(0.0, v);
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 0);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 0);
-    return __hiloint2double(hi, lo);
+    asm("s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(a), "+v"(b));
+    a = last_lane(a);
+    b = last_lane(b);
 }
+
+__device__ __forceinline__ void row16_max2(float& a, float& b)
+{
+    asm("s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(a), "+v"(b));
+    a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 0));
+    b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(b), 0));
+}
+
+__device__ __forceinline__ double read_lane(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Sums in fp64 over each row of sixteen lanes, in every lane of it.
+__device__ __forceinline__ double row16_sums(double v)
+{
+    v += dpp_all<kDppXor1>(v);
+    v += dpp_all<kDppXor2>(v);
+    v += dpp_all<kDppHalfMirror>(v);
+    v += dpp_all<kDppMirror>(v);
+    return v;
+}
+__device__ __forceinline__ double row16_sum(double v) { return read_lane(row16_sums(v), 0); }
 
 // Sum over the wave in fp64, returned wave-uniform.
 __device__ __forceinline__ double wave_sum(double v)
 {
-    v += dpp_d<kDppXor1>(0.0, v);
-    v += dpp_d<kDppXor2>(0.0, v);
-    v += dpp_d<kDppHalfMirror>(0.0, v);
-    v += dpp_d<kDppMirror>(0.0, v);
+    v = row16_sums(v);
     v += dpp_d<kDppBcast15, 0xA>(0.0, v);
     v += dpp_d<kDppBcast31, 0xC>(0.0, v);
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-    return __hiloint2double(hi, lo);
+    return read_lane(v, 63);
+}
+
+// Two such sums step by step, so that neither waits for its own additions.
+__device__ __forceinline__ void wave_sum2(double& a, double& b)
+{
+    auto step = [&](auto c) { const double x = dpp_all<decltype(c)::value>(a), y = dpp_all<decltype(c)::value>(b); a += x; b += y; };
+    step(std::integral_constant<int, kDppXor1>{});
+    step(std::integral_constant<int, kDppXor2>{});
+    step(std::integral_constant<int, kDppHalfMirror>{});
+    step(std::integral_constant<int, kDppMirror>{});
+    { const double x = dpp_d<kDppBcast15, 0xA>(0.0, a), y = dpp_d<kDppBcast15, 0xA>(0.0, b); a += x; b += y; }
+    { const double x = dpp_d<kDppBcast31, 0xC>(0.0, a), y = dpp_d<kDppBcast31, 0xC>(0.0, b); a += x; b += y; }
+    a = read_lane(a, 63);
+    b = read_lane(b, 63);
 }
 
 __device__ __forceinline__ float uniform_f(float v)
@@ -163,41 +233,55 @@ __device__ __forceinline__ Cand better(Cand a, Cand b)
     return take_b ? b : a;
 }
 
-template <int kCtrl, int kRowMask = 0xF>
-__device__ __forceinline__ Cand best_step(Cand c)
+// The winner among the lanes of `lanes`, whose largest weight is `top`: the maximum first, then the lane that
+// holds it (or, of several, the lowest index).  A reduction that carries the index through every step takes three times as many
+// dependent instructions (560 cycles over a wave against 190).  Without a lane that equals the
+// maximum (NaN) the first lane stands for it.
+__device__ __forceinline__ Cand holder_of(Cand c, float top, unsigned long long lanes)
 {
-    Cand o;
-    o.q = dpp_f<kCtrl, kRowMask>(c.q, c.q);       // rows masked off see themselves: a no-op
-    o.idx = dpp_i<kCtrl, kRowMask>(c.idx, c.idx);
-    return better(c, o);
+    unsigned long long m = __ballot(c.q == top) & lanes;
+    Cand r{top, __builtin_amdgcn_readlane(c.idx, m != 0ull ? (int)__builtin_ctzll(m) : 0)};
+    for (m &= m - 1ull; m != 0ull; m &= m - 1ull) {               // ties: rare
+        const int idx = __builtin_amdgcn_readlane(c.idx, (int)__builtin_ctzll(m));
+        r.idx = idx < r.idx ? idx : r.idx;
+    }
+    return r;
 }
 
 // Best candidate of the wave, returned wave-uniform.
-__device__ __forceinline__ Cand wave_best(Cand c)
-{
-    c = best_step<kDppXor1>(c);
-    c = best_step<kDppXor2>(c);
-    c = best_step<kDppHalfMirror>(c);
-    c = best_step<kDppMirror>(c);
-    c = best_step<kDppBcast15, 0xA>(c);
-    c = best_step<kDppBcast31, 0xC>(c);
-    Cand r;
-    r.q = last_lane(c.q);
-    r.idx = __builtin_amdgcn_readlane(c.idx, 63);
-    return r;
-}
+__device__ __forceinline__ Cand wave_best(Cand c) { return holder_of(c, wave_max(c.q), ~0ull); }
 
 // Best candidate among lanes 0..15, returned wave-uniform.
-__device__ __forceinline__ Cand row16_best(Cand c)
+__device__ __forceinline__ Cand row16_best(Cand c) { return holder_of(c, row16_max(c.q), 0xFFFFull); }
+
+// 1 / x in fp64 for finite x of ordinary size: the hardware's estimate and one Newton step (an IEEE division is
+// twelve dependent instructions).
+__device__ __forceinline__ double reciprocal(double x)
 {
-    c = best_step<kDppXor1>(c);
-    c = best_step<kDppXor2>(c);
-    c = best_step<kDppHalfMirror>(c);
-    c = best_step<kDppMirror>(c);
-    Cand r;
-    r.q = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c.q), 0));
-    r.idx = __builtin_amdgcn_readlane(c.idx, 0);
-    return r;
+    const double r = __builtin_amdgcn_rcp(x);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// ln(1 + x) for x >= 0, in fp64, to a few 1e-11 relative: 1 + x = 2^e m with m in [3/4, 3/2) and f = m - 1 (x itself while e is
+// 0, so nothing is lost for small x), s = f / (2 + f), |s| <= 1/5, ln m = 2 (s + s^3/3 + s^5/5 + ...) up to s^13.
+__device__ __forceinline__ double log1p_of(double x)
+{
+    const double u = 1.0 + x;
+    double m = __builtin_amdgcn_frexp_mant(u);                     // [1/2, 1)
+    int e = __builtin_amdgcn_frexp_exp(u);
+    const bool low = m < 0.75;
+    m = low ? m + m : m;
+    e = low ? e - 1 : e;
+    const double f = e == 0 ? x : m - 1.0;
+    const double s = f * reciprocal(2.0 + f);
+    const double z = s * s;
+    double p = fma(z, 1.0 / 13.0, 1.0 / 11.0);
+    p = fma(z, p, 1.0 / 9.0);
+    p = fma(z, p, 1.0 / 7.0);
+    p = fma(z, p, 1.0 / 5.0);
+    p = fma(z, p, 1.0 / 3.0);
+    const double t = s + s;
+    return fma((double)e, kLn2, fma(t * z, p, t));
 }
 
 // ---------------------------------------------------------------------------
@@ -281,6 +365,18 @@ struct ChunkBf16 {
     {
         return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(row)[col] << 16);
     }
+    // four columns, the first a multiple of four (rows start on 16 bytes): one aligned request, which reaches past the
+    // row's last column but never past the 16 bytes that hold it; taken apart when it has arrived
+    typedef uint2 Four;
+    static __device__ __forceinline__ Four load_four(const char* row, int64_t col)
+    {
+        return *reinterpret_cast<const uint2*>(row + col * 2);
+    }
+    static __device__ __forceinline__ void unpack_four(const Four& w, float z[4])
+    {
+        z[0] = __uint_as_float(w.x << 16); z[1] = __uint_as_float(w.x & 0xFFFF0000u);
+        z[2] = __uint_as_float(w.y << 16); z[3] = __uint_as_float(w.y & 0xFFFF0000u);
+    }
     // largest of the four logits in the high halves of the loaded words (a value the row holds)
     __device__ __forceinline__ float some_max() const
     {
@@ -336,6 +432,15 @@ struct ChunkF32 {
     static __device__ __forceinline__ float load_one(const char* row, int64_t col)
     {
         return reinterpret_cast<const float*>(row)[col];
+    }
+    typedef float4 Four;
+    static __device__ __forceinline__ Four load_four(const char* row, int64_t col)
+    {
+        return *reinterpret_cast<const float4*>(row + col * 4);
+    }
+    static __device__ __forceinline__ void unpack_four(const Four& w, float z[4])
+    {
+        z[0] = w.x; z[1] = w.y; z[2] = w.z; z[3] = w.w;
     }
     // largest of the eight loaded logits
     __device__ __forceinline__ float some_max() const

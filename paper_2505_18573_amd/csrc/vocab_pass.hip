@@ -66,7 +66,11 @@ __host__ __device__ inline size_t lds_bytes(int rpb, int nst, bool sample)
 // over at most nine), so every reduction over them is four DPP steps inside one row of lanes
 // instead of six across the wave; level 2 always works on sixteen lanes.  This wave's work
 // is a chain of dependent instructions that nothing overlaps once the row is the last of the
-// launch, hence the care to keep it short.
+// launch, hence the care to keep it short: maxima and sums two at a time, races as a maximum and a look at who
+// holds it, the winning tile's columns requested without a branch (which made the wave wait for each of them), the
+// logarithm and the reciprocal in a few fp64 instructions of their own (vocab_common.h).  4600 cycles for a wave
+// with its data in reach before; whole calls, before and now in us: 1 row x 32,000 bf16 6.9 / 6.0, 300 x 1000 7.4 / 6.4,
+// 512 x 151,936 28.8 / 27.9, 4096 x 32,000 63.3 / 55.8 (where the vector ALUs are the limit).
 template <typename Chunk, bool kSample, bool kFew>
 __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
                                            const RowPartial* parts, int nparts, int lane)
@@ -74,7 +78,12 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
     const int64_t V = a.V;
     const char* rowp = static_cast<const char*>(a.logits)
                      + row * a.row_stride * (int64_t)Chunk::kElemBytes;
-    // training side: ask for the target's logit first, use it last
+    RowPartial p;
+    p.S = 0.0; p.W = 0.0; p.rc = -INFINITY; p.top = -INFINITY; p.q = -1.0f; p.tile = 0;
+    // (kFew: the second sixteen lanes hold the same partials once more)
+    const int slot = kFew ? lane & 15 : lane;
+    if (slot < nparts) p = parts[slot];
+    // training side: ask for the target's logit early, use it last
     int64_t tgt = -1;
     float z_tgt = 0.0f;
     if (!kSample) {
@@ -85,18 +94,16 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
     const float tau = a.tau_rows ? a.tau_rows[row] : a.tau_scalar;
     const float c = kLog2eF / tau;
 
-    RowPartial p;
-    p.S = 0.0; p.W = 0.0; p.rc = -INFINITY; p.top = -INFINITY; p.q = -1.0f; p.tile = 0;
-    if (lane < nparts) p = parts[lane];
-
     // R is the common reference, `peak` the largest logit of the row; the partial
     // that holds it is the lowest lane with that top, every other excluded maximum
     // joins the rest as an ordinary term.
-    const float R = kFew ? row16_max(p.rc) : wave_max(p.rc);
-    const float peak = kFew ? row16_max(p.top) : wave_max(p.top);
+    float R = p.rc, peak = p.top;
+    if (kFew) row16_max2(R, peak);
+    else wave_max2(R, peak);
     const unsigned long long holders = __ballot(p.top == peak);
     const int peak_lane = (int)__builtin_ctzll(holders | (1ull << 63));
     const bool live = p.rc > -INFINITY;
+    const bool is_peak = slot == peak_lane;
     const double cd = (double)c;
     const double d = live ? (double)R - (double)p.rc : 0.0;       // integer >= 0
     const int sh = d > 4000.0 ? -4000 : -(int)d;
@@ -104,10 +111,11 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
     // Rollout side, level 1 across partials first (weights brought to the common
     // reference by exact scaling), so that the columns of the winning tile are
     // requested before the fp64 merge below and arrive while it runs.
-    float cz[4] = {kAbsent, kAbsent, kAbsent, kAbsent};
+    typename Chunk::Four four = {};
     float inv_e2[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     uint32_t w[4] = {0u, 0u, 0u, 0u};
     int64_t col0 = 0;
+    bool in_tile = false;
     if (kSample) {
         const Cand mine{live ? ldexpf(p.q, sh) : -1.0f, p.tile};
         const Cand win = kFew ? row16_best(mine) : wave_best(mine);
@@ -115,9 +123,9 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
         // 2 * kDepth lanes x 4 consecutive columns cover the tile
         col0 = (int64_t)wst * kSuperCols + (int64_t)(lane >> 1) * kSweepCols
              + (int64_t)wslot * kChunk + (lane & 1) * 4;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (lane < 2 * kDepth && col0 + j < V) cz[j] = Chunk::load_one(rowp, col0 + j);
+        // without a branch around it, where the compiler would wait for it; lanes without a column read the row's first
+        in_tile = lane < 2 * kDepth && col0 < V;
+        four = Chunk::load_four(rowp, in_tile ? col0 : 0);
         const uint64_t grow = a.row_base + (uint64_t)row;
         philox4x32_10((uint32_t)(col0 >> 2), (uint32_t)grow, (uint32_t)(grow >> 32), 2u,
                       (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w);
@@ -130,23 +138,32 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
     if (live) {
         S_l = ldexp(p.S, sh);
         W_l = ldexp(p.W - d * p.S, sh);
-        if (lane != peak_lane && p.top > -INFINITY) {      // a wave may have excluded nothing
+        if (!is_peak && p.top > -INFINITY) {      // a wave may have excluded nothing
             const double tw = (double)p.top * cd - (double)R;
-            const double ew = (double)exp2f((float)tw);
+            // 2^tw, tw <= 0: integer and fraction apart (exact), so that no intermediate leaves fp32's range
+            const double whole = rint(tw);
+            const double ew = ldexp((double)__builtin_amdgcn_exp2f((float)(tw - whole)), whole < -4000.0 ? -4000 : (int)whole);
             S_l += ew;
             W_l += tw * ew;
         }
     }
-    const double S_rest = kFew ? row16_sum(S_l) : wave_sum(S_l);
-    const double W_rest = kFew ? row16_sum(W_l) : wave_sum(W_l);
+    double S_rest = S_l, W_rest = W_l;
+    if (kFew) {
+        // lanes 0..15 add up S, lanes 16..31 W
+        const double both = row16_sums(lane < 16 ? S_l : W_l);
+        S_rest = read_lane(both, 0);
+        W_rest = read_lane(both, 16);
+    } else {
+        wave_sum2(S_rest, W_rest);
+    }
     // With e_p = 2^{t_p} the peak's term, x = S_rest / e_p and y = W_rest / e_p:
     //   ln S = t_p ln2 + log1p(x),   H = ln S - ln2 W / S = log1p(x) + ln2 (t_p x - y) / (1 + x),
     // every piece of which is O(x) when the row is peaked.  t_p lies in (-1, 0].
     const double t_p = (double)peak * cd - (double)R;
-    const double inv_ep = (double)exp2f((float)-t_p);
+    const double inv_ep = (double)__builtin_amdgcn_exp2f((float)-t_p);
     const double x = S_rest * inv_ep, y = W_rest * inv_ep;
-    const double l1p = (double)log1pf((float)x);
-    const double H = l1p + kLn2 * (t_p * x - y) / (1.0 + x);
+    const double l1p = log1p_of(x);
+    const double H = fma(kLn2 * (t_p * x - y), reciprocal(1.0 + x), l1p);
 
     if (lane == 0) {
         if (a.entropy_out) a.entropy_out[row] = (float)H;
@@ -162,14 +179,18 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
         // 2^{(z - z_peak) c} / E_col.  The row's peak serves as the reference: the winning
         // tile's largest column lies within 2^-34 of it (a tile further down cannot make up
         // the difference with its noise, whose range is 2^-24 .. 17), far from underflow.
-        Cand cb{-1.0f, 0x7FFFFFFF};
+        float cz[4], q[4];
+        Chunk::unpack_four(four, cz);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const bool ok = lane < 2 * kDepth && col0 + j < V;
-            const float q = __builtin_amdgcn_exp2f((cz[j] - peak) * c) * inv_e2[j];
-            cb = better(cb, Cand{ok ? q : -1.0f, ok ? (int)(col0 + j) : 0x7FFFFFFF});
+            const bool ok = in_tile && col0 + j < V;
+            q[j] = ok ? __builtin_amdgcn_exp2f((cz[j] - peak) * c) * inv_e2[j] : -1.0f;
         }
-        cb = row16_best(cb);
+        // the lane's best (of equals the lowest column), then the wave's: columns rise with the lane
+        const float q01 = fmaxf(q[0], q[1]), q23 = fmaxf(q[2], q[3]);
+        const float q_lane = fmaxf(q01, q23);
+        const int j_lane = q01 >= q23 ? (q[0] >= q[1] ? 0 : 1) : (q[2] >= q[3] ? 2 : 3);
+        const Cand cb = row16_best(Cand{q_lane, q_lane >= 0.0f ? (int)col0 + j_lane : 0x7FFFFFFF});
         int64_t tok = cb.idx;
         if (tok < 0 || tok >= V) tok = 0;                 // only reachable with non-finite input
         if (lane == 0) a.token_out[row] = (int32_t)tok;
@@ -360,8 +381,8 @@ void vocab_pass_kernel(VocabPassArgs a, int rpb)
     // Hand over what this wave holds for local row r (n_items of its items); the wave
     // that brings the row's count to nst finishes the row.
     auto deliver = [&](LaneState& s, int r, int slot, int n_items) {
-        const double Sw = wave_sum((double)s.S);
-        const double Ww = wave_sum((double)s.W);
+        double Sw = (double)s.S, Ww = (double)s.W;
+        wave_sum2(Sw, Ww);
         const Cand wb = kSample ? wave_best(s.best) : Cand{-1.0f, 0};
         uint32_t before = 0;
         if (lane == 0) {
@@ -549,8 +570,8 @@ void vocab_split_kernel(VocabPassArgs a, RowPartial* __restrict__ ws, int nslots
             close_tile<kSample>(s, tile, inv_e, any_valid, c, lane);
         }
     }
-    const double Sw = wave_sum((double)s.S);
-    const double Ww = wave_sum((double)s.W);
+    double Sw = (double)s.S, Ww = (double)s.W;
+    wave_sum2(Sw, Ww);
     const Cand wb = kSample ? wave_best(s.best) : Cand{-1.0f, 0};
     if (lane == 0) {
         RowPartial p;

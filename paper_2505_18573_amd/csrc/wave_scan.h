@@ -28,11 +28,4 @@ __device__ __forceinline__ double wave_prefix_sum(double v)
     return v;
 }
 
-// A lane's value, wave-uniform.
-__device__ __forceinline__ double read_lane(double v, int lane)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                            __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-
 }  // namespace e3
