@@ -350,6 +350,14 @@ struct ChunkBf16 {
     {
         v = stream_load(reinterpret_cast<const u32x4*>(row + col * 2));
     }
+    // by vectors of 16 bytes: a chunk is one of them
+    static constexpr int kHalves = 1, kVecCols = 8;
+    static __device__ __forceinline__ void unpack_vec(const u32x4& x, float z[8])
+    {
+        ChunkBf16 c;
+        c.v = x;
+        c.unpack(z);
+    }
     static __device__ __forceinline__ int sweep_col(int lane) { return lane * 8; }
     static __device__ __forceinline__ int tile_lane(int lane) { return lane; }
     __device__ __forceinline__ void load_sweep(const char* row, int64_t col) { load(row, col); }
@@ -402,6 +410,13 @@ struct ChunkF32 {
         z[2] = __uint_as_float(a.z); z[3] = __uint_as_float(a.w);
         z[4] = __uint_as_float(b.x); z[5] = __uint_as_float(b.y);
         z[6] = __uint_as_float(b.z); z[7] = __uint_as_float(b.w);
+    }
+    // by vectors of 16 bytes: a chunk is two of them
+    static constexpr int kHalves = 2, kVecCols = 4;
+    static __device__ __forceinline__ void unpack_vec(const u32x4& x, float z[4])
+    {
+        z[0] = __uint_as_float(x.x); z[1] = __uint_as_float(x.y);
+        z[2] = __uint_as_float(x.z); z[3] = __uint_as_float(x.w);
     }
     // A sweep of fp32 is 2 KiB: the first load takes 16 bytes per lane from its first
     // KiB, the second from its second KiB.  Lanes 2k and 2k+1 then hold between them

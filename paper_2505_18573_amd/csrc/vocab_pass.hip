@@ -60,6 +60,55 @@ __host__ __device__ inline size_t lds_bytes(int rpb, int nst, bool sample)
          + (sample ? (size_t)rpb * nst * kLanes * sizeof(float) : 0);
 }
 
+// A partial brought to the reference R >= its own (exact scaling; an empty one counts nothing).  Its excluded maximum joins the
+// sums as an ordinary term unless it is the row's.
+__device__ __forceinline__ float scaled_mass(const RowPartial& p, float R)
+{
+    const double d = (double)R - (double)p.rc;                         // integer >= 0
+    return p.rc > -INFINITY ? ldexpf(p.q, d > 4000.0 ? -4000 : -(int)d) : -1.0f;
+}
+__device__ __forceinline__ void scaled_sums(const RowPartial& p, float R, bool is_peak, double cd, double& S, double& W)
+{
+    S = 0.0; W = 0.0;
+    if (p.rc > -INFINITY) {
+        const double d = (double)R - (double)p.rc;
+        const int sh = d > 4000.0 ? -4000 : -(int)d;
+        S = ldexp(p.S, sh);
+        W = ldexp(p.W - d * p.S, sh);
+        if (!is_peak && p.top > -INFINITY) {                           // a wave may have excluded nothing
+            const double tw = (double)p.top * cd - (double)R;
+            // 2^tw, tw <= 0: integer and fraction apart (exact), so that no intermediate leaves fp32's range
+            const double whole = rint(tw);
+            const double ew = ldexp((double)__builtin_amdgcn_exp2f((float)(tw - whole)), whole < -4000.0 ? -4000 : (int)whole);
+            S += ew;
+            W += tw * ew;
+        }
+    }
+}
+
+// Several partials of one row (at most sixteen, in LDS) as one, by the first lanes of a wave: the sums at the largest
+// reference, every excluded maximum but the largest an ordinary term.
+__device__ __forceinline__ RowPartial merge_partials(const RowPartial* parts, int nparts, float c, int lane)
+{
+    RowPartial p;
+    p.S = 0.0; p.W = 0.0; p.rc = -INFINITY; p.top = -INFINITY; p.q = -1.0f; p.tile = 0;
+    const int slot = lane & 15;                                        // lanes 16..31 hold them once more
+    if (slot < nparts) p = parts[slot];
+    float R = p.rc, peak = p.top;
+    row16_max2(R, peak);
+    const bool is_peak = slot == (int)__builtin_ctzll(__ballot(p.top == peak) | (1ull << 63));
+    RowPartial m;
+    m.rc = R; m.top = peak;
+    const Cand best = row16_best(Cand{scaled_mass(p, R), p.tile});
+    double S, W;
+    scaled_sums(p, R, is_peak, (double)c, S, W);
+    m.q = best.q; m.tile = best.idx;
+    const double both = row16_sums(lane < 16 ? S : W);
+    m.S = read_lane(both, 0);
+    m.W = read_lane(both, 16);
+    return m;
+}
+
 // Row epilogue, run by one wave once all of the row's partials are written: merge the
 // partials (one per lane, nparts <= 64), level 2 of the sampler or the target gather,
 // outputs.  kFew: the partials sit in the first sixteen lanes (a row-block workgroup hands
@@ -102,11 +151,8 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
     else wave_max2(R, peak);
     const unsigned long long holders = __ballot(p.top == peak);
     const int peak_lane = (int)__builtin_ctzll(holders | (1ull << 63));
-    const bool live = p.rc > -INFINITY;
     const bool is_peak = slot == peak_lane;
     const double cd = (double)c;
-    const double d = live ? (double)R - (double)p.rc : 0.0;       // integer >= 0
-    const int sh = d > 4000.0 ? -4000 : -(int)d;
 
     // Rollout side, level 1 across partials first (weights brought to the common
     // reference by exact scaling), so that the columns of the winning tile are
@@ -117,7 +163,7 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
     int64_t col0 = 0;
     bool in_tile = false;
     if (kSample) {
-        const Cand mine{live ? ldexpf(p.q, sh) : -1.0f, p.tile};
+        const Cand mine{scaled_mass(p, R), p.tile};
         const Cand win = kFew ? row16_best(mine) : wave_best(mine);
         const int wst = win.idx / kLanes, wslot = win.idx % kLanes;
         // 2 * kDepth lanes x 4 consecutive columns cover the tile
@@ -134,19 +180,8 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
     }
 
     // Row sums in fp64.
-    double S_l = 0.0, W_l = 0.0;
-    if (live) {
-        S_l = ldexp(p.S, sh);
-        W_l = ldexp(p.W - d * p.S, sh);
-        if (!is_peak && p.top > -INFINITY) {      // a wave may have excluded nothing
-            const double tw = (double)p.top * cd - (double)R;
-            // 2^tw, tw <= 0: integer and fraction apart (exact), so that no intermediate leaves fp32's range
-            const double whole = rint(tw);
-            const double ew = ldexp((double)__builtin_amdgcn_exp2f((float)(tw - whole)), whole < -4000.0 ? -4000 : (int)whole);
-            S_l += ew;
-            W_l += tw * ew;
-        }
-    }
+    double S_l, W_l;
+    scaled_sums(p, R, is_peak, cd, S_l, W_l);
     double S_rest = S_l, W_rest = W_l;
     if (kFew) {
         // lanes 0..15 add up S, lanes 16..31 W
@@ -505,78 +540,193 @@ void vocab_pass_kernel(VocabPassArgs a, int rpb)
 // ---------------------------------------------------------------------------
 // Small batches.  When the rows are too few to give every compute unit a workgroup
 // of whole rows, a row is cut into `nslots` runs of consecutive super-tiles and
-// every run gets a one-wave workgroup of its own, so that all of the chip's memory
-// channels are busy even for a single row.  A wave requests a whole super-tile (all
-// kDepth sweeps) at once, refills each register with the same sweep of its next super-tile
-// as soon as it has consumed it, draws the level-1 noise of its own tiles while the
-// loads are in flight, and writes one RowPartial to the workspace.  A second launch
+// every run gets a workgroup of its own, so that all of the chip's memory
+// channels are busy even for a single row; it writes one RowPartial to the workspace, and a second launch
 // of one wave per row merges a row's partials exactly as the row-block kernel's
 // epilogue does.
+//
+// Such a launch is bound by latency: the first data arrive after 1 to 2 us, and a wave alone on its SIMD issues an
+// instruction every five cycles.  So a super-tile is dealt to kParts waves: a wave takes 64 / kParts of its tiles, several lanes
+// share a tile, each reading 16-byte vectors of its own (a wave's request covers whole runs of the row), all vectors are
+// requested at once and the level-1 noise is drawn while they are in flight.  With everything in registers the wave's
+// maximum comes first and the exponentials need no running reference.  The waves' partials meet in LDS.
+// Four waves for every super-tile of fp32 and for a few hundred bf16 ones,
+// one wave for more of those, where four times the fixed work per wave would keep the vector ALUs busy longer (see split_plan).
+// Against one wave per super-tile with a running reference, both launches, us: bf16 x 151,936, 1 row 7.3 -> 5.7, 4 rows
+// 7.6 -> 6.2, 64 rows 10.5 -> 9.0, 128 rows 14.6 -> 12.3; fp32 x 70,005, 100 rows 11.0 -> 10.3, 128 rows 12.6 -> 11.6.
 // ---------------------------------------------------------------------------
-template <typename Chunk, bool kSample>
-__global__ __launch_bounds__(64)
+constexpr int kMaxRun = 4;           // super-tiles of a run: a row has at most 64 runs
+
+template <typename Chunk, int kParts>
+struct SplitShape {
+    static constexpr int kTiles = kLanes / kParts;                  // tiles of a wave
+    static constexpr int kRowVecs = kTiles * Chunk::kHalves;        // vectors of one sweep that belong to them
+    static constexpr int kGroups = 64 / kRowVecs;                   // lanes / kRowVecs: which sweeps a lane reads
+    static constexpr int kVecs = kDepth / kGroups;                  // vectors of a lane, kGroups sweeps apart
+    static_assert(kRowVecs <= 64 && kGroups * kRowVecs == 64 && kGroups <= 4 && kVecs * kGroups == kDepth, "whole shares");
+    // lanes that between them hold every tile of the wave once (sharers agree on its mass)
+    static constexpr unsigned long long kOnce = (kRowVecs == 64 ? ~0ull : (1ull << (kRowVecs & 63)) - 1ull)
+                                              & (Chunk::kHalves == 2 ? 0x5555555555555555ull : ~0ull);
+    // a lane's value and those of its tile's other lanes, added up
+    static __device__ __forceinline__ float sum(float v)
+    {
+        if (Chunk::kHalves == 2) v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kDppXor1, 0xF, 0xF, true));
+        if (kGroups >= 2) {
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+            v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+        if (kGroups >= 4) {
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+            v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+        return v;
+    }
+};
+
+// One super-tile's share of a wave in two steps: the requests, and what it amounts to (wave-uniform).
+template <typename Chunk, int kParts>
+struct SplitShare : SplitShape<Chunk, kParts> {
+    using Shape = SplitShape<Chunk, kParts>;
+    static constexpr int kCols = Chunk::kVecCols;
+    u32x4 x[Shape::kVecs];
+
+    static __device__ __forceinline__ int tile_of(int lane, int part)  // in the super-tile
+    {
+        return part * Shape::kTiles + lane % Shape::kRowVecs / Chunk::kHalves;
+    }
+    static __device__ __forceinline__ int col_of(int lane, int part)   // of the lane's first vector, in the super-tile
+    {
+        return tile_of(lane, part) * kChunk + lane % Chunk::kHalves * kCols + lane / Shape::kRowVecs * kSweepCols;
+    }
+    // Requests without branches.  The 16 bytes that hold a column of the row lie inside its pitch; a vector past
+    // the row's end is replaced by its first.
+    __device__ __forceinline__ void request(const char* rowp, int st, int nfull, int64_t V, int lane, int part)
+    {
+        const int64_t col0 = (int64_t)st * kSuperCols + col_of(lane, part);
+#pragma unroll
+        for (int i = 0; i < Shape::kVecs; ++i) {
+            const int64_t col = col0 + i * Shape::kGroups * kSweepCols;
+            const int64_t at = st < nfull || col < V ? col : 0;
+            x[i] = stream_load(reinterpret_cast<const u32x4*>(rowp + at * Chunk::kElemBytes));
+        }
+    }
+    template <bool kSample>
+    __device__ __forceinline__ RowPartial reduce(int st, int nfull, int64_t V, float c, float inv_e, int lane, int part) const
+    {
+        RowPartial p;
+        p.S = 0.0; p.W = 0.0; p.rc = -INFINITY; p.top = -INFINITY; p.q = -1.0f; p.tile = 0;
+        // (the lowest column of a wave is the first of its first tile)
+        const int64_t first_col = (int64_t)st * kSuperCols;
+        if (first_col + part * Shape::kTiles * kChunk >= V) return p;  // uniform
+        float z[Shape::kVecs][kCols], cm[Shape::kVecs], most = kAbsent;
+#pragma unroll
+        for (int i = 0; i < Shape::kVecs; ++i) {
+            Chunk::unpack_vec(x[i], z[i]);
+            if (st >= nfull) {                                         // columns past V are absent
+                const int64_t left = V - (first_col + col_of(lane, part) + i * Shape::kGroups * kSweepCols);
+#pragma unroll
+                for (int j = 0; j < kCols; ++j) z[i][j] = j < left ? z[i][j] : kAbsent;
+            }
+            cm[i] = kCols == 8 ? fmax3(fmax3(z[i][0], z[i][1], z[i][2]), fmax3(z[i][3], z[i][kCols - 4], z[i][kCols - 3]),
+                                       fmaxf(z[i][kCols - 2], z[i][kCols - 1]))
+                               : fmax3(fmax3(z[i][0], z[i][1], z[i][2]), z[i][3], z[i][3]);
+            most = fmaxf(most, cm[i]);
+        }
+        // The wave's maximum is kept out of the sums (see LaneState): all logits that equal it are struck, and
+        // those beyond the first come back as ordinary terms.
+        const float top = wave_max(most);
+        const float rc = uniform_f(reference_for(top, c));
+        int struck = 0;
+#pragma unroll
+        for (int i = 0; i < Shape::kVecs; ++i) {
+            if (__any(cm[i] == top)) {
+#pragma unroll
+                for (int j = 0; j < kCols; ++j) {
+                    const bool hit = z[i][j] == top;
+                    z[i][j] = hit ? kAbsent : z[i][j];
+                    struck += hit;
+                }
+            }
+        }
+        float s0 = 0.0f, s1 = 0.0f, w0 = 0.0f, w1 = 0.0f;
+#pragma unroll
+        for (int i = 0; i < Shape::kVecs; ++i) {
+#pragma unroll
+            for (int j = 0; j < kCols; ++j) {
+                const float t = fmaf(z[i][j], c, -rc);
+                const float e = __builtin_amdgcn_exp2f(t);
+                if (j & 1) { s1 += e; w1 = fmaf(t, e, w1); }
+                else       { s0 += e; w0 = fmaf(t, e, w0); }
+            }
+        }
+        float s = s0 + s1, w = w0 + w1;
+        const float t_top = fmaf(top, c, -rc), e_top = __builtin_amdgcn_exp2f(t_top);
+        const unsigned long long holders = __ballot(struck != 0);
+        const float mass = fmaf((float)struck, e_top, s);
+        if (__any(struck > 1) || (holders & (holders - 1ull)) != 0ull) {               // rare
+            const float again = (float)(struck - (lane == (int)__builtin_ctzll(holders | 1ull << 63))) * e_top;
+            s += again;
+            w = fmaf(t_top, again, w);
+        }
+        p.S = (double)s; p.W = (double)w;
+        wave_sum2(p.S, p.W);
+        p.rc = rc; p.top = top;
+        if (kSample) {
+            const int tile = tile_of(lane, part);
+            const bool nonempty = first_col + tile * kChunk < V;
+            const Cand mine{nonempty ? Shape::sum(mass) * inv_e : -1.0f, st * kLanes + tile};
+            const Cand best = holder_of(mine, Shape::kRowVecs == 16 ? row16_max(mine.q) : wave_max(mine.q), Shape::kOnce);
+            p.q = best.q; p.tile = best.idx;
+        }
+        return p;
+    }
+};
+
+// 1 / E of level 1 for a sampler tile.
+__device__ __forceinline__ float tile_noise(const VocabPassArgs& a, uint64_t grow, int tile)
+{
+    uint32_t w[4];
+    philox4x32_10((uint32_t)(tile >> 2), (uint32_t)grow, (uint32_t)(grow >> 32), 1u,
+                  (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w);
+    const int k = tile & 3;
+    return inv_exp_variate(k == 0 ? w[0] : k == 1 ? w[1] : k == 2 ? w[2] : w[3]);
+}
+
+template <typename Chunk, bool kSample, int kParts>
+__global__ __launch_bounds__(64 * kParts)
 void vocab_split_kernel(VocabPassArgs a, RowPartial* __restrict__ ws, int nslots)
 {
-    const int lane = threadIdx.x;
+    using Share = SplitShare<Chunk, kParts>;
+    __shared__ RowPartial parts[kMaxRun * kParts];
+    const int lane = threadIdx.x & 63;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t V = a.V;
     const int nst = (int)((V + kSuperCols - 1) / kSuperCols);
     const int nfull = (int)(V / kSuperCols);
-    const int64_t row = (int64_t)blockIdx.x / nslots;
-    const int slot = (int)((int64_t)blockIdx.x - row * nslots);
+    const int64_t row = (int64_t)(blockIdx.x / (unsigned)nslots);
+    const int slot = (int)(blockIdx.x - (unsigned)row * (unsigned)nslots);
     const int st_begin = slot * nst / nslots;        // runs differ by at most one super-tile
     const int st_end = (slot + 1) * nst / nslots;
-
     const char* rowp = static_cast<const char*>(a.logits) + row * a.row_stride * (int64_t)Chunk::kElemBytes;
-    const int64_t lane_col = (int64_t)lane * kChunk;            // own columns (incomplete sweeps)
-    const int64_t sweep_lane_col = Chunk::sweep_col(lane);      // complete sweeps: see the loaders
-    const int tlane = Chunk::tile_lane(lane);
-
-    Chunk buf[kDepth];
-    if (st_begin < nfull) {
-        const int64_t b0 = (int64_t)st_begin * kSuperCols + sweep_lane_col;
-#pragma unroll
-        for (int i = 0; i < kDepth; ++i) buf[i].load_sweep(rowp, b0 + i * kSweepCols);
-    }
-    const float tau = a.tau_rows ? a.tau_rows[row] : a.tau_scalar;
-    const float c = kLog2eF / tau;
     const uint64_t grow = a.row_base + (uint64_t)row;
 
-    LaneState s;
-    start_row(s, -INFINITY, c);
+    float c = 0.0f;
     for (int st = st_begin; st < st_end; ++st) {
-        const int tile = st * kLanes + (st < nfull ? tlane : lane);
-        float inv_e = 0.0f;
-        if (kSample) {
-            uint32_t w[4];
-            philox4x32_10((uint32_t)(tile >> 2), (uint32_t)grow, (uint32_t)(grow >> 32), 1u,
-                          (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w);
-            const int k = tile & 3;
-            inv_e = inv_exp_variate(k == 0 ? w[0] : k == 1 ? w[1] : k == 2 ? w[2] : w[3]);
-        }
-        if (st < nfull) {
-            const bool refill = st + 1 < st_end && st + 1 < nfull;     // uniform
-            const int64_t nb = (int64_t)(st + 1) * kSuperCols + sweep_lane_col;
-#pragma unroll
-            for (int i = 0; i < kDepth; ++i) {
-                float z[8];
-                buf[i].unpack_sweep(z, lane);
-                if (refill) buf[i].load_sweep(rowp, nb + i * kSweepCols);
-                accumulate_chunk(s, z, c, lane);
-            }
-            close_tile<kSample>(s, tile, inv_e, true, c, lane);
-        } else {
-            const bool any_valid = stream_ragged<Chunk>(s, rowp, (int64_t)st * kSuperCols + lane_col,
-                                                        lane_col, V, c, lane);
-            close_tile<kSample>(s, tile, inv_e, any_valid, c, lane);
+        Share share;
+        share.request(rowp, st, nfull, V, lane, part);
+        if (st == st_begin) c = kLog2eF / (a.tau_rows ? a.tau_rows[row] : a.tau_scalar);
+        const float inv_e = kSample ? tile_noise(a, grow, st * kLanes + Share::tile_of(lane, part)) : 0.0f;
+        const RowPartial p = share.template reduce<kSample>(st, nfull, V, c, inv_e, lane, part);
+        if (lane == 0) {
+            if (kParts == 1 && st_end - st_begin == 1) ws[(size_t)blockIdx.x] = p;
+            else parts[(st - st_begin) * kParts + part] = p;
         }
     }
-    double Sw = (double)s.S, Ww = (double)s.W;
-    wave_sum2(Sw, Ww);
-    const Cand wb = kSample ? wave_best(s.best) : Cand{-1.0f, 0};
-    if (lane == 0) {
-        RowPartial p;
-        p.S = Sw; p.W = Ww; p.rc = s.rc; p.top = s.top; p.q = wb.q; p.tile = wb.idx;
-        ws[(size_t)blockIdx.x] = p;
+    if (kParts == 1 && st_end - st_begin == 1) return;
+    __syncthreads();
+    if (part == 0) {
+        const RowPartial m = merge_partials(parts, (st_end - st_begin) * kParts, c, lane);
+        if (lane == 0) ws[(size_t)blockIdx.x] = m;
     }
 }
 
@@ -776,13 +926,18 @@ constexpr int64_t kSplitMaxRows = 1024;          // bound used by the workspace 
 
 struct SplitPlan {
     int nslots;      // runs per row, 1 <= nslots <= min(64, super-tiles per row)
+    int waves;       // of a run's workgroup
 };
 
-static SplitPlan split_plan(int64_t V)
+static SplitPlan split_plan(int64_t rows, int64_t V, bool is_bf16)
 {
     const int nst = (int)((V + kSuperCols - 1) / kSuperCols);
     SplitPlan p;
     p.nslots = nst < 64 ? nst : 64;
+    // One / four waves per super-tile, bf16, us: 8 rows x 33,000 (72 super-tiles) 6.8 / 6.2, 4 x 151,936 (152) 6.7 / 6.2, 32 x 33,000
+    // (288) 7.1 / 6.8, 32 x 40,960 (320) 6.6 / 6.7, 64 x 33,000 (576) 7.4 / 7.5, 128 x 70,005 (2304) 9.1 / 10.8; fp32 loads
+    // twice the bytes for the same arithmetic: four are faster at every count (100 x 70,005 10.9 / 10.3).
+    p.waves = is_bf16 && rows * p.nslots * 4 > (int64_t)compute_units() * 5 ? 1 : 4;
     return p;
 }
 
@@ -799,11 +954,15 @@ static hipError_t launch_split(const VocabPassArgs& a, RowPartial* ws, SplitPlan
     const unsigned blocks = (unsigned)(a.rows * plan.nslots);
     const LaunchEvents ev = take_launch_events();
     const RowPartial* parts = ws;
+    auto kernel = vocab_split_kernel<Chunk, kSample, 4>;
+    if constexpr (Chunk::kHalves == 1) {
+        if (plan.waves == 1) kernel = vocab_split_kernel<Chunk, kSample, 1>;
+    }
     if (ev.start != nullptr)
-        hipExtLaunchKernelGGL((vocab_split_kernel<Chunk, kSample>), dim3(blocks), dim3(64), 0u, stream,
+        hipExtLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * plan.waves), 0u, stream,
                               ev.start, (hipEvent_t) nullptr, 0u, a, ws, plan.nslots);
     else
-        hipLaunchKernelGGL((vocab_split_kernel<Chunk, kSample>), dim3(blocks), dim3(64), 0, stream,
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * plan.waves), 0, stream,
                            a, ws, plan.nslots);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
@@ -846,7 +1005,7 @@ hipError_t launch_vocab_pass(const VocabPassArgs& args, bool is_bf16, bool sampl
     bool few = false;
     const LaunchPlan whole = vocab_pass_plan(a.rows, a.V, sample, &few);
     if (few && workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
-        const SplitPlan plan = split_plan(a.V);
+        const SplitPlan plan = split_plan(a.rows, a.V, is_bf16);
         if ((size_t)a.rows * plan.nslots * sizeof(RowPartial) <= workspace_bytes) {
             RowPartial* ws = static_cast<RowPartial*>(workspace);
             if (a.adv_groups > 0) {

@@ -723,6 +723,29 @@ def test_launch_shapes_of_small_batches(rows, V, dtype):
         assert torch.equal(out[4], e3.e3_grpo_advantages(rewards, offsets))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", [(2, 32_769), (3, 32_772), (2, 32_897), (4, 36_864), (2, 36_871), (35, 36_860), (36, 36_860),
+                                    (1, 64 * 4096 + 4), (2, 130 * 4096 + 513), (1, 254 * 4096)])
+def test_shares_of_cut_rows(rows, V, dtype):
+    # a super-tile is dealt to four waves or one (bf16: up to 320 super-tiles, so 35 rows of nine, or more), the last one may
+    # leave waves, lanes and parts of a vector without columns, runs hold up to four super-tiles; a maximum that
+    # several columns share, in one lane or many, counts as often as it occurs
+    g = torch.Generator(device=DEV).manual_seed(rows * 11 + V)
+    x = torch.randn((rows, -(-V // 8) * 8), generator=g, device=DEV) * 3
+    x[0, V - 1] = 9.0                                                  # the last column is likely
+    if rows > 1:
+        x[1] = x[1].clamp(max=6.0).round()                             # few levels, the largest many times
+    if rows > 2:
+        x[2] = -1.25                                                   # one level
+    if rows > 3:
+        x[3, ::512] = 11.0                                             # once per sweep: every lane of a tile
+    lg = x.to(dtype)[:, :V]
+    tau = (0.6 + 0.8 * torch.rand(rows, generator=g, device=DEV)).float()
+    check_sample(lg, tau, 1.0, seed=rows, row_base=3, label=f"cut {rows}x{V} {dtype}")
+    targets = torch.randint(0, V, (rows,), generator=g, device=DEV).to(torch.int32)
+    check_logprob(lg, targets, None, tau, 1.0, f"cut {rows}x{V} {dtype}")
+
+
 def test_streams_without_the_raw_handle(monkeypatch):
     # the binding takes torch's raw stream handle where there is one and a Stream object otherwise: the same
     # results on a stream of the caller's own either way, ordered behind what that stream did before
