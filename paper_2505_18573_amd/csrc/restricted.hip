@@ -34,7 +34,7 @@
 // What bounds it.  The counting: an LDS atomic on 64 random counters takes 7.7 cycles (4 without a bank
 // conflict), 7.6 us for the 151,936 columns of a row alone on its compute unit, and five vector
 // instructions go with it; two rows together sit between that, the issue of those instructions and HBM.
-// Then five short phases per row (levels and scan 2.2 us, cuts 1.2, race 0.9, look-up 2.2 to 3), chains of
+// Then five short phases per row (levels and scan 2.0 us, cuts 1.2, race 0.9, look-up 2.2 to 3), chains of
 // LDS, barriers and dependent instructions that the last rows of a launch have nothing to overlap with.
 // Hence workgroups of eight waves (per-wave work of the phases is done half as often as with sixteen:
 // 100 rows x 1000 columns 14.6 us with sixteen waves and 64 registers each, 9.8 now), two sets of requests in
@@ -43,8 +43,8 @@
 // about 114,688 columns on (eight / sixteen waves in us: 100 rows x 70,000 15.3 / 15.5, x 100,000 17.5 / 17.6, x 130,000 20.3 /
 // 19.5, x 400,000 45.3 / 39.4; 256 rows x 40,000 13.6 / 15.1, x 100,000 19.0 / 19.4, x 130,000 21.6 / 21.5).
 // Captured launches, top-p 0.9, sixteen waves with a burst of four requests / now: 8 x 151,936 23.0 /
-// 19.4 us, 256 rows 26.2 / 23.4, 512 rows 43.2 / 37.9 (4.1 TB/s), 1024 rows 82.6 / 73.5; 512 x 32,000 26.7 / 16.4,
-// 300 x 70,000 30.8 / 21.4, 512 x 5000 22.6 / 12.0.
+// 18.3 us, 256 rows 26.2 / 22.2, 512 rows 43.2 / 37.2 (4.2 TB/s), 1024 rows 82.6 / 72.1; 512 x 32,000 26.7 / 15.9,
+// 300 x 70,000 30.8 / 21.1, 512 x 5000 22.6 / 11.5.
 //
 // FEW ROWS, given a workspace.  A row alone on its compute unit is bound by that unit's LDS while the others idle.
 // Such rows are cut into eight slices, each counted by a workgroup of its own in the window that 64 vectors spread over the row
@@ -54,7 +54,7 @@
 // does hold, so that a row of small ones needs no list; if a slice then meets others, the second launch counts the
 // row anew (8 x 151,936 clamped to at most 0: 268 us when the window followed the largest value alone, and the
 // negative columns lay below it, 23 so; 3e-4 x ordinary with 30 columns at -30: 150 and 24).
-// 8 x 151,936, top-p 0.9: 19.4 us whole, 14.9 cut; with 100 columns allowed and -1e4 elsewhere 57 and 23 us.
+// 8 x 151,936, top-p 0.9: 18.3 us whole, 14.2 cut; with 100 columns allowed and -1e4 elsewhere 57 and 23 us.
 //
 // A row with values above the window, or with more small ones than the list holds, is counted once
 // more in a window raised to the former or lowered for the latter; its waves give the first count up as
@@ -245,37 +245,40 @@ static __device__ __forceinline__ void own_mass(View& vw, int e, float z_top, do
     if (vw.Cl > 0) {
         vw.w_top = exp(((double)z_top - z1) * inv_tau);
         vw.r = exp(-ldexp(1.0, (e ? e : 1) - 134) * inv_tau);
-        double w = vw.w_top, m = 0.0;
+        // from the lowest level up, in units of level `top`'s weight: levels above it have no columns and leave the sum alone
+        double m = 0.0;
 #pragma unroll kUnroll
-        for (int j = 0; j < kOwn; ++j) {
-            m = fma((double)cnt(j), w, m);
-            w = next_weight(vw, w, j);
+        for (int j = kOwn - 1; j >= 0; --j) {
+            const uint32_t n = (uint32_t)cnt(j);
+            const double up = fma(m, vw.r, (double)n);
+            m = j >= vw.top ? up : m;
         }
-        vw.Ml = m;
+        vw.Ml = m * vw.w_top;
     }
 }
 
+// Prefixes over the waves, one wave per lane (lanes from kRWaves on hold the totals).
+struct Waves { int C; double M; };
+
 // Exclusive scan of counts and masses in thread order = rank order; threads from `mid_at` on
-// also have the middle's totals before them, which one wave has left in LDS.  Returns the totals of the scanned levels.
-static __device__ __forceinline__ void scan_view(View& vw, int carry_C, double carry_M, int mid_at,
-                                          int& Ct, double& Mt, Shared& sh, int tid)
+// also have the middle's totals before them, which one wave has left in LDS.  Returns the inclusive prefixes of the scanned levels over the waves.
+static __device__ __forceinline__ Waves scan_view(View& vw, int carry_C, double carry_M, int mid_at, Shared& sh, int tid)
 {
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int Ci = 0;
     double Mi = 0.0;
-    if (__any(vw.Cl > 0)) { Ci = wave_prefix_sum(vw.Cl); Mi = wave_prefix_sum(vw.Ml); }
+    if (__any(vw.Cl > 0)) wave_prefix_sum2(vw.Cl, vw.Ml, Ci, Mi);
     if (lane == 63) { sh.wave_C[wave] = Ci; sh.wave_M[wave] = Mi; }
     __syncthreads();
-    const int tC = wave_prefix_sum(lane < kRWaves ? sh.wave_C[lane] : 0);
-    const double tM = wave_prefix_sum(lane < kRWaves ? sh.wave_M[lane] : 0.0);
-    Ct = __builtin_amdgcn_readlane(tC, kRWaves - 1);
-    Mt = read_lane(tM, kRWaves - 1);
+    Waves all;
+    row16_prefix_sum2(lane < kRWaves ? sh.wave_C[lane & (kRWaves - 1)] : 0, lane < kRWaves ? sh.wave_M[lane & (kRWaves - 1)] : 0.0, all.C, all.M);
     int Cb = carry_C;
     double Mb = carry_M;
-    if (wave > 0) { Cb += __builtin_amdgcn_readlane(tC, wave - 1); Mb += read_lane(tM, wave - 1); }
+    if (wave > 0) { Cb += __builtin_amdgcn_readlane(all.C, wave - 1); Mb += read_lane(all.M, wave - 1); }
     if (tid >= mid_at) { Cb += sh.mid_C[63]; Mb += sh.mid_M[63]; }
     vw.Cx = Cb + Ci - vw.Cl;
     vw.Mx = Mb + (Mi - vw.Ml);
+    return all;
 }
 
 // Cut search among one thread's levels: the level whose cumulative count reaches k.
@@ -549,10 +552,8 @@ static __device__ __forceinline__ void wide_row(const Row& row, const Restricted
             if (best >= 0.0f) { have_z1 = true; z1 = (double)value_of_pattern(pattern_of_key((int)best)); }
         }
         own_mass<kOwnW, kOwnW>(vw, (p_top >> 7) & 0xFF, value_of_pattern(p_top), z1, inv_tau, [&](int j) { return cnt[j]; });
-        int Ct;
-        double Mt;
-        scan_view(vw, C, M, kRThreads, Ct, Mt, sh, tid);
-        C += Ct; M += Mt;
+        const Waves all = scan_view(vw, C, M, kRThreads, sh, tid);
+        C += __builtin_amdgcn_readlane(all.C, kRWaves - 1); M += read_lane(all.M, kRWaves - 1);
     };
     int C_all = 0;
     double M_all = 0.0;
@@ -665,18 +666,24 @@ struct Near {
     {
         const bool neg = __builtin_amdgcn_readfirstlane(rank0) >= kHalf;         // a wave's levels have one sign
         const uint32_t* h = hist + (neg ? rank0 : kHalf - kOwnN - rank0);
-        uint32_t q01[kOwnN], q23[kOwnN];                          // in rising magnitude
+        uint32_t sum[kOwnN];                                      // in rising magnitude
+        auto from = [&](const uint4& a, const uint4& b, int i) {
+            sum[i] = (uint32_t)total(a.x, b.x); sum[i + 1] = (uint32_t)total(a.y, b.y);
+            sum[i + 2] = (uint32_t)total(a.z, b.z); sum[i + 3] = (uint32_t)total(a.w, b.w);
+        };
+        if (kOwnN == 8) {
+            // (sixteen waves: each four added as it comes, 256 rows x 151,936 22.7 -> 22.2 us)
 #pragma unroll
-        for (int i = 0; i < kOwnN; i += 4) {
-            const uint4 a = *reinterpret_cast<const uint4*>(h + i);
-            const uint4 b = *reinterpret_cast<const uint4*>(h + kArray + i);
-            q01[i] = a.x; q01[i + 1] = a.y; q01[i + 2] = a.z; q01[i + 3] = a.w;
-            q23[i] = b.x; q23[i + 1] = b.y; q23[i + 2] = b.z; q23[i + 3] = b.w;
+            for (int i = 0; i < kOwnN; i += 4) from(*reinterpret_cast<const uint4*>(h + i), *reinterpret_cast<const uint4*>(h + kArray + i), i);
+        } else {
+            uint4 a[kOwnN / 4], b[kOwnN / 4];
+#pragma unroll
+            for (int i = 0; i < kOwnN / 4; ++i) { a[i] = reinterpret_cast<const uint4*>(h)[i]; b[i] = reinterpret_cast<const uint4*>(h + kArray)[i]; }
+#pragma unroll
+            for (int i = 0; i < kOwnN / 4; ++i) from(a[i], b[i], 4 * i);
         }
 #pragma unroll
-        for (int j = 0; j < kOwnN; ++j) q01[j] = (uint32_t)total(q01[j], q23[j]);
-#pragma unroll
-        for (int j = 0; j < kOwnN; ++j) cnt[j] = (int)(neg ? q01[j] : q01[kOwnN - 1 - j]);
+        for (int j = 0; j < kOwnN; ++j) cnt[j] = (int)(neg ? sum[j] : sum[kOwnN - 1 - j]);
         static_assert(kTrash % kOwnN == 0, "a thread's words are levels or spare ones");
         if (rank0 < kTrash || rank0 >= 2 * kHalf - kTrash) {
 #pragma unroll
@@ -1069,21 +1076,30 @@ static __device__ __forceinline__ int gather_slices(const RestrictedArgs& a, int
         const SliceNotes* n = a.slice_notes + r * a.nslices + (lane < a.nslices ? lane : 0);
         const bool mine = lane < a.nslices;
         const int list_n = mine ? n->list_n : 0;
-        const int lists = wave_prefix_sum(list_n);
-        const int zero_p = wave_prefix_sum(mine ? n->zeros[0] : 0), zero_n = wave_prefix_sum(mine ? n->zeros[1] : 0);
-        const int below = wave_prefix_sum(mine ? n->n_below : 0), odd = wave_prefix_sum(mine ? n->n_not_finite : 0);
-        const float lo = -wave_max(mine ? -(float)n->below_lo : -32767.0f), hi = wave_max(mine ? (float)n->below_hi : 0.0f);
-        const int above = (int)wave_max(mine ? (float)n->above_hi : 0.0f), all_listed = __builtin_amdgcn_readlane(lists, 63);
-        if (lane == 63) {
-            sh.zeros[0][0] = zero_p; sh.zeros[1][0] = zero_n;
-            sh.list_n = lists; sh.n_below = below; sh.n_not_finite = odd; sh.n_above = 0;
-            sh.below_lo = (int)lo; sh.below_hi = (int)hi; sh.above_hi = above;
-        }
-        if (lane > 0 && lane < kQuarters) { sh.zeros[0][lane] = 0; sh.zeros[1][lane] = 0; }
-        if (all_listed <= kMidList) {
-            for (int i = 0; i < list_n; ++i) {
-                sh.list_key[lists - list_n + i] = n->list_key[i];
-                sh.list_col[lists - list_n + i] = n->list_col[i];
+        const int outside = mine ? list_n | n->zeros[0] | n->zeros[1] | n->n_below | n->n_not_finite | n->above_hi : 0;
+        if (!__any(outside != 0)) {                               // an ordinary row (8 x 151,936 14.8 -> 14.2 us without the sums)
+            if (lane < 2 * kQuarters) (&sh.zeros[0][0])[lane] = 0;
+            if (lane == 0) {
+                sh.list_n = 0; sh.n_below = 0; sh.n_not_finite = 0; sh.n_above = 0;
+                sh.below_lo = 0x7FFF; sh.below_hi = 0; sh.above_hi = 0;
+            }
+        } else {
+            const int lists = wave_prefix_sum(list_n);
+            const int zero_p = wave_prefix_sum(mine ? n->zeros[0] : 0), zero_n = wave_prefix_sum(mine ? n->zeros[1] : 0);
+            const int below = wave_prefix_sum(mine ? n->n_below : 0), odd = wave_prefix_sum(mine ? n->n_not_finite : 0);
+            const float lo = -wave_max(mine ? -(float)n->below_lo : -32767.0f), hi = wave_max(mine ? (float)n->below_hi : 0.0f);
+            const int above = (int)wave_max(mine ? (float)n->above_hi : 0.0f), all_listed = __builtin_amdgcn_readlane(lists, 63);
+            if (lane == 63) {
+                sh.zeros[0][0] = zero_p; sh.zeros[1][0] = zero_n;
+                sh.list_n = lists; sh.n_below = below; sh.n_not_finite = odd; sh.n_above = 0;
+                sh.below_lo = (int)lo; sh.below_hi = (int)hi; sh.above_hi = above;
+            }
+            if (lane > 0 && lane < kQuarters) { sh.zeros[0][lane] = 0; sh.zeros[1][lane] = 0; }
+            if (all_listed <= kMidList) {
+                for (int i = 0; i < list_n; ++i) {
+                    sh.list_key[lists - list_n + i] = n->list_key[i];
+                    sh.list_col[lists - list_n + i] = n->list_col[i];
+                }
             }
         }
     }
@@ -1198,7 +1214,8 @@ static __device__ __forceinline__ void run(const RestrictedArgs& a, uint32_t* hi
             sh.mid_C[lane] = wave_prefix_sum(n);
             sh.mid_M[lane] = wave_prefix_sum((double)n * w);
         }
-        scan_view(vw, 0, 0.0, has_mid ? kRThreads / 2 : kRThreads, C_win, M_win, sh, tid);
+        const Waves all = scan_view(vw, 0, 0.0, has_mid ? kRThreads / 2 : kRThreads, sh, tid);
+        C_win = __builtin_amdgcn_readlane(all.C, kRWaves - 1); M_win = read_lane(all.M, kRWaves - 1);
         top_key = row16_max(sh.wave_top[lane & (kRWaves - 1)]);
         z1 = top_key >= 0.0f ? (double)value_of_pattern(pattern_of_key((int)top_key)) : 0.0;
         if (again || fabs((z1 - z_ref) * inv_tau) < 256.0) break;                // uniform
