@@ -732,6 +732,56 @@ void vocab_split_kernel(VocabPassArgs a, RowPartial* __restrict__ ws, int nslots
     }
 }
 
+// ---------------------------------------------------------------------------
+// Narrow rows (at most kNarrowTiles super-tiles): a workgroup has a row, and a wave kItems shares (SplitShare) of its super-tiles.
+// The whole row is requested at once, the waves meet at one barrier, and the first merges the partials and finishes
+// the row: one launch, no running reference, no noise table, nothing that waits for another wave before the barrier.
+// Bound by latency up to some hundred rows, then by HBM and the launch of workgroups.  Against the streaming kernel, us: bf16 1 row x
+// 1000 5.5 -> 3.6, 64 x 8000 7.4 -> 4.4, 64 x 32,000 7.8 -> 5.9, 512 x 32,000 11.3 -> 9.6, 4096 x 16,000 33.5 -> 25.0 (5.2 TB/s),
+// 4096 x 32,000 56.5 -> 51.8; fp32 64 x 16,000 7.6 -> 5.3, 1024 x 32,000 26.7 -> 24.4, 4096 x 8000 30.6 -> 24.3.  (Four rows
+// of one super-tile to a workgroup, a wave each: 4096 x 1000 9.6 either way.)
+// ---------------------------------------------------------------------------
+constexpr int kNarrowTiles = 8;
+constexpr int kNarrowWaves = 16;     // of a workgroup at most
+
+template <typename Chunk, bool kSample, int kParts, int kItems>
+__global__ __launch_bounds__(64 * kNarrowWaves)
+void vocab_narrow_kernel(VocabPassArgs a)
+{
+    using Share = SplitShare<Chunk, kParts>;
+    __shared__ RowPartial parts[kNarrowTiles * 2];                     // at most sixteen: one row of lanes merges them
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = (int)(blockDim.x >> 6);
+    const int64_t V = a.V;
+    const int nfull = (int)(V / kSuperCols);
+    const int64_t row = blockIdx.x;
+    const char* rowp = static_cast<const char*>(a.logits) + row * a.row_stride * (int64_t)Chunk::kElemBytes;
+    const uint64_t grow = a.row_base + (uint64_t)row;
+
+    // item i: part i % kParts of super-tile i / kParts; wave w has the items w and, of two, w + waves
+    Share share[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int item = wave + i * waves;
+        share[i].request(rowp, item / kParts, nfull, V, lane, item % kParts);
+    }
+    const float c = kLog2eF / (a.tau_rows ? a.tau_rows[row] : a.tau_scalar);
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int item = wave + i * waves, st = item / kParts, part = item % kParts;
+        const float inv_e = kSample ? tile_noise(a, grow, st * kLanes + Share::tile_of(lane, part)) : 0.0f;
+        const RowPartial p = share[i].template reduce<kSample>(st, nfull, V, c, inv_e, lane, part);
+        if (lane == 0) parts[item] = p;
+    }
+    __syncthreads();
+    if (wave == 0) finish_row<Chunk, kSample, true>(a, row, parts, waves * kItems, lane);
+    // Training side, optional: workgroup b computes group b's advantages (see vocab_pass_kernel), here beside the row's last
+    // steps.  (While the columns are on their way it held 36 registers beside theirs: fp32 1000 x 20,000 25.1 us, 20.7 so.)
+    if (!kSample && a.adv_groups > 0 && wave == waves - 1 && (int)blockIdx.x < a.adv_groups)
+        advantages_of_group(a.adv_rewards, a.adv_offsets, (int)blockIdx.x, a.adv_ddof, a.adv_eps, a.adv_out, lane);
+}
+
 template <typename Chunk, bool kSample>
 __global__ __launch_bounds__(64)
 void row_finish_kernel(VocabPassArgs a, const RowPartial* __restrict__ ws, int nslots)
@@ -863,7 +913,7 @@ static hipError_t launch_groups(const VocabPassArgs& a, int rpb, hipStream_t str
     return hipGetLastError();
 }
 
-// How a batch is launched when rows are not cut.
+// How a batch of whole rows is launched through the streaming kernel.
 // Eight waves per workgroup while the whole batch is at most eight workgroups per
 // compute unit; four waves per workgroup beyond that, where the hardware dispatcher
 // balances across many small groups (measured crossover on MI355X: between 2048 and
@@ -871,29 +921,20 @@ static hipError_t launch_groups(const VocabPassArgs& a, int rpb, hipStream_t str
 // unit: a batch that fills its last round of 2 * CUs workgroups to less than 80 %
 // (768 rows on 256 CUs: 512 + 256) runs as 4-wave workgroups if those are all resident
 // at once (measured at 768 rows: 45.0 us instead of 49.3 us).
-static LaunchPlan whole_rows_plan(int64_t rows, int64_t V, bool sample)
+static LaunchPlan streaming_plan(int64_t rows, int64_t V, bool sample)
 {
     const int64_t cus = compute_units();
     auto plan = [&](int waves, int rpb) -> LaunchPlan {
         return LaunchPlan{waves, rpb, rpb > 0 ? (rows + rpb - 1) / rpb : 0};
     };
     // Several rows per workgroup only where that leaves a resident round of workgroups (nearly) full:
-    // 512 rows x 24,000 bf16 columns (three rows per workgroup before) 20.6 -> 11.8 us, 512 x 48,000
-    // (two) 18.7 -> 15.7 us; at 1000 rows x 32,000 two rows (18.6 us) beat one (19.6 us), hence the quarter.
+    // 512 rows x 48,000 bf16 columns (two rows per workgroup before) 18.7 -> 15.7 us.
     auto spread = [&](int rpb, int64_t round) -> int {
         const int64_t most = (rows + round / 4) / round;
         return rpb > 1 && most < rpb ? (most > 1 ? (int)most : 1) : rpb;
     };
     const int rpb8 = spread(rows_per_group<8>(V, sample), 2 * cus);
     const int rpb4 = spread(rows_per_group<4>(V, sample), 4 * cus);
-    // Rows of at most four super-tiles: four waves per workgroup and just enough rows to give each
-    // an item, while all workgroups are resident at once or nearly so (1100 x 1000 bf16: 14.1 -> 8.0 us,
-    // 1500 x 16,000: 20.4 -> 17.0 us; at 4096 x 8000 the larger groups below take the same time).
-    const int nst = (int)((V + kSuperCols - 1) / kSuperCols);
-    if (nst <= 4 && rpb4 > 0) {
-        const LaunchPlan narrow = plan(4, rows <= 4 * cus ? 1 : (4 + nst - 1) / nst);
-        if (narrow.workgroups <= 6 * cus) return narrow;
-    }
     const LaunchPlan eight = plan(8, rpb8), four = plan(4, rpb4);
     if (rpb8 == 0 || eight.workgroups > 8 * cus) return four;
     const int64_t round8 = 2 * cus;
@@ -903,9 +944,66 @@ static LaunchPlan whole_rows_plan(int64_t rows, int64_t V, bool sample)
     return eight;
 }
 
+// Narrow rows: shares per super-tile and per wave; every share has a place in the kernel's table (sixteen).
+struct NarrowPlan { int parts, items; };
+
+// While the waves of a batch leave the chip idle, more of them per super-tile are faster; beyond that they only multiply what every
+// wave does once.  bf16, one / two / four waves per super-tile, us: 256 rows x 4096 4.7 / 4.4 / 4.2, 512 rows 5.1 / 5.2 / 4.8, 768
+// rows 5.3 / 5.3 / 5.5; 256 x 8000 5.3 / 4.8 / 4.8, 512 rows 6.3 / 5.8 / 6.0, 768 rows 6.6 / 6.7 / 6.9; 256 x 16,000 5.7 / 5.6
+// / 5.7, 512 rows 7.4 / 7.2 / 7.7, 1024 rows 9.8 / 10.0 / 12.8; 256 x 32,000 7.1 / 6.9, 512 rows 9.9 / 10.1, 2048 rows 29.7 / 29.8.
+// fp32 has two to four; more than four super-tiles of two waves each are ten to sixteen waves, of which a compute unit has
+// few workgroups at a time, so that larger batches give a wave two shares (us with one / two): 512 x 20,000 10.4 / 11.6, 768 rows
+// 15.2 / 13.5; 256 x 32,000 9.0 / 9.5, 512 rows 15.5 / 14.4, 1024 rows 28.2 / 24.5, 4096 rows 95.2 / 80.2.
+static NarrowPlan narrow_plan(int64_t rows, int nst, bool is_bf16)
+{
+    const int64_t cus = compute_units();
+    if (!is_bf16) {
+        if (nst > 4) return NarrowPlan{2, rows <= (nst <= 6 ? 2 * cus : cus) ? 1 : 2};
+        return NarrowPlan{rows <= 2 * cus ? 4 : 2, 1};
+    }
+    if (nst <= 2 && rows * nst <= 2 * cus) return NarrowPlan{4, 1};
+    return NarrowPlan{rows <= (nst <= 6 ? 2 * cus : cus) ? 2 : 1, 1};
+}
+
+// Which narrow rows have a workgroup each: all but the larger fp32 batches of five or six super-tiles on the training side, where
+// two shares take 110 registers and the last super-tile's absent columns are worked through (us, the streaming kernel / so: 1000 x
+// 17,000 18.4 / 22.0, x 20,000 20.7 / 22.2, x 24,000 22.5 / 24.3, x 28,000 25.0 / 23.5).
+static bool narrow_serves(int64_t rows, int64_t nst, bool is_bf16, bool sample)
+{
+    return nst <= kNarrowTiles && (is_bf16 || sample || nst < 5 || nst > 6 || rows <= 2 * (int64_t)compute_units());
+}
+
+template <typename Chunk, bool kSample>
+static hipError_t launch_narrow(const VocabPassArgs& a, int nst, hipStream_t stream)
+{
+    const NarrowPlan plan = narrow_plan(a.rows, nst, Chunk::kElemBytes == 2);
+    auto kernel = plan.parts == 4 ? vocab_narrow_kernel<Chunk, kSample, 4, 1> : vocab_narrow_kernel<Chunk, kSample, 2, 1>;
+    if constexpr (Chunk::kHalves == 1) {
+        if (plan.parts == 1) kernel = vocab_narrow_kernel<Chunk, kSample, 1, 1>;
+    } else {
+        if (plan.items == 2) kernel = vocab_narrow_kernel<Chunk, kSample, 2, 2>;
+    }
+    const LaunchEvents ev = take_launch_events();
+    const dim3 blocks((unsigned)a.rows), threads(64u * (unsigned)(nst * plan.parts / plan.items));
+    if (ev.start != nullptr || ev.stop != nullptr)
+        hipExtLaunchKernelGGL(kernel, blocks, threads, 0u, stream, ev.start, ev.stop, 0u, a);
+    else
+        hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, a);
+    return hipGetLastError();
+}
+
+// Whole rows: a workgroup for each narrow one (vocab_narrow_kernel), sized by its super-tiles, else as above.
+static LaunchPlan whole_rows_plan(int64_t rows, int64_t V, bool sample)
+{
+    const int64_t nst = (V + kSuperCols - 1) / kSuperCols;
+    return nst <= kNarrowTiles ? LaunchPlan{nst <= 4 ? 4 : 8, 1, rows} : streaming_plan(rows, V, sample);
+}
+
 template <typename Chunk, bool kSample>
 static hipError_t launch_for(const VocabPassArgs& a, const LaunchPlan& plan, hipStream_t stream)
 {
+    const int64_t nst = (a.V + kSuperCols - 1) / kSuperCols;
+    if (narrow_serves(a.rows, nst, Chunk::kElemBytes == 2, kSample)) return launch_narrow<Chunk, kSample>(a, (int)nst, stream);
     return plan.waves == 8 ? launch_groups<Chunk, kSample, 8>(a, plan.rows_per_group, stream)
                            : launch_groups<Chunk, kSample, 4>(a, plan.rows_per_group, stream);
 }
@@ -923,7 +1021,6 @@ static hipError_t launch_for(const VocabPassArgs& a, const LaunchPlan& plan, hip
 // 12.3 / 14.5, 15.9 / 15.8; 192 rows 11.3 / 11.1, 13.8 / 15.1, 19.0 / 16.8; x 61,000 12.6 / 12.4 at 128 rows and
 // 13.7 / 12.6 at 192.  (Rows of a whole number of super-tiles are faster whole at any count, 128 x
 // 40,960 11.0 / 9.1; x 61,441, one column into the sixteenth, from 112 rows on by 4 %.)
-constexpr int kNarrowTiles = 8;
 constexpr int64_t kSplitMaxRows = 1024;          // bound used by the workspace size
 
 struct SplitPlan {
@@ -1005,7 +1102,9 @@ hipError_t launch_vocab_pass(const VocabPassArgs& args, bool is_bf16, bool sampl
     if (a.adv_groups > 0 && a.rows == 0) return separate_advantages();
     if (a.rows == 0) return hipSuccess;
     bool few = false;
-    const LaunchPlan whole = vocab_pass_plan(a.rows, a.V, sample, &few);
+    LaunchPlan whole = vocab_pass_plan(a.rows, a.V, sample, &few);
+    const int64_t nst = (a.V + kSuperCols - 1) / kSuperCols;
+    if (nst <= kNarrowTiles && !narrow_serves(a.rows, nst, is_bf16, sample)) whole = streaming_plan(a.rows, a.V, sample);
     if (few && workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
         const SplitPlan plan = split_plan(a.rows, a.V, is_bf16);
         if ((size_t)a.rows * plan.nslots * sizeof(RowPartial) <= workspace_bytes) {

@@ -746,6 +746,27 @@ def test_shares_of_cut_rows(rows, V, dtype):
     check_logprob(lg, targets, None, tau, 1.0, f"cut {rows}x{V} {dtype}")
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", [(2, 1), (3, 9), (2, 515), (5, 4_096), (257, 4_099), (256, 8_192), (260, 8_100), (513, 4_095), (515, 12_300),
+                                    (3, 16_387), (257, 20_480), (515, 24_001), (520, 16_500), (2, 28_673), (256, 32_768), (258, 32_761)])
+def test_shares_of_narrow_rows(rows, V, dtype):
+    # one, two or four waves per super-tile and one or two shares per wave, by the width and the number of rows (256 and 512); the
+    # last super-tile may leave waves, lanes and parts of a vector without columns; a maximum that several columns share
+    g = torch.Generator(device=DEV).manual_seed(rows * 5 + V)
+    x = torch.randn((rows, -(-V // 8) * 8), generator=g, device=DEV) * 3
+    x[0, V - 1] = 9.0                                                  # the last column is likely
+    x[1] = x[1].clamp(max=6.0).round()                                 # few levels, the largest many times
+    if rows > 2:
+        x[2] = -1.25                                                   # one level
+    if rows > 3:
+        x[3, ::512] = 11.0                                             # once per sweep: every lane of a tile
+    lg = x.to(dtype)[:, :V]
+    tau = (0.6 + 0.8 * torch.rand(rows, generator=g, device=DEV)).float()
+    check_sample(lg, tau, 1.0, seed=rows, row_base=3, label=f"narrow {rows}x{V} {dtype}")
+    targets = torch.randint(0, V, (rows,), generator=g, device=DEV).to(torch.int32)
+    check_logprob(lg, targets, None, tau, 1.0, f"narrow {rows}x{V} {dtype}")
+
+
 def test_streams_without_the_raw_handle(monkeypatch):
     # the binding takes torch's raw stream handle where there is one and a Stream object otherwise: the same
     # results on a stream of the caller's own either way, ordered behind what that stream did before
