@@ -37,7 +37,7 @@ EXPORTS = ("e3_strerror", "e3_workspace_bytes", "e3_sample_entropy", "e3_sample_
 
 _NATIVE_CALLS = ("e3_grpo_advantages", "e3_grpo_objective", "e3_workspace_bytes", "e3_sample_entropy",
                  "e3_restricted_workspace_bytes", "e3_sample_restricted_ws", "e3_logprob_entropy_advantages",
-                 "e3_temperature_update")
+                 "e3_logprob_entropy_gap", "e3_temperature_update")
 
 _lib: Optional[C.CDLL] = None
 _native = None                     # the native calls, once they are bound to the loaded library
@@ -144,7 +144,8 @@ def _ordinary(name: str, *args):
 
 _ENTRY = {"advantages": "e3_grpo_advantages", "objective": "e3_grpo_objective", "sample": "e3_sample_entropy",
           "restricted": "e3_sample_restricted", "logprob": "e3_logprob_entropy",
-          "logprob_advantages": "e3_logprob_entropy_advantages", "temperature": "e3_temperature_update"}
+          "logprob_advantages": "e3_logprob_entropy_advantages", "logprob_gap": "e3_logprob_entropy_gap",
+          "temperature": "e3_temperature_update"}
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -551,6 +552,9 @@ def e3_logprob_entropy_gap(logits: torch.Tensor, target_ids: Optional[torch.Tens
                            tau_scalar: float, workspace=None):
     """Returns (logp or None, entropy, gap, entropy_sum fp64 [1], gap_sum fp64 [1], count int64 [1]),
     all on the device."""
+    out = _ordinary("logprob_gap", logits, target_ids, row_mask, tau_rows, tau_scalar, workspace)
+    if out is not None:
+        return out
     dt, rows, V, stride = _logits_meta(logits)
     dev = logits.device
     logp = torch.empty(rows, dtype=torch.float32, device=dev) if target_ids is not None else None

@@ -1,7 +1,8 @@
 // The binding's hot calls without Python between the tensors and libe3.so.  A call of a few microseconds on the GPU took as
 // long in Python: about 0.7 us per checked tensor, 0.8 to 1.4 us per foreign call, 1.1 us per allocated output.
 // One pass among others, in Python / here: 64 x 8 advantages 5.7 / 3.6 us (the kernel 2.9), the objective of 512
-// rollouts 11.6 / 9.4 us (its kernels 8.9), a step of 512 rows, whose host work lies between two launches, 72.9 / 69.8 us.
+// rollouts 11.6 / 9.4 us (its kernels 8.9), a step of 512 rows, whose host work lies between two launches, 72.9 / 69.8 us,
+// log-probs with the measured gap of 1 row x 1000 16.5 / 10.9.
 //
 // Every function takes the arguments of the Python function it serves, and does what that does when they are ordinary: plain
 // torch tensors of the right type, size and device, Python ints and floats.  It returns the outputs; or the
@@ -26,6 +27,7 @@ decltype(&e3_sample_entropy) p_sample;
 decltype(&e3_restricted_workspace_bytes) p_restricted_bytes;
 decltype(&e3_sample_restricted_ws) p_restricted;
 decltype(&e3_logprob_entropy_advantages) p_logprob;
+decltype(&e3_logprob_entropy_gap) p_gap;
 decltype(&e3_temperature_update) p_temperature;
 PyObject* raw_stream = nullptr;
 
@@ -362,6 +364,36 @@ PyObject* logprob(PyObject*, PyObject* const* a, Py_ssize_t n_args)
     });
 }
 
+// logits, target_ids, row_mask, tau_rows, tau_scalar, workspace
+PyObject* logprob_gap(PyObject*, PyObject* const* a, Py_ssize_t n_args)
+{
+    if (n_args != 6) return unusual();
+    return guarded([&]() -> PyObject* {
+        Reader r;
+        const Logits l(r, a[0]);
+        const void* target = r.vector(a[1], at::kInt, l.rows);
+        const void* mask = r.vector(a[2], at::kByte, l.rows);
+        const void* tau = r.vector(a[3], at::kFloat, l.rows);
+        const double tau_scalar = r.number(a[4]);
+        if (!r.ok) return unusual();
+        Output logp, entropy, gap, sum, gap_sum, count;
+        if (a[1] == Py_None) logp.take(Py_None);
+        else logp.make(r, at::kFloat, l.rows);
+        entropy.make(r, at::kFloat, l.rows);
+        gap.make(r, at::kFloat, l.rows);
+        sum.make(r, at::kDouble, 1);
+        gap_sum.make(r, at::kDouble, 1);
+        count.make(r, at::kLong, 1);
+        const Workspace ws(r, a[5], l.rows, l.V);
+        return run(r, [&](void* s) {
+                       return p_gap(l.p, l.dtype, l.rows, l.V, l.pitch, (const int32_t*)target, (const uint8_t*)mask, (const float*)tau,
+                                    (float)tau_scalar, (float*)logp.p, (float*)entropy.p, (float*)gap.p, (double*)sum.p, (double*)gap_sum.p,
+                                    (int64_t*)count.p, ws.p, ws.bytes, s);
+                   },
+                   [&] { return PyTuple_Pack(6, logp.object, entropy.object, gap.object, sum.object, gap_sum.object, count.object); });
+    });
+}
+
 // tau_t, H_t, H_init, vocab, t, t_anneal, t_max, eta, tau_min, tau_max
 PyObject* temperature(PyObject*, PyObject* const* a, Py_ssize_t n_args)
 {
@@ -397,6 +429,7 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n_args)
     get("e3_restricted_workspace_bytes", p_restricted_bytes);
     get("e3_sample_restricted_ws", p_restricted);
     get("e3_logprob_entropy_advantages", p_logprob);
+    get("e3_logprob_entropy_gap", p_gap);
     get("e3_temperature_update", p_temperature);
     if (!all) { PyErr_SetString(PyExc_ValueError, "an entry point is missing"); return nullptr; }
     Py_INCREF(a[1]);
@@ -415,6 +448,7 @@ PyMethodDef methods[] = {
     {"restricted", fast(restricted), METH_FASTCALL, nullptr},
     {"logprob", fast(logprob), METH_FASTCALL, nullptr},
     {"logprob_advantages", fast(logprob), METH_FASTCALL, nullptr},
+    {"logprob_gap", fast(logprob_gap), METH_FASTCALL, nullptr},
     {"temperature", fast(temperature), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

@@ -247,3 +247,23 @@ def test_layouts_of_the_logits(layout, dtype, monkeypatch):
             continue
         for a, b in zip(got, want):
             assert a.shape == b.shape and torch.equal(a.view(torch.uint8), b.view(torch.uint8)), (f, kw)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("V", [1_000, 40_000])
+@pytest.mark.parametrize("target,mask,tau,workspace", [(True, True, True, None), (False, False, False, False), (True, False, True, "own")])
+def test_gap_call(V, target, mask, tau, workspace, monkeypatch):
+    c = _calls(DEV, V=V)["logprob"][1]
+    kw = dict(logits=c["logits"], target_ids=c["target_ids"] if target else None, row_mask=c["row_mask"] if mask else None,
+              tau_rows=c["tau_rows"] if tau else None, tau_scalar=0.9,
+              workspace=e3.new_workspace(6, V, DEV) if workspace == "own" else workspace)
+    want = [x.clone() if torch.is_tensor(x) else x for x in _outcome(e3.e3_logprob_entropy_gap, kw, monkeypatch, native=False)]
+    native = e3.binding._native.logprob_gap(kw["logits"], kw["target_ids"], kw["row_mask"], kw["tau_rows"], kw["tau_scalar"], kw["workspace"])
+    for got in (native, _outcome(e3.e3_logprob_entropy_gap, kw, monkeypatch, native=True)):
+        assert len(got) == len(want) == 6
+        for a, b in zip(got, want):
+            assert a is b is None or (a.dtype == b.dtype and a.shape == b.shape and torch.equal(a.view(torch.uint8), b.view(torch.uint8)))
+    for wrong in (dict(tau_scalar=-1.0, tau_rows=None), dict(logits=kw["logits"].half()), dict(target_ids=torch.zeros(5, dtype=torch.int32, device=DEV)),
+                  dict(row_mask=torch.ones(6, device=DEV)), dict(logits=kw["logits"].cpu())):
+        a, b = (_outcome(e3.e3_logprob_entropy_gap, {**kw, **wrong}, monkeypatch, native=n) for n in (True, False))
+        assert a == b and issubclass(a[0], Exception), wrong
