@@ -733,7 +733,7 @@ void vocab_split_kernel(VocabPassArgs a, RowPartial* __restrict__ ws, int nslots
 }
 
 // ---------------------------------------------------------------------------
-// Narrow rows (at most kNarrowTiles super-tiles): a workgroup has a row, and a wave kItems shares (SplitShare) of its super-tiles.
+// Narrow rows (at most kNarrowTiles super-tiles, and some wider ones: narrow_serves): a workgroup has a row, and a wave kItems shares (SplitShare) of its super-tiles.
 // The whole row is requested at once, the waves meet at one barrier, and the first merges the partials and finishes
 // the row: one launch, no running reference, no noise table, nothing that waits for another wave before the barrier.
 // Bound by latency up to some hundred rows, then by HBM and the launch of workgroups.  Against the streaming kernel, us: bf16 1 row x
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves)
 void vocab_narrow_kernel(VocabPassArgs a)
 {
     using Share = SplitShare<Chunk, kParts>;
-    __shared__ RowPartial parts[kNarrowTiles * 2];                     // at most sixteen: one row of lanes merges them
+    __shared__ RowPartial parts[kNarrowWaves];                         // of sixteen shares at most: one row of lanes merges them
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = (int)(blockDim.x >> 6);
@@ -962,15 +962,19 @@ static NarrowPlan narrow_plan(int64_t rows, int nst, bool is_bf16)
         return NarrowPlan{rows <= 2 * cus ? 4 : 2, 1};
     }
     if (nst <= 2 && rows * nst <= 2 * cus) return NarrowPlan{4, 1};
+    if (nst > kNarrowTiles) return NarrowPlan{1, 1};
     return NarrowPlan{rows <= (nst <= 6 ? 2 * cus : cus) ? 2 : 1, 1};
 }
 
 // Which narrow rows have a workgroup each: all but the larger fp32 batches of five or six super-tiles on the training side, where
 // two shares take 110 registers and the last super-tile's absent columns are worked through (us, the streaming kernel / so: 1000 x
 // 17,000 18.4 / 22.0, x 20,000 20.7 / 22.2, x 24,000 22.5 / 24.3, x 28,000 25.0 / 23.5).
+// Rows of nine to sixteen super-tiles, where they are not cut: bf16 with at most a row per compute unit, a wave per super-tile
+// (129 x 33,000 9.0 / 6.8, 256 x 50,000 10.3 / 9.1, 256 x 65,000 12.4 / 10.1, 400 x 50,000 12.7 / 14.4).
 static bool narrow_serves(int64_t rows, int64_t nst, bool is_bf16, bool sample)
 {
-    return nst <= kNarrowTiles && (is_bf16 || sample || nst < 5 || nst > 6 || rows <= 2 * (int64_t)compute_units());
+    if (nst > kNarrowTiles) return is_bf16 && nst <= kNarrowWaves && rows <= (int64_t)compute_units();
+    return (is_bf16 || sample || nst < 5 || nst > 6 || rows <= 2 * (int64_t)compute_units());
 }
 
 template <typename Chunk, bool kSample>

@@ -748,7 +748,8 @@ def test_shares_of_cut_rows(rows, V, dtype):
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("rows,V", [(2, 1), (3, 9), (2, 515), (5, 4_096), (257, 4_099), (256, 8_192), (260, 8_100), (513, 4_095), (515, 12_300),
-                                    (3, 16_387), (257, 20_480), (515, 24_001), (520, 16_500), (2, 28_673), (256, 32_768), (258, 32_761)])
+                                    (3, 16_387), (257, 20_480), (515, 24_001), (520, 16_500), (2, 28_673), (256, 32_768), (258, 32_761),
+                                    (129, 32_769), (5, 40_963), (256, 65_536), (257, 36_865)])
 def test_shares_of_narrow_rows(rows, V, dtype):
     # one, two or four waves per super-tile and one or two shares per wave, by the width and the number of rows (256 and 512); the
     # last super-tile may leave waves, lanes and parts of a vector without columns; a maximum that several columns share
