@@ -58,6 +58,13 @@ __device__ __forceinline__ uint32_t f32_of_key(uint32_t key)
     return (key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key;
 }
 
+// The smallest value above a finite one (both zeros are one).
+__device__ __forceinline__ float next_above(float z)
+{
+    const uint32_t b = __float_as_uint(z);
+    return __uint_as_float(z > 0.0f ? b + 1u : z < 0.0f ? b - 1u : 1u);
+}
+
 // Element access for the two logit types.  A vector is 16 bytes.  Keys are 32-bit; the lower 16
 // bits of a bf16 value's key are all ones or all zeros.
 struct SelBf16 {
@@ -77,6 +84,18 @@ struct SelBf16 {
         return u32x4{word(v.x, 0), word(v.y, 2), word(v.z, 4), word(v.w, 6)};
     }
     static __device__ __forceinline__ uint32_t pattern_of_bits(uint32_t bits) { return bits >> 16; }
+    // The largest value where that is not negative: as signed 16-bit integers the patterns of non-negative values are in
+    // value order, above those of all others.  Something negative, or no number, where it is negative.
+    static __device__ __forceinline__ float quick_max(const u32x4& v)
+    {
+        typedef int16_t s16x2 __attribute__((ext_vector_type(2)));
+        auto halves = [](uint32_t w) { return __builtin_bit_cast(s16x2, w); };
+        const s16x2 m = __builtin_elementwise_max(__builtin_elementwise_max(halves(v.x), halves(v.y)),
+                                                  __builtin_elementwise_max(halves(v.z), halves(v.w)));
+        const uint32_t w = __builtin_bit_cast(uint32_t, m);
+        const int hi = (int)w, lo = (int)(w << 16);
+        return __uint_as_float((uint32_t)(hi > lo ? hi : lo) & 0xFFFF0000u);
+    }
     static __device__ __forceinline__ float vec_max(const u32x4& v)
     {
         return fmax3(fmax3(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16)),
@@ -87,6 +106,7 @@ struct SelBf16 {
 struct SelF32 {
     static constexpr int kElems = 4;
     static constexpr int kKeyBits = 32;
+    static __device__ __forceinline__ float quick_max(const u32x4& v) { return vec_max(v); }
     static __device__ __forceinline__ uint32_t elem_bits(const u32x4& v, int j)
     {
         return j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w;
@@ -371,8 +391,8 @@ __device__ __forceinline__ void finish_short_list(const SelArgs& a, SelShared& s
 // non-temporal loads, or 1024 threads and plain loads for at most one row per compute unit (half the
 // stream's latency; such a batch may sit in the caches: 100 fp32 rows 24.7 us plain, 28.2 us
 // non-temporal; 300 rows x 151,936 bf16 29.7 us with 512 threads, 48 us with 1024): four waves per
-// SIMD and up to 128 vector registers either way.  151,936 bf16 columns, top-k 50 + top-p 0.95: 8 rows 14.2 us,
-// 512 rows 30.2 us (5.1 TB/s), 1024 rows 53.7 us (5.8 TB/s); with one wave finishing a row alone (see finish_short_list)
+// SIMD and up to 128 vector registers either way.  151,936 bf16 columns, top-k 50 + top-p 0.95: 8 rows 13.1 us,
+// 512 rows 30.0 us (5.2 TB/s), 1024 rows 52.8 us (5.9 TB/s); with one wave finishing a row alone (see finish_short_list)
 // and the candidates taken column by column from the listed vectors 16.5, 33.7 and 59.6.
 template <typename T, int kSThreads>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
@@ -438,14 +458,7 @@ void sample_select_kernel(SelArgs a)
         }
         return f;
     };
-    auto set_maxima = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
-        float most = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < kSBatch; ++u) { m[u] = T::vec_max(x[u]); most = fmaxf(most, m[u]); }
-        if (__builtin_expect(__any(most == INFINITY), 0)) {
-#pragma unroll
-            for (int u = 0; u < kSBatch; ++u) m[u] = finite_max(x[u]);
-        }
+    auto past_the_end = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
 #pragma unroll
         for (int u = 0; u < kSBatch; ++u) {
             const int slot = set + u * nsets;
@@ -455,6 +468,35 @@ void sample_select_kernel(SelArgs a)
                 else if (v == nvec - 1 && last < T::kElems) m[u] = finite_max(T::cut_off(x[u], last));
             }
         }
+    };
+    // bf16: the maxima of a set as quick_max leaves them suffice while every lane has a value that is not negative among its
+    // vectors and theta is above zero: then none of those that it gets wrong reaches theta.  Else these.
+    auto exact_maxima = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
+        float most = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < kSBatch; ++u) { m[u] = T::vec_max(x[u]); most = fmaxf(most, m[u]); }
+        if (__builtin_expect(__any(most == INFINITY), 0)) {
+#pragma unroll
+            for (int u = 0; u < kSBatch; ++u) m[u] = finite_max(x[u]);
+        }
+        past_the_end(x, m, set);
+    };
+    auto set_maxima = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
+        float most = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < kSBatch; ++u) m[u] = T::quick_max(x[u]);
+        past_the_end(x, m, set);
+#pragma unroll
+        for (int u = 0; u < kSBatch; ++u) most = fmaxf(most, m[u]);
+        // (no numbers of a positive sign are above infinity as integers, and drop out of `most` as floats: looked for one by one)
+        bool odd = !(most >= 0.0f && most < INFINITY);
+        if (T::kKeyBits == 16) {
+#pragma unroll
+            for (int u = 0; u < kSBatch; ++u) odd |= m[u] != m[u];
+        } else {
+            odd = most == INFINITY;
+        }
+        if (__builtin_expect(__any(odd), 0)) exact_maxima(x, m, set);
     };
     // The wave's m-th largest thread maximum, m = ceil(k / waves with columns), bit by bit from the
     // top with one ballot per bit: the largest value that at least m lanes reach.  The upper 16 bits
@@ -503,30 +545,37 @@ void sample_select_kernel(SelArgs a)
         const uint32_t bits = f32_of_key(t);                      // (a bf16 value has a low half of zeros)
         return t < 0x00800000u ? -3.402823466e38f : __uint_as_float(T::kKeyBits == 16 ? bits & 0xFFFF0000u : bits);
     };
-    // The vectors of a set whose maximum reaches theta go into the list: one reservation per wave.
-    // Where that would be most of most lanes' vectors, theta is a plateau so far, and only what lies above
+    // The vectors of a set whose maximum reaches theta go into the list: one reservation per wave, a ballot per request, and
+    // nothing for a request without a hit (the stream is bound by its instructions where a row has a compute unit: 8 x 151,936
+    // 13.5 us, 14.3 with a prefix sum over the lanes, every request's stores behind its own conditions and floating-point maxima).
+    // Where that would be a quarter of the set, theta is a plateau so far, and only what lies above
     // it is listed (sh.skipped remembers the highest such value): enough if the final theta is higher.
-    auto list_set = [&](const u32x4 (&x)[kSBatch], const float (&m)[kSBatch], int set, float thf, bool all) {
-        uint32_t hits = 0u;
+    auto list_set = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set, float thf, bool all) {
+        if (T::kKeyBits == 16 && __builtin_expect(thf <= 0.0f, 0)) exact_maxima(x, m, set);          // uniform
+        float bound = thf;
+        unsigned long long hit[kSBatch];
+        auto count = [&]() -> int {
+            int n = 0;
 #pragma unroll
-        for (int u = 0; u < kSBatch; ++u) hits |= (uint32_t)(m[u] >= thf) << u;
-        if (!__any(hits != 0u)) return;
-        if (__builtin_expect(!all && (int)__popcll(__ballot(__popc(hits) >= kSBatch / 2)) > 32, 0)) {
-            hits = 0u;
-#pragma unroll
-            for (int u = 0; u < kSBatch; ++u) hits |= (uint32_t)(m[u] > thf) << u;
+            for (int u = 0; u < kSBatch; ++u) { hit[u] = __ballot(m[u] >= bound); n += (int)__popcll(hit[u]); }
+            return n;
+        };
+        int total = count();
+        if (total == 0) return;
+        if (__builtin_expect(!all && total > 16 * kSBatch, 0)) {
+            bound = next_above(thf);
             if (lane == 0) atomicMax(&sh.skipped, key_of_f32(__float_as_uint(thf)));
+            total = count();
         }
-        const int mine = __popc(hits);
-        const int inc = wave_prefix_sum(mine);
         int base = 0;
-        if (lane == 63) base = atomicAdd(&sh.vec_n, inc);
-        int slot = __builtin_amdgcn_readlane(base, 63) + inc - mine;
+        if (lane == 0) base = atomicAdd(&sh.vec_n, total);
+        base = __builtin_amdgcn_readfirstlane(base);
 #pragma unroll
         for (int u = 0; u < kSBatch; ++u) {
-            if (hits & (1u << u)) {
-                if (slot < kSVecCap) { lvec[slot] = x[u]; lvec_at[slot] = tid + (set + u * nsets) * kSThreads; }
-                ++slot;
+            if (hit[u] != 0ull) {                                 // uniform
+                const int slot = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hit[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit[u], (uint32_t)base));
+                if (m[u] >= bound && slot < kSVecCap) { lvec[slot] = x[u]; lvec_at[slot] = tid + (set + u * nsets) * kSThreads; }
+                base += (int)__popcll(hit[u]);
             }
         }
     };
@@ -541,13 +590,17 @@ void sample_select_kernel(SelArgs a)
             for (int u = 0; u < kSBatch; ++u) tmax = fmaxf(tmax, m[u]);
         };
         request(x, 0);
-        if (nsets > 1) request(y, 1);
+        // Sixteen waves ask for their second set when the first has come: its requests would stand in line before the last
+        // waves' first, which everybody waits for (100 x 128,000 fp32, top-k 20 17.1 -> 16.0 us, 8 x 151,936 13.5 -> 13.1; two
+        // rows of eight waves to a compute unit want both in flight, 512 rows 30.4 and 30.0).
+        if (kStream && nsets > 1) request(y, 1);
         if (wave == kSWaves - 1) {                                // while they are in flight
             uint32_t w4[4];
             philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
             if (lane == 0) sh.k23 = w4[0] >> 9;
         }
         maxima(x, 0);
+        if (!kStream && nsets > 1) request(y, 1);
         publish();
         // orders LDS only: __syncthreads() would wait for the loads in flight as well
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");

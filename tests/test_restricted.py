@@ -753,3 +753,44 @@ def test_selection_of_rows_that_are_mostly_a_plateau(kind, rows, V, dtype):
     lg = lg[:, :V]
     for k, p in ((20, 0.9), (50, 0.95), (200, 1.0)):
         check(lg, None, 0.8, k, p, 11, 2, f"plateau {kind} {rows}x{V} {dtype} k={k} p={p}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", [(18, 20_003), (270, 20_003), (18, 140_001)])
+def test_selection_where_maxima_are_not_positive(rows, V, dtype):
+    # the stream takes bf16 maxima as signed integers, which is wrong for vectors without a non-negative value: rows of which all,
+    # most or some lanes or vectors hold none, cuts at zero and below it, and patterns that are no numbers of either sign
+    g = torch.Generator(device=DEV).manual_seed(rows + V)
+    x = torch.randn((rows, -(-V // 8) * 8), generator=g, device=DEV) * 3
+    x[0::9] -= 60.0                                                    # negative throughout
+    x[1::9] = torch.where(torch.rand(x[1::9].shape, generator=g, device=DEV) < 2e-4, x[1::9].abs(), -x[1::9].abs() - 1.0)
+    x[2::9] = -torch.relu(x[2::9])                                     # zeros on top, half of the columns
+    x[3::9] = torch.where(x[3::9] > 11.0, x[3::9], torch.full_like(x[3::9], -0.0))
+    x[4::9, 40:] = -x[4::9, 40:].abs()                                 # forty columns that may be positive
+    x[5::9, ::7] = float("nan")
+    x[5::9, 1::7] = float("-inf")
+    x[6::9, 5::1000] = float("inf")
+    x[6::9] -= 8.0
+    x[7::9] = torch.where(x[7::9] > 6.0, torch.zeros_like(x[7::9]), -x[7::9].abs())        # +0 and -0 at the cut
+    x[7::9, 3::50] = -0.0
+    x[8::9, 4_000:] = -1.0e4
+    full = x.to(dtype)
+    lg = full[:, :V]
+    bits = lg.view(torch.int16 if dtype == torch.bfloat16 else torch.int32)
+    bits[5::9, 2::7] |= -0x8000 if dtype == torch.bfloat16 else -0x80000000    # negative values, and NaN of the negative sign
+    numbers = torch.isfinite(lg).all(1)
+    assert int((~numbers).sum()) == 2 * rows // 9
+    finite = full.clone()[:, :V]                                       # (with its pitch)
+    finite[~numbers] = 0.0
+    for k, p in [(50, 0.95), (64, 1.0), (3, 1.0), (200, 0.9)]:
+        check(finite, None, 0.9, k, p, k, 5, f"not positive {rows}x{V} {dtype} k={k} p={p}")
+        # patterns that are no numbers are no levels: the row without these columns
+        tok, logp, kept = (t.cpu() for t in e3.e3_sample_restricted(lg, None, 0.9, k, p, k, 5))
+        for r in (~numbers).nonzero().squeeze(1).tolist()[:6]:
+            cols = torch.isfinite(lg[r]).nonzero().squeeze(1)
+            ref = o.sample_restricted(wl.host_bits(lg[r, cols].unsqueeze(0)), None, 0.9, k, p, k, 5 + r)
+            assert ref.near_cut[0] or kept[r] == ref.kept[0], (r, k)
+            if not (ref.near_cut[0] or ref.near_tie[0]):
+                assert int(tok[r]) == int(cols[int(ref.token[0])]), (r, k)
+                assert abs(float(logp[r]) - ref.logp[0]) <= 1e-4 * max(abs(ref.logp[0]), 1e-6)
