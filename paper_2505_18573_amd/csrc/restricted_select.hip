@@ -106,7 +106,6 @@ struct SelBf16 {
 struct SelF32 {
     static constexpr int kElems = 4;
     static constexpr int kKeyBits = 32;
-    static __device__ __forceinline__ float quick_max(const u32x4& v) { return vec_max(v); }
     static __device__ __forceinline__ uint32_t elem_bits(const u32x4& v, int j)
     {
         return j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w;
@@ -470,7 +469,10 @@ void sample_select_kernel(SelArgs a)
         }
     };
     // bf16: the maxima of a set as quick_max leaves them suffice while every lane has a value that is not negative among its
-    // vectors and theta is above zero: then none of those that it gets wrong reaches theta.  Else these.
+    // vectors and theta is above zero: then none of those that it gets wrong reaches theta.  Else these, from then on
+    // (`by_value`, wave-uniform: rows of log-probabilities are negative throughout; 8 x 151,936 of them 17.3 -> 15.3 us, where
+    // both maxima in every set took longer than the exact ones alone).
+    bool by_value = T::kKeyBits != 16;
     auto exact_maxima = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
         float most = -INFINITY;
 #pragma unroll
@@ -482,21 +484,23 @@ void sample_select_kernel(SelArgs a)
         past_the_end(x, m, set);
     };
     auto set_maxima = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
-        float most = -INFINITY;
+        if constexpr (T::kKeyBits == 16) {
+            // (two sets in flight: without a branch in front, where the compiler would wait for both, 512 rows 30.0 -> 31.1 us)
+            if (kStream || !by_value) {
+                float most = -INFINITY;
 #pragma unroll
-        for (int u = 0; u < kSBatch; ++u) m[u] = T::quick_max(x[u]);
-        past_the_end(x, m, set);
+                for (int u = 0; u < kSBatch; ++u) m[u] = T::quick_max(x[u]);
+                past_the_end(x, m, set);
+                // (no numbers of a positive sign are above infinity as integers, and drop out of `most` as floats: looked for one by one)
+                bool odd = by_value;
 #pragma unroll
-        for (int u = 0; u < kSBatch; ++u) most = fmaxf(most, m[u]);
-        // (no numbers of a positive sign are above infinity as integers, and drop out of `most` as floats: looked for one by one)
-        bool odd = !(most >= 0.0f && most < INFINITY);
-        if (T::kKeyBits == 16) {
-#pragma unroll
-            for (int u = 0; u < kSBatch; ++u) odd |= m[u] != m[u];
+                for (int u = 0; u < kSBatch; ++u) { most = fmaxf(most, m[u]); odd |= m[u] != m[u]; }
+                by_value = __any(odd || !(most >= 0.0f && most < INFINITY));
+            }
+            if (__builtin_expect(by_value, 0)) exact_maxima(x, m, set);
         } else {
-            odd = most == INFINITY;
+            exact_maxima(x, m, set);
         }
-        if (__builtin_expect(__any(odd), 0)) exact_maxima(x, m, set);
     };
     // The wave's m-th largest thread maximum, m = ceil(k / waves with columns), bit by bit from the
     // top with one ballot per bit: the largest value that at least m lanes reach.  The upper 16 bits
@@ -551,7 +555,10 @@ void sample_select_kernel(SelArgs a)
     // Where that would be a quarter of the set, theta is a plateau so far, and only what lies above
     // it is listed (sh.skipped remembers the highest such value): enough if the final theta is higher.
     auto list_set = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set, float thf, bool all) {
-        if (T::kKeyBits == 16 && __builtin_expect(thf <= 0.0f, 0)) exact_maxima(x, m, set);          // uniform
+        if (T::kKeyBits == 16 && __builtin_expect(thf <= 0.0f && !by_value, 0)) {                    // uniform
+            by_value = true;
+            exact_maxima(x, m, set);
+        }
         float bound = thf;
         unsigned long long hit[kSBatch];
         auto count = [&]() -> int {
