@@ -1013,14 +1013,15 @@ static hipError_t launch_for(const VocabPassArgs& a, const LaunchPlan& plan, hip
 }
 
 // Split path: used when the row-block path would leave compute units without a
-// workgroup and the caller brought enough workspace.  Every super-tile gets a wave of
-// its own (measured on MI355X: one-wave workgroups beyond what is resident are handed
+// workgroup and the caller brought enough workspace.  Every super-tile gets a workgroup of
+// its own (measured on MI355X: small workgroups beyond what is resident are handed
 // out by the hardware dispatcher as earlier ones finish, which balances better than
 // longer static runs), except that a row has at most 64 runs: one partial per lane
 // of the merging wave.
-// Rows of at most kNarrowTiles super-tiles are not cut: a workgroup has a wave for each of them and
-// needs no second launch (64 rows x 32,000 bf16: 10.3 -> 8.6 us).  Wider rows are cut while whole rows
-// would make at most half as many workgroups as there are compute units.  Cut / whole in us, bf16
+// Rows of at most kNarrowTiles super-tiles are not cut: a workgroup holds all of them and needs no second launch (64 rows x
+// 32,000 bf16: 5.9 us).  Wider rows are cut while whole rows would make at most half as many workgroups as there are compute
+// units.  Where the line lies was measured with one wave per super-tile (four have since made the cut form faster, 64 rows x
+// 151,936 9.0, 128 rows 12.3, and whole rows of up to sixteen super-tiles too).  Cut / whole in us, bf16
 // samples: 64 rows x 33,000 9.6 / 9.9, x 70,005 10.6 / 13.9, x 151,936 12.1 / 15.1; 128 rows 10.5 / 10.7,
 // 12.3 / 14.5, 15.9 / 15.8; 192 rows 11.3 / 11.1, 13.8 / 15.1, 19.0 / 16.8; x 61,000 12.6 / 12.4 at 128 rows and
 // 13.7 / 12.6 at 192.  (Rows of a whole number of super-tiles are faster whole at any count, 128 x
