@@ -500,11 +500,14 @@ struct LaneState {
 constexpr float kAbsent = -1.0e30f;
 
 // The integer reference that covers logits up to `z`: ceil(z * c), one more when the fp32
-// product was rounded down onto an integer.
+// product was rounded down onto an integer.  Beyond 2^24 one more is no step and the product is off by up to 2^-24 of itself: up to
+// 90 is left there (sums of 2^90 stay finite, and a merge that scales such a run of columns away scales it to
+// zero), more takes the next values up, so that columns masked with -1e10 or less cannot make a sum infinite.
 __device__ __forceinline__ float reference_for(float z, float c)
 {
     float rc = ceilf(z * c);
-    if (fmaf(z, c, -rc) > 0.0f) rc += 1.0f;
+    const float over = fmaf(z, c, -rc);
+    if (over > 0.0f) rc += over > 90.0f ? fabsf(rc) * 0x1p-23f : 1.0f;
     return rc;
 }
 

@@ -481,6 +481,45 @@ def test_non_finite_inputs_give_nan_outputs_and_valid_tokens():
     assert torch.isnan(ent[1]) and torch.isnan(ent[5])
 
 
+# rows x V of every launch form: one to sixteen super-tiles, narrow, cut and streaming, with and without absent columns
+UNUSUAL_SHAPES = [(1, 100), (1, 4_096), (3, 5_000), (300, 8_192), (2, 12_300), (600, 17_000), (2, 20_480), (300, 28_673), (2, 32_768),
+                  (2, 33_000), (130, 36_864), (300, 33_001), (2, 70_005)]
+
+
+def masked_rows(rows, V, value, dtype, g):
+    """Logits of which a third, the columns of the last super-tile, or all but a hundredth hold `value`, by the row."""
+    x = torch.randn((rows, -(-V // 8) * 8), generator=g, device=DEV) * 3
+    x[0::3, V // 3:] = value
+    x[1::3, (V - 1) // 4096 * 4096 if V > 4096 else V // 2:] = value
+    x[2::3] = torch.where(torch.rand(x[2::3].shape, generator=g, device=DEV) < 0.01, x[2::3], torch.full_like(x[2::3], value))
+    x[2::3, 0] = 1.0
+    return x.to(dtype)[:, :V]
+
+
+def check_against_softmax(lg, tau, label):
+    """Sampled log-probs, given log-probs and entropies of the first and last rows against torch's in 64 bits."""
+    z = torch.cat([lg[:3], lg[-3:]]).double() / tau
+    H = torch.special.entr(torch.softmax(z, 1)).sum(1)
+    for ws in (None, False):
+        tok, logp, ent = e3.e3_sample_entropy(lg, None, tau, seed=lg.shape[0], row_base=0, workspace=ws)
+        lp2, ent2, _, _ = e3.e3_logprob_entropy(lg, tok, None, None, tau, workspace=ws)
+        ends = lambda t: torch.cat([t[:3], t[-3:]])
+        want = torch.log_softmax(z, 1).gather(1, ends(tok).long().unsqueeze(1)).squeeze(1)
+        for got, ref in ((logp, want), (lp2, want), (ent, H), (ent2, H)):
+            assert ((ends(got).double() - ref).abs() <= 1e-4 * ref.abs() + 1e-5).all(), (label, tau, ws)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", UNUSUAL_SHAPES)
+def test_columns_masked_with_large_finite_values(rows, V, dtype):
+    # runs of columns far below the rest, where z / tau in base 2 lies beyond 2^24 and the reference of a wave that holds nothing
+    # else cannot be an exact integer above it: whichever part of a row a wave works on, they weigh nothing
+    g = torch.Generator(device=DEV).manual_seed(rows + V)
+    for tau, values in ((0.7, (-1e8, -3e9, -1e10, -1e20, -1e29)), (1.0, (-1e9, -2e29)), (2.0, (-1e9, -1e12, -9e29))):
+        for value in values:
+            check_against_softmax(masked_rows(rows, V, value, dtype, g), tau, value)
+
+
 @pytest.mark.parametrize("rows", [1, 2, 3, 17])
 def test_odd_row_counts_and_group_tails(rows):
     # workgroups own two rows: an odd count leaves a half-filled last group
