@@ -537,7 +537,9 @@ __device__ __forceinline__ void new_maximum(LaneState& s, float z[8], float chun
         }
     }
     s.rc = new_rc;
-    s.top = top;
+    // The filler is no logit of the row: where it lies above all else (columns of -inf, or below -1e30) there is no
+    // maximum, so that a row of nothing else has no peak and its outputs are NaN.
+    s.top = top > kAbsent ? top : -INFINITY;
     s.thr = top;
     const unsigned long long holders = __ballot(chunk_max == top);
     s.dom_lane = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(holders | (1ull << 63)));

@@ -672,7 +672,8 @@ struct SplitShare : SplitShape<Chunk, kParts> {
         }
         p.S = (double)s; p.W = (double)w;
         wave_sum2(p.S, p.W);
-        p.rc = rc; p.top = top;
+        p.rc = rc;
+        p.top = top > kAbsent ? top : -INFINITY;                       // (see new_maximum)
         if (kSample) {
             const int tile = tile_of(lane, part);
             const bool nonempty = first_col + tile * kChunk < V;

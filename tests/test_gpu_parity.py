@@ -520,6 +520,38 @@ def test_columns_masked_with_large_finite_values(rows, V, dtype):
             check_against_softmax(masked_rows(rows, V, value, dtype, g), tau, value)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", UNUSUAL_SHAPES)
+def test_rows_without_a_number(rows, V, dtype):
+    # a row of -inf has no largest logit: its log-prob and entropy are NaN at every temperature (log2(e): logits are scaled by exactly 1) and
+    # in every launch form, as are those of a row of NaN and of one that holds them in one super-tile only; the rows beside are unaffected
+    g = torch.Generator(device=DEV).manual_seed(rows + V)
+    lg = (torch.randn((rows, -(-V // 8) * 8), generator=g, device=DEV) * 3).to(dtype)[:, :V]
+    lg[0] = float("-inf")
+    poisoned = [0]
+    if rows > 2:
+        lg[rows - 1] = float("nan")
+        poisoned.append(rows - 1)
+    if 2 < rows <= 300:                                                # (a workgroup or more to each row)
+        lg[rows - 2, :4096] = float("nan")
+        poisoned.append(rows - 2)
+    clean = [r for r in range(1, min(rows, 4)) if r not in poisoned]
+    targets = torch.zeros(rows, dtype=torch.int32, device=DEV)
+    for tau in (0.5, 0.7, 0.9, 1.0, 2.0, 1.44269504088896340736):
+        for ws in (None, False):
+            tok, logp, ent = e3.e3_sample_entropy(lg, None, tau, seed=3, row_base=0, workspace=ws)
+            lp2, ent2, gap, _, _, _ = e3.e3_logprob_entropy_gap(lg, targets, None, None, tau, workspace=ws)
+            assert ((tok >= 0) & (tok < V)).all()
+            for x in (logp, ent, lp2, ent2, gap):
+                assert torch.isnan(x[poisoned]).all(), (tau, ws, x[poisoned])
+            if clean:
+                z = lg[clean].double() / tau
+                H = torch.special.entr(torch.softmax(z, 1)).sum(1)
+                want = torch.log_softmax(z, 1)[:, 0]
+                for got, ref in ((lp2, want), (ent, H), (ent2, H)):
+                    assert ((got[clean].double() - ref).abs() <= 1e-4 * ref.abs() + 1e-5).all(), (tau, ws)
+
+
 @pytest.mark.parametrize("rows", [1, 2, 3, 17])
 def test_odd_row_counts_and_group_tails(rows):
     # workgroups own two rows: an odd count leaves a half-filled last group
