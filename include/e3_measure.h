@@ -43,15 +43,17 @@ int e3_time_next_launch(void* start_event, void* stop_event);
 int e3_read_probe(const void* buf, int64_t bytes, uint32_t* sums_out, void* hip_stream);
 
 /*
- * How the vocabulary pass launches a [rows, V] batch (sample: the sampling form) on the current
- * device, or on 256 compute units without one; host only.  *waves, *rows_per_group and *workgroups:
- * the launch of whole rows (rows of at most 32,768 columns, which have a workgroup each: 4 or 8 is
- * its size class, its waves are 1 to 16 by the columns, the element type and the number of rows;
- * fp32 rows of 16,385 to 24,576 columns keep several rows per workgroup on the training side of
- * larger batches).  *cut: 1 if a caller that brings e3_workspace_bytes gets its rows cut
- * over workgroups of one or four waves and a merging launch instead.  E3_ERR_SHAPE for a shape that
- * the library refuses or without rows; no output may be NULL (E3_ERR_NULL).
+ * How the vocabulary pass launches a [rows, V] batch of `dtype` (sample: the sampling form) on the
+ * current device, or on 256 compute units without one; host only.  *waves (of a workgroup),
+ * *rows_per_group and *workgroups: the launch of whole rows.  *cut: 1 if a caller that brings
+ * e3_workspace_bytes gets its rows cut over workgroups of one or four waves and a merging launch
+ * instead.  E3_ERR_SHAPE for a shape that the library refuses or without rows, E3_ERR_DTYPE; no output
+ * may be NULL (E3_ERR_NULL).
  */
+int e3_launch_plan_of(int64_t rows, int64_t V, int dtype, int sample, int32_t* cut, int32_t* waves,
+                      int32_t* rows_per_group, int64_t* workgroups);
+
+/* The same for bf16 logits. */
 int e3_launch_plan(int64_t rows, int64_t V, int sample, int32_t* cut, int32_t* waves,
                    int32_t* rows_per_group, int64_t* workgroups);
 

@@ -33,7 +33,7 @@ EXPORTS = ("e3_strerror", "e3_workspace_bytes", "e3_sample_entropy", "e3_sample_
            "e3_grpo_advantages", "e3_temperature_update", "e3_difficulty_ranks",
            "e3_allocate_budgets", "e3_budget_bounds", "e3_logprob_entropy_gap",
            "e3_temperature_update_gap", "e3_grpo_objective", "e3_read_probe",
-           "e3_time_next_launch", "e3_launch_plan")
+           "e3_time_next_launch", "e3_launch_plan", "e3_launch_plan_of")
 
 _NATIVE_CALLS = ("e3_grpo_advantages", "e3_grpo_objective", "e3_workspace_bytes", "e3_sample_entropy",
                  "e3_restricted_workspace_bytes", "e3_sample_restricted_ws", "e3_logprob_entropy_advantages",
@@ -85,6 +85,8 @@ def lib() -> C.CDLL:
         L.e3_time_next_launch.restype = C.c_int
         L.e3_launch_plan.argtypes = [i64, i64, C.c_int, vp, vp, vp, vp]
         L.e3_launch_plan.restype = C.c_int
+        L.e3_launch_plan_of.argtypes = [i64, i64, C.c_int, C.c_int, vp, vp, vp, vp]
+        L.e3_launch_plan_of.restype = C.c_int
         L.e3_read_probe.argtypes = [vp, i64, vp, vp]
         L.e3_read_probe.restype = C.c_int
         L.e3_logprob_entropy.argtypes = [vp, C.c_int, i64, i64, i64, vp, vp, vp, f32,
@@ -343,12 +345,12 @@ def e3_time_next_launch(start_event: Optional[int], stop_event: Optional[int]) -
     lib().e3_time_next_launch(C.c_void_p(start_event), C.c_void_p(stop_event))
 
 
-def e3_launch_plan(rows: int, V: int, sample: bool = True) -> Tuple[bool, int, int, int]:
+def e3_launch_plan(rows: int, V: int, sample: bool = True, dtype: torch.dtype = torch.bfloat16) -> Tuple[bool, int, int, int]:
     """Host-only: how a [rows, V] batch is launched: (cut, if the caller brings the workspace for it;
     waves and rows per workgroup and number of workgroups of the launch of whole rows)."""
     cut, waves, rows_per_group, workgroups = C.c_int32(), C.c_int32(), C.c_int32(), C.c_int64()
-    rc = lib().e3_launch_plan(rows, V, int(sample), C.byref(cut), C.byref(waves), C.byref(rows_per_group),
-                              C.byref(workgroups))
+    rc = lib().e3_launch_plan_of(rows, V, {torch.bfloat16: E3_BF16, torch.float32: E3_F32}[dtype], int(sample), C.byref(cut), C.byref(waves), C.byref(rows_per_group),
+                                 C.byref(workgroups))
     if rc != E3_OK:
         raise E3Error(rc, "e3_launch_plan")
     return bool(cut.value), waves.value, rows_per_group.value, workgroups.value

@@ -122,10 +122,17 @@ extern "C" int e3_time_next_launch(void* start_event, void* stop_event)
 extern "C" int e3_launch_plan(int64_t rows, int64_t V, int sample, int32_t* cut, int32_t* waves,
                               int32_t* rows_per_group, int64_t* workgroups)
 {
+    return e3_launch_plan_of(rows, V, E3_BF16, sample, cut, waves, rows_per_group, workgroups);
+}
+
+extern "C" int e3_launch_plan_of(int64_t rows, int64_t V, int dtype, int sample, int32_t* cut, int32_t* waves,
+                                 int32_t* rows_per_group, int64_t* workgroups)
+{
+    if (dtype != E3_F32 && dtype != E3_BF16) return E3_ERR_DTYPE;
     if (rows < 1 || rows > (int64_t)0x7FFFFFFF || V < 1 || !e3::vocab_pass_fits(V)) return E3_ERR_SHAPE;
     if (cut == nullptr || waves == nullptr || rows_per_group == nullptr || workgroups == nullptr) return E3_ERR_NULL;
     bool few = false;
-    const e3::LaunchPlan plan = e3::vocab_pass_plan(rows, V, sample != 0, &few);
+    const e3::LaunchPlan plan = e3::vocab_pass_plan(rows, V, dtype == E3_BF16, sample != 0, &few);
     *cut = few;
     *waves = plan.waves;
     *rows_per_group = plan.rows_per_group;

@@ -53,10 +53,11 @@ int compute_units();
 // The launch of a batch in whole rows; *cut: its rows are cut instead if the caller brings the
 // workspace for it.
 struct LaunchPlan {
+    int parts, items;               // narrow rows: shares of a super-tile and of a wave (0: the streaming kernel)
     int waves, rows_per_group;      // of a workgroup
     int64_t workgroups;
 };
-LaunchPlan vocab_pass_plan(int64_t rows, int64_t V, bool sample, bool* cut);
+LaunchPlan vocab_pass_plan(int64_t rows, int64_t V, bool is_bf16, bool sample, bool* cut);
 
 // false when V is so large that the per-workgroup tables do not fit LDS
 bool vocab_pass_fits(int64_t V);

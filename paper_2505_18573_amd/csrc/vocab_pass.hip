@@ -926,7 +926,7 @@ static LaunchPlan streaming_plan(int64_t rows, int64_t V, bool sample)
 {
     const int64_t cus = compute_units();
     auto plan = [&](int waves, int rpb) -> LaunchPlan {
-        return LaunchPlan{waves, rpb, rpb > 0 ? (rows + rpb - 1) / rpb : 0};
+        return LaunchPlan{0, 0, waves, rpb, rpb > 0 ? (rows + rpb - 1) / rpb : 0};
     };
     // Several rows per workgroup only where that leaves a resident round of workgroups (nearly) full:
     // 512 rows x 48,000 bf16 columns (two rows per workgroup before) 18.7 -> 15.7 us.
@@ -946,8 +946,6 @@ static LaunchPlan streaming_plan(int64_t rows, int64_t V, bool sample)
 }
 
 // Narrow rows: shares per super-tile and per wave; every share has a place in the kernel's table (sixteen).
-struct NarrowPlan { int parts, items; };
-
 // While the waves of a batch leave the chip idle, more of them per super-tile are faster; beyond that they only multiply what every
 // wave does once.  bf16, one / two / four waves per super-tile, us: 256 rows x 4096 4.7 / 4.4 / 4.2, 512 rows 5.1 / 5.2 / 4.8, 768
 // rows 5.3 / 5.3 / 5.5; 256 x 8000 5.3 / 4.8 / 4.8, 512 rows 6.3 / 5.8 / 6.0, 768 rows 6.6 / 6.7 / 6.9; 256 x 16,000 5.7 / 5.6
@@ -955,16 +953,17 @@ struct NarrowPlan { int parts, items; };
 // fp32 has two to four; more than four super-tiles of two waves each are ten to sixteen waves, of which a compute unit has
 // few workgroups at a time, so that larger batches give a wave two shares (us with one / two): 512 x 20,000 10.4 / 11.6, 768 rows
 // 15.2 / 13.5; 256 x 32,000 9.0 / 9.5, 512 rows 15.5 / 14.4, 1024 rows 28.2 / 24.5, 4096 rows 95.2 / 80.2.
-static NarrowPlan narrow_plan(int64_t rows, int nst, bool is_bf16)
+static LaunchPlan narrow_plan(int64_t rows, int nst, bool is_bf16)
 {
     const int64_t cus = compute_units();
+    auto plan = [&](int parts, int items) { return LaunchPlan{parts, items, nst * parts / items, 1, rows}; };
     if (!is_bf16) {
-        if (nst > 4) return NarrowPlan{2, rows <= (nst <= 6 ? 2 * cus : cus) ? 1 : 2};
-        return NarrowPlan{rows <= 2 * cus ? 4 : 2, 1};
+        if (nst > 4) return plan(2, rows <= (nst <= 6 ? 2 * cus : cus) ? 1 : 2);
+        return plan(rows <= 2 * cus ? 4 : 2, 1);
     }
-    if (nst <= 2 && rows * nst <= 2 * cus) return NarrowPlan{4, 1};
-    if (nst > kNarrowTiles) return NarrowPlan{1, 1};
-    return NarrowPlan{rows <= (nst <= 6 ? 2 * cus : cus) ? 2 : 1, 1};
+    if (nst <= 2 && rows * nst <= 2 * cus) return plan(4, 1);
+    if (nst > kNarrowTiles) return plan(1, 1);
+    return plan(rows <= (nst <= 6 ? 2 * cus : cus) ? 2 : 1, 1);
 }
 
 // Which narrow rows have a workgroup each: all but the larger fp32 batches of five or six super-tiles on the training side, where
@@ -979,9 +978,9 @@ static bool narrow_serves(int64_t rows, int64_t nst, bool is_bf16, bool sample)
 }
 
 template <typename Chunk, bool kSample>
-static hipError_t launch_narrow(const VocabPassArgs& a, int nst, hipStream_t stream)
+static hipError_t launch_narrow(const VocabPassArgs& a, const LaunchPlan& plan, hipStream_t stream)
 {
-    const NarrowPlan plan = narrow_plan(a.rows, nst, Chunk::kElemBytes == 2);
+    if (plan.waves * plan.items > kNarrowWaves) return hipErrorInvalidValue;
     auto kernel = plan.parts == 4 ? vocab_narrow_kernel<Chunk, kSample, 4, 1> : vocab_narrow_kernel<Chunk, kSample, 2, 1>;
     if constexpr (Chunk::kHalves == 1) {
         if (plan.parts == 1) kernel = vocab_narrow_kernel<Chunk, kSample, 1, 1>;
@@ -989,7 +988,7 @@ static hipError_t launch_narrow(const VocabPassArgs& a, int nst, hipStream_t str
         if (plan.items == 2) kernel = vocab_narrow_kernel<Chunk, kSample, 2, 2>;
     }
     const LaunchEvents ev = take_launch_events();
-    const dim3 blocks((unsigned)a.rows), threads(64u * (unsigned)(nst * plan.parts / plan.items));
+    const dim3 blocks((unsigned)plan.workgroups), threads(64u * (unsigned)plan.waves);
     if (ev.start != nullptr || ev.stop != nullptr)
         hipExtLaunchKernelGGL(kernel, blocks, threads, 0u, stream, ev.start, ev.stop, 0u, a);
     else
@@ -997,18 +996,10 @@ static hipError_t launch_narrow(const VocabPassArgs& a, int nst, hipStream_t str
     return hipGetLastError();
 }
 
-// Whole rows: a workgroup for each narrow one (vocab_narrow_kernel), sized by its super-tiles, else as above.
-static LaunchPlan whole_rows_plan(int64_t rows, int64_t V, bool sample)
-{
-    const int64_t nst = (V + kSuperCols - 1) / kSuperCols;
-    return nst <= kNarrowTiles ? LaunchPlan{nst <= 4 ? 4 : 8, 1, rows} : streaming_plan(rows, V, sample);
-}
-
 template <typename Chunk, bool kSample>
 static hipError_t launch_for(const VocabPassArgs& a, const LaunchPlan& plan, hipStream_t stream)
 {
-    const int64_t nst = (a.V + kSuperCols - 1) / kSuperCols;
-    if (narrow_serves(a.rows, nst, Chunk::kElemBytes == 2, kSample)) return launch_narrow<Chunk, kSample>(a, (int)nst, stream);
+    if (plan.parts != 0) return launch_narrow<Chunk, kSample>(a, plan, stream);
     return plan.waves == 8 ? launch_groups<Chunk, kSample, 8>(a, plan.rows_per_group, stream)
                            : launch_groups<Chunk, kSample, 4>(a, plan.rows_per_group, stream);
 }
@@ -1080,17 +1071,16 @@ static hipError_t launch_split(const VocabPassArgs& a, RowPartial* ws, SplitPlan
     return hipGetLastError();
 }
 
-static bool rows_are_cut(int64_t rows, int64_t V, const LaunchPlan& whole)
+LaunchPlan vocab_pass_plan(int64_t rows, int64_t V, bool is_bf16, bool sample, bool* cut)
 {
-    return (V + kSuperCols - 1) / kSuperCols > kNarrowTiles && rows <= kSplitMaxRows && whole.workgroups > 0
-        && whole.workgroups * E3_SPLIT_BELOW_DEN <= (int64_t)compute_units() * E3_SPLIT_BELOW_NUM;
-}
-
-LaunchPlan vocab_pass_plan(int64_t rows, int64_t V, bool sample, bool* cut)
-{
-    const LaunchPlan whole = whole_rows_plan(rows, V, sample);
-    *cut = rows_are_cut(rows, V, whole);
-    return whole;
+    const int64_t nst = (V + kSuperCols - 1) / kSuperCols;
+    const bool narrow = narrow_serves(rows, nst, is_bf16, sample);
+    *cut = false;
+    if (nst <= kNarrowTiles && narrow) return narrow_plan(rows, (int)nst, is_bf16);
+    const LaunchPlan streaming = streaming_plan(rows, V, sample);
+    *cut = nst > kNarrowTiles && rows <= kSplitMaxRows && streaming.workgroups > 0
+        && streaming.workgroups * E3_SPLIT_BELOW_DEN <= (int64_t)compute_units() * E3_SPLIT_BELOW_NUM;
+    return narrow ? narrow_plan(rows, (int)nst, is_bf16) : streaming;
 }
 
 hipError_t launch_vocab_pass(const VocabPassArgs& args, bool is_bf16, bool sample,
@@ -1108,9 +1098,7 @@ hipError_t launch_vocab_pass(const VocabPassArgs& args, bool is_bf16, bool sampl
     if (a.adv_groups > 0 && a.rows == 0) return separate_advantages();
     if (a.rows == 0) return hipSuccess;
     bool few = false;
-    LaunchPlan whole = vocab_pass_plan(a.rows, a.V, sample, &few);
-    const int64_t nst = (a.V + kSuperCols - 1) / kSuperCols;
-    if (nst <= kNarrowTiles && !narrow_serves(a.rows, nst, is_bf16, sample)) whole = streaming_plan(a.rows, a.V, sample);
+    const LaunchPlan whole = vocab_pass_plan(a.rows, a.V, is_bf16, sample, &few);
     if (few && workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
         const SplitPlan plan = split_plan(a.rows, a.V, is_bf16);
         if ((size_t)a.rows * plan.nslots * sizeof(RowPartial) <= workspace_bytes) {

@@ -1,5 +1,8 @@
 """How the vocabulary pass launches a batch (host only; 256 compute units without a GPU, as on one)."""
+import ctypes as C
+
 import pytest
+import torch
 
 import paper_2505_18573_amd as e3
 
@@ -11,19 +14,44 @@ WIDTHS = [1, 264, 1000, 4000, 4096, 4097, 8000, 16_384, 16_385, 24_000, 32_000, 
           61_441, 70_005, 128_000, 151_936, 262_144, 500_000]
 
 
+def narrow(rows, V, sample, dtype):
+    """A workgroup for each row: at most eight super-tiles but for larger fp32 training batches of five or six, and bf16 rows of nine
+    to sixteen with at most a row per compute unit."""
+    tiles = -(-V // TILE)
+    if tiles > 8:
+        return dtype is torch.bfloat16 and tiles <= 16 and rows <= CUS
+    return dtype is torch.bfloat16 or sample or tiles not in (5, 6) or rows <= 2 * CUS
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("sample", [True, False])
-def test_workgroups_cover_the_rows_and_the_cut_follows_their_number(sample):
+def test_workgroups_cover_the_rows_and_the_cut_follows_their_number(sample, dtype):
     for V in WIDTHS:
         for rows in ROWS:
-            cut, waves, per_group, workgroups = e3.e3_launch_plan(rows, V, sample)
-            assert waves in (4, 8) and per_group >= 1
+            cut, waves, per_group, workgroups = e3.e3_launch_plan(rows, V, sample, dtype)
+            assert per_group >= 1
             assert workgroups == -(-rows // per_group), (rows, V)
-            # a workgroup never holds more rows than give each wave two items
-            assert per_group == 1 or (per_group - 1) * -(-V // TILE) < 2 * waves, (rows, V)
+            tiles = -(-V // TILE)
+            if narrow(rows, V, sample, dtype):
+                # one, two or four waves to a super-tile; their shares, one or two each, have sixteen places
+                assert per_group == 1 and waves in (tiles, 2 * tiles, 4 * tiles) and waves <= 16, (rows, V, waves)
+            else:
+                assert waves in (4, 8), (rows, V, waves)
+                # a workgroup never holds more rows than give each wave two items
+                assert per_group == 1 or (per_group - 1) * tiles < 2 * waves, (rows, V)
             # rows are cut where whole rows leave half of the compute units without a workgroup
             assert cut == (V > 8 * TILE and rows <= 1024 and 2 * workgroups <= CUS), (rows, V)
             # ... which a batch with a row for more than half of them never does
             assert not (cut and rows > CUS // 2), (rows, V)
+
+
+def test_the_plan_without_a_type_is_that_of_bf16():
+    for rows, V in ((100, 1000), (200, 40_000), (600, 20_000), (4096, 151_936)):
+        for sample in (0, 1):
+            out = [C.c_int32(), C.c_int32(), C.c_int32(), C.c_int64()]
+            assert e3.lib().e3_launch_plan(rows, V, sample, *(C.byref(x) for x in out)) == 0
+            assert tuple(x.value for x in out) == e3.e3_launch_plan(rows, V, bool(sample), torch.bfloat16)
+            assert e3.lib().e3_launch_plan_of(rows, V, 2, sample, *(C.byref(x) for x in out)) == -3       # E3_ERR_DTYPE
 
 
 @pytest.mark.parametrize("rows,V,groups", [(512, 4000, 64), (1024, 4000, 128), (512, 1000, 64), (64, 1000, 8)])
