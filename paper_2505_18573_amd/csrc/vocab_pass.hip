@@ -971,10 +971,14 @@ static LaunchPlan narrow_plan(int64_t rows, int nst, bool is_bf16)
 // 17,000 18.4 / 22.0, x 20,000 20.7 / 22.2, x 24,000 22.5 / 24.3, x 28,000 25.0 / 23.5).
 // Rows of nine to sixteen super-tiles, where they are not cut: bf16 with at most a row per compute unit, a wave per super-tile
 // (129 x 33,000 9.0 / 6.8, 256 x 50,000 10.3 / 9.1, 256 x 65,000 12.4 / 10.1, 400 x 50,000 12.7 / 14.4).
+// A launch has fewer than 2^32 threads: rows of 64 to 256 threads each reach that at 2^24 to 2^26 rows, eight of them to a workgroup of the
+// streaming kernel at 2^27.
 static bool narrow_serves(int64_t rows, int64_t nst, bool is_bf16, bool sample)
 {
-    if (nst > kNarrowTiles) return is_bf16 && nst <= kNarrowWaves && rows <= (int64_t)compute_units();
-    return (is_bf16 || sample || nst < 5 || nst > 6 || rows <= 2 * (int64_t)compute_units());
+    const int64_t cus = compute_units();
+    if (nst > kNarrowTiles) return is_bf16 && nst <= kNarrowWaves && rows <= cus;
+    if (rows * narrow_plan(rows, (int)nst, is_bf16).waves * 64 > (int64_t)UINT32_MAX) return false;
+    return is_bf16 || sample || nst < 5 || nst > 6 || rows <= 2 * cus;
 }
 
 template <typename Chunk, bool kSample>

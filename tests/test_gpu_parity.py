@@ -716,6 +716,22 @@ def test_batch_between_resident_rounds_uses_small_workgroups():
     check_logprob(lg, tgt, None, tau, 1.0, "600 x 65544 logprob")
 
 
+@pytest.mark.parametrize("rows,dtype", [(1 << 26, torch.bfloat16), ((1 << 25) + 3, torch.float32)])
+def test_more_rows_than_a_launch_has_workgroups_of_one(rows, dtype):
+    # 64 (fp32 128) threads to each of these rows would be 2^32: several rows to a workgroup then; the last rows are as alone
+    g = torch.Generator(device=DEV).manual_seed(1)
+    lg = torch.randn((rows, 8 if dtype is torch.bfloat16 else 4), generator=g, device=DEV, dtype=dtype)
+    n = 1000
+    got = e3.e3_sample_entropy(lg, None, 0.8, 5, 0)
+    want = e3.e3_sample_entropy(lg[-n:], None, 0.8, 5, rows - n)
+    assert torch.equal(got[0][-n:], want[0])
+    for a, b in zip(got[1:], want[1:]):
+        assert torch.allclose(a[-n:], b, rtol=1e-5, atol=1e-6)
+    lp, ent, hs, count = e3.e3_logprob_entropy(lg, got[0], None, None, 0.8)
+    assert torch.allclose(lp[-n:], want[1], rtol=1e-5, atol=1e-6) and torch.allclose(ent[-n:], want[2], rtol=1e-5, atol=1e-6)
+    assert int(count) == rows
+
+
 # ---------------------------------------------------------------- are the checks sharp?
 def _parity_batch():
     g = torch.Generator(device=DEV).manual_seed(77)

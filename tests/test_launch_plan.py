@@ -45,6 +45,20 @@ def test_workgroups_cover_the_rows_and_the_cut_follows_their_number(sample, dtyp
             assert not (cut and rows > CUS // 2), (rows, V)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("sample", [True, False])
+@pytest.mark.parametrize("V", [1, 1000, 4096, 8192, 16_384, 20_000, 32_768])
+def test_no_launch_has_more_threads_than_a_grid_may(V, sample, dtype):
+    # fewer than 2^32 in all: batches that a workgroup to each row would take beyond go to workgroups of several rows
+    tiles = -(-V // TILE)
+    for rows in sorted({r + d for e in range(20, 28) for r in (1 << e, (1 << e) // tiles, 3 << (e - 2)) for d in (-1, 0, 1)}):
+        _, waves, per_group, workgroups = e3.e3_launch_plan(rows, V, sample, dtype)
+        assert workgroups == -(-rows // per_group)
+        several = 8 // tiles if tiles <= 8 else 1                      # rows of a streaming workgroup of four waves
+        if -(-rows // several) * 256 < 1 << 32:                        # what that kernel can take
+            assert workgroups * waves * 64 < 1 << 32, (rows, V, waves, per_group)
+
+
 def test_the_plan_without_a_type_is_that_of_bf16():
     for rows, V in ((100, 1000), (200, 40_000), (600, 20_000), (4096, 151_936)):
         for sample in (0, 1):
