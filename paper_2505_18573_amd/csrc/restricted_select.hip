@@ -468,11 +468,16 @@ void sample_select_kernel(SelArgs a)
             }
         }
     };
-    // bf16: the maxima of a set as quick_max leaves them suffice while every lane has a value that is not negative among its
-    // vectors and theta is above zero: then none of those that it gets wrong reaches theta.  Else these, from then on
-    // (`by_value`, wave-uniform: rows of log-probabilities are negative throughout; 8 x 151,936 of them 17.3 -> 15.3 us, where
-    // both maxima in every set took longer than the exact ones alone).
-    bool by_value = T::kKeyBits != 16;
+    // bf16 rows that have a compute unit each: the maxima of a set as quick_max leaves them suffice while every lane has a value
+    // that is not negative among its vectors and theta is above zero: then none of those that it gets wrong reaches theta.  Else the
+    // exact ones, from then on (`by_value`, wave-uniform), and from the start for a row of one set, which could not earn back a
+    // second look, and where a wave's first request holds negative columns only (log-probabilities, masks).  With
+    // two rows to a compute unit exact maxima only: both in every set, as the branch there would make the compiler wait for the set in
+    // flight, cost rows that are negative throughout more than the others gained (quick first / exact, us: 512 x 151,936
+    // ordinary 29.8 / 30.0, log-probabilities 32.3 / 30.2; 300 x 70,005 17.7 / 18.1 and 19.8 / 17.9; 300 x 1000 of one set, top-k 50,
+    // 11.1 / 9.8).
+    constexpr bool kQuick = T::kKeyBits == 16 && !kStream;
+    bool by_value = !kQuick;
     auto exact_maxima = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
         float most = -INFINITY;
 #pragma unroll
@@ -484,15 +489,14 @@ void sample_select_kernel(SelArgs a)
         past_the_end(x, m, set);
     };
     auto set_maxima = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set) {
-        if constexpr (T::kKeyBits == 16) {
-            // (two sets in flight: without a branch in front, where the compiler would wait for both, 512 rows 30.0 -> 31.1 us)
-            if (kStream || !by_value) {
+        if constexpr (kQuick) {
+            if (!by_value) {
                 float most = -INFINITY;
 #pragma unroll
                 for (int u = 0; u < kSBatch; ++u) m[u] = T::quick_max(x[u]);
                 past_the_end(x, m, set);
                 // (no numbers of a positive sign are above infinity as integers, and drop out of `most` as floats: looked for one by one)
-                bool odd = by_value;
+                bool odd = false;
 #pragma unroll
                 for (int u = 0; u < kSBatch; ++u) { most = fmaxf(most, m[u]); odd |= m[u] != m[u]; }
                 by_value = __any(odd || !(most >= 0.0f && most < INFINITY));
@@ -555,7 +559,7 @@ void sample_select_kernel(SelArgs a)
     // Where that would be a quarter of the set, theta is a plateau so far, and only what lies above
     // it is listed (sh.skipped remembers the highest such value): enough if the final theta is higher.
     auto list_set = [&](const u32x4 (&x)[kSBatch], float (&m)[kSBatch], int set, float thf, bool all) {
-        if (T::kKeyBits == 16 && __builtin_expect(thf <= 0.0f && !by_value, 0)) {                    // uniform
+        if (kQuick && __builtin_expect(thf <= 0.0f && !by_value, 0)) {                               // uniform
             by_value = true;
             exact_maxima(x, m, set);
         }
@@ -606,6 +610,7 @@ void sample_select_kernel(SelArgs a)
             philox4x32_10(0u, (uint32_t)grow, (uint32_t)(grow >> 32), 4u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), w4);
             if (lane == 0) sh.k23 = w4[0] >> 9;
         }
+        if constexpr (kQuick) by_value = nsets == 1 || __all((x[0].x & x[0].y & x[0].z & x[0].w & 0x80008000u) == 0x80008000u);
         maxima(x, 0);
         if (!kStream && nsets > 1) request(y, 1);
         publish();
