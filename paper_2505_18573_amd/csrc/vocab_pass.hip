@@ -966,19 +966,50 @@ static LaunchPlan narrow_plan(int64_t rows, int nst, bool is_bf16)
     return plan(rows <= (nst <= 6 ? 2 * cus : cus) ? 2 : 1, 1);
 }
 
-// Which narrow rows have a workgroup each: all but the larger fp32 batches of five or six super-tiles on the training side, where
-// two shares take 110 registers and the last super-tile's absent columns are worked through (us, the streaming kernel / so: 1000 x
-// 17,000 18.4 / 22.0, x 20,000 20.7 / 22.2, x 24,000 22.5 / 24.3, x 28,000 25.0 / 23.5).
+// Which narrow rows have a workgroup each (us, the streaming kernel / so).  Two things speak against it: shares of which a wave has two (86
+// registers, training side 110), and a last super-tile with few columns, whose absent ones are worked through, which the streaming
+// kernel does not do.
+// All bf16 rows but those of eight super-tiles in batches of more than sixteen per compute unit (sampling 3500 x 30,000 39.0 /
+// 38.6, 5000 rows 52.3 / 62.4, 10,000 rows 106 / 125; training only with few columns in the last: 10,000 x 28,680 104 / 112, x 32,000 equal).
+// fp32 rows of at most four super-tiles, and of more while a wave has one share.  Beyond that
+//   - training rows of five or six are streamed (1000 x 17,000 18.4 / 22.0, x 20,000 20.7 / 22.2, x 24,000 22.5 / 24.3);
+//   - others up to four (of seven or eight: three and a quarter) per compute unit, where at most half of the last super-tile is
+//     filled or all of it (sampling 600 x 20,484 13.1 / 15.1, x 22,000 14.2 / 15.9, x 24,576 14.4 / 15.6, x 26,000 15.6 / 16.0; but x 24,000
+//     16.2 / 16.2, x 28,000 18.0 / 16.9, and 1280 x 22,000 26.4 / 24.2), or up to one and a half per compute unit;
+//   - and large batches with few columns in the last (training 10,000 x 24,580 152 / 161, sampling 5000 x 28,680 88.5 / 92.0;
+//     training rows of seven also from five to eight per compute unit: 2048 x 26,000 36.9 / 40.1, 2400 rows 47.5 / 44.9).
 // Rows of nine to sixteen super-tiles, where they are not cut: bf16 with at most a row per compute unit, a wave per super-tile
 // (129 x 33,000 9.0 / 6.8, 256 x 50,000 10.3 / 9.1, 256 x 65,000 12.4 / 10.1, 400 x 50,000 12.7 / 14.4).
 // A launch has fewer than 2^32 threads: rows of 64 to 256 threads each reach that at 2^24 to 2^26 rows, eight of them to a workgroup of the
 // streaming kernel at 2^27.
-static bool narrow_serves(int64_t rows, int64_t nst, bool is_bf16, bool sample)
+static bool narrow_serves(int64_t rows, int64_t V, bool is_bf16, bool sample)
 {
     const int64_t cus = compute_units();
+    const int nst = (int)((V + kSuperCols - 1) / kSuperCols);
     if (nst > kNarrowTiles) return is_bf16 && nst <= kNarrowWaves && rows <= cus;
-    if (rows * narrow_plan(rows, (int)nst, is_bf16).waves * 64 > (int64_t)UINT32_MAX) return false;
-    return is_bf16 || sample || nst < 5 || nst > 6 || rows <= 2 * cus;
+    if (rows * narrow_plan(rows, nst, is_bf16).waves * 64 > (int64_t)UINT32_MAX) return false;
+    const int64_t last = V % kSuperCols;                               // columns of an incomplete last super-tile
+    const bool light = last <= kSuperCols / 2, few = light && last != 0;
+    if (is_bf16) return nst < 8 || rows <= 16 * cus || !(sample || few);
+    if (nst < 5 || rows <= (nst <= 6 ? 2 * cus : cus)) return true;
+    if (!sample && nst <= 6) return false;
+    if (4 * rows <= (nst <= 6 ? 16 : 13) * cus) return !light && 2 * rows > 3 * cus;
+    if (!few || nst == 5) return true;
+    if (nst == 6) return rows <= 24 * cus;
+    if (nst == 7) return sample || rows <= 5 * cus || (rows > 8 * cus && rows <= 16 * cus);
+    return rows <= 16 * cus;
+}
+
+// Short rows in large batches: a workgroup of one or two waves, most lanes of which have no column, costs more to launch than to
+// run.  Four rows to a workgroup of the streaming kernel, a wave each (us, so / narrow): bf16 training side 5000 x 64 7.7 / 9.4, 8192 x
+// 64 11.2 / 13.1, 5000 x 1000 8.7 / 10.0, but 6000 x 750 12.0 / 11.1; fp32 8192 x 500 16.4 / 20.5 and 13.0 / 15.7, training side 5000 x 900 12.3 / 11.2;
+// bf16 samples and fp32 rows of at most 256 columns stay narrow (fp32 10,000 x 256 1.0 to 1.05 times as long so).
+static bool four_short_rows(int64_t rows, int64_t V, bool is_bf16, bool sample)
+{
+    const int64_t cus = compute_units();
+    if (rows <= 10 * cus || (rows + 3) * 64 > (int64_t)UINT32_MAX) return false;
+    if (is_bf16) return !sample && V <= (rows <= 20 * cus ? 1024 : 448);
+    return V > 256 && V <= (sample ? 1024 : 768);
 }
 
 template <typename Chunk, bool kSample>
@@ -1078,8 +1109,9 @@ static hipError_t launch_split(const VocabPassArgs& a, RowPartial* ws, SplitPlan
 LaunchPlan vocab_pass_plan(int64_t rows, int64_t V, bool is_bf16, bool sample, bool* cut)
 {
     const int64_t nst = (V + kSuperCols - 1) / kSuperCols;
-    const bool narrow = narrow_serves(rows, nst, is_bf16, sample);
+    const bool narrow = narrow_serves(rows, V, is_bf16, sample);
     *cut = false;
+    if (four_short_rows(rows, V, is_bf16, sample)) return LaunchPlan{0, 0, 4, 4, (rows + 3) / 4};
     if (nst <= kNarrowTiles && narrow) return narrow_plan(rows, (int)nst, is_bf16);
     const LaunchPlan streaming = streaming_plan(rows, V, sample);
     *cut = nst > kNarrowTiles && rows <= kSplitMaxRows && streaming.workgroups > 0

@@ -784,10 +784,12 @@ def test_parity_checks_accept_an_oracle_off_by_a_rounding_error(wrong_oracle):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("rows,V", [(1, 1_000), (3, 4_097), (9, 16_384), (7, 16_385), (5, 32_768), (6, 32_769),
                                     (1025, 264), (1100, 4_104), (1600, 1_000), (896, 4_200), (128, 33_000),
-                                    (130, 33_000), (250, 40_960), (260, 36_872)])
+                                    (130, 33_000), (250, 40_960), (260, 36_872),
+                                    (2_562, 9), (2_604, 300), (2_601, 700), (2_603, 1_024), (5_121, 450), (300, 28_700), (600, 20_490),
+                                    (850, 27_000), (900, 31_000)])
 def test_launch_shapes_of_small_batches(rows, V, dtype):
-    # narrow rows (one launch, 4 or 8 waves, one or a few rows per workgroup), the widest of them and the
-    # first that are cut, and batches around the bounds of the rows-per-workgroup rule
+    # narrow rows (a workgroup each, with a wave or several to a super-tile or, fp32, two shares to a wave), the widest of them and the
+    # first that are cut, rows just beyond the cut, short rows four to a workgroup, and narrow rows left to the streaming kernel
     g = torch.Generator(device=DEV).manual_seed(rows * 7 + V)
     pitch = -(-V // 8) * 8
     lg = (torch.randn((rows, pitch), generator=g, device=DEV) * 3).to(dtype)[:, :V]

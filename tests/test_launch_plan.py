@@ -8,19 +8,29 @@ import paper_2505_18573_amd as e3
 
 CUS = 256
 TILE = 4096
-ROWS = [1, 3, 64, 96, 127, 128, 129, 160, 192, 193, 255, 256, 257, 300, 511, 512, 513, 640, 641, 768, 1000, 1024, 1025,
-        1536, 2048, 2500, 4096, 10_000, 32_768]
-WIDTHS = [1, 264, 1000, 4000, 4096, 4097, 8000, 16_384, 16_385, 24_000, 32_000, 32_768, 32_769, 40_960, 48_000, 61_440,
+ROWS = [1, 3, 64, 96, 127, 128, 129, 160, 192, 193, 255, 256, 257, 300, 384, 385, 511, 512, 513, 640, 641, 768, 832, 833, 1000, 1024, 1025,
+        1280, 1281, 1536, 2048, 2049, 2500, 2560, 2561, 4096, 4097, 5120, 5121, 6144, 6145, 10_000, 32_768]
+WIDTHS = [1, 256, 264, 448, 449, 768, 769, 1000, 1024, 1025, 4000, 4096, 4097, 8000, 16_384, 16_385, 20_480, 20_484, 22_528, 22_529,
+          24_000, 24_576, 24_577, 27_000, 28_672, 30_000, 32_000, 32_768, 32_769, 40_960, 48_000, 61_440,
           61_441, 70_005, 128_000, 151_936, 262_144, 500_000]
 
 
-def narrow(rows, V, sample, dtype):
-    """A workgroup for each row: at most eight super-tiles but for larger fp32 training batches of five or six, and bf16 rows of nine
-    to sixteen with at most a row per compute unit."""
-    tiles = -(-V // TILE)
-    if tiles > 8:
-        return dtype is torch.bfloat16 and tiles <= 16 and rows <= CUS
-    return dtype is torch.bfloat16 or sample or tiles not in (5, 6) or rows <= 2 * CUS
+def streamed(rows, V, sample, dtype):
+    """Rows of at most eight super-tiles that have no workgroup each (CUS: a row to a compute unit)."""
+    tiles, last = -(-V // TILE), V % TILE
+    few = 0 < last <= TILE // 2
+    if dtype is torch.bfloat16:
+        short = not sample and V <= (1024 if rows <= 20 * CUS else 448)
+        return short and rows > 10 * CUS or tiles == 8 and rows > 16 * CUS and (sample or few)
+    if tiles <= 4:
+        return 256 < V <= (1024 if sample else 768) and rows > 10 * CUS
+    if tiles <= 6:
+        return rows > 2 * CUS and (not sample or rows <= 4 * CUS and last <= TILE // 2 or tiles == 6 and few and rows > 24 * CUS)
+    if rows <= CUS:
+        return False
+    if 4 * rows <= 13 * CUS:
+        return last <= TILE // 2 or 2 * rows <= 3 * CUS
+    return few and (rows > 16 * CUS and not (tiles == 7 and sample) or tiles == 7 and not sample and 5 * CUS < rows <= 8 * CUS)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -32,7 +42,7 @@ def test_workgroups_cover_the_rows_and_the_cut_follows_their_number(sample, dtyp
             assert per_group >= 1
             assert workgroups == -(-rows // per_group), (rows, V)
             tiles = -(-V // TILE)
-            if narrow(rows, V, sample, dtype):
+            if not streamed(rows, V, sample, dtype) if tiles <= 8 else dtype is torch.bfloat16 and tiles <= 16 and rows <= CUS:
                 # one, two or four waves to a super-tile; their shares, one or two each, have sixteen places
                 assert per_group == 1 and waves in (tiles, 2 * tiles, 4 * tiles) and waves <= 16, (rows, V, waves)
             else:
