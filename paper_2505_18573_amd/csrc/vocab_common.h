@@ -236,12 +236,13 @@ __device__ __forceinline__ Cand better(Cand a, Cand b)
 // The winner among the lanes of `lanes`, whose largest weight is `top`: the maximum first, then the lane that
 // holds it (or, of several, the lowest index).  A reduction that carries the index through every step takes three times as many
 // dependent instructions (560 cycles over a wave against 190).  Without a lane that equals the
-// maximum (NaN), and where nobody takes part (weights are not negative), any lane stands for it.
+// maximum (NaN), and where nobody takes part or nobody's weight is above zero (negative ones say "takes no part"; a race has a winner
+// above zero, so these lose to it), any lane stands for it.
 __device__ __forceinline__ Cand holder_of(Cand c, float top, unsigned long long lanes)
 {
     unsigned long long m = __ballot(c.q == top) & lanes;
     Cand r{top, __builtin_amdgcn_readlane(c.idx, m != 0ull ? (int)__builtin_ctzll(m) : 0)};
-    if (top < 0.0f) return r;                                     // uniform; otherwise all 64 would be looked through
+    if (!(top > 0.0f)) return r;                                  // uniform; otherwise all 64 would be looked through
     for (m &= m - 1ull; m != 0ull; m &= m - 1ull) {               // ties: rare
         const int idx = __builtin_amdgcn_readlane(c.idx, (int)__builtin_ctzll(m));
         r.idx = idx < r.idx ? idx : r.idx;
