@@ -165,3 +165,12 @@ def test_levels_without_weight_are_not_searched_among_equals():
     ordinary, spread = us(_nucleus(x, 1000, 1.0)), us(_nucleus(300.0 * x, 1000, 1.0))
     print(f"100 x 5000, top-k 1000: ordinary {ordinary:.1f} us, 300 times as large {spread:.1f} us")
     assert spread < 1.065 * ordinary
+
+
+def test_selection_of_negative_rows_looks_at_a_set_once():
+    # 12.7 us ordinary and 14.3 us at -30 + 0.3 N(0, 1); 12.4 and 15.6 when every set's maxima were taken as integers first
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.randn((300, 40_000), generator=g, device=DEV)
+    ordinary, negative = us(_selection((3.0 * x).to(torch.bfloat16), 1, 1.0)), us(_selection((0.3 * x - 30.0).to(torch.bfloat16), 1, 1.0))
+    print(f"300 x 40,000 bf16, top-k 1: ordinary {ordinary:.1f} us, negative throughout {negative:.1f} us")
+    assert negative < 1.185 * ordinary
