@@ -501,16 +501,19 @@ struct LaneState {
 constexpr float kAbsent = -1.0e30f;
 
 // The integer reference that covers logits up to `z`: ceil(z * c), one more when the fp32
-// product was rounded down onto an integer.  Beyond 2^24 one more is no step and the product is off by up to 2^-24 of itself: up to
-// 90 is left there (sums of 2^90 stay finite, and a merge that scales such a run of columns away scales it to
-// zero), more takes the next values up, so that columns masked with -1e10 or less cannot make a sum infinite.
+// product was rounded down onto an integer.  (Beyond 2^24 one more is no step and the product is off by up to 2^-24 of itself: up to 64
+// for logits of -1e9 at temperatures of 0.7 and more, which the sums bear; much more for -1e10, where they may overflow.  Nothing comes
+// of that while the columns are masked ones: what is scaled away is zero, see nothing_left and finite_sums.)
 __device__ __forceinline__ float reference_for(float z, float c)
 {
     float rc = ceilf(z * c);
-    const float over = fmaf(z, c, -rc);
-    if (over > 0.0f) rc += over > 90.0f ? fabsf(rc) * 0x1p-23f : 1.0f;
+    if (fmaf(z, c, -rc) > 0.0f) rc += 1.0f;
     return rc;
 }
+
+// What is left of a sum that is scaled by 2^-d for a large d: nothing, but NaN stays NaN.
+template <typename F>
+__device__ __forceinline__ F nothing_left(F sum) { return sum == sum ? (F)0 : sum; }
 
 // A sweep holds a logit above the wave's running maximum (and above the floor, see
 // start_row).  Move the reference to ceil(new top * c): the shift d is a non-negative
@@ -524,10 +527,17 @@ __device__ __forceinline__ void new_maximum(LaneState& s, float z[8], float chun
     if (s.rc > -INFINITY && new_rc != s.rc) {                  // wave-uniform
         const float d = new_rc - s.rc;
         const float f = __builtin_amdgcn_exp2f(-d);           // exact: d is an integer
-        s.W = fmaf(-d, s.S, s.W) * f;       s.S *= f;
-        s.wT0 = fmaf(-d, s.sT0, s.wT0) * f; s.sT0 *= f;
-        s.wT1 = fmaf(-d, s.sT1, s.wT1) * f; s.sT1 *= f;
-        s.best.q *= f;
+        if (f > 0.0f) {
+            s.W = fmaf(-d, s.S, s.W) * f;       s.S *= f;
+            s.wT0 = fmaf(-d, s.sT0, s.wT0) * f; s.sT0 *= f;
+            s.wT1 = fmaf(-d, s.sT1, s.wT1) * f; s.sT1 *= f;
+            s.best.q *= f;
+        } else {
+            s.W = nothing_left(s.W);     s.S = nothing_left(s.S);
+            s.wT0 = nothing_left(s.wT0); s.sT0 = nothing_left(s.sT0);
+            s.wT1 = nothing_left(s.wT1); s.sT1 = nothing_left(s.sT1);
+            s.best.q = s.best.q < 0.0f ? s.best.q : 0.0f;
+        }
     }
     if (s.top > -INFINITY) {                                   // wave-uniform
         const float t_old = fmaf(s.top, c, -new_rc);

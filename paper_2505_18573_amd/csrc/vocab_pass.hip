@@ -60,6 +60,20 @@ __host__ __device__ inline size_t lds_bytes(int rpb, int nst, bool sample)
          + (sample ? (size_t)rpb * nst * kLanes * sizeof(float) : 0);
 }
 
+// Logits of -1e10, or 1e10, and beyond lie up to 2^-24 of themselves off their fp32 reference (see reference_for), which can make
+// the sums of a wave infinite.  As a rule these are masked columns, to be scaled away: to zero, so what is handed over is finite.  A
+// row that overflows with its own largest columns is no number, as the value tells.
+constexpr double kOverflow = 0x1p200;          // no sum of fp32 terms comes near it
+constexpr float kHugeReference = 0x1p31f;      // below it a reference is off by 64 at most, which all sums bear
+__device__ __forceinline__ void finite_sums(RowPartial& p)
+{
+    // (NaN stays; products with a distance between references, up to 2^128, stay finite)
+    p.S = p.S > kOverflow ? 0x1p800 : p.S;
+    p.W = p.W > kOverflow ? 0x1p800 : p.W;
+    p.q = fminf(p.q, 3.402823466e38f);
+    p.top = p.top > kAbsent ? p.top : -INFINITY;                       // (see new_maximum)
+}
+
 // A partial brought to the reference R >= its own (exact scaling; an empty one counts nothing).  Its excluded maximum joins the
 // sums as an ordinary term unless it is the row's.
 __device__ __forceinline__ float scaled_mass(const RowPartial& p, float R)
@@ -106,6 +120,7 @@ __device__ __forceinline__ RowPartial merge_partials(const RowPartial* parts, in
     const double both = row16_sums(lane < 16 ? S : W);
     m.S = read_lane(both, 0);
     m.W = read_lane(both, 16);
+    if (!(fabsf(R) < kHugeReference)) finite_sums(m);                  // uniform
     return m;
 }
 
@@ -196,7 +211,8 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
     // every piece of which is O(x) when the row is peaked.  t_p lies in (-1, 0].
     const double t_p = (double)peak * cd - (double)R;
     const double inv_ep = (double)__builtin_amdgcn_exp2f((float)-t_p);
-    const double x = S_rest * inv_ep, y = W_rest * inv_ep;
+    // (a sum that overflowed with the row's own columns is no number: finite_sums)
+    const double x = S_rest < kOverflow ? S_rest * inv_ep : __builtin_nan(""), y = W_rest * inv_ep;
     const double l1p = log1p_of(x);
     const double H = fma(kLn2 * (t_p * x - y), reciprocal(1.0 + x), l1p);
 
@@ -425,6 +441,7 @@ void vocab_pass_kernel(VocabPassArgs a, int rpb)
         if (lane == 0) {
             RowPartial p;
             p.S = Sw; p.W = Ww; p.rc = s.rc; p.top = s.top; p.q = wb.q; p.tile = wb.idx;
+            if (!(fabsf(s.rc) < kHugeReference)) finite_sums(p);
             parts[r * (kWaves + 1) + slot] = p;
             // Release: the partial is visible to the workgroup before the counter moves.
             // The fence is restricted to the LDS address space, so it waits for this
@@ -662,18 +679,18 @@ struct SplitShare : SplitShape<Chunk, kParts> {
             }
         }
         float s = s0 + s1, w = w0 + w1;
-        const float t_top = fmaf(top, c, -rc), e_top = __builtin_amdgcn_exp2f(t_top);
+        const float t_top = fmaf(top, c, -rc), e_top = __builtin_amdgcn_exp2f(t_top);  // (infinite: see finite_sums)
         const unsigned long long holders = __ballot(struck != 0);
-        const float mass = fmaf((float)struck, e_top, s);
+        const float mass = struck != 0 ? fmaf((float)struck, e_top, s) : s;
         if (__any(struck > 1) || (holders & (holders - 1ull)) != 0ull) {               // rare
-            const float again = (float)(struck - (lane == (int)__builtin_ctzll(holders | 1ull << 63))) * e_top;
+            const int others = struck - (lane == (int)__builtin_ctzll(holders | 1ull << 63));
+            const float again = others > 0 ? (float)others * e_top : 0.0f;
             s += again;
             w = fmaf(t_top, again, w);
         }
         p.S = (double)s; p.W = (double)w;
         wave_sum2(p.S, p.W);
-        p.rc = rc;
-        p.top = top > kAbsent ? top : -INFINITY;                       // (see new_maximum)
+        p.rc = rc; p.top = top;
         if (kSample) {
             const int tile = tile_of(lane, part);
             const bool nonempty = first_col + tile * kChunk < V;
@@ -681,6 +698,7 @@ struct SplitShare : SplitShape<Chunk, kParts> {
             const Cand best = holder_of(mine, Shape::kRowVecs == 16 ? row16_max(mine.q) : wave_max(mine.q), Shape::kOnce);
             p.q = best.q; p.tile = best.idx;
         }
+        if (!(fabsf(rc) < kHugeReference)) finite_sums(p);             // uniform
         return p;
     }
 };

@@ -521,6 +521,31 @@ def test_columns_masked_with_large_finite_values(rows, V, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("V", [1, 3, 40, 5_000, 33_000, 70_005])
+def test_rows_of_nothing_but_a_mask(V, dtype):
+    # rows masked throughout are uniform.  Their reference differs from z / tau in base 2 by `over`, which the fp32 sums bear
+    # up to a hundred either way: all of those rows at -1e8, most at -1e9 and lower temperatures, a few at -4e9
+    g = torch.Generator(device=DEV).manual_seed(V)
+    tau = (0.3 + 2.0 * torch.rand(300, generator=g, device=DEV)).float()
+    values = torch.tensor([-1e8, -1e9, -4e9], device=DEV).to(dtype)
+    lg = values.repeat(100).unsqueeze(1).expand(300, -(-V // 8) * 8).contiguous()[:, :V]
+    c = np.float32(1.44269504088896340736) / tau.cpu().numpy()
+    z = lg[:, 0].float().cpu().numpy()
+    over = z.astype(np.float64) * c - np.ceil(z * c).astype(np.float64)
+    borne = torch.from_numpy(np.abs(over) < 100).to(DEV)
+    assert borne[0::3].all() and (over > 90).any() and int(borne.sum()) > 200
+    targets = torch.full((300,), V - 1, dtype=torch.int32, device=DEV)
+    for rows in (300, 60):                                             # (wider rows: streamed, and cut)
+        for ws in (None, False):
+            tok, logp, ent = e3.e3_sample_entropy(lg[:rows], tau[:rows], 1.0, seed=3, row_base=0, workspace=ws)
+            lp2, ent2, _, _ = e3.e3_logprob_entropy(lg[:rows], targets[:rows], None, tau[:rows], 1.0, workspace=ws)
+            assert ((tok >= 0) & (tok < V)).all()
+            for got, want in ((logp, -np.log(V)), (lp2, -np.log(V)), (ent, np.log(V)), (ent2, np.log(V))):
+                off = ((got - want).abs() > 1e-4 * abs(want) + 1e-5) & borne[:rows]
+                assert not (off | (torch.isnan(got) & borne[:rows])).any(), (V, rows, ws, off.nonzero()[:5], over[:rows][off.cpu().numpy()][:5])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("rows,V", UNUSUAL_SHAPES)
 def test_rows_without_a_number(rows, V, dtype):
     # a row of -inf has no largest logit: its log-prob and entropy are NaN at every temperature (log2(e): logits are scaled by exactly 1) and
