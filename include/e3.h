@@ -97,8 +97,10 @@ size_t e3_workspace_bytes(int64_t rows, int64_t V);
  * logits      [rows, row_stride] elements of `dtype`, row-major, first V of each
  *             row used; base 16-byte aligned and row_stride*sizeof(elem) a
  *             multiple of 16 (else E3_ERR_ALIGN).  Values must be finite; a row
- *             holding NaN or +-inf produces NaN outputs and an unspecified token
- *             in [0, V).
+ *             holding NaN or +inf produces NaN outputs and an unspecified token
+ *             in [0, V).  A row holding -inf produces a NaN entropy, and a
+ *             log-prob and token that are unspecified unless it holds nothing
+ *             else (NaN).  Mask with a finite value such as -1e9 instead.
  * tau_rows    [rows] fp32 or NULL; when NULL tau_scalar (host, finite, > 0, else
  *             E3_ERR_VALUE) applies to every row.  Per-row values are not checked:
  *             a row with tau <= 0 produces NaN outputs.

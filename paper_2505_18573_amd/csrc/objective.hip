@@ -35,7 +35,8 @@ void grpo_seq_terms_kernel(const float* __restrict__ logp_new, const float* __re
     const float A = adv[i];
     const float lo = 1.0f - clip_eps, hi = 1.0f + clip_eps;
     double acc = 0.0;
-    // kN steps of the rollout's waves from token t on, all requested before the first is used
+    // kN steps of the rollout's waves from token t on, requested together.  (Not quite: in blocks of two steps and more the compiler moves the first
+    // step's two requests behind the branch on its bound, where they wait once more, after the others have left.)
     auto terms = [&](auto steps, int64_t t) {
         constexpr int kN = decltype(steps)::value;
         float n[kN], o[kN];

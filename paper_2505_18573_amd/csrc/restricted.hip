@@ -257,11 +257,11 @@ static __device__ __forceinline__ void own_mass(View& vw, int e, float z_top, do
     }
 }
 
-// Prefixes over the waves, one wave per lane (lanes from kRWaves on hold the totals).
+// Inclusive prefixes over the waves, one wave per lane of the first sixteen: lanes kRWaves - 1 to 15 hold the totals, lanes behind them nothing.
 struct Waves { int C; double M; };
 
 // Exclusive scan of counts and masses in thread order = rank order; threads from `mid_at` on
-// also have the middle's totals before them, which one wave has left in LDS.  Returns the inclusive prefixes of the scanned levels over the waves.
+// also have the middle's totals before them, which one wave has left in LDS.  Returns the scanned levels' prefixes over the waves.
 static __device__ __forceinline__ Waves scan_view(View& vw, int carry_C, double carry_M, int mid_at, Shared& sh, int tid)
 {
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

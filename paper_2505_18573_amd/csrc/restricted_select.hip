@@ -38,7 +38,8 @@
 namespace e3 {
 namespace {
 
-constexpr int kSBatch = 8;              // 16-byte requests of a thread made together; two such sets are in flight
+constexpr int kSBatch = 8;              // 16-byte requests of a thread made together.  (Two sets of registers; as compiled, a set has
+                                       // arrived whole before the next is asked for, which is in flight while it is worked through)
 constexpr int kSMaxWaves = 16;
 constexpr int kSVecCap = 2688;          // vectors listed in LDS (what two workgroups per compute unit leave room for)
 constexpr int kSMaxK = 256;             // top_k served here; the gt-list holds at most kSMaxK - 1 columns

@@ -208,7 +208,7 @@ __device__ __forceinline__ void finish_row(const VocabPassArgs& a, int64_t row,
     }
     // With e_p = 2^{t_p} the peak's term, x = S_rest / e_p and y = W_rest / e_p:
     //   ln S = t_p ln2 + log1p(x),   H = ln S - ln2 W / S = log1p(x) + ln2 (t_p x - y) / (1 + x),
-    // every piece of which is O(x) when the row is peaked.  t_p lies in (-1, 0].
+    // every piece of which is O(x) when the row is peaked.  t_p lies in (-1, 0] (while the reference is exact, see reference_for).
     const double t_p = (double)peak * cd - (double)R;
     const double inv_ep = (double)__builtin_amdgcn_exp2f((float)-t_p);
     // (a sum that overflowed with the row's own columns is no number: finite_sums)
@@ -812,9 +812,10 @@ void row_finish_kernel(VocabPassArgs a, const RowPartial* __restrict__ ws, int n
 // ---------------------------------------------------------------------------
 // Batch sums for the scheduler's H_t (mean entropy of the current step, Eq. 4) and the mean gap:
 // one workgroup, fp64, fixed summation order (thread t takes rows t, t + 1024, ...).  Bound by
-// latency: a thread's next eight rows are requested together, mask and values alike and without a
-// branch between them (32,768 masked entropies: one row at a time behind its mask 21.0 us, so
-// 7.2 us), and entropies and gaps share a launch (1000 rows: two launches 4 us each, one 3.9 us).
+// latency: a thread's next eight rows are requested together (32,768 masked entropies: one row at a time behind its mask
+// 21.0 us, so 7.2 us), and entropies and gaps share a launch (1000 rows: two launches 4 us each, one 3.9 us).  With a mask the
+// compiler waits for the first row's byte before the other requests leave and reads its value in the branch behind it:
+// three waits for eight rows, one without a mask.
 // ---------------------------------------------------------------------------
 template <bool kGap, bool kMask>
 __global__ __launch_bounds__(1024)
@@ -1065,8 +1066,9 @@ static hipError_t launch_for(const VocabPassArgs& a, const LaunchPlan& plan, hip
 // of the merging wave.
 // Rows of at most kNarrowTiles super-tiles are not cut: a workgroup holds all of them and needs no second launch (64 rows x
 // 32,000 bf16: 5.9 us).  Wider rows are cut while whole rows would make at most half as many workgroups as there are compute
-// units.  Where the line lies was measured with one wave per super-tile (four have since made the cut form faster, 64 rows x
-// 151,936 9.0, 128 rows 12.3, and whole rows of up to sixteen super-tiles too).  Cut / whole in us, bf16
+// units.  The line was drawn with kernels that both have since become faster, one wave per super-tile in the one and the streaming
+// kernel in the other, and has not been drawn again: for bf16 rows of nine to sixteen super-tiles, narrow when whole, it is
+// too high (64 x 33,000 cut 7.4, 129 x 33,000 whole 6.8); rows x 151,936 cut are now 9.0 at 64 and 12.3 at 128.  Then, cut / whole in us, bf16
 // samples: 64 rows x 33,000 9.6 / 9.9, x 70,005 10.6 / 13.9, x 151,936 12.1 / 15.1; 128 rows 10.5 / 10.7,
 // 12.3 / 14.5, 15.9 / 15.8; 192 rows 11.3 / 11.1, 13.8 / 15.1, 19.0 / 16.8; x 61,000 12.6 / 12.4 at 128 rows and
 // 13.7 / 12.6 at 192.  (Rows of a whole number of super-tiles are faster whole at any count, 128 x
